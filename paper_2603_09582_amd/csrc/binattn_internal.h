@@ -71,12 +71,15 @@ __host__ __device__ inline int k_chunk(int pos, int chunk, int KP) {
 // FP4 e2m1 codes of +1.0 and -1.0
 constexpr unsigned FP4_PLUS1 = 0x2u, FP4_MINUS1 = 0xAu;
 
-// 8 sign bits -> 8 FP4 nibbles (bit i -> nibble i): +1.0 where set, -1.0 where clear.
+// 8 sign bits -> 8 FP4 nibbles, +1.0 where set, -1.0 where clear.  Bit 2 k goes to nibble k, bit
+// 2 k + 1 to nibble 4 + k: the order in which two bf16 values per dword give their signs
+// (fp4_pm1_abs).  The order inside a group of 8 channels is free as long as the Q and the K
+// operand share it: every FP4 word of the library comes from these two routines.
 __device__ __forceinline__ unsigned fp4_pm1_from_bits8(unsigned b) {
-    unsigned x = (b | (b << 12)) & 0x000F000Fu;  // 4 bits per half word
-    x = (x | (x << 6)) & 0x03030303u;            // 2 bits per byte
-    x = (x | (x << 3)) & 0x11111111u;            // 1 bit per nibble, at its lowest position
-    return 0xAAAAAAAAu - (x << 3);               // 0xA - 8 = 0x2 where the bit is set
+    unsigned x = (b & 0x55u) | ((b & 0xAAu) << 15);     // even bits at 2 k, odd bits at 16 + 2 k
+    x = (x & 0x00050005u) | ((x & 0x00500050u) << 4);
+    x = (x & 0x01010101u) | ((x & 0x04040404u) << 2);   // one bit per nibble, at its lowest position
+    return 0xAAAAAAAAu - (x << 3);                      // 0xA - 8 = 0x2 where the bit is set
 }
 
 inline int image_bytes(int DK) {

@@ -236,13 +236,15 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     float Of[DK][16];         // output carry, channel 32 cb + 8 (r/4) + 4 g + r % 4
 
     // registers fetched ahead for the NEXT item
-    unsigned pend_q[2 * DK2];
-    unsigned pend_q2[ONEHEAD4 ? 2 * DK2 : 1];  // ONEHEAD4: sign words of this lane's row in the second row block
+    // (sign words; in the single-launch forms the FP4 operand words themselves)
+    constexpr int PQ = ONEHEAD ? 4 * DK2 : 2 * DK2;
+    unsigned pend_q[PQ];
+    unsigned pend_q2[ONEHEAD4 ? PQ : 1];  // ONEHEAD4: this lane's row in the second row block
     float pend_muq = 1.0f, pend_muk = 1.0f;
     auto fetch_item_regs = [&](const Item &t) {
         if constexpr (ONEHEAD4) {  // made by the prologue
 #pragma unroll
-            for (int w = 0; w < 2 * DK2; ++w) pend_q[w] = pend_q2[w];
+            for (int w = 0; w < PQ; ++w) pend_q[w] = pend_q2[w];
             return;
         }
         const int qc = min(t.rb * BR + wave * ROWS_PER_WAVE + m, N - 1);
@@ -288,7 +290,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         inv_alpha = 1.0f / a_abs;
         a2 = a_abs * LOG2E_F;  // exponent multiplier in base 2
         // (BIAS_LUT lets the matrix core SUBTRACT the logit from a constant, see the block loop)
-        load_q_operand<DK2>(pend_q, d, g, LUT ? !a_neg : a_neg, a_zero, qB);
+        if constexpr (ONEHEAD) {
+#pragma unroll
+            for (int i = 0; i < PQ; ++i)
+                qB[i / 4][i % 4] = a_zero ? 0 : (int)(pend_q[i] ^ ((LUT ? !a_neg : a_neg) && pend_q[i] ? 0x88888888u : 0u));
+        } else {
+            load_q_operand<DK2>(pend_q, d, g, LUT ? !a_neg : a_neg, a_zero, qB);
+        }
         if (LUT) {
             // (the previous item's last block is behind every wave; the barrier publishes the table)
             for (int i = threadIdx.x; i < LUTN; i += FUSED_THREADS * NB)
@@ -811,7 +819,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         // phi and psi of Alg. 1 for this head, straight into the two LDS images.
         constexpr int NT = FUSED_THREADS * NB;
         __shared__ int sabs[DKP];            // per-channel absmax of V (bit patterns)
-        __shared__ __attribute__((aligned(16))) float srlo[DKP], srhi[DKP];  // bracketing reciprocals of delta_v
+        __shared__ __attribute__((aligned(16))) float srcp[DKP];  // the quantiser's multipliers
         __shared__ float ssum[2][NT / 64];   // |q| and |k| partial sums per wave
         const int C16 = d / 8, nblk = p.nblk;
         auto imgp = [&](int blk) -> char * { return blk ? bufB : bufA; };
@@ -840,16 +848,18 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
                     qx[sI][j] = *reinterpret_cast<const u4 *>(qb_ + (int64_t)min(row, N - 1) * p.xqs.n + (c0 < d ? c0 : 0));
                 }
         };
-        auto q_row_words = [&](int row, unsigned *words) {  // sign words of the loaded row, |q| into qsum
+        auto q_row_words = [&](int row, unsigned *words) {  // FP4 words of the loaded row, |q| into qsum
 #pragma unroll
-            for (int w = 0; w < 2 * DK2; ++w) words[w] = 0u;
-#pragma unroll
-            for (int sI = 0; sI < DK2; ++sI) {
-                unsigned word = 0;
+            for (int sI = 0; sI < DK2; ++sI)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    if (row < N && 32 * (2 * sI + g) + 8 * j < d) word |= sign_bits8_abs(qx[sI][j], qsum) << (8 * j);
-                if (g) words[2 * sI + 1] = word; else words[2 * sI] = word;
+                    words[4 * sI + j] = row < N && 32 * (2 * sI + g) + 8 * j < d ? fp4_pm1_abs(qx[sI][j], qsum) : 0u;
+            if (qsum != qsum) {  // a NaN among this lane's queries: the words once more, exactly
+#pragma unroll
+                for (int i = 0; i < PQ; ++i)
+                    if (words[i] != 0u)
+                        words[i] = fp4_pm1_exact(*reinterpret_cast<const u4 *>(
+                            qb_ + (int64_t)row * p.xqs.n + 32 * (2 * (i / 4) + g) + 8 * (i % 4)));
             }
         };
         load_q_row(qrow);
@@ -905,10 +915,19 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             const int ic = div_c16(i), c8 = i - ic * C16, pos = ic % BV, blk = ic / BV;
             const int key = blk * BV + key_of_position(pos);
             if (blk < nblk && key < N) {
-                const unsigned bits = sign_bits8_abs(kx[kk], ksum);
                 *reinterpret_cast<unsigned *>(imgp(blk) + L::K_OFF + pos * L::KP +
                                               16 * k_chunk(pos, c8 >> 2, L::KP) + 4 * (c8 & 3)) =
-                    fp4_pm1_from_bits8(bits);
+                    fp4_pm1_abs(kx[kk], ksum);
+            }
+        }
+        if (ksum != ksum) {  // a NaN among this thread's keys: its words once more, exactly
+            for (int i = threadIdx.x; i < KPT * NT; i += NT) {
+                const int ic = div_c16(i), c8 = i - ic * C16, pos = ic % BV, blk = ic / BV;
+                const int key = blk * BV + key_of_position(pos);
+                if (blk < nblk && key < N)
+                    *reinterpret_cast<unsigned *>(imgp(blk) + L::K_OFF + pos * L::KP +
+                                                  16 * k_chunk(pos, c8 >> 2, L::KP) + 4 * (c8 & 3)) =
+                        fp4_pm1_exact(*reinterpret_cast<const u4 *>(kb_ + (int64_t)key * p.xks.n + 8 * c8));
             }
         }
         if constexpr (ONEHEAD4) q_row_words(qrow + BR, pend_q2);
@@ -941,7 +960,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         __syncthreads();
         if (threadIdx.x < 8 * C16) {
             float dl;
-            quant_consts(__int_as_float(sabs[threadIdx.x]), &dl, &srlo[threadIdx.x], &srhi[threadIdx.x]);
+            quant_consts(__int_as_float(sabs[threadIdx.x]), &dl, &srcp[threadIdx.x]);
             sdelta[0][0][threadIdx.x] = dl;
         }
         float tq = 0.0f, tk = 0.0f;
@@ -960,13 +979,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         __syncthreads();
         // V codes, channel-major, into the images
         if (von) {
-            const QuantConsts8 kc = load_quant_consts8(&sdelta[0][0][0], srlo, srhi, vc);
+            const QuantConsts8 kc = load_quant_consts8(srcp, vc);
 #pragma unroll
             for (int kq = 0; kq < KQ; ++kq) {
                 const int quad = vr + kq * RT;
                 if (4 * quad < N && quad < 2 * BV / 4) {
                     unsigned packed[8];
-                    quant_quad(vw[kq], kc, packed);
+                    quant_quad(vw[kq], kc, &sdelta[0][0][0], vc, packed);
                     char *imgq = imgp(quad / (BV / 4));
                     char *dstv = imgq + L::V_OFF + 4 * (quad % (BV / 4));
 #pragma unroll

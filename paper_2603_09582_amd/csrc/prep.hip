@@ -82,7 +82,7 @@ __device__ __forceinline__ float absmax_rows(const uint16_t *__restrict__ vb, in
 template <int C16>
 __device__ __forceinline__ void quant_v_block(const uint16_t *__restrict__ vb, int64_t stride_n,
                                               int N, int DKP, int blk, const float *sdelta,
-                                              const float *srlo, const float *srhi, int8_t *tile,
+                                              const float *srcp, int8_t *tile,
                                               int v_off, int cs_off, char *__restrict__ dst) {
     constexpr int LDT = BV + 16;  // LDS row pitch in bytes = Image::VP
     for (int i = threadIdx.x; i < DKP * LDT / 4; i += PREP_THREADS)
@@ -106,7 +106,7 @@ __device__ __forceinline__ void quant_v_block(const uint16_t *__restrict__ vb, i
             if (4 * jq + k < nrow)
                 w[k] = *reinterpret_cast<const u4 *>(vb + (int64_t)(j0 + 4 * jq + k) * stride_n + 8 * c);
         }
-        quant_quad(w, load_quant_consts8(sdelta, srlo, srhi, c), packed);
+        quant_quad(w, load_quant_consts8(srcp, c), sdelta, c, packed);
         const int col = jq ^ (((c >> 1) & 3) << 3);
 #pragma unroll
         for (int i = 0; i < 8; ++i)
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(PREP_THREADS) void v_quant_kernel(
     // A workgroup takes bpw consecutive key blocks of one head (more than one for long
     // sequences, where re-reading all absmax partials for every single block would cost more
     // than the block itself).
-    __shared__ __attribute__((aligned(16))) float sdelta[8 * C16], srlo[8 * C16], srhi[8 * C16];
+    __shared__ __attribute__((aligned(16))) float sdelta[8 * C16], srcp[8 * C16];
     __shared__ __attribute__((aligned(16))) int8_t tile[128 * (BV + 16)];
     const int ngrp = (nblk + bpw - 1) / bpw;
     const int blk0 = (blockIdx.x % ngrp) * bpw, bh = blockIdx.x / ngrp;
@@ -223,12 +223,12 @@ __global__ __launch_bounds__(PREP_THREADS) void v_quant_kernel(
     __syncthreads();
     if (threadIdx.x < 8 * C16) {
         float dl;
-        quant_consts(__int_as_float(sabs[threadIdx.x]), &dl, &srlo[threadIdx.x], &srhi[threadIdx.x]);
+        quant_consts(__int_as_float(sabs[threadIdx.x]), &dl, &srcp[threadIdx.x]);
         sdelta[threadIdx.x] = dl;
         if (blk0 == 0) delta[(int64_t)bh * DKP + threadIdx.x] = dl;
     }
     for (int blk = blk0; blk < min(nblk, blk0 + bpw); ++blk) {
-        quant_v_block<C16>(vb, vs.n, N, DKP, blk, sdelta, srlo, srhi, tile, v_off, cs_off,
+        quant_v_block<C16>(vb, vs.n, N, DKP, blk, sdelta, srcp, tile, v_off, cs_off,
                            img + ((int64_t)bh * nblk + blk) * img_bytes);
         __syncthreads();  // the tile is reused
     }
@@ -309,11 +309,17 @@ __global__ __launch_bounds__(PREP_THREADS) void phi_psi1_kernel(const PhiPsi1Arg
         const int tok = n0 + r0 + p * RT;
         if (on && r0 + p * RT < BV && tok < n1) {
             bytes[(tok - n0) * (4 * W) + c] = (uint8_t)sign_bits8_abs(xq[p], qsum);
-            const unsigned kbits = sign_bits8_abs(xk[p], ksum);
             const int pos = position_of_key(tok - n0);
             *reinterpret_cast<unsigned *>(image + pos * (4 * KW) + 16 * k_chunk(pos, c >> 2, 4 * KW) + 4 * (c & 3)) =
-                fp4_pm1_from_bits8(kbits);
+                fp4_pm1_abs(xk[p], ksum);
             absmax_acc(mb, xv[p]);
+        }
+    }
+    if (ksum != ksum) {  // a NaN among this thread's keys: its words once more, exactly
+        for (int tok = n0 + r0; on && tok < n1; tok += RT) {
+            const int pos = position_of_key(tok - n0);
+            *reinterpret_cast<unsigned *>(image + pos * (4 * KW) + 16 * k_chunk(pos, c >> 2, 4 * KW) + 4 * (c & 3)) =
+                fp4_pm1_exact(*reinterpret_cast<const u4 *>(kb + (int64_t)tok * a.ks.n + 8 * c));
         }
     }
     if (on) {
@@ -363,7 +369,7 @@ __global__ __launch_bounds__(PREP_THREADS) void prep_head_kernel(
     constexpr int MAXQ = (NQ + RT - 1) / RT;
     constexpr int LDT = BV + 16;            // = Image::VP
     __shared__ float smax[RT * D];
-    __shared__ __attribute__((aligned(16))) float sdelta[D], srlo[D], srhi[D];
+    __shared__ __attribute__((aligned(16))) float sdelta[D], srcp[D];
     __shared__ __attribute__((aligned(16))) int8_t tile[2 * 128 * LDT];
     const int bh = blockIdx.x, b = bh / H, h = bh % H;
     const int W = (d + 31) / 32;
@@ -402,20 +408,20 @@ __global__ __launch_bounds__(PREP_THREADS) void prep_head_kernel(
         float a = 0.0f;
         for (int r = 0; r < RT; ++r) a = fmaxf(a, smax[r * D + threadIdx.x]);
         float dl;
-        quant_consts(a, &dl, &srlo[threadIdx.x], &srhi[threadIdx.x]);
+        quant_consts(a, &dl, &srcp[threadIdx.x]);
         sdelta[threadIdx.x] = dl;
         delta[(int64_t)bh * DKP + threadIdx.x] = dl;
     }
     __syncthreads();
 
     if (on) {
-        const QuantConsts8 kc = load_quant_consts8(sdelta, srlo, srhi, c);
+        const QuantConsts8 kc = load_quant_consts8(srcp, c);
 #pragma unroll
         for (int k = 0; k < MAXQ; ++k) {
             const int quad = r0 + k * RT;
             if (4 * quad < N && quad < NQ) {
                 unsigned packed[8];
-                quant_quad(w[k], kc, packed);
+                quant_quad(w[k], kc, sdelta, c, packed);
                 const int blk = quad / (BV / 4), jq = quad % (BV / 4);
                 const int col = jq ^ (((c >> 1) & 3) << 3);  // see quant_v_block
 #pragma unroll
