@@ -170,8 +170,7 @@ int binattn_attend_axial(const uint32_t *q_bits, const float *mu_q, const float 
  *     b_ij = table[h][iy - jy + Gy - 1][ix - jx + Gx - 1].
  *   table : float32 [H, 2 Gy - 1, 2 Gx - 1] contiguous, shared over the batch, finite values.
  *   Gx    : a power of two in [16, 256];  Gy in [1, 256]  (BINATTN_ERR_SHAPE otherwise).
- *           Up to 32 x 32 the head's whole table is held in LDS; larger grids stage, per key
- *           block, only the table rows that block touches.
+ *           Every key block stages only the table rows it touches.
  * Everything else as binattn_attend; BINATTN_FLAG_NO_BIAS ignores the table.
  */
 int binattn_attend_relpos(const uint32_t *q_bits, const float *mu_q, const float *mu_k,

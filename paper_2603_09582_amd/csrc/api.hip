@@ -191,8 +191,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     if (ax != nullptr) {
         if ((rc = check_axial(*ax, N, raw != nullptr && ax->table != nullptr)) != BINATTN_OK) return rc;
         while ((1 << gx_shift) < ax->Gx) ++gx_shift;
-        const bool small_grid = ax->Gx <= TABLE_MAX_G && ax->Gy <= TABLE_MAX_G;
-        if (!no_bias) mode = !ax->table ? BIAS_AXIAL : small_grid ? BIAS_TABLE : BIAS_TABLE_BLK;
+        if (!no_bias) mode = !ax->table ? BIAS_AXIAL : raw != nullptr ? BIAS_TABLE : BIAS_TABLE_BLK;
     } else if (use_bias) {
         if (bias_dtype != BINATTN_BIAS_BF16 && bias_dtype != BINATTN_BIAS_F32) return BINATTN_ERR_DTYPE;
         if (!bias_strides) return BINATTN_ERR_NULL;

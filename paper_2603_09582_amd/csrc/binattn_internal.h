@@ -159,15 +159,14 @@ enum BiasMode {
     BIAS_F32_VEC = 3,   // fp32 bias, 16-byte loads at use
     BIAS_BF16_LDS = 5,  // rows 16-byte aligned, N % 8 == 0: tile staged global -> LDS asynchronously
     BIAS_AXIAL = 7,     // b_ij = y[iy - jy] + x[ix - jx] on a Gy x Gx token grid, tables held in LDS
-    BIAS_TABLE = 9,     // b_ij = t[iy - jy][ix - jx]: the full relative-position table of the head in LDS
-    BIAS_TABLE_BLK = 13, // the same table for larger grids: only the rows a key block needs, staged per block
+    BIAS_TABLE = 9,     // b_ij = t[iy - jy][ix - jx]: the full relative-position table of the head in LDS (single-launch forms)
+    BIAS_TABLE_BLK = 13, // the same table, only the rows a key block needs, staged per block
     BIAS_LUT = 11       // no bias: 255 exp(S - m) read from a per-head table indexed by (m - I) / 2
 };
 
 // largest grid side of BIAS_AXIAL (the tables of one head live in LDS)
 constexpr int AXIAL_MAX_G = 256;
-// largest grid side of BIAS_TABLE ((2 G - 1)^2 entries per head held in LDS); larger grids
-// (up to AXIAL_MAX_G) take BIAS_TABLE_BLK
+// largest grid side of BIAS_TABLE (4 N - 2 Gx <= 1024 entries of a head's table held in LDS)
 constexpr int TABLE_MAX_G = 32;
 
 struct FusedParams {
@@ -201,7 +200,7 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream);
 constexpr int ONEHEAD4_MIN_HEADS = 256;
 // ... in the variants whose 256-thread prologue holds a head's loads in registers without spilling
 constexpr bool onehead4_built(int DK, int mode) {
-    return DK <= 2 || (DK == 3 && (mode == BIAS_NONE || mode == BIAS_F32_VEC || mode == BIAS_BF16_LDS || mode == BIAS_AXIAL));
+    return DK <= 2 || (DK == 3 && (mode == BIAS_NONE || mode == BIAS_F32_VEC || mode == BIAS_BF16_LDS || mode == BIAS_AXIAL || mode == BIAS_TABLE));
 }
 
 template <int DK>

@@ -127,26 +127,27 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     constexpr int AXL = 2 * AXIAL_MAX_G + 16;  // pitch of a copy, in entries
     __shared__ __attribute__((aligned(16))) float axu[AXIAL ? 4 * AXL : 4];
     __shared__ float axw[AXIAL ? AXL : 4];
-    // BIAS_TABLE: the head's (2 Gy - 1) x (2 Gx - 1) table divided by alpha, every row reversed
-    // in x (a lane's 16-entry window then ascends with the key index) at a pitch of TBP
-    // entries.  Windows start at any entry, so they are read entry by entry; the 32 lanes of a
-    // row group read 32 consecutive entries per access (or two runs 16 banks apart when the
-    // group spans two grid rows).
-    constexpr bool TABLE = MODE == BIAS_TABLE;
-    constexpr int TBP = 2 * TABLE_MAX_G + 16;
-    __shared__ float tab2[TABLE ? (2 * TABLE_MAX_G - 1) * TBP : 4];
-    // BIAS_TABLE_BLK: the same bias for grids whose table does not fit LDS.  A 128-key block
-    // covers 128 / Gx grid rows (or part of one) and so do the item's 128 queries, so a block
-    // needs only the table rows iy - jy in [iy_lo - jy_hi, iy_hi - jy_lo]: at most 15 rows of
-    // 2 Gx - 1 entries.  They are staged per block, divided by alpha and reversed in x, at a
-    // pitch of 4 Gx entries (a power of two, at most 1024 entries in all), double-buffered: the
-    // entries for the next block of the stream are loaded at the start of a block and written
-    // to the other buffer at its end.  Lane windows are read as in BIAS_TABLE.
-    constexpr bool TBLK = MODE == BIAS_TABLE_BLK;
-    constexpr int TBLK_N = 1024;
-    constexpr int TBLK_PER = TBLK_N / FUSED_THREADS;   // entries a thread stages (NB = 1 only)
+    // BIAS_TABLE / BIAS_TABLE_BLK: rows of the head's (2 Gy - 1) x (2 Gx - 1) table divided by alpha,
+    // reversed in x (a lane's 16-entry window then ascends with the key index), at a pitch of
+    // 2 Gx entries, in four copies, copy j shifted by j entries as in axu: a window may start at
+    // any entry, and its lane reads it with four 16-byte loads from the copy that aligns it
+    // (one copy read entry by entry took 64 dword reads per lane and block and was 12 % slower
+    // at the 128 x 128 grid, d = 64).  An entry is written to all four copies; the up to three
+    // places before a row's first entry that this touches are the unused tail of the row (or
+    // copy) before it.
+    //   BIAS_TABLE (single-launch forms, Gy * Gx <= 256): the whole table, 4 N - 2 Gx entries.
+    //   BIAS_TABLE_BLK: a 128-key block covers 128 / Gx grid rows (or part of one) and so do the
+    //   item's 128 queries, so a block needs only the table rows iy - jy in
+    //   [iy_lo - jy_hi, iy_hi - jy_lo]: (256 / Gx - 1) rows, or one, i.e. at most 512 entries.
+    //   They are double-buffered: the entries for the next block of the stream are loaded at
+    //   the start of a block and written to the other buffer at its end.
+    constexpr bool TABLE = MODE == BIAS_TABLE, TBLK = MODE == BIAS_TABLE_BLK;
+    constexpr int TB_N = TABLE ? 1024 : 512;           // entries of a copy
+    constexpr int TB_CP = TB_N + 16;                   // copy pitch (bank spread as for axu)
+    constexpr int TB_PER = TB_N / (FUSED_THREADS * NB); // entries a thread stages
     static_assert(!TBLK || (NB == 1 && WIDE == WIDE_NONE), "per-block table rows: 4-wave workgroups");
-    __shared__ float tblk[TBLK ? 2 * TBLK_N : 4];
+    static_assert(!TABLE || ONEHEAD, "whole table: single-launch forms");
+    __shared__ __attribute__((aligned(16))) float tab[TABLE ? 4 * TB_CP : TBLK ? 2 * 4 * TB_CP : 4];
     // BIAS_LUT (no bias): the logit takes only the d + 1 values alpha * I, I = d, d - 2, ..., -d, and
     // the running maximum is one of them, so 255 * exp(S - m) is one of d + 1 numbers that depend
     // on the head alone: lut[k] = 255 * exp(-2 alpha k) for m - I = 2 k.  Entries d + 1 ... 2 d + 1
@@ -277,6 +278,38 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     auto image_ptr = [&](const Item &t) -> const char * {
         return uniform_ptr(p.img + (int64_t)t.bh * p.nblk * L::BYTES);
     };
+    // ---- BIAS_TABLE / BIAS_TABLE_BLK: staging of table rows [row0, row0 + nrows) -------------
+    float tstage[TABLE || TBLK ? TB_PER : 1];
+    auto table_load = [&](const Item &t, int row0, int nrows) {  // global loads only
+        const int LX = 2 * p.Gx - 1, LY = 2 * p.Gy - 1, sh = p.gx_shift + 1;
+        const float *tb = p.table + (int64_t)t.h * LY * LX;
+#pragma unroll
+        for (int j = 0; j < TB_PER; ++j) {
+            const int i = threadIdx.x + j * FUSED_THREADS * NB;
+            const int row = i >> sh, kk = i & ((1 << sh) - 1);
+            const bool on = row < nrows && kk < LX;
+            const float x = tb[on ? (int64_t)(row0 + row) * LX + (LX - 1 - kk) : 0];
+            tstage[j] = on ? x : 0.0f;
+        }
+    };
+    auto table_store = [&](float *dst, float ia) {
+#pragma unroll
+        for (int j = 0; j < TB_PER; ++j) {
+            const int i = threadIdx.x + j * FUSED_THREADS * NB;
+            if (TBLK && j > 0 && p.Gx == 128) break;  // one row of 256 entries (the other grids need more than half)
+            const float x = tstage[j] * ia;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                dst[c * TB_CP + i - c] = x;
+        }
+    };
+    // BIAS_TABLE_BLK: the rows of one (item, key block)
+    auto tblk_load = [&](const Item &t, int blk) {
+        const int iy_lo = (t.rb * BR) >> p.gx_shift, iy_hi = min((t.rb * BR + BR - 1) >> p.gx_shift, p.Gy - 1);
+        const int jy_lo = (blk * BV) >> p.gx_shift, jy_hi = min((blk * BV + BV - 1) >> p.gx_shift, p.Gy - 1);
+        const int dy_min = iy_lo - jy_hi;
+        table_load(t, dy_min + p.Gy - 1, iy_hi - jy_lo - dy_min + 1);
+    };
     // turn the fetched registers into the item's state
     auto begin_item = [&](const Item &t) {
         imgs = image_ptr(t);
@@ -352,38 +385,18 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         }
         if (TABLE) {
             // (as above: the previous item's last block is behind every wave)
-            const int LX = 2 * p.Gx - 1, LY = 2 * p.Gy - 1;
-            const float *tb = p.table + (int64_t)t.h * LY * LX;
-            // (all loads of a thread go out before the first LDS write: one memory latency)
-            constexpr int NTT = FUSED_THREADS * NB;
-            constexpr int TBN = ((2 * TABLE_MAX_G - 1) * TBP + NTT - 1) / NTT;
-            // (the thread index is made opaque so that the per-thread table indices are
-            // recomputed here instead of being kept in registers across the whole block loop)
-            int tid = threadIdx.x;
-            asm volatile("" : "+v"(tid));
-            float tv[TBN];
-#pragma unroll
-            for (int j = 0; j < TBN; ++j) {
-                const int i = tid + j * NTT;
-                const int ry = i / TBP, kk = i % TBP;
-                const bool on = i < LY * TBP && kk < LX;
-                tv[j] = tb[on ? ry * LX + (LX - 1 - kk) : 0];
-                if (!on) tv[j] = 0.0f;
-            }
-#pragma unroll
-            for (int j = 0; j < TBN; ++j) {
-                const int i = tid + j * NTT;
-                if (i < LY * TBP) tab2[i] = tv[j] * inv_alpha;
-            }
+            table_load(t, 0, 2 * p.Gy - 1);
+            table_store(tab, inv_alpha);
             const int qc = min(q, N - 1);
-            ax_ub = p.Gx - 1 - (qc & (p.Gx - 1));       // reversed-row index of key column 0
-            ax_wb = (qc >> p.gx_shift) + p.Gy - 1;      // table row of key row 0
+            const int s0 = p.Gx - 1 - (qc & (p.Gx - 1));  // reversed-row index of key column 0
+            ax_ub = (s0 & 3) * TB_CP + (s0 & ~3) + (((qc >> p.gx_shift) + p.Gy - 1) << (p.gx_shift + 1));
             __syncthreads();
         }
         if (TBLK) {
             const int qc = min(q, N - 1);
-            ax_ub = p.Gx - 1 - (qc & (p.Gx - 1));                               // reversed-row index of key column 0
-            ax_wb = (qc >> p.gx_shift) - ((t.rb * BR) >> p.gx_shift);           // grid row inside the item's range
+            const int s0 = p.Gx - 1 - (qc & (p.Gx - 1));  // reversed-row index of key column 0
+            // ... of the row with jy = jy_hi of a block (row 0 of the staged rows: iy = iy_lo, jy = jy_hi)
+            ax_ub = (s0 & 3) * TB_CP + (s0 & ~3) + (((qc >> p.gx_shift) - ((t.rb * BR) >> p.gx_shift)) << (p.gx_shift + 1));
         }
         m_run = -INFINITY;
         l_run = 0.0f;
@@ -501,33 +514,6 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             }
     };
 
-    // ---- BIAS_TABLE_BLK: the table rows of one (item, key block) ------------------------
-    // first row difference iy - jy of the block, and how many
-    auto tblk_range = [&](const Item &t, int blk, int *dy_min) -> int {
-        const int iy_lo = (t.rb * BR) >> p.gx_shift, iy_hi = min((t.rb * BR + BR - 1) >> p.gx_shift, p.Gy - 1);
-        const int jy_lo = (blk * BV) >> p.gx_shift, jy_hi = min((blk * BV + BV - 1) >> p.gx_shift, p.Gy - 1);
-        *dy_min = iy_lo - jy_hi;
-        return iy_hi - jy_lo - *dy_min + 1;
-    };
-    float tstage[TBLK ? TBLK_PER : 1];
-    auto tblk_load = [&](const Item &t, int blk) {  // global loads only
-        int dy_min;
-        const int nrows = tblk_range(t, blk, &dy_min);
-        const int LX = 2 * p.Gx - 1, LY = 2 * p.Gy - 1, sh = p.gx_shift + 2;
-        const float *tb = p.table + (int64_t)t.h * LY * LX;
-#pragma unroll
-        for (int j = 0; j < TBLK_PER; ++j) {
-            const int i = threadIdx.x + j * FUSED_THREADS;
-            const int row = i >> sh, kk = i & ((4 << p.gx_shift) - 1);
-            const bool on = row < nrows && kk < LX;
-            const float x = tb[on ? (int64_t)(dy_min + row + p.Gy - 1) * LX + (LX - 1 - kk) : 0];
-            tstage[j] = on ? x : 0.0f;
-        }
-    };
-    auto tblk_store = [&](float *dst, float ia) {
-#pragma unroll
-        for (int j = 0; j < TBLK_PER; ++j) dst[threadIdx.x + j * FUSED_THREADS] = tstage[j] * ia;
-    };
     // 1 / |alpha| of an item from the abs-means fetched for it (as begin_item computes it)
     auto inv_alpha_of = [&](float muq, float muk) {
         const float alpha = p.scale * muq * muk;
@@ -602,29 +588,21 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
                 wt[t] = axw[ax_wb - jy];
                 T[t] = qk_mfma<DK2>(ka[t], qB, cin);
             }
-        } else if (TABLE) {
+        } else if (TABLE || TBLK) {
+            const float *tcur = tab + (TBLK ? tpar * 4 * TB_CP : 0) + ax_ub;
+            const int jy0 = TBLK ? min((it * BV + BV - 1) >> p.gx_shift, p.Gy - 1) : 0;
+            // offset of the window of 16 keys of one grid row (Gx >= 16), scalar arithmetic
+            auto window = [&](int key0) { return (key0 & (p.Gx - 1)) + (jy0 - min(key0 >> p.gx_shift, p.Gy - 1)) * (2 * p.Gx); };
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
-                const int key0 = it * BV + 64 * g + 16 * t;  // 16 keys of one grid row (Gx >= 16)
-                const int jx0 = key0 & (p.Gx - 1), jy = min(key0 >> p.gx_shift, p.Gy - 1);
-                const float *win = tab2 + (ax_wb - jy) * TBP + ax_ub + jx0;
+                const int o0 = window(it * BV + 16 * t), o1 = window(it * BV + 64 + 16 * t);
+                const float *win = tcur + (g ? o1 : o0);
                 v16f cin;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) cin[r] = win[r];
-                wt[t] = 0.0f;
-                T[t] = qk_mfma<DK2>(ka[t], qB, cin);
-            }
-        } else if (TBLK) {
-            const float *tcur = tblk + tpar * TBLK_N;
-            const int jy_hi = min((it * BV + BV - 1) >> p.gx_shift, p.Gy - 1);
-#pragma unroll
-            for (int t = 0; t < KT; ++t) {
-                const int key0 = it * BV + 64 * g + 16 * t;  // 16 keys of one grid row (Gx >= 16)
-                const int jx0 = key0 & (p.Gx - 1), jy = min(key0 >> p.gx_shift, p.Gy - 1);
-                const float *win = tcur + ((ax_wb + jy_hi - jy) << (p.gx_shift + 2)) + ax_ub + jx0;
-                v16f cin;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) cin[r] = win[r];
+                for (int i = 0; i < 4; ++i) {
+                    const f4v x = *reinterpret_cast<const f4v *>(win + 4 * i);
+                    cin[4 * i] = x[0]; cin[4 * i + 1] = x[1]; cin[4 * i + 2] = x[2]; cin[4 * i + 3] = x[3];
+                }
                 wt[t] = 0.0f;
                 T[t] = qk_mfma<DK2>(ka[t], qB, cin);
             }
@@ -793,7 +771,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
 #pragma unroll
             for (int r = 0; r < 16; ++r) Of[cb][r] = fmaf(Of[cb][r], resc, __int_as_float(acc[cb][r]));
         if (TBLK && more)
-            tblk_store(tblk + (tpar ^ 1) * TBLK_N, sw ? inv_alpha_of(pend_muq, pend_muk) : inv_alpha);
+            table_store(tab + (tpar ^ 1) * 4 * TB_CP, sw ? inv_alpha_of(pend_muq, pend_muk) : inv_alpha);
         __builtin_amdgcn_sched_barrier(0);  // keep the wait at the very end of the block
         wait_vmem();      // this wave's copies for the next block have landed
         __syncthreads();  // everyone is done with this block's buffers, the next ones are complete
@@ -1005,7 +983,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     }
     if (TBLK) {
         tblk_load(cur, 0);
-        tblk_store(tblk, inv_alpha);
+        table_store(tab, inv_alpha);
     }
     wait_vmem();
     __syncthreads();
@@ -1074,8 +1052,7 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
     }
     switch (mode) {
 #define CASE(M) case M: hipLaunchKernelGGL((fused_kernel<DK, M, 1>), grid, block, 0, stream, p); break;
-        CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE)
-        CASE(BIAS_TABLE_BLK)
+        CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE_BLK)
 #undef CASE
         case BIAS_BF16_LDS:
             if constexpr (DK <= 3) {
