@@ -202,15 +202,15 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         const int esz = bias_dtype == BINATTN_BIAS_BF16 ? 2 : 4;
         if (!aligned(bias, esz)) return BINATTN_ERR_ALIGN;
         if (bias_dtype == BINATTN_BIAS_BF16) {
-            // LDS staging needs 16-byte aligned rows made of whole 16-byte chunks, and LDS
-            // room for two workgroups per CU (d <= 96); everything else takes register loads.
-            const bool rows16 = aligned(bias, 16) && bs.b % 8 == 0 && bs.h % 8 == 0 && bs.n % 8 == 0;
-            // (and a row pitch whose 7-fold fits a 32-bit lane offset)
-            // (d > 96 and at least two row blocks: 8-wave workgroups over row-block pairs)
-            // (N no multiple of 8: the chunk that straddles the row end must lie inside the row pitch)
-            const bool lds_ok = rows16 && (N % 8 == 0 || bs.n >= (N + 7) / 8 * 8) && bs.n < (1 << 27);
+            // LDS staging takes rows of any alignment whose pitch times 7 fits the copies' 32-bit
+            // lane offset.  d > 96 leaves no LDS room for two workgroups with bias tiles per compute
+            // unit: there the 8-wave forms are used (the single launch, or row-block pairs where there
+            // is more than one row block).  What is left loads its rows into registers, every
+            // lane its own: 64 cache lines per load instruction (N = 197, d = 64, 768 heads, one
+            // launch: 50.9 us that way, 42.2 us through LDS; N = 1370, d = 80: 90.5 / 85.5 us).
+            const bool lds_ok = bs.n < (1 << 27);
             wide_rows2 = lds_ok && s.DK == 4 && N > BR && raw == nullptr;
-            mode = (lds_ok && (s.DK <= 3 || wide_rows2)) ? BIAS_BF16_LDS : BIAS_BF16_VEC;
+            mode = (lds_ok && (s.DK <= 3 || raw != nullptr || wide_rows2)) ? BIAS_BF16_LDS : BIAS_BF16_VEC;
         } else {
             mode = BIAS_F32_VEC;
         }
@@ -226,6 +226,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     p.mu_k = use_mu ? mu_k : nullptr;
     p.bias = use_bias ? bias : nullptr;
     p.bs = bs;
+    p.bias_end = (int64_t)(B - 1) * bs.b + (int64_t)(H - 1) * bs.h + (int64_t)(N - 1) * bs.n + N;
     p.scale = scale;
     p.out = static_cast<uint16_t *>(out);
     p.os = os;

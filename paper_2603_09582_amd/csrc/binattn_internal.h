@@ -155,9 +155,9 @@ int launch_probe_valu(int op, int iters, int blocks, float *out, hipStream_t str
 
 enum BiasMode {
     BIAS_NONE = 0,
-    BIAS_BF16_VEC = 1,  // any element-aligned rows: 16-byte loads into registers, one block ahead
+    BIAS_BF16_VEC = 1,  // rows straight into registers, one block ahead (row pitch >= 2^27; d > 96 with one row block)
     BIAS_F32_VEC = 3,   // fp32 bias, 16-byte loads at use
-    BIAS_BF16_LDS = 5,  // rows 16-byte aligned, N % 8 == 0: tile staged global -> LDS asynchronously
+    BIAS_BF16_LDS = 5,  // rows of any alignment: tile staged global -> LDS asynchronously
     BIAS_AXIAL = 7,     // b_ij = y[iy - jy] + x[ix - jx] on a Gy x Gx token grid, tables held in LDS
     BIAS_TABLE = 9,     // b_ij = t[iy - jy][ix - jx]: the full relative-position table of the head in LDS (single-launch forms)
     BIAS_TABLE_BLK = 13, // the same table, only the rows a key block needs, staged per block
@@ -174,6 +174,7 @@ struct FusedParams {
     const float *mu_q, *mu_k;  // may be null (taken as 1)
     const void *bias;          // may be null
     Strides3 bs;               // bias element strides (batch, head, row)
+    int64_t bias_end;          // elements of the dense bias from its first to its last one
     float scale;
     uint16_t *out;
     Strides3 os;

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     // V operand rows of this many channel blocks are fetched from LDS before the
     // exponential phase (the rest just before their MFMAs): hides the LDS latency
     // where the register budget allows it.
-    constexpr int PRE = DK <= 2 ? DK : 1;
+    constexpr int PRE = DK <= 2 ? DK : (DK == 4 && MODE == BIAS_TABLE_BLK) ? 0 : 1;
     // key blocks between two removals of the accumulator's float-bit offset (a power of two)
     constexpr int REBASE = 8;
     __shared__ __attribute__((aligned(1024))) char bufA[NIMG * L::BYTES];
@@ -408,22 +408,41 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     };
 
     // ---- bias access ----------------------------------------------------------
-    auto dma_bias = [&](const BiasSrc &src, int blk, unsigned region) {  // region: LDS offset of the 8 KiB tile
-#pragma unroll
-        for (int j = 0; j < RGW; ++j)
-#pragma unroll
-            for (int gh = 0; gh < 2; ++gh) {
-                const int key0 = blk * BV + 64 * gh + 8 * dma_c[j];
-                if (key0 < N)  // (a last chunk that straddles N lies inside the row pitch: the host checked)
-                    dma16(src.base[j] + (blk * BV + 64 * gh) * 2, src.voff[j],
-                          region + ((rg0 + j) * 2 + gh) * 1024);
-            }
+    // The copies' source may start at any element: they take 2-byte-aligned addresses like ordinary
+    // loads do.  The last chunk of a row that straddles N reads on into whatever follows the row,
+    // which is still inside the tensor except behind its very last row: a wave whose rows
+    // include one that would read past bias_end leaves that chunk out (key limit N - 7 instead
+    // of N) and writes it element by element (bias_tail).
+    auto bias_klimit = [&](const Item &t, int blk) -> int {
+        if (blk * BV + BV <= N || (N & 7) == 0) return N;
+        const int row1 = min(t.rb * BR + wave * ROWS_PER_WAVE + ROWS_PER_WAVE, N) - 1;
+        const int64_t e1 = (int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)row1 * p.bs.n + ((N + 7) & ~7);
+        return e1 > p.bias_end ? N - 7 : N;
     };
-    auto dma_bias_one = [&](const BiasSrc &src, int blk, unsigned region, int idx) {  // copy idx = 2 j + gh of dma_bias
+    auto bias_tail = [&](const Item &t, int blk, unsigned region) {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int r = ln & 7, rg = ln >> 3, k0 = (N & ~7) - blk * BV;  // the chunk's first key inside the block
+        if (rg < rg0 || rg >= rg0 + RGW) return;
+        const int row = min(t.rb * BR + wave * ROWS_PER_WAVE + ln, N - 1);
+        const uint16_t *src = static_cast<const uint16_t *>(p.bias) + (int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h +
+                              (int64_t)row * p.bs.n + (N & ~7);
+        const unsigned dst = region + (rg * 2 + (k0 >> 6)) * 1024 + 128 * (r ^ (rg & 1)) + 16 * (((k0 >> 3) & 7) ^ r);
+#pragma unroll 1
+        for (int i = 0; i < (N & 7); ++i)
+            *reinterpret_cast<__attribute__((address_space(3))) uint16_t *>((size_t)(dst + 2 * i)) = src[i];
+    };
+    auto dma_bias_one = [&](const BiasSrc &src, int blk, int klim, unsigned region, int idx) {  // copy idx = 2 j + gh
         const int j = idx >> 1, gh = idx & 1;
         const int key0 = blk * BV + 64 * gh + 8 * dma_c[j];
-        if (key0 < N)
+        if (key0 < klim)
             dma16(src.base[j] + (blk * BV + 64 * gh) * 2, src.voff[j], region + ((rg0 + j) * 2 + gh) * 1024);
+    };
+    auto dma_bias = [&](const Item &t, const BiasSrc &src, int blk, unsigned region) {  // region: LDS offset of the 8 KiB tile
+        const int klim = bias_klimit(t, blk);
+        if (klim != N) bias_tail(t, blk, region);
+#pragma unroll
+        for (int idx = 0; idx < 2 * RGW; ++idx) dma_bias_one(src, blk, klim, region, idx);
     };
     u4v braw[8];  // the 64 bf16 bias values of this lane for the current block
     auto load_bias_vec = [&](const char *row, int blk) {  // BIAS_BF16_VEC: registers straight from global memory
@@ -541,6 +560,11 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         if (!ONEHEAD && it == 0 && (ROWS2 ? wreg : wave) == 0 && lane < DKP / 4)  // delta_v of this item, for its epilogue
             dma16(p.delta + (int64_t)cur.bh * DKP, 16 * lane, lds_offset(&sdelta[parity][isel][0]));
         if (sw && nxt.valid) fetch_item_regs(nxt);
+        int nklim = N;  // key limit of the shared bias tile's copies below
+        if (BIAS_DB && more && nblkidx * BV + BV > N) {
+            nklim = bias_klimit(cur, nblkidx);
+            if (nklim != N) bias_tail(cur, nblkidx, bnxt);
+        }
         if (TBLK && more) tblk_load(sw ? nxt : cur, nblkidx);  // lands during this block, stored at its end
 
         // Two 4-wave workgroups share a CU, and the SIMDs issue the older wave first: the
@@ -631,7 +655,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             load_bias_vec(sw ? bias_row_ptr(nxt) : brow, nblkidx);
         if (LDS_BIAS && !BIAS_DB && more) {
             wait_lds();                       // this block's tile has been read into registers
-            dma_bias(nsrc, nblkidx, bnxt);    // refill the wave's own region
+            dma_bias(sw ? nxt : cur, nsrc, nblkidx, bnxt);    // refill the wave's own region
         }
         //    the LDS reads of the P.V phase go out now and land during the exponentials
         v16i acc[DK];
@@ -738,7 +762,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             // The shared bias tile of the next block (BIAS_DB), one copy per tile of exponentials:
             // issued in one burst at the start of the block, beside the image copies, they fill
             // the memory pipeline's queue and hold the wave there (1.5 % of the block time).
-            if (BIAS_DB && more && t < 2 * RGW) dma_bias_one(nsrc, nblkidx, bnxt, t);
+            if (BIAS_DB && more && t < 2 * RGW) dma_bias_one(nsrc, nblkidx, nklim, bnxt, t);
         }
         }
         l_run = fmaf(l_run, resc, ls0 + ls1);
@@ -809,7 +833,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         // the order of use: the bias tile, this lane's query chunks, the V rows, the key chunks.
         if (LDS_BIAS) {
             bsrc = bias_dma_src(cur);
-            dma_bias(bsrc, 0, lds_offset(bA));
+            dma_bias(cur, bsrc, 0, lds_offset(bA));
         }
         if (MODE == BIAS_BF16_VEC) load_bias_vec(bias_row_ptr(cur), 0);
         // this lane's query row: the chunks of the sign words its B operand needs (channels
@@ -979,7 +1003,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     begin_item(cur);
     if (!ONEHEAD) {
         if (MODE == BIAS_BF16_VEC) load_bias_vec(brow, 0);
-        if (LDS_BIAS) dma_bias(bsrc, 0, lds_offset(bA));
+        if (LDS_BIAS) dma_bias(cur, bsrc, 0, lds_offset(bA));
     }
     if (TBLK) {
         tblk_load(cur, 0);
@@ -1088,13 +1112,8 @@ int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
     switch (mode) {
 #define CASE(M) case M: hipLaunchKernelGGL((fused_kernel<DK, M, 2, WIDE_ONEHEAD>), grid, block, 0, stream, p); break;
         CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE)
+        CASE(BIAS_BF16_LDS)
 #undef CASE
-        case BIAS_BF16_LDS:
-            if constexpr (DK <= 3) {
-                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2, WIDE_ONEHEAD>), grid, block, 0, stream, p);
-                break;
-            }
-            return BINATTN_ERR_SHAPE;
         default: return BINATTN_ERR_DTYPE;
     }
     return check_launch();

@@ -1,0 +1,65 @@
+"""Where the rows of a dense bias lie in memory (alignment of the base, row pitch, what follows the last row)
+never changes the result: every layout against the oracle, and bit-identical to the contiguous one."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_09582_amd import binding as ba
+from tests.test_gpu_parity import check_close, dev, gpu_out_f64, oracle_algorithm1, say, small_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def placed(bias, offset, extra):
+    """The same [H, N, N] values with the first element at `offset` and rows N + extra apart, as the very end
+    of a buffer whose other elements are NaN."""
+    H, N, _ = bias.shape
+    pitch = N + extra
+    n = (H * N - 1) * pitch + N
+    store = torch.full((offset + n,), float("nan"), dtype=bias.dtype, device="cuda")
+    view = store[offset:].as_strided((H, N, N), (N * pitch, pitch, 1))
+    view.copy_(bias)
+    return view
+
+
+# (block edges and remainders of the 8-key copy chunks; d = 64 with an even batch and >= 8 key blocks shares
+# its tiles between two batch entries, d = 128 takes 8-wave workgroups)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,H,N,d", [(1, 2, 1, 64), (1, 3, 7, 64), (2, 1, 127, 72), (1, 2, 129, 64), (2, 2, 197, 64),
+                                     (1, 2, 255, 104), (130, 2, 131, 64), (1, 1, 257, 72), (1, 2, 391, 128), (2, 2, 642, 80),
+                                     (3, 1, 577, 64), (2, 2, 577, 32), (4, 1, 965, 64), (2, 1, 1030, 64)])
+def test_bias_rows_of_any_alignment(B, H, N, d, dtype):
+    x = small_inputs(B, H, N, d, 900 + N)
+    bias = (x.bias.float() * 40.0).to(dtype)  # strong enough that every entry shows in the output
+    q, k, v, db = dev(x.q), dev(x.k), dev(x.v), dev(bias)
+    ws = ba.alloc_workspace(B, H, N, d)
+    qb, kb, mq, mk = ba.pack_qk(q, k)
+    plain = {}
+    for offset, extra in [(0, 0), (1, 0), (0, 1), (3, 3), (0, -N % 8), (8, 8)]:
+        say(f"bias rows B={B} H={H} N={N} d={d} {dtype} offset={offset} pitch=N+{extra}")
+        pb = placed(db, offset, extra)
+        for name, out in (("packed", ba.forward(qb, kb, mq, mk, v, pb, x.scale, workspace=ws)),
+                          ("one call", ba.attention(q, k, v, pb, x.scale, workspace=ws))):
+            torch.cuda.synchronize()
+            if name not in plain:
+                plain[name] = out
+                if B * H * N <= 4096:
+                    ref = oracle_algorithm1(x, bias)
+                    check_close(gpu_out_f64(out), ref, f"{name}: out vs Alg. 1")
+            assert torch.equal(out, plain[name]), (name, offset, extra)
+
+
+@pytest.mark.parametrize("N,d", [(9, 64), (5, 128)])
+def test_bias_rows_further_apart_than_a_copy_offset_reaches(N, d):
+    """Row pitches from 2^27 elements on take the register path."""
+    x = small_inputs(1, 1, N, d, 77)
+    pitch = 1 << 27
+    store = torch.empty((N - 1) * pitch + N, dtype=torch.bfloat16, device="cuda")
+    view = store.as_strided((1, N, N), (N * pitch, pitch, 1))
+    view.copy_(dev(x.bias))
+    q, k, v = dev(x.q), dev(x.k), dev(x.v)
+    qb, kb, mq, mk = ba.pack_qk(q, k)
+    ref = oracle_algorithm1(x, x.bias)
+    for out in (ba.forward(qb, kb, mq, mk, v, view, x.scale), ba.attention(q, k, v, view, x.scale)):
+        torch.cuda.synchronize()
+        check_close(gpu_out_f64(out), ref, "giant pitch: out vs Alg. 1")
