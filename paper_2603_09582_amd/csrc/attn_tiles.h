@@ -63,7 +63,7 @@ __device__ __forceinline__ void load_k_operand(const char *img, int t, int m, in
 }
 
 // QK tile: for this lane's query, register r of the result is
-// cin[r] + (s_i . t_j) with key j = block start + 64 g + 16 t + r.
+// cin[r] + (s_i . t_j) with key j = block start + 32 t + 16 g + r.
 template <int DK2>
 __device__ __forceinline__ v16f qk_mfma(const v4i ka[DK2], const v4i qB[DK2], v16f cin) {
 #pragma unroll

@@ -3,7 +3,7 @@
 // softmax, unsigned 8-bit P, int8 P.V with int32 accumulation, fp32 carry.
 //
 // One wave owns 32 query rows; a lane owns ONE query row and half of the keys
-// of every block (g = lane / 32 selects keys [64 g, 64 g + 64) of the block).
+// of every block: of tile t's 32 keys those at 32 t + 16 g + [0, 16), g = lane / 32.
 // The vector ALU is the binding unit of this kernel, so the design removes
 // vector instructions wherever another unit can do the work.  Per key block of
 // BV = 128 keys:
@@ -108,6 +108,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     // exponential phase (the rest just before their MFMAs): hides the LDS latency
     // where the register budget allows it.
     constexpr int PRE = DK <= 2 ? DK : (DK == 4 && MODE == BIAS_TABLE_BLK) ? 0 : 1;
+    // The generated biases leave the memory pipeline idle: there the prefetched channel blocks'
+    // matrix instructions of a tile are issued right behind its codes and run under the next
+    // tile's exponentials.
+    constexpr bool PV_EARLY = MODE == BIAS_AXIAL || MODE == BIAS_TABLE_BLK;
     // key blocks between two removals of the accumulator's float-bit offset (a power of two)
     constexpr int REBASE = 8;
     __shared__ __attribute__((aligned(1024))) char bufA[NIMG * L::BYTES];
@@ -446,29 +450,30 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     };
     u4v braw[8];  // the 64 bf16 bias values of this lane for the current block
     auto load_bias_vec = [&](const char *row, int blk) {  // BIAS_BF16_VEC: registers straight from global memory
-        const int k0 = blk * BV + 64 * g;
+        const int k0 = blk * BV + 16 * g;
         const uint16_t *src = reinterpret_cast<const uint16_t *>(row) + k0;
         if (blk * BV + BV <= N) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) braw[i] = *reinterpret_cast<const u4v_a2 *>(src + 8 * i);
+            for (int i = 0; i < 8; ++i) braw[i] = *reinterpret_cast<const u4v_a2 *>(src + 32 * (i >> 1) + 8 * (i & 1));
         } else {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                if (k0 + 8 * i + 8 <= N) {
-                    braw[i] = *reinterpret_cast<const u4v_a2 *>(src + 8 * i);
+                const int o = 32 * (i >> 1) + 8 * (i & 1);
+                if (k0 + o + 8 <= N) {
+                    braw[i] = *reinterpret_cast<const u4v_a2 *>(src + o);
                 } else {
                     unsigned e[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) e[j] = (k0 + 8 * i + j < N) ? src[8 * i + j] : 0u;
+                    for (int j = 0; j < 8; ++j) e[j] = (k0 + o + j < N) ? src[o + j] : 0u;
                     braw[i] = u4v{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16),
                                   e[6] | (e[7] << 16)};
                 }
             }
         }
     };
-    // accumulator input of QK tile t: bias / alpha for keys blk*BV + 64 g + 16 t + [0, 16)
+    // accumulator input of QK tile t: bias / alpha for keys blk*BV + 32 t + 16 g + [0, 16)
     auto bias_tile = [&](int blk, int t) -> v16f {
-        const int k0 = blk * BV + 64 * g + 16 * t;
+        const int k0 = blk * BV + 32 * t + 16 * g;
         v16f bt;
         if (MODE == BIAS_NONE) {
 #pragma unroll
@@ -578,17 +583,19 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         }
         // 1. all LDS reads of the logit phase go out together: bias tile, key rows
         if (LDS_BIAS) {
-            // chunk i of this lane's row sits at row + 16 (i ^ (m & 7)) = (row + 16 (m & 7)) ^ 16 i (rows are
+            // chunk c of this lane's row sits at row + 16 (c ^ (m & 7)) = (row + 16 (m & 7)) ^ 16 c (rows are
             // 128-byte aligned); the lane number is made opaque so that the addresses are formed here
             // instead of being carried through the block loop in eight registers per buffer
             int ln = lane;
             asm volatile("" : "+v"(ln));
             const int mm = ln & 31, gg = ln >> 5;
-            const unsigned a0 = lds_offset(bbuf) + ((mm >> 3) * 2 + gg) * 1024 +
-                                128 * ((mm & 7) ^ ((mm >> 3) & 1)) + 16 * (mm & 7);
+            const unsigned a0 = lds_offset(bbuf) + (mm >> 3) * 2048 + 128 * ((mm & 7) ^ ((mm >> 3) & 1)) +
+                                16 * ((mm & 7) ^ (2 * gg));
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                braw[i] = *reinterpret_cast<const __attribute__((address_space(3))) u4v *>((size_t)(a0 ^ (16u * i)));
+            for (int i = 0; i < 8; ++i) {  // chunk 2 gg + 4 (t & 1) + i % 2 of the 64-key half t / 2, t = i / 2
+                const unsigned c = 16u * (4 * ((i >> 1) & 1) + (i & 1));
+                braw[i] = *reinterpret_cast<const __attribute__((address_space(3))) u4v *>((size_t)((a0 ^ c) + 1024u * (i >> 2)));
+            }
         }
         v4i ka[KT][DK2];
 #pragma unroll
@@ -600,7 +607,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         if (AXIAL) {
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
-                const int key0 = it * BV + 64 * g + 16 * t;
+                const int key0 = it * BV + 32 * t + 16 * g;
                 const int jx0 = key0 & (p.Gx - 1), jy = min(key0 >> p.gx_shift, p.Gy - 1);
                 const float *win = axu + ax_ub + jx0;
                 v16f cin;
@@ -619,7 +626,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             auto window = [&](int key0) { return (key0 & (p.Gx - 1)) + (jy0 - min(key0 >> p.gx_shift, p.Gy - 1)) * (2 * p.Gx); };
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
-                const int o0 = window(it * BV + 16 * t), o1 = window(it * BV + 64 + 16 * t);
+                const int o0 = window(it * BV + 32 * t), o1 = window(it * BV + 32 * t + 16);
                 const float *win = tcur + (g ? o1 : o0);
                 v16f cin;
 #pragma unroll
@@ -670,7 +677,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             }
 #pragma unroll
             for (int t = 0; t < KT; ++t)
-                va[cb][t] = *reinterpret_cast<const v4i *>(ibuf + L::V_OFF + (32 * cb + m) * L::VP + 64 * g + 16 * t);
+                va[cb][t] = *reinterpret_cast<const v4i *>(ibuf + L::V_OFF + (32 * cb + m) * L::VP + 32 * t + 16 * g);
         }
 
         const bool ragged = it * BV + BV > N;
@@ -679,7 +686,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             for (int t = 0; t < KT; ++t)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    if (it * BV + 64 * g + 16 * t + r >= N)
+                    if (it * BV + 32 * t + 16 * g + r >= N)
                         T[t][r] = LUT ? PV_MAGIC_F + (float)(4 * d + 2) : -INFINITY;
         }
 
@@ -747,6 +754,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         // 3. p = 255 * exp(S - m), its row sum, and the byte codes
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
+            if (t == 0) __builtin_amdgcn_sched_barrier(0);
             const float ce = AXIAL ? fmaf(wt[t], a2, cexp) : cexp;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -759,6 +767,12 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
                 }
                 pk[t][i] = (int)(w ^ 0x80808080u);  // code - 128 as signed bytes
             }
+            if constexpr (PV_EARLY) {
+#pragma unroll
+                for (int cb = 0; cb < PRE; ++cb)
+                    acc[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(va[cb][t], pk[t], acc[cb], 0, 0, 0);
+                if (AXIAL) __builtin_amdgcn_sched_barrier(0);
+            }
             // The shared bias tile of the next block (BIAS_DB), one copy per tile of exponentials:
             // issued in one burst at the start of the block, beside the image copies, they fill
             // the memory pipeline's queue and hold the wave there (1.5 % of the block time).
@@ -769,6 +783,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         rho = fmaf(rho, resc, 1.0f);
 
         // 4. P~ . V~ : the prefetched channel blocks as interleaved MFMA chains ...
+        if (!PV_EARLY)
 #pragma unroll
         for (int t = 0; t < KT; ++t)
 #pragma unroll
@@ -785,7 +800,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             }
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
-                const v4i a = *reinterpret_cast<const v4i *>(ibuf + L::V_OFF + (32 * cb + m) * L::VP + 64 * g + 16 * t);
+                const v4i a = *reinterpret_cast<const v4i *>(ibuf + L::V_OFF + (32 * cb + m) * L::VP + 32 * t + 16 * g);
                 acc[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, pk[t], acc[cb], 0, 0, 0);
             }
         }
@@ -822,7 +837,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         constexpr int NT = FUSED_THREADS * NB;
         __shared__ int sabs[DKP];            // per-channel absmax of V (bit patterns)
         __shared__ __attribute__((aligned(16))) float srcp[DKP];  // the quantiser's multipliers
-        __shared__ float ssum[2][NT / 64];   // |q| and |k| partial sums per wave
+        // |q| and |k| partial sums of eight waves: the 4-wave form keeps what waves w and w + 4 of the
+        // 8-wave form add in two sums, so that both forms give the same abs-means to the last bit
+        constexpr int NS = ONEHEAD4 ? 2 : 1;
+        __shared__ float ssum[2][8];
         const int C16 = d / 8, nblk = p.nblk;
         auto imgp = [&](int blk) -> char * { return blk ? bufB : bufA; };
         const uint16_t *qb_ = p.xq + (int64_t)cur.b * p.xqs.b + (int64_t)cur.h * p.xqs.h;
@@ -840,7 +858,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         // 64 s + 32 g + 8 j); addresses are clamped into the row, unused chunks are skipped below
         const int qrow = cur.rb * BR + wave * ROWS_PER_WAVE + m;
         u4 qx[DK2][4];
-        float qsum = 0.0f;
+        float qsum[NS] = {}, ksum[NS] = {};
         auto load_q_row = [&](int row) {
 #pragma unroll
             for (int sI = 0; sI < DK2; ++sI)
@@ -850,13 +868,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
                     qx[sI][j] = *reinterpret_cast<const u4 *>(qb_ + (int64_t)min(row, N - 1) * p.xqs.n + (c0 < d ? c0 : 0));
                 }
         };
-        auto q_row_words = [&](int row, unsigned *words) {  // FP4 words of the loaded row, |q| into qsum
+        auto q_row_words = [&](int row, unsigned *words, float &sum) {  // FP4 words of the loaded row, |q| into sum
 #pragma unroll
             for (int sI = 0; sI < DK2; ++sI)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    words[4 * sI + j] = row < N && 32 * (2 * sI + g) + 8 * j < d ? fp4_pm1_abs(qx[sI][j], qsum) : 0u;
-            if (qsum != qsum) {  // a NaN among this lane's queries: the words once more, exactly
+                    words[4 * sI + j] = row < N && 32 * (2 * sI + g) + 8 * j < d ? fp4_pm1_abs(qx[sI][j], sum) : 0u;
+            if (sum != sum) {  // a NaN among this lane's queries: the words once more, exactly
 #pragma unroll
                 for (int i = 0; i < PQ; ++i)
                     if (words[i] != 0u)
@@ -904,13 +922,12 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         }
         if (threadIdx.x < DKP) sabs[threadIdx.x] = 0;
         // the sign words of the query row (the oldest loads: V and K may still be in flight)
-        q_row_words(qrow, pend_q);
+        q_row_words(qrow, pend_q, qsum[0]);
         // (ONEHEAD4: the lane's row in the second row block takes the same registers; its loads
         // land during the key phase below)
         if constexpr (ONEHEAD4) load_q_row(qrow + BR);
         __syncthreads();
         // keys: sign bits -> FP4 codes of +-1 at the row position the QK tile reads
-        float ksum = 0.0f;
 #pragma unroll
         for (int kk = 0; kk < KPT; ++kk) {
             const int i = threadIdx.x + kk * NT;
@@ -919,10 +936,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             if (blk < nblk && key < N) {
                 *reinterpret_cast<unsigned *>(imgp(blk) + L::K_OFF + pos * L::KP +
                                               16 * k_chunk(pos, c8 >> 2, L::KP) + 4 * (c8 & 3)) =
-                    fp4_pm1_abs(kx[kk], ksum);
+                    fp4_pm1_abs(kx[kk], ksum[kk % NS]);
             }
         }
-        if (ksum != ksum) {  // a NaN among this thread's keys: its words once more, exactly
+        if (ksum[0] != ksum[0] || ksum[NS - 1] != ksum[NS - 1]) {  // a NaN among this thread's keys: its words once more, exactly
             for (int i = threadIdx.x; i < KPT * NT; i += NT) {
                 const int ic = div_c16(i), c8 = i - ic * C16, pos = ic % BV, blk = ic / BV;
                 const int key = blk * BV + key_of_position(pos);
@@ -932,7 +949,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
                         fp4_pm1_exact(*reinterpret_cast<const u4 *>(kb_ + (int64_t)key * p.xks.n + 8 * c8));
             }
         }
-        if constexpr (ONEHEAD4) q_row_words(qrow + BR, pend_q2);
+        if constexpr (ONEHEAD4) q_row_words(qrow + BR, pend_q2, qsum[1]);
         // V: absmax per channel through LDS integer maxima
         if (von) {
             unsigned mb[4] = {0u, 0u, 0u, 0u};
@@ -951,13 +968,18 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         }
         // abs-means: wave sums, then the eight partials
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            qsum += __shfl_down(qsum, off, 64);
-            ksum += __shfl_down(ksum, off, 64);
-        }
+        for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                qsum[i] += __shfl_down(qsum[i], off, 64);
+                ksum[i] += __shfl_down(ksum[i], off, 64);
+            }
         if (lane == 0) {
-            ssum[0][threadIdx.x >> 6] = qsum;
-            ssum[1][threadIdx.x >> 6] = ksum;
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                ssum[0][(threadIdx.x >> 6) + 4 * i] = qsum[i];
+                ssum[1][(threadIdx.x >> 6) + 4 * i] = ksum[i];
+            }
         }
         __syncthreads();
         if (threadIdx.x < 8 * C16) {
@@ -967,7 +989,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         }
         float tq = 0.0f, tk = 0.0f;
 #pragma unroll
-        for (int i = 0; i < NT / 64; ++i) {
+        for (int i = 0; i < 8; ++i) {
             tq += ssum[0][i];
             tk += ssum[1][i];
         }

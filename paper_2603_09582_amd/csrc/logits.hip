@@ -82,7 +82,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void logits_fp4_kernel(
         for (int t = 0; t < KT; ++t) {
             const v16f zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             const v16f acc = qk_tile<DK>(buf, t, m, g, qB, zero);
-            const int k0 = blk * BV + 64 * g + 16 * t;
+            const int k0 = blk * BV + 32 * t + 16 * g;
             if (ROWSUM) {  // keys beyond N are zero rows of the image: they add nothing
 #pragma unroll
                 for (int i = 0; i < 16; ++i) rs += acc[i];

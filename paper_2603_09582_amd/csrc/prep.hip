@@ -236,7 +236,7 @@ __global__ __launch_bounds__(PREP_THREADS) void v_quant_kernel(
 
 // Inverse of key_of_position: where key offset o (0 <= o < BV) sits in a block image.
 __device__ __forceinline__ int position_of_key(int o) {
-    const int g = o >> 6, t = (o >> 4) & 3, r = o & 15;
+    const int t = o >> 5, g = (o >> 4) & 1, r = o & 15;
     return 32 * t + 8 * (r >> 2) + 4 * g + (r & 3);
 }
 

@@ -51,14 +51,14 @@ __device__ __forceinline__ unsigned fp4_pm1_exact(u4 w) {
 
 // Row position inside a key block <-> key offset.  The fused kernel's lane
 // (g = lane / 32) holds, for MFMA tile t and accumulator register r, the key
-// j0 + 64 g + 16 t + r; the MFMA puts accumulator register r of lane group g
+// j0 + 32 t + 16 g + r; the MFMA puts accumulator register r of lane group g
 // at tile row m = 8 (r / 4) + 4 g + (r % 4).  Rows are stored at position
 // 32 t + m so that the A operand reads consecutive LDS rows.
 __device__ __forceinline__ int key_of_position(int pos) {
     const int t = pos >> 5, m = pos & 31;
     const int g = (m >> 2) & 1;
     const int r = ((m >> 3) << 2) | (m & 3);
-    return 64 * g + 16 * t + r;
+    return 32 * t + 16 * g + r;
 }
 
 __device__ __forceinline__ void unpack8(u4 w, float f[8]) {

@@ -44,3 +44,20 @@ def test_signs_of_special_values_without_sign_words(N, d):
     got = ba.attention(q, k, v, None, d ** -0.5, flags=ba.FLAG_NO_MU)
     # the same signs, the same scale: the same logits, so the same codes on both paths
     assert torch.equal(want, got)
+
+
+@pytest.mark.parametrize("N,d", [(1, 64), (63, 64), (129, 32), (197, 64), (256, 72), (200, 96)])
+def test_both_single_launch_forms_give_the_same_bits(N, d):
+    """The 4-wave form adds the magnitudes in the 8-wave form's order: abs-means and outputs agree exactly."""
+    B, H = 2, 130
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + d)
+    q, k, v = (torch.randn(B, H, N, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    bias = torch.randn(H, N, N, generator=g, device="cuda").to(torch.bfloat16)
+    res = []
+    for flags in (0, ba.FLAG_WIDE8):
+        mq, mk = torch.zeros(B, H, device="cuda"), torch.zeros(B, H, device="cuda")
+        res.append((ba.forward_fused(q, k, v, bias, d ** -0.5, mu_q=mq, mu_k=mk, flags=flags), mq, mk))
+    torch.cuda.synchronize()
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
