@@ -277,6 +277,13 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     // Long sequences with a batch-shared, LDS-staged bias: pair batch entries in one
     // workgroup so that the bias stream is fetched once per pair.
     p.nb = (mode == BIAS_BF16_LDS && bs.b == 0 && B % 2 == 0 && s.DK <= 2 && s.nblk >= 8) ? 2 : 1;
+    // A bias shared over the batch and larger than the 256 MB Infinity Cache streams through once per
+    // call: its copies are marked as not worth keeping.  Only where rows start on 128-byte lines (else two
+    // blocks read the same line).  Measured with / without: N = 16384, 16 heads 2764 / 2805 us; N = 4096, 12 heads,
+    // batch 8 518 / 527; but N = 2048, 8 heads (67 MB) 180.0 / 178.6 and N = 3137 (odd rows) 156 / 148.
+    if (p.nb == 2 && aligned(bias, 128) && bs.h % 64 == 0 && bs.n % 64 == 0 &&
+        (int64_t)H * N * bs.n * 2 > ((int64_t)256 << 20))
+        p.wide = 4;
     p.total_wg = p.nrb * H * (B / p.nb);
     switch (s.DK) {
         case 1: return launch_fused_dk<1>(p, mode, st);

@@ -102,13 +102,21 @@ __device__ __forceinline__ const T *uniform_ptr(const T *p) {
 // sbase + voff (sbase wave-uniform, kept in scalar registers; voff this lane's byte offset),
 // land at lds_base + 16 L (lds_base wave-uniform).  Issued through inline assembly so that
 // the compiler does not serialise later LDS reads of OTHER buffers against it; the callers
-// order it by hand (wait_vmem + barrier before the data is read).
+// order it by hand (wait_vmem + barrier before the data is read).  ONCE: data that no other
+// workgroup is about to read ("nt": first to leave the caches).
+template <bool ONCE = false>
 __device__ __forceinline__ void dma16(const void *sbase, unsigned voff, unsigned lds_base) {
     const uint64_t u = reinterpret_cast<uint64_t>(uniform_ptr(static_cast<const char *>(sbase)));
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(voff), "s"(u)
-                 : "memory", "m0");
+    if constexpr (ONCE)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :
+                     : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(voff), "s"(u)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(voff), "s"(u)
+                     : "memory", "m0");
 }
 
 // Asynchronous copy of one block image (L::BYTES, a multiple of 1 KiB) from

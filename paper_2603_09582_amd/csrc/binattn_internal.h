@@ -182,7 +182,7 @@ struct FusedParams {
     const float *delta;
     int B, H, N, d, nblk, nrb, total_wg;
     int nb;              // batch entries per workgroup (1 or 2)
-    int wide;            // 0; 1 / 3: single-launch forms (8 / 4 waves); 2: 8-wave workgroups over row-block pairs (nrb counts pairs)
+    int wide;            // 0; 1 / 3: single-launch forms (8 / 4 waves); 2: 8-wave workgroups over row-block pairs (nrb counts pairs); 4: paired form, bias copied past the caches
     // single-launch short-sequence kernel: the bf16 inputs, whether mu is applied, optional mu exports
     const uint16_t *xq, *xk, *xv;
     Strides3 xqs, xks, xvs;

@@ -88,7 +88,10 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 // the same prologue with 256 threads, then the head's two 128-row blocks one after the other
 // as two items of the persistent stream (the images stay where they are).  Two such workgroups
 // share a compute unit, so one head's loads and preparation overlap the other's block loop.
-enum { WIDE_NONE = 0, WIDE_ONEHEAD = 1, WIDE_ROWS2 = 2, WIDE_ONEHEAD4 = 3 };
+//
+// WIDE_PAIR_ONCE is the paired form (NB = 2) with the bias copies marked as not worth keeping in the
+// caches, for biases larger than those.
+enum { WIDE_NONE = 0, WIDE_ONEHEAD = 1, WIDE_ROWS2 = 2, WIDE_ONEHEAD4 = 3, WIDE_PAIR_ONCE = 4 };
 template <int DK, int MODE, int NB, int WIDE = WIDE_NONE>
 __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const FusedParams p) {
     using L = Image<DK>;
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     constexpr bool ONEHEAD = WIDE == WIDE_ONEHEAD || ONEHEAD4, ROWS2 = WIDE == WIDE_ROWS2;
     static_assert(WIDE == WIDE_NONE || ONEHEAD4 || NB == 2, "the wide forms use 8 waves");
     static_assert(!ONEHEAD4 || NB == 1, "the 4-wave single-launch form");
-    constexpr bool PAIR = NB == 2 && WIDE == WIDE_NONE;  // two batch entries sharing bias tiles
+    constexpr bool PAIR = NB == 2 && (WIDE == WIDE_NONE || WIDE == WIDE_PAIR_ONCE);  // two batch entries sharing bias tiles
     constexpr int NWI = ROWS2 ? 8 : 4;                   // waves that copy one operand image
     constexpr int NIMG = PAIR ? 2 : 1;          // operand images per buffer
     constexpr bool PERSIST = NB == 1 || ROWS2;
@@ -118,7 +121,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     __shared__ __attribute__((aligned(1024))) char bufB[NIMG * L::BYTES];
     // BIAS_BF16_LDS: staging of the 32 x 128 bias tiles, 8 KiB per 32-row group.
     // NB = 1: one region per wave, private to it.  NB = 2: two buffers shared by the pair.
-    __shared__ __attribute__((aligned(1024))) char biasA[LDS_BIAS ? (NB == 2 && WIDE != WIDE_NONE ? 8 : 4) * 8192 : 1024];
+    __shared__ __attribute__((aligned(1024))) char biasA[LDS_BIAS ? (NB == 2 && !PAIR ? 8 : 4) * 8192 : 1024];
     __shared__ __attribute__((aligned(1024))) char biasB[BIAS_DB ? 4 * 8192 : 1024];
     // BIAS_AXIAL: the head's two relative-position tables, already divided by alpha.
     //   axu: four copies of the REVERSED x table, copy j shifted by j entries, so that every
@@ -169,7 +172,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);  // 32-row group
     const int bsel = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);        // half of the workgroup
     const int isel = PAIR ? bsel : 0;                // which resident image / delta copy
-    const int wreg = (NB == 2 && WIDE != WIDE_NONE) ? 4 * bsel + wave : wave;  // this wave's private bias region / copy share
+    const int wreg = (NB == 2 && !PAIR) ? 4 * bsel + wave : wave;  // this wave's private bias region / copy share
     const int m = lane & 31, g = lane >> 5;
     const int N = p.N, d = p.d, W = (d + 31) / 32;
     const int nbp = p.B / NIMG;
@@ -440,7 +443,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
         const int j = idx >> 1, gh = idx & 1;
         const int key0 = blk * BV + 64 * gh + 8 * dma_c[j];
         if (key0 < klim)
-            dma16(src.base[j] + (blk * BV + 64 * gh) * 2, src.voff[j], region + ((rg0 + j) * 2 + gh) * 1024);
+            dma16<WIDE == WIDE_PAIR_ONCE>(src.base[j] + (blk * BV + 64 * gh) * 2, src.voff[j],
+                                          region + ((rg0 + j) * 2 + gh) * 1024);
     };
     auto dma_bias = [&](const Item &t, const BiasSrc &src, int blk, unsigned region) {  // region: LDS offset of the 8 KiB tile
         const int klim = bias_klimit(t, blk);
@@ -1091,7 +1095,10 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
     if (p.nb == 2) {
         if constexpr (DK <= 2) {
             if (mode != BIAS_BF16_LDS) return BINATTN_ERR_DTYPE;
-            hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2>), grid, block, 0, stream, p);
+            if (p.wide == WIDE_PAIR_ONCE)
+                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2, WIDE_PAIR_ONCE>), grid, block, 0, stream, p);
+            else
+                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2>), grid, block, 0, stream, p);
             return check_launch();
         }
         return BINATTN_ERR_SHAPE;
