@@ -128,7 +128,7 @@ int binattn_prepare_kv(const uint32_t *k_bits, const void *v, const int64_t v_st
  *   bias       : [.., N, N] of bias_dtype, element strides bias_strides for
  *                (batch, head, row); a batch stride of 0 shares one bias over
  *                the batch.  May be NULL (no bias).  Rows need only element
- *                alignment (bf16 tiles are staged through LDS wherever rows
+ *                alignment (tiles are staged through LDS wherever rows
  *                lie); elements between the rows may be read and are ignored,
  *                nothing before the first or behind the last element is read.
  *   scale      : multiplies the +-1 inner product (1/sqrt(d) in Eq. 6); the

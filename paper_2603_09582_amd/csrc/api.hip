@@ -201,19 +201,17 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         bs.b = bias_strides[0]; bs.h = bias_strides[1]; bs.n = bias_strides[2];
         const int esz = bias_dtype == BINATTN_BIAS_BF16 ? 2 : 4;
         if (!aligned(bias, esz)) return BINATTN_ERR_ALIGN;
-        if (bias_dtype == BINATTN_BIAS_BF16) {
-            // LDS staging takes rows of any alignment whose pitch times 7 fits the copies' 32-bit
-            // lane offset.  d > 96 leaves no LDS room for two workgroups with bias tiles per compute
-            // unit: there the 8-wave forms are used (the single launch, or row-block pairs where there
-            // is more than one row block).  What is left loads its rows into registers, every
-            // lane its own: 64 cache lines per load instruction (N = 197, d = 64, 768 heads, one
-            // launch: 50.9 us that way, 42.2 us through LDS; N = 1370, d = 80: 90.5 / 85.5 us).
-            const bool lds_ok = bs.n < (1 << 27);
-            wide_rows2 = lds_ok && s.DK == 4 && N > BR && raw == nullptr;
-            mode = (lds_ok && (s.DK <= 3 || raw != nullptr || wide_rows2)) ? BIAS_BF16_LDS : BIAS_BF16_VEC;
-        } else {
-            mode = BIAS_F32_VEC;
-        }
+        // LDS staging takes rows of any alignment whose pitch times 7 fits the copies' 32-bit lane
+        // offset.  d > 96 leaves no LDS room for two workgroups with bias tiles per compute unit: there
+        // the 8-wave forms are used (the single launch, or row-block pairs where there is more than
+        // one row block).  What is left loads its rows into registers, every lane its own: 64 cache
+        // lines per load instruction (N = 197, d = 64, 768 heads, one launch: 50.9 us that way,
+        // 42.2 us through LDS; N = 1370, d = 80: 90.5 / 85.5 us).
+        const bool lds_ok = bs.n < (1 << 27);
+        wide_rows2 = lds_ok && s.DK == 4 && N > BR && raw == nullptr;
+        const bool lds = lds_ok && (s.DK <= 3 || raw != nullptr || wide_rows2);
+        if (bias_dtype == BINATTN_BIAS_BF16) mode = lds ? BIAS_BF16_LDS : BIAS_BF16_VEC;
+        else mode = lds ? BIAS_F32_LDS : BIAS_F32_VEC;
     }
     if (!raw && (rc = check_workspace(workspace, workspace_bytes, w)) != BINATTN_OK) return rc;
 

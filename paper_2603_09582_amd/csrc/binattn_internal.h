@@ -156,7 +156,8 @@ int launch_probe_valu(int op, int iters, int blocks, float *out, hipStream_t str
 enum BiasMode {
     BIAS_NONE = 0,
     BIAS_BF16_VEC = 1,  // rows straight into registers, one block ahead (row pitch >= 2^27; d > 96 with one row block)
-    BIAS_F32_VEC = 3,   // fp32 bias, 16-byte loads at use
+    BIAS_F32_VEC = 3,   // fp32 rows, 16-byte loads at use (where BIAS_BF16_VEC would be taken)
+    BIAS_F32_LDS = 15,  // fp32 rows of any alignment: most of the tile staged global -> LDS, the rest into registers
     BIAS_BF16_LDS = 5,  // rows of any alignment: tile staged global -> LDS asynchronously
     BIAS_AXIAL = 7,     // b_ij = y[iy - jy] + x[ix - jx] on a Gy x Gx token grid, tables held in LDS
     BIAS_TABLE = 9,     // b_ij = t[iy - jy][ix - jx]: the full relative-position table of the head in LDS (single-launch forms)

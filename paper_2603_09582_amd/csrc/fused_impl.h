@@ -31,6 +31,8 @@
 // the factor 255 is already inside the row sum).
 #pragma once
 
+#include <type_traits>
+
 #include "attn_tiles.h"
 #include "quant_v.h"
 
@@ -105,12 +107,21 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     constexpr bool PERSIST = NB == 1 || ROWS2;
     constexpr int DKP = 32 * DK;
     constexpr int DK2 = L::DK2;
-    constexpr bool LDS_BIAS = MODE == BIAS_BF16_LDS;
+    constexpr bool F32L = MODE == BIAS_F32_LDS;
+    constexpr bool LDS_BIAS = MODE == BIAS_BF16_LDS || F32L;
+    // Staged bias rows: SEGS segments of 128 bytes per row and block.  A bf16 tile is staged whole
+    // (two segments); an fp32 tile would be 16 KiB per wave, so its first SEGS 32-key quarters (one per
+    // QK tile) are staged and the others go straight into registers, one block ahead: three
+    // quarters where two 4-wave workgroups (or one of 8 waves) fit a compute unit's LDS that way.
+    constexpr int SEGS = !F32L ? 2 : (NB == 1 && DK == 3) ? 2 : 3;
+    constexpr int ESZ = F32L ? 4 : 2, KSEG = 128 / ESZ, EC = 16 / ESZ;  // element size, keys per segment / 16-byte chunk
+    constexpr int REGION = SEGS * 4096;  // bytes of a wave's 32-row tile
+    static_assert(!F32L || !PAIR, "fp32 tiles are private");
     constexpr bool BIAS_DB = LDS_BIAS && PAIR;  // bias tiles double-buffered and shared
     // V operand rows of this many channel blocks are fetched from LDS before the
     // exponential phase (the rest just before their MFMAs): hides the LDS latency
     // where the register budget allows it.
-    constexpr int PRE = DK <= 2 ? DK : (DK == 4 && MODE == BIAS_TABLE_BLK) ? 0 : 1;
+    constexpr int PRE = DK <= 2 ? DK : ((DK == 4 && MODE == BIAS_TABLE_BLK) || MODE == BIAS_F32_LDS) ? 0 : 1;
     // The generated biases leave the memory pipeline idle: there the prefetched channel blocks'
     // matrix instructions of a tile are issued right behind its codes and run under the next
     // tile's exponentials.
@@ -119,10 +130,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     constexpr int REBASE = 8;
     __shared__ __attribute__((aligned(1024))) char bufA[NIMG * L::BYTES];
     __shared__ __attribute__((aligned(1024))) char bufB[NIMG * L::BYTES];
-    // BIAS_BF16_LDS: staging of the 32 x 128 bias tiles, 8 KiB per 32-row group.
+    // Staging of the 32 x 128 bias tiles, REGION bytes per 32-row group.
     // NB = 1: one region per wave, private to it.  NB = 2: two buffers shared by the pair.
-    __shared__ __attribute__((aligned(1024))) char biasA[LDS_BIAS ? (NB == 2 && !PAIR ? 8 : 4) * 8192 : 1024];
-    __shared__ __attribute__((aligned(1024))) char biasB[BIAS_DB ? 4 * 8192 : 1024];
+    __shared__ __attribute__((aligned(1024))) char biasA[LDS_BIAS ? (NB == 2 && !PAIR ? 8 : 4) * REGION : 1024];
+    __shared__ __attribute__((aligned(1024))) char biasB[BIAS_DB ? 4 * REGION : 1024];
     // BIAS_AXIAL: the head's two relative-position tables, already divided by alpha.
     //   axu: four copies of the REVERSED x table, copy j shifted by j entries, so that every
     //        lane finds its 16-entry window (ascending with the key index) 16-byte aligned.
@@ -178,7 +189,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     const int nbp = p.B / NIMG;
     const int per_xcd = (p.total_wg + 7) >> 3;
     const int vmax = 8 * per_xcd;
-    const int bsb = (MODE == BIAS_F32_VEC) ? 4 : 2;  // bytes per bias element
+    const int bsb = (MODE == BIAS_F32_VEC || F32L) ? 4 : 2;  // bytes per bias element
 
     // Work item v -> (batch, head, row block).  Consecutive ids go to different XCDs, so v
     // is first turned into (xcd, slot); items that share a bias slab (same head and row
@@ -277,8 +288,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             const int row0 = min(t.rb * BR + wave * ROWS_PER_WAVE + 8 * rg, N - 1);  // uniform
             const int row = min(row0 + r, N - 1);
             o.base[j] = uniform_ptr(static_cast<const char *>(p.bias) +
-                                    ((int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)row0 * p.bs.n) * 2);
-            o.voff[j] = (unsigned)(row - row0) * (unsigned)p.bs.n * 2u + 16u * dma_c[j];
+                                    ((int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)row0 * p.bs.n) * ESZ);
+            o.voff[j] = (unsigned)(row - row0) * (unsigned)p.bs.n * (unsigned)ESZ + 16u * dma_c[j];
         }
         return o;
     };
@@ -344,7 +355,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             hb_run = 0x7fffffff;
             __syncthreads();
         }
-        if (MODE == BIAS_BF16_VEC || MODE == BIAS_F32_VEC) brow = bias_row_ptr(t);
+        if (MODE == BIAS_BF16_VEC || MODE == BIAS_F32_VEC || F32L) brow = bias_row_ptr(t);
         if (LDS_BIAS) {
             bsrc = bias_dma_src(t);
         }
@@ -418,39 +429,60 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     // The copies' source may start at any element: they take 2-byte-aligned addresses like ordinary
     // loads do.  The last chunk of a row that straddles N reads on into whatever follows the row,
     // which is still inside the tensor except behind its very last row: a wave whose rows
-    // include one that would read past bias_end leaves that chunk out (key limit N - 7 instead
-    // of N) and writes it element by element (bias_tail).
+    // include one that would read past bias_end leaves that chunk out (key limit N - EC + 1
+    // instead of N) and writes it element by element (bias_tail).
     auto bias_klimit = [&](const Item &t, int blk) -> int {
-        if (blk * BV + BV <= N || (N & 7) == 0) return N;
+        if (blk * BV + BV <= N || (N & (EC - 1)) == 0) return N;
         const int row1 = min(t.rb * BR + wave * ROWS_PER_WAVE + ROWS_PER_WAVE, N) - 1;
-        const int64_t e1 = (int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)row1 * p.bs.n + ((N + 7) & ~7);
-        return e1 > p.bias_end ? N - 7 : N;
+        const int64_t e1 = (int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)row1 * p.bs.n + ((N + EC - 1) & -EC);
+        return e1 > p.bias_end ? N - (EC - 1) : N;
     };
     auto bias_tail = [&](const Item &t, int blk, unsigned region) {
+        typedef typename std::conditional<F32L, uint32_t, uint16_t>::type elem;
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        const int r = ln & 7, rg = ln >> 3, k0 = (N & ~7) - blk * BV;  // the chunk's first key inside the block
-        if (rg < rg0 || rg >= rg0 + RGW) return;
+        const int r = ln & 7, rg = ln >> 3, k0 = (N & -EC) - blk * BV;  // the chunk's first key inside the block
+        if (rg < rg0 || rg >= rg0 + RGW || k0 >= SEGS * KSEG) return;
         const int row = min(t.rb * BR + wave * ROWS_PER_WAVE + ln, N - 1);
-        const uint16_t *src = static_cast<const uint16_t *>(p.bias) + (int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h +
-                              (int64_t)row * p.bs.n + (N & ~7);
-        const unsigned dst = region + (rg * 2 + (k0 >> 6)) * 1024 + 128 * (r ^ (rg & 1)) + 16 * (((k0 >> 3) & 7) ^ r);
+        const elem *src = static_cast<const elem *>(p.bias) + (int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h +
+                          (int64_t)row * p.bs.n + (N & -EC);
+        const unsigned dst = region + (rg * SEGS + k0 / KSEG) * 1024 + 128 * (r ^ (rg & 1)) + 16 * ((k0 / EC & 7) ^ r);
 #pragma unroll 1
-        for (int i = 0; i < (N & 7); ++i)
-            *reinterpret_cast<__attribute__((address_space(3))) uint16_t *>((size_t)(dst + 2 * i)) = src[i];
+        for (int i = 0; i < (N & (EC - 1)); ++i)
+            *reinterpret_cast<__attribute__((address_space(3))) elem *>((size_t)(dst + ESZ * i)) = src[i];
     };
-    auto dma_bias_one = [&](const BiasSrc &src, int blk, int klim, unsigned region, int idx) {  // copy idx = 2 j + gh
-        const int j = idx >> 1, gh = idx & 1;
-        const int key0 = blk * BV + 64 * gh + 8 * dma_c[j];
+    auto dma_bias_one = [&](const BiasSrc &src, int blk, int klim, unsigned region, int idx) {  // copy idx = SEGS j + segment
+        const int j = idx / SEGS, seg = idx % SEGS;
+        const int key0 = blk * BV + KSEG * seg + EC * dma_c[j];
         if (key0 < klim)
-            dma16<WIDE == WIDE_PAIR_ONCE>(src.base[j] + (blk * BV + 64 * gh) * 2, src.voff[j],
-                                          region + ((rg0 + j) * 2 + gh) * 1024);
+            dma16<WIDE == WIDE_PAIR_ONCE>(src.base[j] + (blk * BV + KSEG * seg) * ESZ, src.voff[j],
+                                          region + ((rg0 + j) * SEGS + seg) * 1024);
     };
-    auto dma_bias = [&](const Item &t, const BiasSrc &src, int blk, unsigned region) {  // region: LDS offset of the 8 KiB tile
+    auto dma_bias = [&](const Item &t, const BiasSrc &src, int blk, unsigned region) {  // region: LDS offset of the tile
         const int klim = bias_klimit(t, blk);
         if (klim != N) bias_tail(t, blk, region);
 #pragma unroll
-        for (int idx = 0; idx < 2 * RGW; ++idx) dma_bias_one(src, blk, klim, region, idx);
+        for (int idx = 0; idx < SEGS * RGW; ++idx) dma_bias_one(src, blk, klim, region, idx);
+    };
+    f4v fraw[F32L ? SEGS : 1][4];      // F32L: the staged quarters of the current block
+    f4v freg[F32L ? 4 - SEGS : 1][4];  // F32L: this lane's values of the quarters that are not staged
+    auto load_bias_quarters = [&](const char *row, int blk) {
+        const float *src = reinterpret_cast<const float *>(row) + blk * BV + 16 * g;
+#pragma unroll
+        for (int t = SEGS; t < KT; ++t) {
+            if (blk * BV + 32 * t + 32 <= N) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) freg[t - SEGS][i] = *reinterpret_cast<const f4v_a4 *>(src + 32 * t + 4 * i);
+            } else if (blk * BV + 32 * t < N) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int o = 32 * t + 4 * i + j;
+                        freg[t - SEGS][i][j] = blk * BV + 16 * g + o < N ? src[o] : 0.0f;
+                    }
+            }
+        }
     };
     u4v braw[8];  // the 64 bf16 bias values of this lane for the current block
     auto load_bias_vec = [&](const char *row, int blk) {  // BIAS_BF16_VEC: registers straight from global memory
@@ -491,6 +523,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
                     bt[8 * i + 2 * j] = bf16_lo(w[j]) * inv_alpha;
                     bt[8 * i + 2 * j + 1] = bf16_hi(w[j]) * inv_alpha;
                 }
+            }
+        } else if (F32L) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f4v w = t < SEGS ? fraw[t < SEGS ? t : 0][i] : freg[t < SEGS ? 0 : t - SEGS][i];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) bt[4 * i + j] = w[j] * inv_alpha;
             }
         } else {  // BIAS_F32_VEC: 16-byte loads at float alignment, guarded at the row end
             const float *src = reinterpret_cast<const float *>(brow) + k0;
@@ -593,12 +632,21 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             int ln = lane;
             asm volatile("" : "+v"(ln));
             const int mm = ln & 31, gg = ln >> 5;
-            const unsigned a0 = lds_offset(bbuf) + (mm >> 3) * 2048 + 128 * ((mm & 7) ^ ((mm >> 3) & 1)) +
-                                16 * ((mm & 7) ^ (2 * gg));
+            const unsigned row = lds_offset(bbuf) + (mm >> 3) * (SEGS * 1024) + 128 * ((mm & 7) ^ ((mm >> 3) & 1));
+            if (F32L) {
+                const unsigned a0 = row + 16 * ((mm & 7) ^ (4 * gg));  // chunk 4 gg + i of segment t
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {  // chunk 2 gg + 4 (t & 1) + i % 2 of the 64-key half t / 2, t = i / 2
-                const unsigned c = 16u * (4 * ((i >> 1) & 1) + (i & 1));
-                braw[i] = *reinterpret_cast<const __attribute__((address_space(3))) u4v *>((size_t)((a0 ^ c) + 1024u * (i >> 2)));
+                for (int t = 0; t < SEGS; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        fraw[t][i] = *reinterpret_cast<const __attribute__((address_space(3))) f4v *>((size_t)((a0 ^ (16u * i)) + 1024u * t));
+            } else {
+                const unsigned a0 = row + 16 * ((mm & 7) ^ (2 * gg));
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {  // chunk 2 gg + 4 (t & 1) + i % 2 of the 64-key half t / 2, t = i / 2
+                    const unsigned c = 16u * (4 * ((i >> 1) & 1) + (i & 1));
+                    braw[i] = *reinterpret_cast<const __attribute__((address_space(3))) u4v *>((size_t)((a0 ^ c) + 1024u * (i >> 2)));
+                }
             }
         }
         v4i ka[KT][DK2];
@@ -662,6 +710,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             }
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (F32L && more) load_bias_quarters(sw ? bias_row_ptr(nxt) : brow, nblkidx);
         if (MODE == BIAS_BF16_VEC && more)  // braw is free again
             load_bias_vec(sw ? bias_row_ptr(nxt) : brow, nblkidx);
         if (LDS_BIAS && !BIAS_DB && more) {
@@ -835,7 +884,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     };
 
     // ---- prologue: first block of the first item --------------------------------
-    const char *bA = biasA + wreg * 8192, *bB = BIAS_DB ? biasB + wave * 8192 : bA;
+    const char *bA = biasA + wreg * REGION, *bB = BIAS_DB ? biasB + wave * REGION : bA;
     if constexpr (ONEHEAD) {
         // phi and psi of Alg. 1 for this head, straight into the two LDS images.
         constexpr int NT = FUSED_THREADS * NB;
@@ -858,6 +907,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
             dma_bias(cur, bsrc, 0, lds_offset(bA));
         }
         if (MODE == BIAS_BF16_VEC) load_bias_vec(bias_row_ptr(cur), 0);
+        if (F32L) load_bias_quarters(bias_row_ptr(cur), 0);
         // this lane's query row: the chunks of the sign words its B operand needs (channels
         // 64 s + 32 g + 8 j); addresses are clamped into the row, unused chunks are skipped below
         const int qrow = cur.rb * BR + wave * ROWS_PER_WAVE + m;
@@ -1029,6 +1079,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     begin_item(cur);
     if (!ONEHEAD) {
         if (MODE == BIAS_BF16_VEC) load_bias_vec(brow, 0);
+        if (F32L) load_bias_quarters(brow, 0);
         if (LDS_BIAS) dma_bias(cur, bsrc, 0, lds_offset(bA));
     }
     if (TBLK) {
@@ -1083,9 +1134,13 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
     const int needed = ((p.total_wg + 7) / 8) * 8;
     if (p.wide == WIDE_ROWS2) {  // persistent, one 8-wave workgroup per CU
         if constexpr (DK == 4) {
-            if (mode != BIAS_BF16_LDS) return BINATTN_ERR_DTYPE;
             const dim3 grid((unsigned)(needed < 256 ? needed : 256)), block(FUSED_THREADS * 2);
-            hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2, WIDE_ROWS2>), grid, block, 0, stream, p);
+            if (mode == BIAS_BF16_LDS)
+                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2, WIDE_ROWS2>), grid, block, 0, stream, p);
+            else if (mode == BIAS_F32_LDS)
+                hipLaunchKernelGGL((fused_kernel<DK, BIAS_F32_LDS, 2, WIDE_ROWS2>), grid, block, 0, stream, p);
+            else
+                return BINATTN_ERR_DTYPE;
             return check_launch();
         }
         return BINATTN_ERR_SHAPE;
@@ -1113,6 +1168,12 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
                 break;
             }
             return BINATTN_ERR_SHAPE;
+        case BIAS_F32_LDS:
+            if constexpr (DK <= 3) {
+                hipLaunchKernelGGL((fused_kernel<DK, BIAS_F32_LDS, 1>), grid, block, 0, stream, p);
+                break;
+            }
+            return BINATTN_ERR_SHAPE;
         default: return BINATTN_ERR_DTYPE;
     }
     return check_launch();
@@ -1132,7 +1193,7 @@ int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
         return BINATTN_ERR_SHAPE;
         switch (mode) {
             CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE)
-            CASE(BIAS_BF16_LDS)
+            CASE(BIAS_BF16_LDS) CASE(BIAS_F32_LDS)
             default: return BINATTN_ERR_DTYPE;
         }
 #undef CASE
@@ -1141,7 +1202,7 @@ int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
     switch (mode) {
 #define CASE(M) case M: hipLaunchKernelGGL((fused_kernel<DK, M, 2, WIDE_ONEHEAD>), grid, block, 0, stream, p); break;
         CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE)
-        CASE(BIAS_BF16_LDS)
+        CASE(BIAS_BF16_LDS) CASE(BIAS_F32_LDS)
 #undef CASE
         default: return BINATTN_ERR_DTYPE;
     }
