@@ -93,13 +93,17 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 //
 // WIDE_PAIR_ONCE is the paired form (NB = 2) with the bias copies marked as not worth keeping in the
 // caches, for biases larger than those.
-enum { WIDE_NONE = 0, WIDE_ONEHEAD = 1, WIDE_ROWS2 = 2, WIDE_ONEHEAD4 = 3, WIDE_PAIR_ONCE = 4 };
+//
+// WIDE_WAVES3 is the ordinary 4-wave form compiled for three waves per SIMD (168 registers), three
+// workgroups per compute unit, in the variants of use_waves3.
+enum { WIDE_NONE = 0, WIDE_ONEHEAD = 1, WIDE_ROWS2 = 2, WIDE_ONEHEAD4 = 3, WIDE_PAIR_ONCE = 4, WIDE_WAVES3 = 5 };
 template <int DK, int MODE, int NB, int WIDE = WIDE_NONE>
-__global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const FusedParams p) {
+__global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) void fused_kernel(const FusedParams p) {
     using L = Image<DK>;
     constexpr bool ONEHEAD4 = WIDE == WIDE_ONEHEAD4;
     constexpr bool ONEHEAD = WIDE == WIDE_ONEHEAD || ONEHEAD4, ROWS2 = WIDE == WIDE_ROWS2;
-    static_assert(WIDE == WIDE_NONE || ONEHEAD4 || NB == 2, "the wide forms use 8 waves");
+    constexpr bool WAVES3 = WIDE == WIDE_WAVES3;
+    static_assert(WIDE == WIDE_NONE || ONEHEAD4 || WAVES3 || NB == 2, "the wide forms use 8 waves");
     static_assert(!ONEHEAD4 || NB == 1, "the 4-wave single-launch form");
     constexpr bool PAIR = NB == 2 && (WIDE == WIDE_NONE || WIDE == WIDE_PAIR_ONCE);  // two batch entries sharing bias tiles
     constexpr int NWI = ROWS2 ? 8 : 4;                   // waves that copy one operand image
@@ -121,11 +125,14 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     // V operand rows of this many channel blocks are fetched from LDS before the
     // exponential phase (the rest just before their MFMAs): hides the LDS latency
     // where the register budget allows it.
-    constexpr int PRE = DK <= 2 ? DK : ((DK == 4 && MODE == BIAS_TABLE_BLK) || MODE == BIAS_F32_LDS) ? 0 : 1;
+    constexpr int PRE = (DK == 2 && WAVES3) ? (MODE == BIAS_AXIAL ? 1 : 0) : DK <= 2 ? DK : ((DK == 4 && MODE == BIAS_TABLE_BLK) || MODE == BIAS_F32_LDS) ? 0 : 1;
     // The generated biases leave the memory pipeline idle: there the prefetched channel blocks'
     // matrix instructions of a tile are issued right behind its codes and run under the next
-    // tile's exponentials.
-    constexpr bool PV_EARLY = MODE == BIAS_AXIAL || MODE == BIAS_TABLE_BLK;
+    // tile's exponentials (128 x 128 grid, d = 64: 2155 -> 2083 us; nothing or a loss above d = 64).
+    constexpr bool PV_EARLY = (MODE == BIAS_AXIAL || MODE == BIAS_TABLE_BLK) && DK <= 2;
+    // ... and at three waves per SIMD each tile's V rows are read under its own exponentials (the
+    // registers do not hold them all).
+    constexpr bool VDEMAND = PV_EARLY && WAVES3;
     // key blocks between two removals of the accumulator's float-bit offset (a power of two)
     constexpr int REBASE = 8;
     __shared__ __attribute__((aligned(1024))) char bufA[NIMG * L::BYTES];
@@ -163,7 +170,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     constexpr int TB_N = TABLE ? 1024 : 512;           // entries of a copy
     constexpr int TB_CP = TB_N + 16;                   // copy pitch (bank spread as for axu)
     constexpr int TB_PER = TB_N / (FUSED_THREADS * NB); // entries a thread stages
-    static_assert(!TBLK || (NB == 1 && WIDE == WIDE_NONE), "per-block table rows: 4-wave workgroups");
+    static_assert(!TBLK || (NB == 1 && (WIDE == WIDE_NONE || WAVES3)), "per-block table rows: 4-wave workgroups");
     static_assert(!TABLE || ONEHEAD, "whole table: single-launch forms");
     __shared__ __attribute__((aligned(16))) float tab[TABLE ? 4 * TB_CP : TBLK ? 2 * 4 * TB_CP : 4];
     // BIAS_LUT (no bias): the logit takes only the d + 1 values alpha * I, I = d, d - 2, ..., -d, and
@@ -300,14 +307,17 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     float tstage[TABLE || TBLK ? TB_PER : 1];
     auto table_load = [&](const Item &t, int row0, int nrows) {  // global loads only
         const int LX = 2 * p.Gx - 1, LY = 2 * p.Gy - 1, sh = p.gx_shift + 1;
-        const float *tb = p.table + (int64_t)t.h * LY * LX;
+        const char *tb = uniform_ptr(reinterpret_cast<const char *>(p.table + (int64_t)t.h * LY * LX + row0 * LX));
+        int tid = threadIdx.x;  // (opaque: the 32-bit offsets are formed here, not carried through the block loop)
+        asm volatile("" : "+v"(tid));
 #pragma unroll
         for (int j = 0; j < TB_PER; ++j) {
-            const int i = threadIdx.x + j * FUSED_THREADS * NB;
+            const int i = tid + j * FUSED_THREADS * NB;
             const int row = i >> sh, kk = i & ((1 << sh) - 1);
             const bool on = row < nrows && kk < LX;
-            const float x = tb[on ? (int64_t)(row0 + row) * LX + (LX - 1 - kk) : 0];
-            tstage[j] = on ? x : 0.0f;
+            // (places that hold no entry get the first one: only keys past the end of the sequence,
+            // whose logits are replaced, read them.  A select on the loaded value would wait for it here.)
+            tstage[j] = *reinterpret_cast<const float *>(tb + (on ? 4u * (unsigned)(row * LX + (LX - 1 - kk)) : 0u));
         }
     };
     auto table_store = [&](float *dst, float ia) {
@@ -729,7 +739,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
                 acc[cb][4 * q4 + 2] = c4[2]; acc[cb][4 * q4 + 3] = c4[3];
             }
 #pragma unroll
-            for (int t = 0; t < KT; ++t)
+            for (int t = 0; t < (VDEMAND ? 0 : KT); ++t)
                 va[cb][t] = *reinterpret_cast<const v4i *>(ibuf + L::V_OFF + (32 * cb + m) * L::VP + 32 * t + 16 * g);
         }
 
@@ -808,6 +818,11 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
             if (t == 0) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (VDEMAND) {
+#pragma unroll
+                for (int cb = 0; cb < PRE; ++cb)
+                    va[cb][t] = *reinterpret_cast<const v4i *>(ibuf + L::V_OFF + (32 * cb + m) * L::VP + 32 * t + 16 * g);
+            }
             const float ce = AXIAL ? fmaf(wt[t], a2, cexp) : cexp;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -1126,6 +1141,19 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, 2) void fused_kernel(const Fuse
     }
 }
 
+// Three waves per SIMD instead of two hide more of a block's LDS and matrix latencies where the biases are
+// generated (two / three waves: decomposed, d = 64, N = 16384 2073 / 1918 us, N = 4096, 96 heads 436 / 412; table,
+// d = 32 120 / 110; at d = 64 the table form spills).  Without a bias or with dense tiles (up to 32
+// channels: LDS) a workgroup's block takes as much longer as there are more of them, and what counts is
+// the last round, which leaves the chip less idle unless the 512 slots of two waves fill theirs: 96 heads,
+// N = 1024, d = 64 43.6 / 41.1 us (768 items), 480 heads, N = 600, d = 48 88.8 / 84.1 (2400), 36 heads, N = 2048, d = 32, bf16
+// bias 80.9 / 67.5 (576), but 96 heads, N = 2048, d = 32 97.2 / 98.5 (1536), 12 heads, N = 4096 69.0 / 72.0 (384).
+constexpr bool use_waves3(int DK, int mode, int items) {
+    const bool generated = (mode == BIAS_AXIAL && DK <= 2) || (mode == BIAS_TABLE_BLK && DK == 1);
+    const bool other = (mode == BIAS_NONE && DK <= 2) || (mode == BIAS_BF16_LDS && DK == 1);
+    return generated || (other && items > 512 && items % 512 != 0 && items % 512 <= 384);
+}
+
 template <int DK>
 int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
     // NB = 1, persistent grid: as many workgroups as fit on the chip at once (two 4-wave
@@ -1145,7 +1173,9 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
         }
         return BINATTN_ERR_SHAPE;
     }
-    const dim3 grid((unsigned)(p.nb == 2 || needed < 512 ? needed : 512));
+    const bool waves3 = p.nb == 1 && use_waves3(DK, mode, p.total_wg);
+    const int slots = waves3 ? 768 : 512;
+    const dim3 grid((unsigned)(p.nb == 2 || needed < slots ? needed : slots));
     const dim3 block(FUSED_THREADS * p.nb);
     if (p.nb == 2) {
         if constexpr (DK <= 2) {
@@ -1159,15 +1189,25 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
         return BINATTN_ERR_SHAPE;
     }
     switch (mode) {
-#define CASE(M) case M: hipLaunchKernelGGL((fused_kernel<DK, M, 1>), grid, block, 0, stream, p); break;
+// (the form of three waves per SIMD where use_waves3 may choose it, the other one unless it always does)
+#define CASE(M)                                                                                       \
+    case M:                                                                                           \
+        if constexpr (use_waves3(DK, M, 513)) {                                                       \
+            if (waves3) {                                                                             \
+                hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_WAVES3>), grid, block, 0, stream, p); \
+                break;                                                                                \
+            }                                                                                         \
+        }                                                                                             \
+        if constexpr (!use_waves3(DK, M, 1)) hipLaunchKernelGGL((fused_kernel<DK, M, 1>), grid, block, 0, stream, p); \
+        break;
         CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE_BLK)
-#undef CASE
         case BIAS_BF16_LDS:
             if constexpr (DK <= 3) {
-                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 1>), grid, block, 0, stream, p);
+                switch (mode) { CASE(BIAS_BF16_LDS) }
                 break;
             }
             return BINATTN_ERR_SHAPE;
+#undef CASE
         case BIAS_F32_LDS:
             if constexpr (DK <= 3) {
                 hipLaunchKernelGGL((fused_kernel<DK, BIAS_F32_LDS, 1>), grid, block, 0, stream, p);
