@@ -122,14 +122,14 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     constexpr int REGION = SEGS * 4096;  // bytes of a wave's 32-row tile
     static_assert(!F32L || !PAIR, "fp32 tiles are private");
     constexpr bool BIAS_DB = LDS_BIAS && PAIR;  // bias tiles double-buffered and shared
-    // V operand rows of this many channel blocks are fetched from LDS before the
-    // exponential phase (the rest just before their MFMAs): hides the LDS latency
-    // where the register budget allows it.
-    constexpr int PRE = (DK == 2 && WAVES3) ? (MODE == BIAS_AXIAL ? 1 : 0) : DK <= 2 ? DK : ((DK == 4 && MODE == BIAS_TABLE_BLK) || MODE == BIAS_F32_LDS) ? 0 : 1;
     // The generated biases leave the memory pipeline idle: there the prefetched channel blocks'
     // matrix instructions of a tile are issued right behind its codes and run under the next
     // tile's exponentials (128 x 128 grid, d = 64: 2155 -> 2083 us; nothing or a loss above d = 64).
     constexpr bool PV_EARLY = (MODE == BIAS_AXIAL || MODE == BIAS_TABLE_BLK) && DK <= 2;
+    // V operand rows of this many channel blocks are fetched from LDS before the
+    // exponential phase (the rest just before their MFMAs): hides the LDS latency
+    // where the register budget allows it.
+    constexpr int PRE = (DK == 2 && WAVES3) ? (PV_EARLY ? 1 : 0) : DK <= 2 ? DK : ((DK == 4 && MODE == BIAS_TABLE_BLK) || MODE == BIAS_F32_LDS) ? 0 : 1;
     // ... and at three waves per SIMD each tile's V rows are read under its own exponentials (the
     // registers do not hold them all).
     constexpr bool VDEMAND = PV_EARLY && WAVES3;
@@ -835,11 +835,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                 }
                 pk[t][i] = (int)(w ^ 0x80808080u);  // code - 128 as signed bytes
             }
+            // (the sums are finished here: the compiler would keep all 64 terms until the block's end and spill)
+            if (TBLK && DK == 2 && WAVES3) asm volatile("" : "+v"(ls0), "+v"(ls1));
             if constexpr (PV_EARLY) {
 #pragma unroll
                 for (int cb = 0; cb < PRE; ++cb)
                     acc[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(va[cb][t], pk[t], acc[cb], 0, 0, 0);
-                if (AXIAL) __builtin_amdgcn_sched_barrier(0);
+                if (AXIAL || WAVES3) __builtin_amdgcn_sched_barrier(0);
             }
             // The shared bias tile of the next block (BIAS_DB), one copy per tile of exponentials:
             // issued in one burst at the start of the block, beside the image copies, they fill
@@ -1143,13 +1145,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 
 // Three waves per SIMD instead of two hide more of a block's LDS and matrix latencies where the biases are
 // generated (two / three waves: decomposed, d = 64, N = 16384 2073 / 1918 us, N = 4096, 96 heads 436 / 412; table,
-// d = 32 120 / 110; at d = 64 the table form spills).  Without a bias or with dense tiles (up to 32
+// d = 32 120 / 110, d = 64 2170 / 1987, but 24 items, d = 64 26.5 / 26.9).  Without a bias or with dense tiles (up to 32
 // channels: LDS) a workgroup's block takes as much longer as there are more of them, and what counts is
 // the last round, which leaves the chip less idle unless the 512 slots of two waves fill theirs: 96 heads,
 // N = 1024, d = 64 43.6 / 41.1 us (768 items), 480 heads, N = 600, d = 48 88.8 / 84.1 (2400), 36 heads, N = 2048, d = 32, bf16
 // bias 80.9 / 67.5 (576), but 96 heads, N = 2048, d = 32 97.2 / 98.5 (1536), 12 heads, N = 4096 69.0 / 72.0 (384).
 constexpr bool use_waves3(int DK, int mode, int items) {
-    const bool generated = (mode == BIAS_AXIAL && DK <= 2) || (mode == BIAS_TABLE_BLK && DK == 1);
+    const bool generated = (mode == BIAS_AXIAL && DK <= 2) || (mode == BIAS_TABLE_BLK && (DK == 1 || (DK == 2 && items > 512)));
     const bool other = (mode == BIAS_NONE && DK <= 2) || (mode == BIAS_BF16_LDS && DK == 1);
     return generated || (other && items > 512 && items % 512 != 0 && items % 512 <= 384);
 }

@@ -66,19 +66,27 @@ def test_bias_rows_further_apart_than_a_copy_offset_reaches(N, d):
 
 
 @pytest.mark.parametrize("B,H,N,d,kind", [(3, 57, 300, 64, "none"), (1, 256, 257, 40, "none"), (1, 129, 513, 16, "none"),
-                                          (3, 58, 290, 32, "bf16"), (1, 290, 257, 8, "bf16"), (1, 224, 400, 24, "bf16")])
+                                          (2, 65, 512, 64, "table"), (1, 87, 720, 40, "table"), (3, 58, 290, 32, "bf16"), (1, 290, 257, 8, "bf16"), (1, 224, 400, 24, "bf16")])
 def test_three_workgroups_per_compute_unit_give_the_same_bits(B, H, N, d, kind):
     """More than 512 work items that leave the last round of 512 part empty take the kernels built for three
     waves per SIMD; a few heads of the same call take the others.  Heads are independent: same bits."""
     say(f"three waves B={B} H={H} N={N} d={d} {kind}")
     items = B * H * -(-N // 128)
-    assert items > 512 and 0 < items % 512 <= 384
+    assert items > 512 and (kind == "table" or 0 < items % 512 <= 384)
     x = small_inputs(B, H, N, d, 300 + N)
     q, k, v = dev(x.q), dev(x.k), dev(x.v)
     bias = None if kind == "none" else dev(x.bias)
-    out = ba.attention(q, k, v, bias, x.scale)
+    if kind == "table":  # token grid of 16 columns
+        table = torch.randn(H, 2 * (N // 16) - 1, 31, generator=torch.Generator().manual_seed(N)).cuda()
+
+    def run(hs):
+        if kind == "table":
+            return ba.attention_relpos(q[:, hs], k[:, hs], v[:, hs], table[hs], x.scale)
+        return ba.attention(q[:, hs], k[:, hs], v[:, hs], None if bias is None else bias[hs], x.scale)
+
+    out = run(slice(0, H))
     for h0 in (0, H - 3):
         hs = slice(h0, h0 + 3)
-        part = ba.attention(q[:, hs], k[:, hs], v[:, hs], None if bias is None else bias[hs], x.scale)
+        part = run(hs)
         torch.cuda.synchronize()
         assert torch.equal(part, out[:, hs]), h0
