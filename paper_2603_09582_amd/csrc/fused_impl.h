@@ -599,7 +599,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 
     // ---- stream position --------------------------------------------------------
     int it = 0;        // key block inside the current item
-    const bool younger = 2 * blockIdx.x >= gridDim.x;
+    const bool younger = WAVES3 && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
     int parity = 0;    // items alternate between the two delta_v copies
     Item nxt = decode(PERSIST ? v + gridDim.x : vmax);
 
@@ -629,7 +629,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         // workgroup dispatched first then runs ~25 % faster than the other and leaves the CU
         // half empty at the end.  The second half of the grid (dispatched after every CU has
         // its first workgroup) therefore raises its priority on every other block.  Only a
-        // scheduling hint: results do not depend on it.
+        // scheduling hint: results do not depend on it.  With three workgroups per CU the last third does
+        // (128 x 128 grid, d = 64: table 1968 us with the second half, 1912 with the last third, 2143 without).
         if (NB == 1) {
             if (younger && (it & 1)) __builtin_amdgcn_s_setprio(1);
             else __builtin_amdgcn_s_setprio(0);
