@@ -61,3 +61,26 @@ def test_both_single_launch_forms_give_the_same_bits(N, d):
     torch.cuda.synchronize()
     for a, b in zip(*res):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,H,N,d,flags", [(1, 2, 300, 72, 0), (2, 2, 577, 40, 0), (1, 1, 391, 104, 0), (1, 2, 257, 8, 0),
+                                           (1, 2, 300, 72, ba.FLAG_LUT), (2, 1, 1030, 48, 0)])
+@pytest.mark.parametrize("with_bias", [False, True])
+def test_what_the_workspace_held_before_does_not_matter(B, H, N, d, flags, with_bias):
+    """Places of the operand images that no key or channel fills keep the workspace's old bytes."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + d)
+    q, k, v = (torch.randn(B, H, N, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    bias = torch.randn(H, N, N, generator=g, device="cuda").to(torch.bfloat16) if with_bias else None
+    ws = ba.alloc_workspace(B, H, N, d)
+    res = []
+    for fill in (0x00, 0xFF, 0x7F, 0x80):
+        ws.fill_(fill)
+        one = ba.attention(q, k, v, bias, d ** -0.5, workspace=ws, flags=flags)
+        ws.fill_(fill)
+        qb, kb, mq, mk = ba.pack_qk(q, k)
+        res.append((one, ba.forward(qb, kb, mq, mk, v, bias, d ** -0.5, workspace=ws, flags=flags)))
+    torch.cuda.synchronize()
+    for one, packed in res[1:]:
+        assert torch.equal(one, res[0][0]) and torch.equal(packed, res[0][1])
+        assert torch.isfinite(one).all()
