@@ -249,6 +249,11 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         // the head's two row blocks in turn; otherwise one 8-wave workgroup per head.
         const bool four = B * H > ONEHEAD4_MIN_HEADS && onehead4_built(s.DK, mode) && !(flags & BINATTN_FLAG_WIDE8);
         p.wide = four ? 3 : 1;
+        // (which order the 4-wave form adds the abs-means in: the relative-position table and bf16 rows that
+        // are not whole 16-byte chunks take the 8-wave form's at 64 < d <= 96)
+        const bool chunk_rows = aligned(bias, 16) && bs.b % 8 == 0 && bs.h % 8 == 0 && bs.n % 8 == 0 &&
+                                (N % 8 == 0 || bs.n >= (N + 7) / 8 * 8);
+        p.split_sums = s.DK == 3 && (mode == BIAS_TABLE || (mode == BIAS_BF16_LDS && !chunk_rows)) ? 1 : 0;
         p.nrb = four ? (N + BR - 1) / BR : 1;
         p.nb = four ? 1 : 2;
         p.total_wg = B * H;
@@ -260,6 +265,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
             default: return BINATTN_ERR_SHAPE;
         }
     }
+    p.split_sums = 0;
     p.xq = p.xk = p.xv = nullptr;
     p.xqs = p.xks = p.xvs = Strides3{0, 0, 0};
     p.mu_q_out = p.mu_k_out = nullptr;

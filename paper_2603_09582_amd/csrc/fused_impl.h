@@ -908,10 +908,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         constexpr int NT = FUSED_THREADS * NB;
         __shared__ int sabs[DKP];            // per-channel absmax of V (bit patterns)
         __shared__ __attribute__((aligned(16))) float srcp[DKP];  // the quantiser's multipliers
-        // |q| and |k| partial sums of eight waves: the 4-wave form keeps what waves w and w + 4 of the
-        // 8-wave form add in two sums, so that both forms give the same abs-means to the last bit
-        constexpr int NS = ONEHEAD4 ? 2 : 1;
-        __shared__ float ssum[2][8];
+        // |q| and |k| partial sums.  The 4-wave form adds what a lane sees of both row blocks in one
+        // sum (kept in the second of two, the first stays 0); with p.split_sums it keeps what waves w
+        // and w + 4 of the 8-wave form add apart, which gives the 8-wave form's abs-means to the last bit.
+        constexpr bool SPLIT_BUILT = ONEHEAD4 && DK == 3 && (MODE == BIAS_TABLE || MODE == BIAS_BF16_LDS);
+        constexpr int NS = SPLIT_BUILT ? 2 : 1;
+        constexpr int NSUM = NS * NT / 64;
+        __shared__ float ssum[2][NSUM];
         const int C16 = d / 8, nblk = p.nblk;
         auto imgp = [&](int blk) -> char * { return blk ? bufB : bufA; };
         const uint16_t *qb_ = p.xq + (int64_t)cur.b * p.xqs.b + (int64_t)cur.h * p.xqs.h;
@@ -980,11 +983,16 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         // this thread's key chunks (8 channels of one key each), loaded before the first barrier
         constexpr int KPT = (2 * BV * 4 * DK + NT - 1) / NT;  // chunks per thread, at most
         u4 kx[KPT];
+        unsigned kdst[KPT];  // where its FP4 word goes (LDS offset), 0xffffffff for a chunk that does not exist
 #pragma unroll
         for (int kk = 0; kk < KPT; ++kk) {
             const int i = threadIdx.x + kk * NT;
-            const int ic = div_c16(i), c8 = i - ic * C16, pos = ic % BV, blk = ic / BV;
-            const int key = blk * BV + key_of_position(pos);
+            const int ic = div_c16(i), c8 = i - ic * C16, blk = ic / BV;
+            const int o = key_of_chunk(ic % BV), pos = position_of_key(o);
+            const int key = blk * BV + o;
+            kdst[kk] = blk < nblk && key < N ? lds_offset(imgp(blk)) + L::K_OFF + pos * L::KP +
+                                                   16 * k_chunk(pos, c8 >> 2, L::KP) + 4 * (c8 & 3)
+                                             : 0xffffffffu;
             kx[kk] = *reinterpret_cast<const u4 *>(kb_ + (int64_t)min(key, N - 1) * p.xks.n + 8 * c8);
         }
         // clear both images, the absmax cells
@@ -1002,26 +1010,33 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         // keys: sign bits -> FP4 codes of +-1 at the row position the QK tile reads
 #pragma unroll
         for (int kk = 0; kk < KPT; ++kk) {
-            const int i = threadIdx.x + kk * NT;
-            const int ic = div_c16(i), c8 = i - ic * C16, pos = ic % BV, blk = ic / BV;
-            const int key = blk * BV + key_of_position(pos);
-            if (blk < nblk && key < N) {
-                *reinterpret_cast<unsigned *>(imgp(blk) + L::K_OFF + pos * L::KP +
-                                              16 * k_chunk(pos, c8 >> 2, L::KP) + 4 * (c8 & 3)) =
-                    fp4_pm1_abs(kx[kk], ksum[kk % NS]);
+            if (kdst[kk] != 0xffffffffu) {
+                const bool first = NS == 1 || (kk % 2 == 0 && p.split_sums);
+                float sum = first ? ksum[0] : ksum[NS - 1];
+                *reinterpret_cast<__attribute__((address_space(3))) unsigned *>((size_t)kdst[kk]) =
+                    fp4_pm1_abs(kx[kk], sum);
+                ksum[0] = first ? sum : ksum[0];
+                ksum[NS - 1] = first ? ksum[NS - 1] : sum;
             }
         }
         if (ksum[0] != ksum[0] || ksum[NS - 1] != ksum[NS - 1]) {  // a NaN among this thread's keys: its words once more, exactly
             for (int i = threadIdx.x; i < KPT * NT; i += NT) {
-                const int ic = div_c16(i), c8 = i - ic * C16, pos = ic % BV, blk = ic / BV;
-                const int key = blk * BV + key_of_position(pos);
+                const int ic = div_c16(i), c8 = i - ic * C16, blk = ic / BV;
+                const int o = key_of_chunk(ic % BV), pos = position_of_key(o);
+                const int key = blk * BV + o;
                 if (blk < nblk && key < N)
                     *reinterpret_cast<unsigned *>(imgp(blk) + L::K_OFF + pos * L::KP +
                                                   16 * k_chunk(pos, c8 >> 2, L::KP) + 4 * (c8 & 3)) =
                         fp4_pm1_exact(*reinterpret_cast<const u4 *>(kb_ + (int64_t)key * p.xks.n + 8 * c8));
             }
         }
-        if constexpr (ONEHEAD4) q_row_words(qrow + BR, pend_q2, qsum[1]);
+        if constexpr (ONEHEAD4) {
+            if (NS == 2 && !p.split_sums) {
+                qsum[NS - 1] = qsum[0];
+                qsum[0] = 0.0f;
+            }
+            q_row_words(qrow + BR, pend_q2, qsum[NS - 1]);
+        }
         // V: absmax per channel through LDS integer maxima
         if (von) {
             unsigned mb[4] = {0u, 0u, 0u, 0u};
@@ -1061,7 +1076,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         float tq = 0.0f, tk = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < NSUM; ++i) {
             tq += ssum[0][i];
             tk += ssum[1][i];
         }

@@ -232,12 +232,6 @@ __global__ __launch_bounds__(PREP_THREADS) void v_quant_kernel(
     }
 }
 
-// Inverse of key_of_position: where key offset o (0 <= o < BV) sits in a block image.
-__device__ __forceinline__ int position_of_key(int o) {
-    const int t = o >> 5, g = (o >> 4) & 1, r = o & 15;
-    return 32 * t + 8 * (r >> 2) + 4 * g + (r & 3);
-}
-
 // phi of Alg. 1 (Eq. 5) for Q and K and the first half of psi (Eq. 7) in ONE pass over the bf16
 // inputs, for the entry point that takes Q, K and V themselves: a workgroup owns the BV = 128
 // tokens of one key block of one head (many small workgroups: the loads of one overlap the

@@ -60,6 +60,16 @@ __device__ __forceinline__ int key_of_position(int pos) {
     const int r = ((m >> 3) << 2) | (m & 3);
     return 32 * t + 16 * g + r;
 }
+// Inverse of key_of_position: where key offset o (0 <= o < BV) sits in a block image.
+__device__ __forceinline__ int position_of_key(int o) {
+    return (o & 0x63) | ((o & 0x0C) << 1) | ((o >> 2) & 4);
+}
+// Single-launch forms: the key (offset inside its block) that the i-th group of a block's chunks belongs
+// to.  Which keys a thread adds |k| of, and in which order, decides the last bits of the abs-mean:
+// this assignment is part of the results and does not follow the layout of the image.
+__device__ __forceinline__ int key_of_chunk(int i) {
+    return ((i & 4) << 4) | ((i >> 1) & 0x3C) | (i & 3);  // 64 ((m >> 2) & 1) + 16 t + 4 (m >> 3) + (m & 3), i = 32 t + m
+}
 
 __device__ __forceinline__ void unpack8(u4 w, float f[8]) {
 #pragma unroll

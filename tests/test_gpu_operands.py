@@ -46,21 +46,69 @@ def test_signs_of_special_values_without_sign_words(N, d):
     assert torch.equal(want, got)
 
 
-@pytest.mark.parametrize("N,d", [(1, 64), (63, 64), (129, 32), (197, 64), (256, 72), (200, 96)])
-def test_both_single_launch_forms_give_the_same_bits(N, d):
-    """The 4-wave form adds the magnitudes in the 8-wave form's order: abs-means and outputs agree exactly."""
-    B, H = 2, 130
+def ordered_abs_mean(x, waves, keys):
+    """Mean of |x| (fp32 [N, d]) in the order a workgroup of the single-launch forms adds it: every lane the
+    chunks of 8 channels it owns, in turn; a tree over the 64 lanes; the waves one after the other."""
+    N, d = x.shape
+    DK, C16 = -(-d // 32), d // 8
+    lane, wave = np.arange(64)[None, :], np.arange(waves)[:, None]
+    s = np.zeros((waves, 64), np.float32)
+    ax = np.abs(np.concatenate([x, np.zeros((1, d), np.float32)]))  # row N stands for "no row"
+
+    def add(row, c0, live):
+        nonlocal s
+        row, c0 = np.where(live, row, N), np.where(live, c0, 0)
+        for i in range(0, 8, 2):
+            s = np.where(live, s + (ax[row, c0 + i] + ax[row, c0 + i + 1]), s)
+
+    if keys:
+        for kk in range(-(-(256 * 4 * DK) // (64 * waves))):
+            i = 64 * waves * kk + 64 * wave + lane
+            ic, c8 = i // C16, i % C16
+            m, t = ic % 32, ic % 128 // 32
+            key = ic // 128 * 128 + 64 * (m // 4 % 2) + 16 * t + 4 * (m // 8) + m % 4
+            add(key, 8 * c8, (ic < 256) & (key < N))
+    else:
+        for row0 in range(0, 256, 32 * waves):
+            row = row0 + 32 * wave + lane % 32
+            for sI in range((DK + 1) // 2):
+                for j in range(4):
+                    c0 = 64 * sI + 32 * (lane // 32) + 8 * j + 0 * wave
+                    add(row, c0, (row < N) & (c0 < d))
+    for off in (32, 16, 8, 4, 2, 1):
+        s[:, :64 - off] = s[:, :64 - off] + s[:, off:]
+    total = np.float32(0.0)
+    for w in range(waves):
+        total = total + s[w, 0]
+    return total * (np.float32(1.0) / (np.float32(N) * np.float32(d)))
+
+
+# (kind of bias decides between the forms above 256 heads and 64 channels)
+@pytest.mark.parametrize("H,flags,kind", [(6, 0, "rows16"), (260, 0, "rows16"), (260, ba.FLAG_WIDE8, "rows16"), (260, 0, "odd"),
+                                          (260, 0, "none"), (260, 0, "table")])
+@pytest.mark.parametrize("N,d", [(1, 64), (96, 64), (208, 64), (256, 32), (240, 72), (256, 96), (128, 80)])
+def test_abs_means_of_the_single_launch_are_added_in_a_fixed_order(N, d, H, flags, kind):
+    """The logit multiplier is made of these two numbers: their last bits decide single 8-bit codes of P.  So
+    the order of the sums is part of the result, whichever kernel a call is given to."""
+    if kind == "table" and N % 16:
+        pytest.skip("token grids have rows of 16")
     g = torch.Generator(device="cuda")
     g.manual_seed(N + d)
-    q, k, v = (torch.randn(B, H, N, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
-    bias = torch.randn(H, N, N, generator=g, device="cuda").to(torch.bfloat16)
-    res = []
-    for flags in (0, ba.FLAG_WIDE8):
-        mq, mk = torch.zeros(B, H, device="cuda"), torch.zeros(B, H, device="cuda")
-        res.append((ba.forward_fused(q, k, v, bias, d ** -0.5, mu_q=mq, mu_k=mk, flags=flags), mq, mk))
+    q, k, v = (torch.randn(1, H, N, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    mq, mk = torch.zeros(1, H, device="cuda"), torch.zeros(1, H, device="cuda")
+    if kind == "table":
+        table = torch.randn(H, 2 * (N // 16) - 1, 31, generator=g, device="cuda")
+        ba.forward_fused_relpos(q, k, v, table, d ** -0.5, mu_q=mq, mu_k=mk, flags=flags)
+    else:
+        pitch = N + (1 if kind == "odd" else -N % 8)
+        bias = None if kind == "none" else torch.randn(H, N, pitch, generator=g, device="cuda").to(torch.bfloat16)[:, :, :N]
+        ba.forward_fused(q, k, v, bias, d ** -0.5, mu_q=mq, mu_k=mk, flags=flags)
     torch.cuda.synchronize()
-    for a, b in zip(*res):
-        assert torch.equal(a, b)
+    eight = H <= 256 or flags or (d > 64 and kind in ("odd", "table"))
+    for h in range(0, H, 3 if H < 256 else 37):
+        for t, mu, keys in ((q, mq, False), (k, mk, True)):
+            want = ordered_abs_mean(t[0, h].float().cpu().numpy(), 8 if eight else 4, keys)
+            assert mu[0, h].item() == want, (h, "k" if keys else "q")
 
 
 @pytest.mark.parametrize("B,H,N,d,flags", [(1, 2, 300, 72, 0), (2, 2, 577, 40, 0), (1, 1, 391, 104, 0), (1, 2, 257, 8, 0),
