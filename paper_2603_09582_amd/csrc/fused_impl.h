@@ -1152,10 +1152,17 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             for (int r = 0; r < 16; ++r) Of[cb][r] = fmaf(-PV_MAGIC_F, rho, Of[cb][r]);
         rho = 0.0f;
     };
+    // An item that starts on buffer B (an odd number of blocks per item, after an odd number of items) is
+    // rebased before blocks 9, 17, ... instead of 8, 16, ...: which it is shows in the last bits of the
+    // carry.  The grid of three workgroups per compute unit deals items out differently from the grid of
+    // two; it follows the latter (item v is the (v / 512)-th of its workgroup there), so that a call has the
+    // same bits on both.
     for (;;) {
         if (!step(imgA, lds_offset(bufB), bA, lds_offset(bB), 0)) break;
+        if (WAVES3 && it >= REBASE && (it & (REBASE - 1)) == ((v >> 9) & p.nblk & 1)) rebase();
         if (!step(imgB, lds_offset(bufA), bB, lds_offset(bA), 1)) break;
-        if (it >= REBASE && (it & (REBASE - 2)) == 0) rebase();  // `it`: the block that comes next
+        if (WAVES3 ? it >= REBASE && (it & (REBASE - 1)) == ((v >> 9) & p.nblk & 1)
+                   : it >= REBASE && (it & (REBASE - 2)) == 0) rebase();  // `it`: the block that comes next
     }
 }
 

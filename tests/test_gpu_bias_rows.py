@@ -69,7 +69,8 @@ def test_bias_rows_further_apart_than_a_copy_offset_reaches(N, d):
                                           (2, 65, 512, 64, "table"), (1, 87, 720, 40, "table"), (3, 58, 290, 32, "bf16"), (1, 290, 257, 8, "bf16"), (1, 224, 400, 24, "bf16")])
 def test_three_workgroups_per_compute_unit_give_the_same_bits(B, H, N, d, kind):
     """More than 512 work items that leave the last round of 512 part empty take the kernels built for three
-    waves per SIMD; a few heads of the same call take the others.  Heads are independent: same bits."""
+    waves per SIMD; a few heads of the same call take the others.  Up to 8 key blocks (the accumulator's offset is
+    never removed) a head's bits do not depend on what else is in the call."""
     say(f"three waves B={B} H={H} N={N} d={d} {kind}")
     items = B * H * -(-N // 128)
     assert items > 512 and (kind == "table" or 0 < items % 512 <= 384)
@@ -90,3 +91,43 @@ def test_three_workgroups_per_compute_unit_give_the_same_bits(B, H, N, d, kind):
         part = run(hs)
         torch.cuda.synchronize()
         assert torch.equal(part, out[:, hs]), h0
+
+
+def removal_phase(heads, nrb):
+    """[heads, nrb]: whether the accumulator's offset leaves a row block before key blocks 9, 17, ... (1) or
+    8, 16, ... (0), for an odd number of key blocks and batch 1: item u of a call is dealt out as the v-th, and
+    v / 512 items of its workgroup come before it in a grid of 512."""
+    per = -(-heads * nrb // 8)
+    return (np.arange(heads * nrb) % per * 8 // 512 % 2).reshape(heads, nrb)
+
+
+@pytest.mark.parametrize("kind,d,H1,H2", [("none", 64, 98, 100), ("none", 48, 98, 100), ("bf16", 32, 98, 100), ("table", 64, 150, 3),
+                                          ("table", 32, 150, 140), ("axial", 64, 150, 3), ("axial", 32, 150, 140)])
+def test_more_than_eight_key_blocks_give_the_same_bits_in_every_grid(kind, d, H1, H2):
+    """The same row blocks in calls of H1 and H2 heads, on grids of three or two workgroups per compute unit: where
+    the offset is removed before the same key blocks the bits are the same."""
+    N, nrb = 1104, 9  # token grid of 69 x 16
+    say(f"same bits {kind} d={d} heads {H1} / {H2}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    H = max(H1, H2)
+    q, k, v = (torch.randn(1, H, N, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    bias = torch.randn(H, N, N, generator=g, device="cuda").to(torch.bfloat16) if kind == "bf16" else None
+    table = torch.randn(H, 137, 31, generator=g, device="cuda")
+
+    def run(h):
+        if kind == "table":
+            return ba.attention_relpos(q[:, :h], k[:, :h], v[:, :h], table[:h], d ** -0.5)
+        if kind == "axial":
+            qb, kb, mq, mk = ba.pack_qk(q[:, :h], k[:, :h])
+            return ba.forward_axial(qb, kb, mq, mk, v[:, :h], table[:h, :, 0].contiguous(), table[:h, 0].contiguous(), d ** -0.5)
+        return ba.attention(q[:, :h], k[:, :h], v[:, :h], None if bias is None else bias[:h], d ** -0.5)
+
+    n = min(H1, H2)
+    a, b = run(H1), run(H2)
+    torch.cuda.synchronize()
+    same = removal_phase(H1, nrb)[:n] == removal_phase(H2, nrb)[:n]
+    assert same.sum() > 10
+    for h, rb in zip(*np.nonzero(same)):
+        rows = slice(128 * rb, 128 * rb + 128)
+        assert torch.equal(a[0, h, rows], b[0, h, rows]), (h, rb)
