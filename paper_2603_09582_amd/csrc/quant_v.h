@@ -117,6 +117,7 @@ __device__ __forceinline__ float delta_of_absmax(float a) {
 // instead of 2 and was two thirds of the V phase of the single-launch kernel.
 constexpr float QMAGIC = 12582912.0f;  // 1.5 * 2^23
 __device__ __forceinline__ float quant_exact(float v, float delta) {
+    if (delta == INFINITY) return QMAGIC;  // an infinity in the channel: code 0 (0 x inf, not a number, comes out)
     return fminf(fmaxf(rintf(__fdiv_rn(v, delta)), -127.0f), 127.0f) + QMAGIC;
 }
 // The multipliers of 8 consecutive channels, read from LDS with 16-byte loads up front (the

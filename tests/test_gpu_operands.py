@@ -28,6 +28,30 @@ def test_v_codes_for_every_pair_of_significands(exponent):
     assert np.array_equal(vq[0, 0].cpu().numpy(), ref_q)
 
 
+@pytest.mark.parametrize("N,d", [(100, 64), (128, 72), (300, 40)])
+def test_an_infinity_in_v_gives_code_zero_and_stays_in_its_channel(N, d):
+    """Outside what the calls promise (V is finite), but no number may come out of an infinite scale."""
+    g = torch.Generator().manual_seed(N)
+    q, k, v = (torch.randn(1, 2, N, d, generator=g).to(torch.bfloat16) for _ in range(3))
+    clean = v.clone()
+    v[0, 0, 5, 3], v[0, 0, 7, d - 1], v[0, 0, 9, d - 1] = float("inf"), float("-inf"), float("inf")
+    hit = [3, d - 1]
+    vq, delta = ba.quant_v_debug(v.cuda())
+    assert (vq[0, 0][:, hit] == 0).all() and torch.isinf(delta[0, 0, hit]).all()
+    q, k = q.cuda(), k.cuda()
+    qb, kb, mq, mk = ba.pack_qk(q, k)
+
+    def outs(v):
+        return [ba.attention(q, k, v.cuda(), None, d ** -0.5), ba.forward(qb, kb, mq, mk, v.cuda(), None, d ** -0.5)]
+
+    for got, want in zip(outs(v), outs(clean)):
+        keep = torch.ones(2, d, dtype=torch.bool)
+        keep[0, hit] = False
+        assert torch.equal(got.cpu().transpose(2, 3)[0][keep], want.cpu().transpose(2, 3)[0][keep])
+        if N <= 128:  # one key block: the codes' zero times the scale
+            assert torch.isnan(got[0, 0][:, hit]).all()
+
+
 @pytest.mark.parametrize("N,d", [(100, 64), (250, 72), (300, 40), (333, 128)])
 def test_signs_of_special_values_without_sign_words(N, d):
     g = torch.Generator().manual_seed(N)
