@@ -187,7 +187,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     int mode = (flags & BINATTN_FLAG_LUT) ? BIAS_LUT : BIAS_NONE;
     Strides3 bs = {0, 0, 0};
     int gx_shift = 0;
-    bool wide_rows2 = false;
+    bool wide_rows2 = false, chunk_rows = false;
     if (ax != nullptr) {
         if ((rc = check_axial(*ax, N, raw != nullptr && ax->table != nullptr)) != BINATTN_OK) return rc;
         while ((1 << gx_shift) < ax->Gx) ++gx_shift;
@@ -201,6 +201,9 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         bs.b = bias_strides[0]; bs.h = bias_strides[1]; bs.n = bias_strides[2];
         const int esz = bias_dtype == BINATTN_BIAS_BF16 ? 2 : 4;
         if (!aligned(bias, esz)) return BINATTN_ERR_ALIGN;
+        // rows of whole 16-byte chunks
+        chunk_rows = aligned(bias, 16) && bs.b % 8 == 0 && bs.h % 8 == 0 && bs.n % 8 == 0 &&
+                     (N % 8 == 0 || bs.n >= (N + 7) / 8 * 8);
         // LDS staging takes rows of any alignment whose pitch times 7 fits the copies' 32-bit lane
         // offset.  d > 96 leaves no LDS room for two workgroups with bias tiles per compute unit: there
         // the 8-wave forms are used (the single launch, or row-block pairs where there is more than
@@ -208,7 +211,14 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         // lines per load instruction (N = 197, d = 64, 768 heads, one launch: 50.9 us that way,
         // 42.2 us through LDS; N = 1370, d = 80: 90.5 / 85.5 us).
         const bool lds_ok = bs.n < (1 << 27);
-        wide_rows2 = lds_ok && s.DK == 4 && N > BR && raw == nullptr;
+        // Row-block pairs leave half as many workgroups and copy rows of odd alignment piece by piece: where
+        // bf16 rows are no whole 16-byte chunks but start on 4-byte words, the register path is as fast or
+        // faster (registers / pairs, attention stage, d = 128: 1 x 16 heads N = 300 13.1 / 16.1 us, N = 1370 33.4 / 41.0,
+        // 20 x 3 heads N = 3572 341 / 357, 8 x 16 heads N = 1370 115 / 118, N = 3572 689 / 677; 2-byte rows: 1 x 16 heads
+        // N = 577 26.0 / 23.1, N = 611 21.7 / 22.9, 4 x 16 heads N = 577 39.9 / 24.7, N = 2047 232 / 122).
+        const bool word_rows = bias_dtype == BINATTN_BIAS_BF16 && !chunk_rows && aligned(bias, 4) && bs.b % 2 == 0 &&
+                               bs.h % 2 == 0 && bs.n % 2 == 0;
+        wide_rows2 = lds_ok && s.DK == 4 && N > BR && raw == nullptr && !word_rows;
         const bool lds = lds_ok && (s.DK <= 3 || raw != nullptr || wide_rows2);
         if (bias_dtype == BINATTN_BIAS_BF16) mode = lds ? BIAS_BF16_LDS : BIAS_BF16_VEC;
         else mode = lds ? BIAS_F32_LDS : BIAS_F32_VEC;
@@ -251,8 +261,6 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         p.wide = four ? 3 : 1;
         // (which order the 4-wave form adds the abs-means in: the relative-position table and bf16 rows that
         // are not whole 16-byte chunks take the 8-wave form's at 64 < d <= 96)
-        const bool chunk_rows = aligned(bias, 16) && bs.b % 8 == 0 && bs.h % 8 == 0 && bs.n % 8 == 0 &&
-                                (N % 8 == 0 || bs.n >= (N + 7) / 8 * 8);
         p.split_sums = s.DK == 3 && (mode == BIAS_TABLE || (mode == BIAS_BF16_LDS && !chunk_rows)) ? 1 : 0;
         p.nrb = four ? (N + BR - 1) / BR : 1;
         p.nb = four ? 1 : 2;
