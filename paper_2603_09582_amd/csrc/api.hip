@@ -187,7 +187,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     int mode = (flags & BINATTN_FLAG_LUT) ? BIAS_LUT : BIAS_NONE;
     Strides3 bs = {0, 0, 0};
     int gx_shift = 0;
-    bool wide_rows2 = false, chunk_rows = false;
+    bool wide_rows2 = false, chunk_rows = false, word_rows = false;
     if (ax != nullptr) {
         if ((rc = check_axial(*ax, N, raw != nullptr && ax->table != nullptr)) != BINATTN_OK) return rc;
         while ((1 << gx_shift) < ax->Gx) ++gx_shift;
@@ -216,8 +216,8 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         // faster (registers / pairs, attention stage, d = 128: 1 x 16 heads N = 300 13.1 / 16.1 us, N = 1370 33.4 / 41.0,
         // 20 x 3 heads N = 3572 341 / 357, 8 x 16 heads N = 1370 115 / 118, N = 3572 689 / 677; 2-byte rows: 1 x 16 heads
         // N = 577 26.0 / 23.1, N = 611 21.7 / 22.9, 4 x 16 heads N = 577 39.9 / 24.7, N = 2047 232 / 122).
-        const bool word_rows = bias_dtype == BINATTN_BIAS_BF16 && !chunk_rows && aligned(bias, 4) && bs.b % 2 == 0 &&
-                               bs.h % 2 == 0 && bs.n % 2 == 0;
+        word_rows = bias_dtype == BINATTN_BIAS_BF16 && !chunk_rows && aligned(bias, 4) && bs.b % 2 == 0 &&
+                    bs.h % 2 == 0 && bs.n % 2 == 0;
         wide_rows2 = lds_ok && s.DK == 4 && N > BR && raw == nullptr && !word_rows;
         const bool lds = lds_ok && (s.DK <= 3 || raw != nullptr || wide_rows2);
         if (bias_dtype == BINATTN_BIAS_BF16) mode = lds ? BIAS_BF16_LDS : BIAS_BF16_VEC;
@@ -287,15 +287,18 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         return launch_fused_dk<4>(p, mode, st);
     }
     // Long sequences with a batch-shared, LDS-staged bias: pair batch entries in one
-    // workgroup so that the bias stream is fetched once per pair.
-    p.nb = (mode == BIAS_BF16_LDS && bs.b == 0 && B % 2 == 0 && s.DK <= 2 && s.nblk >= 8) ? 2 : 1;
+    // workgroup so that the bias stream is fetched once per pair.  Rows that start on 4-byte words only: where the
+    // bias exceeds the 256 MB Infinity Cache (pairs / single entries, attention stage: 2 x 3 heads, d = 64, N = 1370 30.5 / 25.9 us,
+    // 8 x 12 heads N = 1370 89.3 / 82.5, d = 32 83.5 / 68.9, 16 x 16 heads, d = 32, N = 1374 166 / 138; 2 x 16 heads, d = 64, N = 3572
+    // (408 MB) 152 / 165, 4 x 16 heads N = 5002 (800 MB) 525 / 576; 2-byte rows, 8 x 12 heads, d = 64, N = 1027 51.1 / 57.9,
+    // N = 2047 127 / 145).
+    const bool streamed = (int64_t)H * N * bs.n * 2 > ((int64_t)256 << 20);
+    p.nb = (mode == BIAS_BF16_LDS && (!word_rows || streamed) && bs.b == 0 && B % 2 == 0 && s.DK <= 2 && s.nblk >= 8) ? 2 : 1;
     // A bias shared over the batch and larger than the 256 MB Infinity Cache streams through once per
     // call: its copies are marked as not worth keeping.  Only where rows start on 128-byte lines (else two
     // blocks read the same line).  Measured with / without: N = 16384, 16 heads 2764 / 2805 us; N = 4096, 12 heads,
     // batch 8 518 / 527; but N = 2048, 8 heads (67 MB) 180.0 / 178.6 and N = 3137 (odd rows) 156 / 148.
-    if (p.nb == 2 && aligned(bias, 128) && bs.h % 64 == 0 && bs.n % 64 == 0 &&
-        (int64_t)H * N * bs.n * 2 > ((int64_t)256 << 20))
-        p.wide = 4;
+    if (p.nb == 2 && aligned(bias, 128) && bs.h % 64 == 0 && bs.n % 64 == 0 && streamed) p.wide = 4;
     p.total_wg = p.nrb * H * (B / p.nb);
     switch (s.DK) {
         case 1: return launch_fused_dk<1>(p, mode, st);
