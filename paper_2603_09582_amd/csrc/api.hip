@@ -274,6 +274,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         }
     }
     p.split_sums = 0;
+    p.phase512 = bias_dtype == BINATTN_BIAS_BF16 && chunk_rows ? 0 : 1;
     p.xq = p.xk = p.xv = nullptr;
     p.xqs = p.xks = p.xvs = Strides3{0, 0, 0};
     p.mu_q_out = p.mu_k_out = nullptr;

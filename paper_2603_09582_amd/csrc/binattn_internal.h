@@ -188,6 +188,7 @@ struct FusedParams {
     const uint16_t *xq, *xk, *xv;
     Strides3 xqs, xks, xvs;
     int use_mu;
+    int phase512;        // 8-wave forms: the accumulator's offset is removed where the 4-wave form on the grid of 512 does
     int split_sums;      // 4-wave single launch: abs-means in the 8-wave form's order
     float *mu_q_out, *mu_k_out;
     const float *ax_y, *ax_x;  // BIAS_AXIAL: fp32 [H][2 Gy - 1], [H][2 Gx - 1]

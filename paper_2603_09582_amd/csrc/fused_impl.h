@@ -1152,17 +1152,32 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             for (int r = 0; r < 16; ++r) Of[cb][r] = fmaf(-PV_MAGIC_F, rho, Of[cb][r]);
         rho = 0.0f;
     };
-    // An item that starts on buffer B (an odd number of blocks per item, after an odd number of items) is
+    // A 4-wave item that starts on buffer B (an odd number of blocks per item, after an odd number of items) is
     // rebased before blocks 9, 17, ... instead of 8, 16, ...: which it is shows in the last bits of the
-    // carry.  The grid of three workgroups per compute unit deals items out differently from the grid of
-    // two; it follows the latter (item v is the (v / 512)-th of its workgroup there), so that a call has the
-    // same bits on both.
+    // carry.  The grid of three workgroups per compute unit deals items out differently, and the 8-wave forms
+    // deal out pairs of them: they follow the grid of 512, where the item with index u is the
+    // (u % per / 64)-th of its workgroup, so that a row block has the same bits whichever form serves it.  (Rows of
+    // whole 16-byte chunks, which the 8-wave forms have always served, keep those forms' own order.)
+    auto rebase_phase = [&]() -> int {
+        if (WAVES3) return (v >> 9) & p.nblk & 1;
+        if (!p.phase512) return ROWS2 ? (v >> 8) & p.nblk & 1 : 0;
+        const int nrb1 = (N + BR - 1) / BR, per = (p.B * p.H * nrb1 + 7) >> 3;
+        const int u = (cur.h * nrb1 + min(cur.rb, nrb1 - 1)) * p.B + cur.b;
+        return ((u % per) >> 6) & p.nblk & 1;
+    };
+    constexpr bool PHASE = WAVES3 || PAIR || ROWS2;
+    int phase = PHASE ? rebase_phase() : 0;
+    // `it`: the block that comes next
+    auto rebase_now = [&]() -> bool {
+        if (!PHASE) return it >= REBASE && (it & (REBASE - 2)) == 0;
+        if (WAVES3 || (ROWS2 && it == 0)) phase = rebase_phase();
+        return it >= REBASE && (it & (REBASE - 1)) == phase;
+    };
     for (;;) {
         if (!step(imgA, lds_offset(bufB), bA, lds_offset(bB), 0)) break;
-        if (WAVES3 && it >= REBASE && (it & (REBASE - 1)) == ((v >> 9) & p.nblk & 1)) rebase();
+        if (PHASE && rebase_now()) rebase();
         if (!step(imgB, lds_offset(bufA), bB, lds_offset(bA), 1)) break;
-        if (WAVES3 ? it >= REBASE && (it & (REBASE - 1)) == ((v >> 9) & p.nblk & 1)
-                   : it >= REBASE && (it & (REBASE - 2)) == 0) rebase();  // `it`: the block that comes next
+        if (rebase_now()) rebase();
     }
 }
 

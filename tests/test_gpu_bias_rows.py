@@ -131,3 +131,19 @@ def test_more_than_eight_key_blocks_give_the_same_bits_in_every_grid(kind, d, H1
     for h, rb in zip(*np.nonzero(same)):
         rows = slice(128 * rb, 128 * rb + 128)
         assert torch.equal(a[0, h, rows], b[0, h, rows]), (h, rb)
+
+
+@pytest.mark.parametrize("B,H,N,d", [(2, 40, 1101, 64), (2, 40, 1101, 32), (2, 40, 1101, 128), (4, 20, 1149, 104)])
+def test_more_than_eight_key_blocks_give_the_same_bits_for_odd_and_even_rows(B, H, N, d):
+    """Rows of odd alignment go to 8-wave workgroups (pairs of batch entries, of row blocks), rows on 4-byte words
+    to 4-wave ones: more than 512 row blocks of an odd number of key blocks, the same bits."""
+    assert B * H * (-(-N // 128)) > 512 and -(-N // 128) % 2 == 1
+    say(f"odd and even rows B={B} H={H} N={N} d={d}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    q, k, v = (torch.randn(B, H, N, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    bias = torch.randn(H, N, N, generator=g, device="cuda").to(torch.bfloat16)
+    odd = ba.attention(q, k, v, placed(bias, 0, 0), d ** -0.5)
+    even = ba.attention(q, k, v, placed(bias, 0, 1), d ** -0.5)
+    torch.cuda.synchronize()
+    assert torch.equal(odd, even)
