@@ -204,7 +204,8 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream);
 constexpr int ONEHEAD4_MIN_HEADS = 256;
 // ... in the variants whose 256-thread prologue holds a head's loads in registers without spilling
 constexpr bool onehead4_built(int DK, int mode) {
-    return DK <= 2 || (DK == 3 && (mode == BIAS_NONE || mode == BIAS_F32_VEC || mode == BIAS_BF16_LDS || mode == BIAS_AXIAL || mode == BIAS_TABLE));
+    return DK <= 2 || (DK == 3 && (mode == BIAS_NONE || mode == BIAS_F32_VEC || mode == BIAS_F32_LDS || mode == BIAS_BF16_LDS ||
+                       mode == BIAS_AXIAL || mode == BIAS_TABLE));
 }
 
 template <int DK>

@@ -476,6 +476,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     };
     f4v fraw[F32L ? SEGS : 1][4];      // F32L: the staged quarters of the current block
     f4v freg[F32L ? 4 - SEGS : 1][4];  // F32L: this lane's values of the quarters that are not staged
+    // ... loaded before the exponentials of the block before; where the registers do not hold them then
+    // (24 bytes per lane were spilled), behind them, and the bias addresses are formed in every block
+    constexpr bool BIAS_LATE = F32L && ONEHEAD4 && DK == 3;
     auto load_bias_quarters = [&](const char *row, int blk) {
         const float *src = reinterpret_cast<const float *>(row) + blk * BV + 16 * g;
 #pragma unroll
@@ -613,7 +616,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         const bool sw = PERSIST && last;  // ... which belongs to the next item
         const char *nimg = sw ? image_ptr(nxt) : imgs + (int64_t)(it + 1) * L::BYTES;
         const int nblkidx = sw ? 0 : it + 1;
-        const BiasSrc nsrc = (LDS_BIAS && sw) ? bias_dma_src(nxt) : bsrc;
+        const BiasSrc nsrc = (LDS_BIAS && (sw || BIAS_LATE)) ? bias_dma_src(sw ? nxt : cur) : bsrc;
         if (!ONEHEAD && more) dma_image<DK, NWI>(nimg, inxt + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
         if (!ONEHEAD && it == 0 && (ROWS2 ? wreg : wave) == 0 && lane < DKP / 4)  // delta_v of this item, for its epilogue
             dma16(p.delta + (int64_t)cur.bh * DKP, 16 * lane, lds_offset(&sdelta[parity][isel][0]));
@@ -721,7 +724,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (F32L && more) load_bias_quarters(sw ? bias_row_ptr(nxt) : brow, nblkidx);
+        if (F32L && !BIAS_LATE && more) load_bias_quarters(sw ? bias_row_ptr(nxt) : brow, nblkidx);
         if (MODE == BIAS_BF16_VEC && more)  // braw is free again
             load_bias_vec(sw ? bias_row_ptr(nxt) : brow, nblkidx);
         if (LDS_BIAS && !BIAS_DB && more) {
@@ -850,6 +853,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             if (BIAS_DB && more && t < 2 * RGW) dma_bias_one(nsrc, nblkidx, nklim, bnxt, t);
         }
         }
+        if (BIAS_LATE) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) load_bias_quarters(bias_row_ptr(sw ? nxt : cur), nblkidx);
+        }
         l_run = fmaf(l_run, resc, ls0 + ls1);
         rho = fmaf(rho, resc, 1.0f);
 
@@ -928,7 +935,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             dma_bias(cur, bsrc, 0, lds_offset(bA));
         }
         if (MODE == BIAS_BF16_VEC) load_bias_vec(bias_row_ptr(cur), 0);
-        if (F32L) load_bias_quarters(bias_row_ptr(cur), 0);
+        if (F32L && !BIAS_LATE) load_bias_quarters(bias_row_ptr(cur), 0);
         // this lane's query row: the chunks of the sign words its B operand needs (channels
         // 64 s + 32 g + 8 j); addresses are clamped into the row, unused chunks are skipped below
         const int qrow = cur.rb * BR + wave * ROWS_PER_WAVE + m;
@@ -1110,6 +1117,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         fetch_item_regs(cur);
     }
     begin_item(cur);
+    if (BIAS_LATE) load_bias_quarters(brow, 0);
     if (!ONEHEAD) {
         if (MODE == BIAS_BF16_VEC) load_bias_vec(brow, 0);
         if (F32L) load_bias_quarters(brow, 0);

@@ -109,7 +109,7 @@ def ordered_abs_mean(x, waves, keys):
 
 # (kind of bias decides between the forms above 256 heads and 64 channels)
 @pytest.mark.parametrize("H,flags,kind", [(6, 0, "rows16"), (260, 0, "rows16"), (260, ba.FLAG_WIDE8, "rows16"), (260, 0, "odd"),
-                                          (260, 0, "none"), (260, 0, "table")])
+                                          (260, 0, "none"), (260, 0, "table"), (260, 0, "f32")])
 @pytest.mark.parametrize("N,d", [(1, 64), (96, 64), (208, 64), (256, 32), (240, 72), (256, 96), (128, 80)])
 def test_abs_means_of_the_single_launch_are_added_in_a_fixed_order(N, d, H, flags, kind):
     """The logit multiplier is made of these two numbers: their last bits decide single 8-bit codes of P.  So
@@ -125,7 +125,8 @@ def test_abs_means_of_the_single_launch_are_added_in_a_fixed_order(N, d, H, flag
         ba.forward_fused_relpos(q, k, v, table, d ** -0.5, mu_q=mq, mu_k=mk, flags=flags)
     else:
         pitch = N + (1 if kind == "odd" else -N % 8)
-        bias = None if kind == "none" else torch.randn(H, N, pitch, generator=g, device="cuda").to(torch.bfloat16)[:, :, :N]
+        dtype = torch.float32 if kind == "f32" else torch.bfloat16
+        bias = None if kind == "none" else torch.randn(H, N, pitch, generator=g, device="cuda").to(dtype)[:, :, :N]
         ba.forward_fused(q, k, v, bias, d ** -0.5, mu_q=mq, mu_k=mk, flags=flags)
     torch.cuda.synchronize()
     eight = H <= 256 or flags or (d > 64 and kind in ("odd", "table"))
