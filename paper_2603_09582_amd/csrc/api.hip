@@ -301,6 +301,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     // batch 8 518 / 527; but N = 2048, 8 heads (67 MB) 180.0 / 178.6 and N = 3137 (odd rows) 156 / 148.
     if (p.nb == 2 && aligned(bias, 128) && bs.h % 64 == 0 && bs.n % 64 == 0 && streamed) p.wide = 4;
     p.total_wg = p.nrb * H * (B / p.nb);
+    if (mode == BIAS_BF16_LDS && p.nb == 1 && N % 8 == 0) mode = BIAS_BF16_LDS8;
     switch (s.DK) {
         case 1: return launch_fused_dk<1>(p, mode, st);
         case 2: return launch_fused_dk<2>(p, mode, st);

@@ -159,6 +159,7 @@ enum BiasMode {
     BIAS_F32_VEC = 3,   // fp32 rows, 16-byte loads at use (where BIAS_BF16_VEC would be taken)
     BIAS_F32_LDS = 15,  // fp32 rows of any alignment: most of the tile staged global -> LDS, the rest into registers
     BIAS_BF16_LDS = 5,  // rows of any alignment: tile staged global -> LDS asynchronously
+    BIAS_BF16_LDS8 = 17, // the same for N a multiple of 8 (4-wave workgroups over a prepared workspace): no copy reads past a row
     BIAS_AXIAL = 7,     // b_ij = y[iy - jy] + x[ix - jx] on a Gy x Gx token grid, tables held in LDS
     BIAS_TABLE = 9,     // b_ij = t[iy - jy][ix - jx]: the full relative-position table of the head in LDS (single-launch forms)
     BIAS_TABLE_BLK = 13, // the same table, only the rows a key block needs, staged per block

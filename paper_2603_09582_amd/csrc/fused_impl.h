@@ -112,7 +112,12 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     constexpr int DKP = 32 * DK;
     constexpr int DK2 = L::DK2;
     constexpr bool F32L = MODE == BIAS_F32_LDS;
-    constexpr bool LDS_BIAS = MODE == BIAS_BF16_LDS || F32L;
+    constexpr bool BF16L = MODE == BIAS_BF16_LDS || MODE == BIAS_BF16_LDS8, LDS_BIAS = BF16L || F32L;
+    // A chunk can straddle the end of a row.  Where none can, the block loop is built without the code for it:
+    // its branches sit between the logits and the exponentials and cost 2-3 % even where they are never taken
+    // (attention stage, with / without: N = 520, d = 64, 192 heads 34.0 / 33.0 us, N = 1024, d = 72, 128 heads 52.0 / 51.5, N = 1376, d = 96,
+    // 192 heads 152.3 / 149.4; nothing in the 8-wave forms).
+    constexpr bool STRADDLE = MODE != BIAS_BF16_LDS8;
     // Staged bias rows: SEGS segments of 128 bytes per row and block.  A bf16 tile is staged whole
     // (two segments); an fp32 tile would be 16 KiB per wave, so its first SEGS 32-key quarters (one per
     // QK tile) are staged and the others go straight into registers, one block ahead: three
@@ -469,8 +474,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                                           region + ((rg0 + j) * SEGS + seg) * 1024);
     };
     auto dma_bias = [&](const Item &t, const BiasSrc &src, int blk, unsigned region) {  // region: LDS offset of the tile
-        const int klim = bias_klimit(t, blk);
-        if (klim != N) bias_tail(t, blk, region);
+        const int klim = STRADDLE ? bias_klimit(t, blk) : N;
+        if (STRADDLE && klim != N) bias_tail(t, blk, region);
 #pragma unroll
         for (int idx = 0; idx < SEGS * RGW; ++idx) dma_bias_one(src, blk, klim, region, idx);
     };
@@ -527,7 +532,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         if (MODE == BIAS_NONE) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) bt[r] = 0.0f;
-        } else if (MODE == BIAS_BF16_VEC || MODE == BIAS_BF16_LDS) {
+        } else if (MODE == BIAS_BF16_VEC || BF16L) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const u4v w = braw[2 * t + i];
@@ -1198,7 +1203,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 // bias 80.9 / 67.5 (576), but 96 heads, N = 2048, d = 32 97.2 / 98.5 (1536), 12 heads, N = 4096 69.0 / 72.0 (384).
 constexpr bool use_waves3(int DK, int mode, int items) {
     const bool generated = (mode == BIAS_AXIAL && DK <= 2) || (mode == BIAS_TABLE_BLK && (DK == 1 || (DK == 2 && items > 512)));
-    const bool other = (mode == BIAS_NONE && DK <= 2) || (mode == BIAS_BF16_LDS && DK == 1);
+    const bool other = (mode == BIAS_NONE && DK <= 2) || ((mode == BIAS_BF16_LDS || mode == BIAS_BF16_LDS8) && DK == 1);
     return generated || (other && items > 512 && items % 512 != 0 && items % 512 <= 384);
 }
 
@@ -1250,8 +1255,9 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
         break;
         CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE_BLK)
         case BIAS_BF16_LDS:
+        case BIAS_BF16_LDS8:
             if constexpr (DK <= 3) {
-                switch (mode) { CASE(BIAS_BF16_LDS) }
+                switch (mode) { CASE(BIAS_BF16_LDS) CASE(BIAS_BF16_LDS8) }
                 break;
             }
             return BINATTN_ERR_SHAPE;

@@ -27,7 +27,9 @@ def placed(bias, offset, extra):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("B,H,N,d", [(1, 2, 1, 64), (1, 3, 7, 64), (2, 1, 127, 72), (1, 2, 129, 64), (2, 2, 197, 64),
                                      (1, 2, 255, 104), (130, 2, 131, 64), (1, 1, 257, 72), (1, 2, 391, 128), (2, 2, 642, 80),
-                                     (3, 1, 577, 64), (2, 2, 577, 32), (4, 1, 965, 64), (2, 1, 1030, 64)])
+                                     (3, 1, 577, 64), (2, 2, 577, 32), (4, 1, 965, 64), (2, 1, 1030, 64),
+                                     # multiples of 8: no chunk straddles the end of a row
+                                     (1, 2, 8, 64), (2, 1, 200, 72), (1, 2, 264, 32), (3, 1, 520, 96), (2, 2, 384, 64)])
 def test_bias_rows_of_any_alignment(B, H, N, d, dtype):
     x = small_inputs(B, H, N, d, 900 + N)
     bias = (x.bias.float() * 40.0).to(dtype)  # strong enough that every entry shows in the output
