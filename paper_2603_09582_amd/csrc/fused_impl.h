@@ -1196,13 +1196,15 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 
 // Three waves per SIMD instead of two hide more of a block's LDS and matrix latencies where the biases are
 // generated (two / three waves: decomposed, d = 64, N = 16384 2073 / 1918 us, N = 4096, 96 heads 436 / 412; table,
-// d = 32 120 / 110, d = 64 2170 / 1987, but 24 items, d = 64 26.5 / 26.9).  Without a bias or with dense tiles (up to 32
+// d = 32 120 / 110, d = 64 2170 / 1987), but not where all items fit two workgroups per compute unit (table, 24 items,
+// d = 64 26.5 / 26.9; decomposed, attention stage, d = 32, N = 2048, 128 items 24.4 / 25.2, d = 64, N = 16384, 256 items 188 / 192,
+// N = 1024, 384 items 20.8 / 21.2, though d = 32, N = 2048, 384 items 32.8 / 32.2).  Without a bias or with dense tiles (up to 32
 // channels: LDS) a workgroup's block takes as much longer as there are more of them, and what counts is
 // the last round, which leaves the chip less idle unless the 512 slots of two waves fill theirs: 96 heads,
 // N = 1024, d = 64 43.6 / 41.1 us (768 items), 480 heads, N = 600, d = 48 88.8 / 84.1 (2400), 36 heads, N = 2048, d = 32, bf16
 // bias 80.9 / 67.5 (576), but 96 heads, N = 2048, d = 32 97.2 / 98.5 (1536), 12 heads, N = 4096 69.0 / 72.0 (384).
 constexpr bool use_waves3(int DK, int mode, int items) {
-    const bool generated = (mode == BIAS_AXIAL && DK <= 2) || (mode == BIAS_TABLE_BLK && (DK == 1 || (DK == 2 && items > 512)));
+    const bool generated = (mode == BIAS_AXIAL && DK <= 2 && items > 512) || (mode == BIAS_TABLE_BLK && (DK == 1 || (DK == 2 && items > 512)));
     const bool other = (mode == BIAS_NONE && DK <= 2) || ((mode == BIAS_BF16_LDS || mode == BIAS_BF16_LDS8) && DK == 1);
     return generated || (other && items > 512 && items % 512 != 0 && items % 512 <= 384);
 }
