@@ -611,6 +611,24 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     int parity = 0;    // items alternate between the two delta_v copies
     Item nxt = decode(PERSIST ? v + gridDim.x : vmax);
 
+    // The block before which the accumulator's offset is next removed (see the loop).  A 4-wave item that
+    // starts on buffer B (an odd number of blocks per item, after an odd number of items) is rebased before
+    // blocks 9, 17, ... instead of 8, 16, ...: which it is shows in the last bits of the carry.  The grid of
+    // three workgroups per compute unit deals items out differently, and the 8-wave forms deal out pairs of
+    // them: they follow the grid of 512, where the item with index u is the (u % per / 64)-th of its
+    // workgroup, so that a row block has the same bits whichever form serves it.  (Rows of whole 16-byte chunks,
+    // which the 8-wave forms have always served, keep those forms' own order.)
+    constexpr bool PHASE = WAVES3 || PAIR || ROWS2;
+    auto first_rebase = [&]() -> int {
+        if (!PHASE) return 0;
+        if (WAVES3) return REBASE + ((v >> 9) & p.nblk & 1);
+        if (!p.phase512) return REBASE + (ROWS2 ? (v >> 8) & p.nblk & 1 : 0);
+        const int nrb1 = (N + BR - 1) / BR, per = (p.B * p.H * nrb1 + 7) >> 3;
+        const int u = (cur.h * nrb1 + min(cur.rb, nrb1 - 1)) * p.B + cur.b;
+        return REBASE + (((u % per) >> 6) & p.nblk & 1);
+    };
+    int next_rebase = PAIR ? 0 : first_rebase();
+
     // One key/value block of the stream: compute block `it` of item `cur` from the image at
     // `ibuf` (and bias tile at `bbuf`), prefetch the next block of the stream into the LDS
     // offsets `inxt` / `bnxt`.  Returns false after the last block of the last item.
@@ -909,6 +927,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         nxt = decode(v + gridDim.x);
         begin_item(cur);
         it = 0;
+        if (!PAIR) next_rebase = first_rebase();
         if (!ONEHEAD4) parity ^= 1;  // (the single-launch forms keep one copy of delta_v)
         return true;
     };
@@ -1164,27 +1183,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 #pragma unroll
             for (int r = 0; r < 16; ++r) Of[cb][r] = fmaf(-PV_MAGIC_F, rho, Of[cb][r]);
         rho = 0.0f;
+        if (!PAIR) next_rebase += REBASE;
     };
-    // A 4-wave item that starts on buffer B (an odd number of blocks per item, after an odd number of items) is
-    // rebased before blocks 9, 17, ... instead of 8, 16, ...: which it is shows in the last bits of the
-    // carry.  The grid of three workgroups per compute unit deals items out differently, and the 8-wave forms
-    // deal out pairs of them: they follow the grid of 512, where the item with index u is the
-    // (u % per / 64)-th of its workgroup, so that a row block has the same bits whichever form serves it.  (Rows of
-    // whole 16-byte chunks, which the 8-wave forms have always served, keep those forms' own order.)
-    auto rebase_phase = [&]() -> int {
-        if (WAVES3) return (v >> 9) & p.nblk & 1;
-        if (!p.phase512) return ROWS2 ? (v >> 8) & p.nblk & 1 : 0;
-        const int nrb1 = (N + BR - 1) / BR, per = (p.B * p.H * nrb1 + 7) >> 3;
-        const int u = (cur.h * nrb1 + min(cur.rb, nrb1 - 1)) * p.B + cur.b;
-        return ((u % per) >> 6) & p.nblk & 1;
-    };
-    constexpr bool PHASE = WAVES3 || PAIR || ROWS2;
-    int phase = PHASE ? rebase_phase() : 0;
-    // `it`: the block that comes next
-    auto rebase_now = [&]() -> bool {
-        if (!PHASE) return it >= REBASE && (it & (REBASE - 2)) == 0;
-        if (WAVES3 || (ROWS2 && it == 0)) phase = rebase_phase();
-        return it >= REBASE && (it & (REBASE - 1)) == phase;
+    // (paired form: one item, its phase formed here: 2 % faster than a running block number)
+    const int phase = PAIR ? first_rebase() - REBASE : 0;
+    auto rebase_now = [&]() -> bool {  // `it`: the block that comes next
+        if (PAIR) return it >= REBASE && (it & (REBASE - 1)) == phase;
+        return PHASE ? it == next_rebase : it >= REBASE && (it & (REBASE - 2)) == 0;
     };
     for (;;) {
         if (!step(imgA, lds_offset(bufB), bA, lds_offset(bB), 0)) break;
