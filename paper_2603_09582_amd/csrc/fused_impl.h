@@ -1207,11 +1207,22 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 // channels: LDS) a workgroup's block takes as much longer as there are more of them, and what counts is
 // the last round, which leaves the chip less idle unless the 512 slots of two waves fill theirs: 96 heads,
 // N = 1024, d = 64 43.6 / 41.1 us (768 items), 480 heads, N = 600, d = 48 88.8 / 84.1 (2400), 36 heads, N = 2048, d = 32, bf16
-// bias 80.9 / 67.5 (576), but 96 heads, N = 2048, d = 32 97.2 / 98.5 (1536), 12 heads, N = 4096 69.0 / 72.0 (384).
+// bias 80.9 / 67.5 (576), but 96 heads, N = 2048, d = 32 97.2 / 98.5 (1536), 12 heads, N = 4096 69.0 / 72.0 (384).  Between
+// 769 and 896 items, where both take two rounds, and over tens of rounds three waves stay ahead (whole calls):
+// N = 1024, d = 64 97 heads 48.5 / 46.6, 112 heads 49.6 / 48.1, d = 32 112 heads 42.2 / 41.2, bf16 bias 60.0 / 59.2; N = 600, d = 48
+// 1501 heads (7505 items) 258 / 245, N = 1000, d = 64 1501 heads (12008) 574 / 555.  At a remainder of 0 or above 384 it goes
+// either way (attention stage: d = 64, N = 1024 1024 heads 240 / 231, but d = 32, bf16 bias, N = 1000 1024 heads 452 / 460, 128 heads
+// 51.8 / 55.4).
 constexpr bool use_waves3(int DK, int mode, int items) {
     const bool generated = (mode == BIAS_AXIAL && DK <= 2 && items > 512) || (mode == BIAS_TABLE_BLK && (DK == 1 || (DK == 2 && items > 512)));
     const bool other = (mode == BIAS_NONE && DK <= 2) || ((mode == BIAS_BF16_LDS || mode == BIAS_BF16_LDS8) && DK == 1);
     return generated || (other && items > 512 && items % 512 != 0 && items % 512 <= 384);
+}
+// Dense tiles up to 32 channels are built once: both forms take 162 registers and run alike on the grid of two (N = 1024,
+// 63 heads 26.1 / 26.0 us).  Without a bias the accumulator's offset removal between the two blocks of the loop costs the
+// three-wave form 4 % there (4 heads, N = 8192 73.9 / 76.9).
+constexpr bool waves2_built(int DK, int mode) {
+    return !use_waves3(DK, mode, 1) && !(DK == 1 && (mode == BIAS_BF16_LDS || mode == BIAS_BF16_LDS8));
 }
 
 template <int DK>
@@ -1249,16 +1260,16 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
         return BINATTN_ERR_SHAPE;
     }
     switch (mode) {
-// (the form of three waves per SIMD where use_waves3 may choose it, the other one unless it always does)
+// (the form of three waves per SIMD where use_waves3 may choose it or is the only one)
 #define CASE(M)                                                                                       \
     case M:                                                                                           \
         if constexpr (use_waves3(DK, M, 513)) {                                                       \
-            if (waves3) {                                                                             \
+            if (waves3 || !waves2_built(DK, M)) {                                                     \
                 hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_WAVES3>), grid, block, 0, stream, p); \
                 break;                                                                                \
             }                                                                                         \
         }                                                                                             \
-        if constexpr (!use_waves3(DK, M, 1)) hipLaunchKernelGGL((fused_kernel<DK, M, 1>), grid, block, 0, stream, p); \
+        if constexpr (waves2_built(DK, M)) hipLaunchKernelGGL((fused_kernel<DK, M, 1>), grid, block, 0, stream, p); \
         break;
         CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE_BLK)
         case BIAS_BF16_LDS:
