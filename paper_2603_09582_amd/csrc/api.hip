@@ -297,8 +297,9 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     p.nb = (mode == BIAS_BF16_LDS && (!word_rows || streamed) && bs.b == 0 && B % 2 == 0 && s.DK <= 2 && s.nblk >= 8) ? 2 : 1;
     // A bias shared over the batch and larger than the 256 MB Infinity Cache streams through once per
     // call: its copies are marked as not worth keeping.  Only where rows start on 128-byte lines (else two
-    // blocks read the same line).  Measured with / without: N = 16384, 16 heads 2764 / 2805 us; N = 4096, 12 heads,
-    // batch 8 518 / 527; but N = 2048, 8 heads (67 MB) 180.0 / 178.6 and N = 3137 (odd rows) 156 / 148.
+    // blocks read the same line).  Attention stage with / without, three rounds of 15 turns each, the same to 0.3 %: N = 16384,
+    // 2 x 16 heads 2681 / 2719 us, 2 x 8 heads 1338 / 1357, d = 32 2475 / 2512; N = 8192, 2 x 16 heads 674 / 684; N = 4096, 2 x 16 heads 174 / 179,
+    // 8 x 12 heads 464 / 467; but N = 2048, 8 heads (67 MB) 180.0 / 178.6 and N = 3137 (odd rows) 156 / 148.
     if (p.nb == 2 && aligned(bias, 128) && bs.h % 64 == 0 && bs.n % 64 == 0 && streamed) p.wide = 4;
     p.total_wg = p.nrb * H * (B / p.nb);
     if (mode == BIAS_BF16_LDS && p.nb == 1 && N % 8 == 0) mode = BIAS_BF16_LDS8;
