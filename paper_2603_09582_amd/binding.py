@@ -123,8 +123,15 @@ def _strides3(t: torch.Tensor):
     return _i64x3(st[0], st[1], st[2])
 
 
+# (neither function is a public one of torch: without them the Stream object is built)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _check(rc: int, where: str):

@@ -246,3 +246,17 @@ def test_probe_rejects_bad_arguments():
     assert L.binattn_probe_valu(0, 0, 4, FAKE, None) == -2 and L.binattn_probe_valu(0, 16, 0, FAKE, None) == -2
     assert L.binattn_probe_valu(0, 16, 4, FAKE + 2, None) == -4
     assert L.binattn_probe_valu(99, 16, 4, FAKE, None) == -8 and L.binattn_probe_valu(2 | (3 << 8), 16, 4, FAKE, None) == -8
+
+
+@pytest.mark.parametrize("gone", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_handle_without_torchs_private_functions(gone, monkeypatch):
+    import importlib.util
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, gone, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    spec = importlib.util.spec_from_file_location("binding_again", ba.__file__)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    assert mod._stream() == 1234
