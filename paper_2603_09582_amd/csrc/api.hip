@@ -1,5 +1,6 @@
 // C ABI of libbinattn: argument validation (before anything is launched) and
 // the launch sequences.  See include/binattn.h for the contract.
+#include "bias_rows.h"
 #include "binattn_internal.h"
 
 #include <mutex>
@@ -234,7 +235,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     p.mu_k = use_mu ? mu_k : nullptr;
     p.bias = use_bias ? bias : nullptr;
     p.bs = bs;
-    p.bias_end = (int64_t)(B - 1) * bs.b + (int64_t)(H - 1) * bs.h + (int64_t)(N - 1) * bs.n + N;
+    p.bias_end = bias_extent(B, H, N, bs.b, bs.h, bs.n);
     p.scale = scale;
     p.out = static_cast<uint16_t *>(out);
     p.os = os;

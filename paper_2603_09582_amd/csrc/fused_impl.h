@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "attn_tiles.h"
+#include "bias_rows.h"
 #include "quant_v.h"
 
 namespace binattn {
@@ -237,12 +238,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     float inv_alpha, a2;
     v4i qB[DK2];
     const char *brow = nullptr;  // this lane's bias row (register modes)
-    // BIAS_BF16_LDS: the tile is fetched with full-cache-line requests (8 lanes cover the
-    // 128 bytes of one row segment) straight into LDS.  Copy instruction (rg, gh) moves rows
-    // 8 rg + [0, 8) x keys 64 gh + [0, 64); lane 8 r' + s fetches 16-byte chunk c = s ^ r of
-    // row r = r' ^ (rg & 1), so that chunk c of row r lands at 128 (r ^ (rg & 1)) + 16 (c ^ r):
-    // the later 16-byte reads of 16 consecutive rows (two row groups) at one chunk index hit
-    // 16 different 16-byte bank groups of the 256-byte LDS row.
+    // Dense tiles are fetched with full-cache-line requests (8 lanes cover the 128 bytes of one row
+    // segment) straight into LDS; which lane fetches what and where it lands: bias_rows.h.
     // A wave copies RGW of the four 8-row groups of its 32-row tile: all four when the
     // tile is its own (NB = 1), two when the tile is shared with the other batch entry.
     constexpr int RGW = PAIR ? 2 : 4;
@@ -259,7 +256,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     for (int j = 0; j < RGW; ++j) {
         bsrc.base[j] = nullptr;
         bsrc.voff[j] = 0;
-        dma_c[j] = (lane & 7) ^ (lane >> 3) ^ ((rg0 + j) & 1);
+        dma_c[j] = bias_copy_chunk(rg0 + j, lane);
     }
     int ax_ub = 0, ax_wb = 0;  // BIAS_AXIAL: this lane's window base in axu (floats), its y-table base
     float m_run, l_run, rho;  // running max (units of T = S / alpha), sum of 255 exp(S - m), rescale sum
@@ -296,9 +293,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 #pragma unroll
         for (int j = 0; j < RGW; ++j) {
             const int rg = rg0 + j;
-            const int r = (lane >> 3) ^ (rg & 1);
-            const int row0 = min(t.rb * BR + wave * ROWS_PER_WAVE + 8 * rg, N - 1);  // uniform
-            const int row = min(row0 + r, N - 1);
+            const int row0 = bias_group_row(t.rb * BR + wave * ROWS_PER_WAVE, rg, N);  // uniform
+            const int row = bias_copy_row(row0, rg, lane, N);
             o.base[j] = uniform_ptr(static_cast<const char *>(p.bias) +
                                     ((int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)row0 * p.bs.n) * ESZ);
             o.voff[j] = (unsigned)(row - row0) * (unsigned)p.bs.n * (unsigned)ESZ + 16u * dma_c[j];
@@ -442,26 +438,22 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 
     // ---- bias access ----------------------------------------------------------
     // The copies' source may start at any element: they take 2-byte-aligned addresses like ordinary
-    // loads do.  The last chunk of a row that straddles N reads on into whatever follows the row,
-    // which is still inside the tensor except behind its very last row: a wave whose rows
-    // include one that would read past bias_end leaves that chunk out (key limit N - EC + 1
-    // instead of N) and writes it element by element (bias_tail).
+    // loads do.  A chunk that would read behind the tensor's last element is left out and written
+    // element by element (bias_tail).
     auto bias_klimit = [&](const Item &t, int blk) -> int {
-        if (blk * BV + BV <= N || (N & (EC - 1)) == 0) return N;
-        const int row1 = min(t.rb * BR + wave * ROWS_PER_WAVE + ROWS_PER_WAVE, N) - 1;
-        const int64_t e1 = (int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)row1 * p.bs.n + ((N + EC - 1) & -EC);
-        return e1 > p.bias_end ? N - (EC - 1) : N;
+        return bias_key_limit((int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h, t.rb * BR + wave * ROWS_PER_WAVE, N, p.bs.n,
+                              p.bias_end, blk * BV, EC);
     };
     auto bias_tail = [&](const Item &t, int blk, unsigned region) {
         typedef typename std::conditional<F32L, uint32_t, uint16_t>::type elem;
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        const int r = ln & 7, rg = ln >> 3, k0 = (N & -EC) - blk * BV;  // the chunk's first key inside the block
+        const int rg = ln >> 3, k0 = (N & -EC) - blk * BV;  // the chunk's first key inside the block
         if (rg < rg0 || rg >= rg0 + RGW || k0 >= SEGS * KSEG) return;
         const int row = min(t.rb * BR + wave * ROWS_PER_WAVE + ln, N - 1);
         const elem *src = static_cast<const elem *>(p.bias) + (int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h +
                           (int64_t)row * p.bs.n + (N & -EC);
-        const unsigned dst = region + (rg * SEGS + k0 / KSEG) * 1024 + 128 * (r ^ (rg & 1)) + 16 * ((k0 / EC & 7) ^ r);
+        const unsigned dst = region + bias_lds_chunk(ln, k0 / KSEG, k0 / EC & 7, SEGS);
 #pragma unroll 1
         for (int i = 0; i < (N & (EC - 1)); ++i)
             *reinterpret_cast<__attribute__((address_space(3))) elem *>((size_t)(dst + ESZ * i)) = src[i];
