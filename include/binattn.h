@@ -231,7 +231,7 @@ int binattn_forward_relpos(const uint32_t *q_bits, const uint32_t *k_bits, const
  *   mu_q_out,
  *   mu_k_out   : optional (may be NULL) float32 [B, H]: the abs-means that were used.
  * Results equal binattn_pack_qk + binattn_forward up to the summation order of the
- * abs-means.  N > 256 returns BINATTN_ERR_SHAPE.  A call with more than 256 (batch, head)
+ * abs-means (fixed: the same bits on every run).  N > 256 returns BINATTN_ERR_SHAPE.  A call with more than 256 (batch, head)
  * pairs runs 4-wave workgroups, two per compute unit, each taking a head's two 128-row
  * blocks in turn (BINATTN_FLAG_WIDE8 keeps one 8-wave workgroup per head; same results up
  * to the summation order of the abs-means).
@@ -247,7 +247,7 @@ int binattn_forward_fused(const void *q, const void *k, const void *v, const int
  * loop behind one call.  N <= 256 is binattn_forward_fused (one launch, workspace unused and
  * may be NULL).  Longer sequences take three launches: one pass over Q, K, V that packs the
  * query signs, writes the keys' +-1 operand rows directly (no key sign words in memory),
- * and reduces the V absmax and the |q|, |k| sums per 256 tokens; the V quantisation, which
+ * and reduces the V absmax and the |q|, |k| sums per 128 tokens; the V quantisation, which
  * also adds those partial sums in a fixed order (the abs-means are the same bits on every
  * run, unlike binattn_pack_qk's atomics for N > 2048); and binattn_attend.
  *   arguments as binattn_forward_fused, plus the workspace of binattn_workspace_bytes.

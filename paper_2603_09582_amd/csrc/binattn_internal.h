@@ -44,11 +44,16 @@ inline Shape make_shape(int B, int H, int N, int d) {
 // Operand image of one key/value block (BV keys) of one head, stored in the
 // workspace exactly as the attention kernel wants it in LDS, so that a block is
 // one flat asynchronous copy:
-//   K  [BV positions][KP bytes]  FP4 codes of the +-1 keys (0 beyond d / beyond N),
-//                                32 bytes per 64 channels, rows in MFMA order; the
-//                                16-byte chunks of a row are XOR-swizzled (k_chunk)
-//   VT [DKP channels][VP bytes]  V codes, channel-major, BV key bytes per row + 16 pad
+//   K  [BV positions][KP bytes]  FP4 codes of the +-1 keys, 32 bytes per 64 channels, rows in
+//                                MFMA order; the 16-byte chunks of a row are XOR-swizzled (k_chunk)
+//   VT [DKP channels][VP bytes]  V codes, channel-major, BV key bytes per row + 16 pad; 0 for keys
+//                                beyond N
 //   CS [DKP] int32               PV_MAGIC + 128 * (sum of the block's V codes)
+// What no key or channel fills: expand_k_block (sign words) writes zeros for channels beyond d and keys
+// beyond N, phi_psi1_kernel (one call from Q, K, V) leaves old bytes in both; prep_head_kernel zeroes V rows
+// and seeds beyond d, v_quant_kernel leaves old bytes there; the single-launch forms clear their images.  So a
+// consumer replaces the logits of keys beyond N, keeps its query operand zero beyond d and drops the
+// accumulators beyond d.
 // Swizzle and padding make the 16-byte reads of 16 consecutive rows fall into 16
 // different 16-byte bank groups of the 256-byte LDS row.
 template <int DK>
@@ -155,8 +160,9 @@ int launch_probe_valu(int op, int iters, int blocks, float *out, hipStream_t str
 
 enum BiasMode {
     BIAS_NONE = 0,
-    BIAS_BF16_VEC = 1,  // rows straight into registers, one block ahead (row pitch >= 2^27; d > 96 with one row block)
-    BIAS_F32_VEC = 3,   // fp32 rows, 16-byte loads at use (where BIAS_BF16_VEC would be taken)
+    BIAS_BF16_VEC = 1,  // rows straight into registers, one block ahead (row pitch >= 2^27; d > 96 with one row block, or with
+                        // rows on 4-byte words that are no whole 16-byte chunks)
+    BIAS_F32_VEC = 3,   // fp32 rows, 16-byte loads at use (row pitch >= 2^27; d > 96 with one row block)
     BIAS_F32_LDS = 15,  // fp32 rows of any alignment: most of the tile staged global -> LDS, the rest into registers
     BIAS_BF16_LDS = 5,  // rows of any alignment: tile staged global -> LDS asynchronously
     BIAS_BF16_LDS8 = 17, // the same for N a multiple of 8 (4-wave workgroups over a prepared workspace): no copy reads past a row

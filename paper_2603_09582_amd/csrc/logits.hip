@@ -83,7 +83,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void logits_fp4_kernel(
             const v16f zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             const v16f acc = qk_tile<DK>(buf, t, m, g, qB, zero);
             const int k0 = blk * BV + 32 * t + 16 * g;
-            if (ROWSUM) {  // keys beyond N are zero rows of the image: they add nothing
+            if (ROWSUM) {  // keys beyond N add nothing: zero rows, written by launch_expand_k before every call
 #pragma unroll
                 for (int i = 0; i < 16; ++i) rs += acc[i];
             } else if (r < nrows) {

@@ -899,7 +899,7 @@ def test_forward_fused_four_wave_form_modes(kind, d):
     elif kind == "bf16_per_batch":
         obias = (torch.randn(B, H, N, N, generator=g) * 0.3).to(torch.bfloat16)
         bias = dev(obias)
-    elif kind == "bf16_odd_rows":                # rows of 201 elements: loaded into registers, not staged
+    elif kind == "bf16_odd_rows":                # rows of 201 elements: staged from 2-byte aligned addresses
         store = torch.zeros(H, N, 201, dtype=torch.bfloat16, device="cuda")
         store[:, :, :N] = dev(x.bias)
         bias = store[:, :, :N]
