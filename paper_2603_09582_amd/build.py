@@ -9,8 +9,10 @@ from __future__ import annotations
 
 import concurrent.futures as cf
 import glob
+import hashlib
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -81,6 +83,16 @@ def _compile(src: str, force: bool) -> str:
     with open(res, "w") as f:
         json.dump(table, f, indent=0, sort_keys=True)
     return obj
+
+
+def kernel_source_id(sources=None) -> str:
+    """Names the kernels' source text: 12 hex digits that change with the code and not with comments or layout.
+    The rocprofv3 summaries under profiles/ carry it, so that their figures are used for these kernels only."""
+    h = hashlib.sha256()
+    for p in sources or sorted(_sources() + _headers(), key=os.path.basename):
+        text = re.sub(r"//[^\n]*|/\*.*?\*/", " ", open(p).read(), flags=re.S)
+        h.update(" ".join(text.split()).encode())
+    return h.hexdigest()[:12]
 
 
 def kernel_resources() -> dict:
