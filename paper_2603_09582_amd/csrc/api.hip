@@ -212,10 +212,10 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         // lines per load instruction (N = 197, d = 64, 768 heads, one launch: 50.9 us that way,
         // 42.2 us through LDS; N = 1370, d = 80: 90.5 / 85.5 us).
         const bool lds_ok = bs.n < (1 << 27);
-        // Row-block pairs leave half as many workgroups and copy rows of odd alignment piece by piece: where
-        // bf16 rows are no whole 16-byte chunks but start on 4-byte words, the register path is as fast or
-        // faster (registers / pairs, attention stage, d = 128: 1 x 16 heads N = 300 13.1 / 16.1 us, N = 1370 33.4 / 41.0,
-        // 20 x 3 heads N = 3572 341 / 357, 8 x 16 heads N = 1370 115 / 118, N = 3572 689 / 677; 2-byte rows: 1 x 16 heads
+        // Row-block pairs leave half as many workgroups, and the register path reads rows on 4-byte words well:
+        // where bf16 rows are no whole 16-byte chunks but start on such words, it is as fast or faster
+        // (registers / pairs, attention stage, d = 128: 1 x 16 heads N = 300 13.1 / 16.1 us, N = 1370 33.4 / 41.0,
+        // 20 x 3 heads N = 3572 341 / 357, 8 x 16 heads N = 1370 115 / 118, but N = 3572 689 / 677; 2-byte rows: 1 x 16 heads
         // N = 577 26.0 / 23.1, N = 611 21.7 / 22.9, 4 x 16 heads N = 577 39.9 / 24.7, N = 2047 232 / 122).
         word_rows = bias_dtype == BINATTN_BIAS_BF16 && !chunk_rows && aligned(bias, 4) && bs.b % 2 == 0 &&
                     bs.h % 2 == 0 && bs.n % 2 == 0;
