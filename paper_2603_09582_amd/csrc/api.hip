@@ -151,6 +151,13 @@ struct RawInputs {
     float *mu_q_out, *mu_k_out;
 };
 
+// abs-means that the attention kernel adds up itself (launch_phi_psi up to PSI_MAX_BLOCKS key blocks), and their copies
+// for the caller
+struct MuSums {
+    const float *psum;
+    float *mu_q_out, *mu_k_out;
+};
+
 // BIAS_AXIAL arguments: tables present and aligned, Gx a power of two in [16, 256],
 // Gy in [1, 256], Gy * Gx = N.
 // Full table: present and aligned, same grid limits; the single-launch form (small = true)
@@ -171,7 +178,7 @@ int check_axial(const AxialBias &ax, int N, bool small = false) {
 int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, const void *bias,
                 int bias_dtype, const int64_t bias_strides[3], const AxialBias *ax, const RawInputs *raw,
                 float scale, int B, int H, int N, int d, void *out, const int64_t out_strides[3],
-                const void *workspace, size_t workspace_bytes, unsigned flags, void *stream) {
+                const void *workspace, size_t workspace_bytes, unsigned flags, void *stream, const MuSums *ms = nullptr) {
     if ((!raw && !q_bits) || !out) return BINATTN_ERR_NULL;
     if (!shape_ok(B, H, N, d)) return BINATTN_ERR_SHAPE;
     const Shape s = make_shape(B, H, N, d);
@@ -233,6 +240,8 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     const bool use_mu = !(flags & BINATTN_FLAG_NO_MU);
     p.mu_q = use_mu ? mu_q : nullptr;
     p.mu_k = use_mu ? mu_k : nullptr;
+    p.psum = ms ? ms->psum : nullptr;
+    p.inv_count = (float)(1.0 / ((double)N * (double)d));
     p.bias = use_bias ? bias : nullptr;
     p.bs = bs;
     p.bias_end = bias_extent(B, H, N, bs.b, bs.h, bs.n);
@@ -278,7 +287,8 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     p.phase512 = bias_dtype == BINATTN_BIAS_BF16 && chunk_rows ? 0 : 1;
     p.xq = p.xk = p.xv = nullptr;
     p.xqs = p.xks = p.xvs = Strides3{0, 0, 0};
-    p.mu_q_out = p.mu_k_out = nullptr;
+    p.mu_q_out = ms ? ms->mu_q_out : nullptr;
+    p.mu_k_out = ms ? ms->mu_k_out : nullptr;
     p.wide = 0;
     p.nrb = (N + BR - 1) / BR;
     if (wide_rows2) {
@@ -501,9 +511,10 @@ int binattn_attention(const void *q, const void *k, const void *v, const int64_t
     hipStream_t st = static_cast<hipStream_t>(stream);
     if ((rc = launch_phi_psi(q, qs, k, ks, v, vs, s, ws, w, mu_q_out, mu_k_out, st)) != BINATTN_OK) return rc;
     const float *mu = reinterpret_cast<const float *>(ws + w.mu);
-    return binattn_attend(reinterpret_cast<const uint32_t *>(ws + w.qbits), mu, mu + s.BH, bias, bias_dtype,
-                          bias_strides, scale, B, H, N, d, out, out_strides, workspace, workspace_bytes, flags,
-                          stream);
+    const MuSums ms = {reinterpret_cast<const float *>(ws + w.psum), mu_q_out, mu_k_out};
+    return attend_impl(reinterpret_cast<const uint32_t *>(ws + w.qbits), mu, mu + s.BH, bias, bias_dtype, bias_strides,
+                       nullptr, nullptr, scale, B, H, N, d, out, out_strides, workspace, workspace_bytes, flags, stream,
+                       s.nblk <= PSI_MAX_BLOCKS ? &ms : nullptr);
 }
 
 int binattn_forward_fused_relpos(const void *q, const void *k, const void *v, const int64_t q_strides[3],
@@ -551,8 +562,10 @@ int binattn_attention_relpos(const void *q, const void *k, const void *v, const 
         BINATTN_OK)
         return rc;
     const float *mu = reinterpret_cast<const float *>(ws + w.mu);
-    return binattn_attend_relpos(reinterpret_cast<const uint32_t *>(ws + w.qbits), mu, mu + s.BH, table, Gy, Gx, scale,
-                                 B, H, N, d, out, out_strides, workspace, workspace_bytes, flags, stream);
+    const MuSums ms = {reinterpret_cast<const float *>(ws + w.psum), mu_q_out, mu_k_out};
+    return attend_impl(reinterpret_cast<const uint32_t *>(ws + w.qbits), mu, mu + s.BH, nullptr, 0, nullptr, &ax, nullptr,
+                       scale, B, H, N, d, out, out_strides, workspace, workspace_bytes, flags, stream,
+                       s.nblk <= PSI_MAX_BLOCKS ? &ms : nullptr);
 }
 
 int binattn_logits_debug(const uint32_t *q_bits, const uint32_t *k_bits, int B, int H, int N, int d,

@@ -132,6 +132,10 @@ inline Workspace make_workspace(const Shape &s) {
     return w;
 }
 
+// Up to this many key blocks psi is one launch whose workgroups hold whole channel slabs of V, and the abs-means of
+// the entry point that takes Q, K, V are added up by the attention kernel from their partial sums.
+constexpr int PSI_MAX_BLOCKS = 32;
+
 struct Strides3 {
     int64_t b, h, n;
 };
@@ -180,6 +184,8 @@ constexpr int TABLE_MAX_G = 32;
 struct FusedParams {
     const uint32_t *q_bits;
     const float *mu_q, *mu_k;  // may be null (taken as 1)
+    const float *psum;         // partial sums of the abs-means, [BH][nblk][2] (then nblk <= 64 and mu_q, mu_k unused), or null
+    float inv_count;           // 1 / (N d)
     const void *bias;          // may be null
     Strides3 bs;               // bias element strides (batch, head, row)
     int64_t bias_end;          // elements of the dense bias from its first to its last one

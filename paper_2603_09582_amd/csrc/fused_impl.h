@@ -191,6 +191,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     __shared__ float lut[LUT ? LUTN : 4];
     // delta_v of the current item (two copies: consecutive items alternate)
     __shared__ __attribute__((aligned(16))) float sdelta[2][NIMG][DKP];
+    // partial sums of the abs-means of the next item's head
+    __shared__ __attribute__((aligned(16))) float spsum[PERSIST && !ONEHEAD ? 2 * PSI_MAX_BLOCKS + 4 : 4];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);  // 32-row group
@@ -281,6 +283,29 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         for (int w = 0; w < 2 * DK2; ++w) pend_q[w] = w < W ? qw[w] : 0u;
         pend_muq = p.mu_q ? p.mu_q[t.bh] : 1.0f;
         pend_muk = p.mu_k ? p.mu_k[t.bh] : 1.0f;
+    };
+    // The abs-means of an item from the partial sums of its key blocks: one pair per lane, at most PSI_MAX_BLOCKS, in
+    // the tree over lanes i, i + 16, i + 8, i + 4, i + 2, i + 1 (the same bits on every run, and those of the tree in
+    // v_quant_kernel); exported with the head's first row block.
+    auto item_mu = [&](const Item &t, const float *ps) {
+        float s[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            s[i] = lane < p.nblk ? ps[2 * lane + i] : 0.0f;
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[i]), __float_as_uint(s[i]), false, false);
+            s[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+            s[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s[i]), 0x128, 0xf, 0xf, false));  // row_ror:8
+            s[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s[i]), 0x124, 0xf, 0xf, false));
+            s[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s[i]), 0x122, 0xf, 0xf, false));
+            s[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s[i]), 0x121, 0xf, 0xf, false));
+            s[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s[i]))) * p.inv_count;
+        }
+        if (t.rb == 0 && wave == 0 && lane == 0) {
+            if (p.mu_q_out) p.mu_q_out[t.bh] = s[0];
+            if (p.mu_k_out) p.mu_k_out[t.bh] = s[1];
+        }
+        pend_muq = p.use_mu ? s[0] : 1.0f;
+        pend_muk = p.use_mu ? s[1] : 1.0f;
     };
     // bias pointers of an item (no memory access)
     auto bias_row_ptr = [&](const Item &t) -> const char * {
@@ -591,12 +616,6 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             }
     };
 
-    // 1 / |alpha| of an item from the abs-means fetched for it (as begin_item computes it)
-    auto inv_alpha_of = [&](float muq, float muk) {
-        const float alpha = p.scale * muq * muk;
-        return fabsf(alpha) < 1e-30f ? 1.0f : 1.0f / fabsf(alpha);
-    };
-
     // ---- stream position --------------------------------------------------------
     int it = 0;        // key block inside the current item
     const bool younger = WAVES3 && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
@@ -633,8 +652,12 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         const int nblkidx = sw ? 0 : it + 1;
         const BiasSrc nsrc = (LDS_BIAS && (sw || BIAS_LATE)) ? bias_dma_src(sw ? nxt : cur) : bsrc;
         if (!ONEHEAD && more) dma_image<DK, NWI>(nimg, inxt + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
-        if (!ONEHEAD && it == 0 && (ROWS2 ? wreg : wave) == 0 && lane < DKP / 4)  // delta_v of this item, for its epilogue
-            dma16(p.delta + (int64_t)cur.bh * DKP, 16 * lane, lds_offset(&sdelta[parity][isel][0]));
+        if (!ONEHEAD && it == 0 && (ROWS2 ? wreg : wave) == 0) {
+            if (lane < DKP / 4)  // delta_v of this item, for its epilogue
+                dma16(p.delta + (int64_t)cur.bh * DKP, 16 * lane, lds_offset(&sdelta[parity][isel][0]));
+            if (PERSIST && p.psum && nxt.valid && 2 * lane < p.nblk)  // the next item's, for item_mu
+                dma16(p.psum + (int64_t)nxt.bh * p.nblk * 2, 16 * lane, lds_offset(spsum));
+        }
         if (sw && nxt.valid) fetch_item_regs(nxt);
         int nklim = N;  // key limit of the shared bias tile's copies below
         if (BIAS_DB && more && nblkidx * BV + BV > N) {
@@ -902,8 +925,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         for (int cb = 0; cb < DK; ++cb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) Of[cb][r] = fmaf(Of[cb][r], resc, __int_as_float(acc[cb][r]));
-        if (TBLK && more)
-            table_store(tab + (tpar ^ 1) * 4 * TB_CP, sw ? inv_alpha_of(pend_muq, pend_muk) : inv_alpha);
+        if (TBLK && more && !sw) table_store(tab + (tpar ^ 1) * 4 * TB_CP, inv_alpha);
         __builtin_amdgcn_sched_barrier(0);  // keep the wait at the very end of the block
         wait_vmem();      // this wave's copies for the next block have landed
         __syncthreads();  // everyone is done with this block's buffers, the next ones are complete
@@ -917,7 +939,12 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         cur = nxt;
         v += gridDim.x;
         nxt = decode(v + gridDim.x);
+        if (!ONEHEAD && p.psum) item_mu(cur, spsum);
         begin_item(cur);
+        if (TBLK) {  // (the next item's first rows: divided by ITS alpha)
+            table_store(tab + (tpar ^ 1) * 4 * TB_CP, inv_alpha);
+            __syncthreads();
+        }
         it = 0;
         if (!PAIR) next_rebase = first_rebase();
         if (!ONEHEAD4) parity ^= 1;  // (the single-launch forms keep one copy of delta_v)
@@ -1131,6 +1158,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     } else {
         dma_image<DK, NWI>(image_ptr(cur), lds_offset(bufA) + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
         fetch_item_regs(cur);
+        if (p.psum) item_mu(cur, p.psum + (int64_t)cur.bh * p.nblk * 2);
     }
     begin_item(cur);
     if (BIAS_LATE) load_bias_quarters(brow, 0);

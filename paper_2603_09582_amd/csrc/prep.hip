@@ -341,6 +341,276 @@ __global__ __launch_bounds__(PREP_THREADS) void phi_psi1_kernel(const PhiPsi1Arg
     for (int i = threadIdx.x; i < (n1 - n0) * W; i += PREP_THREADS) ob[i] = words[i];
 }
 
+// psi of Alg. 1 (Eq. 7) for sequences of at most PSI_MAX_BLOCKS key blocks in ONE pass over V: a 4- or 8-wave
+// workgroup owns a slab of up to 32 channels of one head, all of whose rows it holds in registers between the
+// absmax and the codes, so V is read once and nothing waits for another workgroup.  A wave owns whole key
+// blocks (PB of them): lane = 4 (token quad) + (8-channel chunk), so that a load reads 64-byte row
+// segments; the codes are transposed through a tile of the wave's own, without a barrier.  The slabs of a head
+// run on one XCD, whose L2 holds the rows' other parts.
+// The same launch holds, behind the slabs, phi (Eq. 5) for the entry point that takes Q and K themselves, a key
+// block per 256 threads (phi_block), or the expansion of the keys' sign words (expand_k_blocks).
+// HBM bound; before, V was read twice and there was a launch more (partial maxima, then codes).
+struct PsiArgs {
+    const uint16_t *v;
+    Strides3 vs;
+    const uint32_t *k_bits;  // the sign words of the keys, or null
+    int kblocks;             // key blocks of all heads (k_bits)
+    float *delta;            // [BH][DKP]
+    char *img;
+    int H, N, d, DKP, nblk, img_bytes, v_off, cs_off;
+    int slabs;               // slabs in all
+    // phi
+    const uint16_t *q, *k;
+    Strides3 qs, ks;
+    uint32_t *q_bits;        // [BH][N][W]
+    float *psum;             // [BH][nblk][2]
+};
+constexpr int PSI_K_BLOCKS = 4;  // key blocks whose sign words one workgroup expands
+constexpr int psi_slabs(int C16) { return (C16 + 3) / 4; }                               // slabs of a head
+constexpr int psi_chunks(int C16) { return (C16 + psi_slabs(C16) - 1) / psi_slabs(C16); }  // 8-channel chunks of a slab, at most 4
+
+// maximum over the lanes that hold the same chunk (lane % 4), two 16-bit patterns per dword
+__device__ __forceinline__ unsigned max_u16x2(unsigned a, unsigned b) {
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(us2, a), __builtin_bit_cast(us2, b)));
+}
+__device__ __forceinline__ unsigned max_same_chunk(unsigned x) {
+    x = max_u16x2(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xf, 0xf, false));  // row_ror:4
+    x = max_u16x2(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false));  // row_ror:8
+    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = max_u16x2(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return max_u16x2(b[0], b[1]);
+}
+
+template <int C16, int NT>
+__device__ __forceinline__ void phi_block(const PsiArgs &a, int wg, uint32_t *words, float (*wsum)[NT / 64]) {
+    constexpr int W = (C16 + 3) / 4;
+    constexpr int RT = PREP_THREADS / C16;  // tokens per pass (256 threads take a key block)
+    constexpr int NP = (BV + RT - 1) / RT;  // passes
+    constexpr int KW = 8 * ((W + 1) / 2);   // 4-byte words (8 channels each) per image row
+    constexpr int NB = NT / PREP_THREADS;   // key blocks per workgroup
+    const int half = threadIdx.x / PREP_THREADS, tid = threadIdx.x % PREP_THREADS;
+    const int ngrp = (a.nblk + NB - 1) / NB;
+    const int chunk = NB * (wg % ngrp) + half, bh = wg / ngrp;  // chunk = key block
+    const int b = bh / a.H, h = bh % a.H;
+    const int N = a.N, n0 = chunk * BV, n1 = min(N, n0 + BV);  // (an odd last pair: n1 <= n0, nothing to do)
+    char *image = a.img + ((int64_t)bh * a.nblk + chunk) * a.img_bytes;
+    const uint16_t *qb = a.q + (int64_t)b * a.qs.b + (int64_t)h * a.qs.h;
+    const uint16_t *kb = a.k + (int64_t)b * a.ks.b + (int64_t)h * a.ks.h;
+    const int c = tid % C16, r0 = tid / C16;
+    const bool on = r0 < RT;
+    words += half * BV * W;
+
+    // (unconditional loads from clamped rows, masked where they are used)
+    u4 xq[NP], xk[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int tok = min(n0 + r0 + p * RT, N - 1);
+        xq[p] = *reinterpret_cast<const u4 *>(qb + (int64_t)tok * a.qs.n + 8 * c);
+        xk[p] = *reinterpret_cast<const u4 *>(kb + (int64_t)tok * a.ks.n + 8 * c);
+    }
+    for (int i = tid; i < BV * W; i += PREP_THREADS) words[i] = 0u;
+    // (Image words no key fills - channels beyond d, positions beyond N - stay as they are: the query
+    // operand is zero in those channels, FP4 has no NaN, and logits of keys beyond N are replaced.)
+    __syncthreads();
+
+    float qsum = 0.0f, ksum = 0.0f;
+    uint8_t *bytes = reinterpret_cast<uint8_t *>(words);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int tok = n0 + r0 + p * RT;
+        if (on && r0 + p * RT < BV && tok < n1) {
+            bytes[(tok - n0) * (4 * W) + c] = (uint8_t)sign_bits8_abs(xq[p], qsum);
+            const int pos = position_of_key(tok - n0);
+            *reinterpret_cast<unsigned *>(image + pos * (4 * KW) + 16 * k_chunk(pos, c >> 2, 4 * KW) + 4 * (c & 3)) =
+                fp4_pm1_abs(xk[p], ksum);
+        }
+    }
+    if (ksum != ksum) {  // a NaN among this thread's keys: its words once more, exactly
+        for (int tok = n0 + r0; on && tok < n1; tok += RT) {
+            const int pos = position_of_key(tok - n0);
+            *reinterpret_cast<unsigned *>(image + pos * (4 * KW) + 16 * k_chunk(pos, c >> 2, 4 * KW) + 4 * (c & 3)) =
+                fp4_pm1_exact(*reinterpret_cast<const u4 *>(kb + (int64_t)tok * a.ks.n + 8 * c));
+        }
+    }
+    // the two partial sums of the key block, in a fixed order
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        qsum += __shfl_down(qsum, off, 64);
+        ksum += __shfl_down(ksum, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        wsum[0][threadIdx.x >> 6] = qsum;
+        wsum[1][threadIdx.x >> 6] = ksum;
+    }
+    __syncthreads();
+    if (tid < 2 && chunk < a.nblk) {
+        float t = 0.0f;
+        for (int i = 0; i < PREP_THREADS / 64; ++i) t += wsum[tid][half * (PREP_THREADS / 64) + i];
+        a.psum[((int64_t)bh * a.nblk + chunk) * 2 + tid] = t;
+    }
+    uint32_t *ob = a.q_bits + ((int64_t)bh * N + n0) * W;
+    for (int i = tid; i < (n1 - n0) * W; i += PREP_THREADS) ob[i] = words[i];
+}
+
+// Key blocks 4 wg ... 4 wg + 3 of all heads: sign words -> FP4 rows of the block images.
+template <int C16, int NT>
+__device__ __forceinline__ void expand_k_blocks(const PsiArgs &a, int wg) {
+    constexpr int W = (C16 + 3) / 4, W2 = 2 * ((W + 1) / 2), KP = 16 * W2;
+    constexpr int NI = PSI_K_BLOCKS * BV * W2 / NT;  // words of a thread
+    uint32_t word[NI];
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {  // (all loads first; unused words: the row's first one)
+        const int i = threadIdx.x + j * NT, pos = i / W2 % BV, w = i % W2;
+        const int kb = min(PSI_K_BLOCKS * wg + i / (W2 * BV), a.kblocks - 1), bh = kb / a.nblk;
+        const int key = (kb - bh * a.nblk) * BV + key_of_position(pos);
+        word[j] = a.k_bits[((int64_t)bh * a.N + min(key, a.N - 1)) * W + (w < W ? w : 0)];
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int i = threadIdx.x + j * NT, pos = i / W2 % BV, w = i % W2;
+        const int kb = PSI_K_BLOCKS * wg + i / (W2 * BV), bh = kb / a.nblk;
+        if (kb >= a.kblocks) break;
+        const bool live = (kb - bh * a.nblk) * BV + key_of_position(pos) < a.N;
+        u4 o;
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+            o[n] = live && 4 * w + n < C16 ? fp4_pm1_from_bits8((word[j] >> (8 * n)) & 0xFFu) : 0u;
+        *reinterpret_cast<u4 *>(a.img + (int64_t)kb * a.img_bytes + pos * KP + 16 * k_chunk(pos, w, KP)) = o;
+    }
+}
+
+template <int C16, int NT, int PB>
+__global__ __launch_bounds__(NT, PB == 4 ? 2 : 4) void psi_kernel(const PsiArgs a) {
+    constexpr int W = (C16 + 3) / 4, S = psi_slabs(C16), CH = psi_chunks(C16);
+    constexpr int NW = NT / 64, LDT = BV + 16;
+    __shared__ __attribute__((aligned(16))) int8_t tiles[NW * 32 * LDT];  // phi_block: the sign words
+    __shared__ __attribute__((aligned(16))) unsigned smax[NW][4][4];     // phi_block: the partial sums
+    __shared__ __attribute__((aligned(16))) float sdelta[32], srcp[32];
+    static_assert(NT / PREP_THREADS * BV * W * 4 <= sizeof(tiles) && 2 * NW * 4 <= sizeof(smax), "phi_block's LDS");
+    const int per = (a.slabs + 7) >> 3;  // slabs of an XCD (consecutive workgroups go to different ones)
+    if ((int)blockIdx.x >= 8 * per) {
+        if (a.k_bits != nullptr)
+            expand_k_blocks<C16, NT>(a, (int)blockIdx.x - 8 * per);
+        else
+            phi_block<C16, NT>(a, (int)blockIdx.x - 8 * per, reinterpret_cast<uint32_t *>(tiles),
+                           reinterpret_cast<float(*)[NW]>(&smax[0][0][0]));
+        return;
+    }
+    const int u = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+    if (u >= a.slabs) return;  // uniform over the workgroup
+    const int bh = u / S, c0 = (u % S) * CH;  // first chunk
+    const int b = bh / a.H, h = bh % a.H, N = a.N;
+    const uint16_t *vb = a.v + (int64_t)b * a.vs.b + (int64_t)h * a.vs.h;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int cl = lane & 3, quad = lane >> 2;
+    const int nch = min(CH, C16 - c0);  // chunks of this slab
+    const int chunk = c0 + min(cl, nch - 1);
+
+    // (unconditional loads from clamped rows, masked where they are used)
+    u4 w[PB][2][4];
+#pragma unroll
+    for (int i = 0; i < PB; ++i)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int tok = min((wave + NW * i) * BV + 64 * hf + 4 * quad + t, N - 1);
+                w[i][hf][t] = *reinterpret_cast<const u4 *>(vb + (int64_t)tok * a.vs.n + 8 * chunk);
+            }
+    unsigned mb[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+        const int left = N - (wave + NW * i) * BV;  // rows from this block on
+        if (left < BV) {                            // uniform: rows beyond N read as zeros: no effect on a maximum, code 0
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (64 * hf + 4 * quad + t >= left) w[i][hf][t] = u4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) absmax_acc(mb, w[i][hf][t]);
+    }
+    // A NaN (outside what the calls promise) must not hide its channel's other values: patterns above infinity's.
+    unsigned nan = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) nan |= (mb[j] + 0x007F007Fu) & 0x80008000u;
+    if (nan) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mb[j] = 0u;
+#pragma unroll
+        for (int i = 0; i < PB; ++i)
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    u4 x = w[i][hf][t];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if ((x[j] & 0x7FFFu) > 0x7F80u) x[j] &= 0xFFFF0000u;
+                        if ((x[j] & 0x7FFF0000u) > 0x7F800000u) x[j] &= 0x0000FFFFu;
+                    }
+                    absmax_acc(mb, x);
+                }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) mb[j] = max_same_chunk(mb[j]);
+    if (lane < 4) *reinterpret_cast<u4 *>(&smax[wave][lane][0]) = u4{mb[0], mb[1], mb[2], mb[3]};
+    __syncthreads();
+    if (threadIdx.x < 32) {
+        const uint16_t *sm = reinterpret_cast<const uint16_t *>(&smax[0][0][0]) + threadIdx.x;
+        unsigned m = 0u;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) m = max(m, (unsigned)sm[32 * i]);
+        float dl;
+        quant_consts(__uint_as_float(m << 16), &dl, &srcp[threadIdx.x]);
+        sdelta[threadIdx.x] = dl;
+        if ((int)threadIdx.x < 8 * nch) a.delta[(int64_t)bh * a.DKP + 8 * c0 + threadIdx.x] = dl;
+    }
+    __syncthreads();
+    const QuantConsts8 kc = load_quant_consts8(srcp, cl);
+    int8_t *tile = tiles + wave * (32 * LDT);
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+        const int blk = wave + NW * i;
+        if (blk >= a.nblk) break;  // uniform over the wave; no barrier follows
+        // Transposed 4-byte writes (16 quads x 4 chunks): chunks 2 and 3 take the other half of the row, or they
+        // would meet 0 and 1 on the same banks.  The copy-out below undoes it at 16-byte granularity.
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            unsigned packed[8];
+            quant_quad(w[i][hf], kc, sdelta, cl, packed);
+            const int col = (16 * hf + quad) ^ ((cl >> 1) << 4);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) *reinterpret_cast<unsigned *>(tile + (8 * cl + j) * LDT + 4 * col) = packed[j];
+        }
+        __builtin_amdgcn_wave_barrier();
+        char *dst = a.img + ((int64_t)bh * a.nblk + blk) * a.img_bytes;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int c = 8 * j + (lane >> 3), part = lane & 7;
+            if (j < nch)
+                *reinterpret_cast<u4 *>(dst + a.v_off + (8 * c0 + c) * LDT + 16 * part) =
+                    *reinterpret_cast<const u4 *>(tile + c * LDT + 16 * (part ^ ((j >> 1) << 2)));
+        }
+        // column sums: lanes c and c + 32 take half a row each, four signed bytes per dot
+        int sum = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const u4 x = *reinterpret_cast<const u4 *>(tile + (lane & 31) * LDT + 64 * (lane >> 5) + 16 * j);
+#pragma unroll
+            for (int n = 0; n < 4; ++n) sum = __builtin_amdgcn_sdot4((int)x[n], 0x01010101, sum, false);
+        }
+        const auto s2 = __builtin_amdgcn_permlane32_swap((unsigned)sum, (unsigned)sum, false, false);
+        if (lane < 8 * nch)
+            reinterpret_cast<int *>(dst + a.cs_off)[8 * c0 + lane] = PV_MAGIC_BITS + 128 * ((int)s2[0] + (int)s2[1]);
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 // Short sequences (at most two key blocks): everything for one head in ONE launch and ONE
 // pass over V.  All of the head's V rows go into registers first (a thread owns quads of
 // consecutive tokens of one 8-channel chunk; consecutive lanes take consecutive chunks, so a
@@ -475,6 +745,33 @@ int launch_expand_k(const uint32_t *k_bits, const Shape &s, char *ws, const Work
 // head); longer ones take absmax partials + one more launch.
 constexpr int PREP_FUSED_MAX_BLOCKS = 2;
 
+// psi (and phi, if a.q is set) in one launch.
+template <int C16>
+static void launch_psi_t(PsiArgs a, int BH, hipStream_t stream) {
+    a.slabs = BH * psi_slabs(C16);
+    a.kblocks = BH * a.nblk;
+    // a wave per key block, up to eight of them, then two or four blocks per wave
+    const int nt = a.nblk <= 4 ? 256 : 512, blocks = nt / PREP_THREADS;
+    const int keys = a.q ? BH * ((a.nblk + blocks - 1) / blocks) : a.k_bits ? (a.kblocks + PSI_K_BLOCKS - 1) / PSI_K_BLOCKS : 0;
+    const dim3 grid((unsigned)((a.slabs + 7) / 8 * 8 + keys)), block(nt);
+    if (a.nblk <= 4) hipLaunchKernelGGL((psi_kernel<C16, 256, 1>), grid, block, 0, stream, a);
+    else if (a.nblk <= 8) hipLaunchKernelGGL((psi_kernel<C16, 512, 1>), grid, block, 0, stream, a);
+    else if (a.nblk <= 16) hipLaunchKernelGGL((psi_kernel<C16, 512, 2>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((psi_kernel<C16, 512, 4>), grid, block, 0, stream, a);
+}
+static PsiArgs psi_args(const void *v, Strides3 vs, const Shape &s, char *ws, const Workspace &w) {
+    PsiArgs a = {};
+    a.v = static_cast<const uint16_t *>(v);
+    a.vs = vs;
+    a.delta = reinterpret_cast<float *>(ws + w.delta);
+    a.img = ws + w.img;
+    a.H = s.H; a.N = s.N; a.d = s.d; a.DKP = s.DKP; a.nblk = s.nblk;
+    a.img_bytes = w.img_bytes;
+    int KP;
+    image_offsets(s.DK, &KP, &a.v_off, &a.cs_off);
+    return a;
+}
+
 template <int C16>
 static void launch_quant_v_t(const void *v, Strides3 vs, const uint32_t *k_bits, const Shape &s,
                              char *ws, const Workspace &w, hipStream_t stream) {
@@ -489,6 +786,12 @@ static void launch_quant_v_t(const void *v, Strides3 vs, const uint32_t *k_bits,
                            v_off, cs_off, ws + w.img);
         return;
     }
+    if (s.nblk <= PSI_MAX_BLOCKS) {
+        PsiArgs a = psi_args(v, vs, s, ws, w);
+        a.k_bits = k_bits;
+        launch_psi_t<C16>(a, s.BH, stream);
+        return;
+    }
     hipLaunchKernelGGL(v_absmax_kernel<C16>, dim3((unsigned)s.nchunk * s.BH), dim3(PREP_THREADS),
                        0, stream, vp, vs, s.H, s.N, s.DKP, s.nchunk, amax);
     hipLaunchKernelGGL(v_quant_kernel<C16>, dim3((unsigned)s.nblk * s.BH), dim3(PREP_THREADS), 0,
@@ -496,11 +799,21 @@ static void launch_quant_v_t(const void *v, Strides3 vs, const uint32_t *k_bits,
                        w.img_bytes, KP, v_off, cs_off, ws + w.img, MuReduce{nullptr, nullptr, nullptr, nullptr, nullptr, 0.0f}, 1);
 }
 
-// phi + psi for the entry point that takes Q, K, V: two launches (see phi_psi1_kernel).
+// phi + psi for the entry point that takes Q, K, V: one launch (see psi_kernel), the abs-means' partial sums
+// are left to the attention kernel; for more key blocks two launches (see phi_psi1_kernel).
 template <int C16>
 static void launch_phi_psi_t(const void *q, Strides3 qs, const void *k, Strides3 ks, const void *v, Strides3 vs,
                              const Shape &s, char *ws, const Workspace &w, float *mu_q_out, float *mu_k_out,
                              hipStream_t stream) {
+    if (s.nblk <= PSI_MAX_BLOCKS) {
+        PsiArgs p = psi_args(v, vs, s, ws, w);
+        p.q = static_cast<const uint16_t *>(q); p.k = static_cast<const uint16_t *>(k);
+        p.qs = qs; p.ks = ks;
+        p.q_bits = reinterpret_cast<uint32_t *>(ws + w.qbits);
+        p.psum = reinterpret_cast<float *>(ws + w.psum);
+        launch_psi_t<C16>(p, s.BH, stream);
+        return;
+    }
     int KP, v_off, cs_off;
     image_offsets(s.DK, &KP, &v_off, &cs_off);
     float *amax = reinterpret_cast<float *>(ws + w.amax);
