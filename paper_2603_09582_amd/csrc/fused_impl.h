@@ -191,8 +191,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     __shared__ float lut[LUT ? LUTN : 4];
     // delta_v of the current item (two copies: consecutive items alternate)
     __shared__ __attribute__((aligned(16))) float sdelta[2][NIMG][DKP];
-    // partial sums of the abs-means of the next item's head
-    __shared__ __attribute__((aligned(16))) float spsum[PERSIST && !ONEHEAD ? 2 * PSI_MAX_BLOCKS + 4 : 4];
+    // partial sums of the abs-means of the next item's head (the decomposed bias has no entry point that leaves them)
+    constexpr bool PSUM = PERSIST && !ONEHEAD && !AXIAL;
+    __shared__ __attribute__((aligned(16))) float spsum[PSUM ? 2 * PSI_MAX_BLOCKS + 4 : 4];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);  // 32-row group
@@ -200,10 +201,23 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     const int isel = PAIR ? bsel : 0;                // which resident image / delta copy
     const int wreg = (NB == 2 && !PAIR) ? 4 * bsel + wave : wave;  // this wave's private bias region / copy share
     const int m = lane & 31, g = lane >> 5;
-    const int N = p.N, d = p.d, W = (d + 31) / 32;
-    const int nbp = p.B / NIMG;
-    const int per_xcd = (p.total_wg + 7) >> 3;
-    const int vmax = 8 * per_xcd;
+    const int N = p.N, d = p.d;
+    // The kernel's arguments, read again from the argument segment where only the switch from one item to the next needs
+    // them: carried through the block loop they (and what is computed from them) did not fit the scalar registers, and
+    // 16 to 60 v_readlane per block brought them back from vector lanes.  (Attention stage and its preparation, before / after:
+    // 128 x 128 grid, d = 64, 32 heads, decomposed 1927 / 1892 us, table 1941 / 1908; N = 2207, d = 96, 96 heads, fp32 bias
+    // 353 / 338; N = 1370, d = 80, 64 heads 72.2 / 70.7.)  The forms that compute one item, or hold one head, have the registers.
+    constexpr bool COLD_ARGS = PERSIST && !ONEHEAD;
+    typedef typename std::conditional<COLD_ARGS, const __attribute__((address_space(4))) FusedParams, const FusedParams>::type Args;
+    auto args = [&]() -> Args & {
+        if constexpr (COLD_ARGS) {
+            uint64_t a = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(a));  // (opaque: not hoisted, not kept)
+            return *(Args *)a;
+        } else {
+            return p;
+        }
+    };
     const int bsb = (MODE == BIAS_F32_VEC || F32L) ? 4 : 2;  // bytes per bias element
 
     // Work item v -> (batch, head, row block).  Consecutive ids go to different XCDs, so v
@@ -216,6 +230,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     };
     auto decode = [&](int v) -> Item {
         Item t;
+        Args &p = args();
+        const int nbp = p.B / NIMG, per_xcd = (p.total_wg + 7) >> 3, vmax = 8 * per_xcd;
         // (ONEHEAD4: ids v, v + grid size are the two row blocks of one head; grid size = vmax)
         const int j4 = ONEHEAD4 ? (v >= 2 * vmax ? 2 : v >= vmax ? 1 : 0) : 0;
         if (ONEHEAD4) v -= j4 * vmax;
@@ -277,7 +293,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             for (int w = 0; w < PQ; ++w) pend_q[w] = pend_q2[w];
             return;
         }
-        const int qc = min(t.rb * BR + wave * ROWS_PER_WAVE + m, N - 1);
+        Args &p = args();
+        const int qc = min(t.rb * BR + wave * ROWS_PER_WAVE + m, N - 1), W = (d + 31) / 32;
         const uint32_t *qw = p.q_bits + ((int64_t)t.bh * N + qc) * W;
 #pragma unroll
         for (int w = 0; w < 2 * DK2; ++w) pend_q[w] = w < W ? qw[w] : 0u;
@@ -288,10 +305,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // the tree over lanes i, i + 16, i + 8, i + 4, i + 2, i + 1 (the same bits on every run, and those of the tree in
     // v_quant_kernel); exported with the head's first row block.
     auto item_mu = [&](const Item &t, const float *ps) {
+        Args &p = args();
         float s[2];
+        int ln = lane;  // (opaque: no address is kept for this in the block loop)
+        asm volatile("" : "+v"(ln));
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            s[i] = lane < p.nblk ? ps[2 * lane + i] : 0.0f;
+            s[i] = ln < p.nblk ? ps[2 * ln + i] : 0.0f;
             const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[i]), __float_as_uint(s[i]), false, false);
             s[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
             s[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s[i]), 0x128, 0xf, 0xf, false));  // row_ror:8
@@ -309,12 +329,14 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     };
     // bias pointers of an item (no memory access)
     auto bias_row_ptr = [&](const Item &t) -> const char * {
+        Args &p = args();
         const int qc = min(t.rb * BR + wave * ROWS_PER_WAVE + m, N - 1);
         return static_cast<const char *>(p.bias) +
                ((int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)qc * p.bs.n) * bsb;
     };
     auto bias_dma_src = [&](const Item &t) -> BiasSrc {
         BiasSrc o;
+        Args &p = args();
 #pragma unroll
         for (int j = 0; j < RGW; ++j) {
             const int rg = rg0 + j;
@@ -327,6 +349,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         return o;
     };
     auto image_ptr = [&](const Item &t) -> const char * {
+        Args &p = args();
         return uniform_ptr(p.img + (int64_t)t.bh * p.nblk * L::BYTES);
     };
     // ---- BIAS_TABLE / BIAS_TABLE_BLK: staging of table rows [row0, row0 + nrows) -------------
@@ -334,7 +357,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     auto table_load = [&](const Item &t, int row0, int nrows) {  // global loads only
         const int LX = 2 * p.Gx - 1, LY = 2 * p.Gy - 1, sh = p.gx_shift + 1;
         const char *tb = uniform_ptr(reinterpret_cast<const char *>(p.table + (int64_t)t.h * LY * LX + row0 * LX));
-        int tid = threadIdx.x;  // (opaque: the 32-bit offsets are formed here, not carried through the block loop)
+        int tid = 64 * (4 * bsel + wave) + lane;  // (opaque: the 32-bit offsets are formed here, not carried through the block loop)
         asm volatile("" : "+v"(tid));
 #pragma unroll
         for (int j = 0; j < TB_PER; ++j) {
@@ -349,7 +372,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     auto table_store = [&](float *dst, float ia) {
 #pragma unroll
         for (int j = 0; j < TB_PER; ++j) {
-            const int i = threadIdx.x + j * FUSED_THREADS * NB;
+            const int i = 64 * (4 * bsel + wave) + lane + j * FUSED_THREADS * NB;
             if (TBLK && j > 0 && p.Gx == 128) break;  // one row of 256 entries (the other grids need more than half)
             const float x = tstage[j] * ia;
 #pragma unroll
@@ -366,6 +389,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     };
     // turn the fetched registers into the item's state
     auto begin_item = [&](const Item &t) {
+        Args &p = args();
         imgs = image_ptr(t);
         q = t.rb * BR + wave * ROWS_PER_WAVE + m;
         // Logit multiplier alpha of Eq. 6.  Its sign goes into the Q operand and a vanishing
@@ -404,7 +428,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             constexpr int NTA = FUSED_THREADS * NB;
             constexpr int NU = (4 * AXL + NTA - 1) / NTA, NW = (AXL + NTA - 1) / NTA;
             float tu[NU], tw[NW];
-            int tid = threadIdx.x;  // (opaque: keeps the index arithmetic out of the block loop's registers)
+            int tid = 64 * (4 * bsel + wave) + lane;  // (opaque: keeps the index arithmetic out of the block loop's registers)
             asm volatile("" : "+v"(tid));
 #pragma unroll
             for (int j = 0; j < NU; ++j) {
@@ -466,11 +490,14 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // loads do.  A chunk that would read behind the tensor's last element is left out and written
     // element by element (bias_tail).
     auto bias_klimit = [&](const Item &t, int blk) -> int {
+        if (blk * BV + BV <= N) return N;
+        Args &p = args();
         return bias_key_limit((int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h, t.rb * BR + wave * ROWS_PER_WAVE, N, p.bs.n,
                               p.bias_end, blk * BV, EC);
     };
     auto bias_tail = [&](const Item &t, int blk, unsigned region) {
         typedef typename std::conditional<F32L, uint32_t, uint16_t>::type elem;
+        Args &p = args();
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const int rg = ln >> 3, k0 = (N & -EC) - blk * BV;  // the chunk's first key inside the block
@@ -589,6 +616,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // One permlane32 swap per dword regroups two such quads so that the lower lane owns 8
     // consecutive channels of quad 2k and the upper lane those of quad 2k + 1: 16-byte stores.
     auto finish_item = [&](const Item &t, const float *dl) {
+        Args &p = args();
         const float l_tot = pair_sum(l_run);
         const float inv = 1.0f / l_tot;
         const float off = PV_MAGIC_F * rho;
@@ -620,7 +648,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     int it = 0;        // key block inside the current item
     const bool younger = WAVES3 && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
     int parity = 0;    // items alternate between the two delta_v copies
-    Item nxt = decode(PERSIST ? v + gridDim.x : vmax);
+    Item nxt = {0, 0, 0, 0, false};
+    if (PERSIST) nxt = decode(v + gridDim.x);
 
     // The block before which the accumulator's offset is next removed (see the loop).  A 4-wave item that
     // starts on buffer B (an odd number of blocks per item, after an odd number of items) is rebased before
@@ -632,6 +661,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     constexpr bool PHASE = WAVES3 || PAIR || ROWS2;
     auto first_rebase = [&]() -> int {
         if (!PHASE) return 0;
+        Args &p = args();
         if (WAVES3) return REBASE + ((v >> 9) & p.nblk & 1);
         if (!p.phase512) return REBASE + (ROWS2 ? (v >> 8) & p.nblk & 1 : 0);
         const int nrb1 = (N + BR - 1) / BR, per = (p.B * p.H * nrb1 + 7) >> 3;
@@ -653,9 +683,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         const BiasSrc nsrc = (LDS_BIAS && (sw || BIAS_LATE)) ? bias_dma_src(sw ? nxt : cur) : bsrc;
         if (!ONEHEAD && more) dma_image<DK, NWI>(nimg, inxt + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
         if (!ONEHEAD && it == 0 && (ROWS2 ? wreg : wave) == 0) {
+            Args &p = args();
             if (lane < DKP / 4)  // delta_v of this item, for its epilogue
                 dma16(p.delta + (int64_t)cur.bh * DKP, 16 * lane, lds_offset(&sdelta[parity][isel][0]));
-            if (PERSIST && p.psum && nxt.valid && 2 * lane < p.nblk)  // the next item's, for item_mu
+            if (PSUM && p.psum && nxt.valid && 2 * lane < p.nblk)  // the next item's, for item_mu
                 dma16(p.psum + (int64_t)nxt.bh * p.nblk * 2, 16 * lane, lds_offset(spsum));
         }
         if (sw && nxt.valid) fetch_item_regs(nxt);
@@ -702,8 +733,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             }
         }
         v4i ka[KT][DK2];
+        int kln = lane;
+        if (DK == 4 && (TBLK || LUT)) asm volatile("" : "+v"(kln));  // (addresses formed here: carried, they were spilled)
 #pragma unroll
-        for (int t = 0; t < KT; ++t) load_k_operand<DK>(ibuf, t, m, g, ka[t]);
+        for (int t = 0; t < KT; ++t) load_k_operand<DK>(ibuf, t, kln & 31, kln >> 5, ka[t]);
         __builtin_amdgcn_sched_barrier(0);  // all of them in flight before the first use
         //    T = I + b / alpha
         v16f T[KT];
@@ -939,7 +972,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         cur = nxt;
         v += gridDim.x;
         nxt = decode(v + gridDim.x);
-        if (!ONEHEAD && p.psum) item_mu(cur, spsum);
+        if (PSUM && args().psum) item_mu(cur, spsum);
         begin_item(cur);
         if (TBLK) {  // (the next item's first rows: divided by ITS alpha)
             table_store(tab + (tpar ^ 1) * 4 * TB_CP, inv_alpha);
@@ -1158,7 +1191,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     } else {
         dma_image<DK, NWI>(image_ptr(cur), lds_offset(bufA) + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
         fetch_item_regs(cur);
-        if (p.psum) item_mu(cur, p.psum + (int64_t)cur.bh * p.nblk * 2);
+        if (!AXIAL && p.psum) item_mu(cur, p.psum + (int64_t)cur.bh * p.nblk * 2);
     }
     begin_item(cur);
     if (BIAS_LATE) load_bias_quarters(brow, 0);
