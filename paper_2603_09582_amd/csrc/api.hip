@@ -265,6 +265,8 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         p.xv = static_cast<const uint16_t *>(raw->v);
         p.xqs = raw->qs; p.xks = raw->ks; p.xvs = raw->vs;
         p.mu_q_out = raw->mu_q_out; p.mu_k_out = raw->mu_k_out;
+        const int64_t far = (int64_t)1 << 22;
+        p.small_pitch = raw->qs.n < far && raw->ks.n < far && raw->vs.n < far;
         // More heads than compute units: 4-wave workgroups, two per compute unit, each taking
         // the head's two row blocks in turn; otherwise one 8-wave workgroup per head.
         const bool four = B * H > ONEHEAD4_MIN_HEADS && onehead4_built(s.DK, mode) && !(flags & BINATTN_FLAG_WIDE8);
@@ -283,7 +285,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
             default: return BINATTN_ERR_SHAPE;
         }
     }
-    p.split_sums = 0;
+    p.split_sums = p.small_pitch = 0;
     p.phase512 = bias_dtype == BINATTN_BIAS_BF16 && chunk_rows ? 0 : 1;
     p.xq = p.xk = p.xv = nullptr;
     p.xqs = p.xks = p.xvs = Strides3{0, 0, 0};

@@ -232,15 +232,11 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         Item t;
         Args &p = args();
         const int nbp = p.B / NIMG, per_xcd = (p.total_wg + 7) >> 3, vmax = 8 * per_xcd;
-        // (ONEHEAD4: ids v, v + grid size are the two row blocks of one head; grid size = vmax)
-        const int j4 = ONEHEAD4 ? (v >= 2 * vmax ? 2 : v >= vmax ? 1 : 0) : 0;
-        if (ONEHEAD4) v -= j4 * vmax;
         const int u = (v & 7) * per_xcd + (v >> 3);
         t.valid = v < vmax && u < p.total_wg;
-        if (ONEHEAD4) t.valid = t.valid && j4 < p.nrb;
         const int uu = t.valid ? u : 0;
         t.b = ONEHEAD ? uu / p.H : (uu % nbp) * NIMG + isel;
-        t.rb = ONEHEAD4 ? j4 : ONEHEAD ? bsel : ROWS2 ? 2 * ((uu / nbp) % p.nrb) + bsel : (uu / nbp) % p.nrb;
+        t.rb = ONEHEAD4 ? 0 : ONEHEAD ? bsel : ROWS2 ? 2 * ((uu / nbp) % p.nrb) + bsel : (uu / nbp) % p.nrb;
         t.h = ONEHEAD ? uu % p.H : uu / (nbp * p.nrb);
         t.bh = t.b * p.H + t.h;
         return t;
@@ -312,12 +308,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             s[i] = ln < p.nblk ? ps[2 * ln + i] : 0.0f;
-            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[i]), __float_as_uint(s[i]), false, false);
-            s[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-            s[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s[i]), 0x128, 0xf, 0xf, false));  // row_ror:8
-            s[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s[i]), 0x124, 0xf, 0xf, false));
-            s[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s[i]), 0x122, 0xf, 0xf, false));
-            s[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s[i]), 0x121, 0xf, 0xf, false));
+            s[i] = row_tree_sum(s[i]);
             s[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s[i]))) * p.inv_count;
         }
         if (t.rb == 0 && wave == 0 && lane == 0) {
@@ -388,7 +379,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         table_load(t, dy_min + p.Gy - 1, iy_hi - jy_lo - dy_min + 1);
     };
     // turn the fetched registers into the item's state
-    auto begin_item = [&](const Item &t) {
+    // (same_head: the head's tables are in LDS already)
+    auto begin_item = [&](const Item &t, auto same_head) {
+        constexpr bool SAME_HEAD = decltype(same_head)::value;
         Args &p = args();
         imgs = image_ptr(t);
         q = t.rb * BR + wave * ROWS_PER_WAVE + m;
@@ -408,18 +401,18 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         } else {
             load_q_operand<DK2>(pend_q, d, g, LUT ? !a_neg : a_neg, a_zero, qB);
         }
-        if (LUT) {
+        if (LUT && !SAME_HEAD) {
             // (the previous item's last block is behind every wave; the barrier publishes the table)
             for (int i = threadIdx.x; i < LUTN; i += FUSED_THREADS * NB)
                 lut[i] = i <= d ? __builtin_amdgcn_exp2f(fmaf(-2.0f * (float)i, a2, LOG2_255_F)) : 0.0f;
-            hb_run = 0x7fffffff;
             __syncthreads();
         }
+        if (LUT) hb_run = 0x7fffffff;
         if (MODE == BIAS_BF16_VEC || MODE == BIAS_F32_VEC || F32L) brow = bias_row_ptr(t);
         if (LDS_BIAS) {
             bsrc = bias_dma_src(t);
         }
-        if (AXIAL) {
+        if (AXIAL && !SAME_HEAD) {
             // every wave is past the previous item's last block (begin_item follows its closing
             // barrier), so the tables can be overwritten; a barrier publishes the new ones
             const int LX = 2 * p.Gx - 1, LY = 2 * p.Gy - 1;
@@ -454,21 +447,25 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                 const int i = tid + j * NTA;
                 if (i < AXL) axw[i] = tw[j] * inv_alpha;
             }
+            __syncthreads();
+        }
+        if (AXIAL) {
             const int qc = min(q, N - 1);
             const int ix = qc & (p.Gx - 1), iy = qc >> p.gx_shift;
             const int s0 = p.Gx - 1 - ix;  // reversed-table index of key column 0
             ax_ub = (s0 & 3) * AXL + (s0 & ~3);
             ax_wb = iy + p.Gy - 1;
-            __syncthreads();
         }
-        if (TABLE) {
+        if (TABLE && !SAME_HEAD) {
             // (as above: the previous item's last block is behind every wave)
             table_load(t, 0, 2 * p.Gy - 1);
             table_store(tab, inv_alpha);
+            __syncthreads();
+        }
+        if (TABLE) {
             const int qc = min(q, N - 1);
             const int s0 = p.Gx - 1 - (qc & (p.Gx - 1));  // reversed-row index of key column 0
             ax_ub = (s0 & 3) * TB_CP + (s0 & ~3) + (((qc >> p.gx_shift) + p.Gy - 1) << (p.gx_shift + 1));
-            __syncthreads();
         }
         if (TBLK) {
             const int qc = min(q, N - 1);
@@ -652,7 +649,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     const bool younger = WAVES3 && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
     int parity = 0;    // items alternate between the two delta_v copies
     Item nxt = {0, 0, 0, 0, false};
-    if (PERSIST) nxt = decode(v + gridDim.x);
+    if (ONEHEAD4) {  // a head's two row blocks, one workgroup
+        nxt = cur;
+        nxt.rb = 1;
+        nxt.valid = p.nrb > 1;
+    } else if (PERSIST) {
+        nxt = decode(v + gridDim.x);
+    }
 
     // The block before which the accumulator's offset is next removed (see the loop).  A 4-wave item that
     // starts on buffer B (an odd number of blocks per item, after an odd number of items) is rebased before
@@ -969,7 +972,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         if (TBLK && more && !sw) table_store(tab + (tpar ^ 1) * 4 * TB_CP, inv_alpha);
         __builtin_amdgcn_sched_barrier(0);  // keep the wait at the very end of the block
         wait_vmem();      // this wave's copies for the next block have landed
-        __syncthreads();  // everyone is done with this block's buffers, the next ones are complete
+        // everyone is done with this block's buffers, the next ones are complete (the single-launch forms have nothing
+        // but tiles of a wave's own to fill again)
+        if (!ONEHEAD) __syncthreads();
 
         if (!last) {
             ++it;
@@ -979,9 +984,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         if (!PERSIST || !nxt.valid) return false;
         cur = nxt;
         v += gridDim.x;
-        nxt = decode(v + gridDim.x);
+        if (ONEHEAD4) nxt.valid = false;  // (two row blocks)
+        else nxt = decode(v + gridDim.x);
         if (PSUM && args().psum) item_mu(cur, spsum);
-        begin_item(cur);
+        begin_item(cur, std::integral_constant<bool, ONEHEAD4>{});
         if (TBLK) {  // (the next item's first rows: divided by ITS alpha)
             table_store(tab + (tpar ^ 1) * 4 * TB_CP, inv_alpha);
             __syncthreads();
@@ -997,7 +1003,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     if constexpr (ONEHEAD) {
         // phi and psi of Alg. 1 for this head, straight into the two LDS images.
         constexpr int NT = FUSED_THREADS * NB;
-        __shared__ int sabs[DKP];            // per-channel absmax of V (bit patterns)
+        __shared__ int sabs[NT / 64][DKP];   // per-channel absmax of V (bit patterns), a wave's own
         __shared__ __attribute__((aligned(16))) float srcp[DKP];  // the quantiser's multipliers
         // |q| and |k| partial sums.  The 4-wave form adds what a lane sees of both row blocks in one
         // sum (kept in the second of two, the first stays 0); with p.split_sums it keeps what waves w
@@ -1006,7 +1012,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         constexpr int NS = SPLIT_BUILT ? 2 : 1;
         constexpr int NSUM = NS * NT / 64;
         __shared__ float ssum[2][NSUM];
-        const int C16 = d / 8, nblk = p.nblk;
+        const int C16 = d / 8;
+        const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         auto imgp = [&](int blk) -> char * { return blk ? bufB : bufA; };
         const uint16_t *qb_ = p.xq + (int64_t)cur.b * p.xqs.b + (int64_t)cur.h * p.xqs.h;
         const uint16_t *kb_ = p.xk + (int64_t)cur.b * p.xks.b + (int64_t)cur.h * p.xks.h;
@@ -1020,27 +1027,58 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         if (MODE == BIAS_BF16_VEC) load_bias_vec(bias_row_ptr(cur), 0);
         if (F32L && !BIAS_LATE) load_bias_quarters(bias_row_ptr(cur), 0);
-        // this lane's query row: the chunks of the sign words its B operand needs (channels
-        // 64 s + 32 g + 8 j); addresses are clamped into the row, unused chunks are skipped below
-        const int qrow = cur.rb * BR + wave * ROWS_PER_WAVE + m;
-        u4 qx[DK2][4];
-        float qsum[NS] = {}, ksum[NS] = {};
-        auto load_q_row = [&](int row) {
-#pragma unroll
-            for (int sI = 0; sI < DK2; ++sI)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int c0 = 32 * (2 * sI + g) + 8 * j;
-                    qx[sI][j] = *reinterpret_cast<const u4 *>(qb_ + (int64_t)min(row, N - 1) * p.xqs.n + (c0 < d ? c0 : 0));
-                }
+        // Row loads go through buffer descriptors that end with the tensor's last row: rows beyond N read as zeros (no effect on
+        // a sum or a maximum, code 0), an address is one 32-bit offset, and nothing is clamped or masked.  (Pitches from
+        // 2^22 elements on do not fit the offsets and take 64-bit addresses.)  With that, nothing cleared that no result
+        // depends on, passes without work left out, wave sums by lane swaps and no barrier between the key blocks: 3 heads,
+        // N = 197, d = 64 13.3 -> 12.1 us, 768 heads 41.5 -> 37.9, 768 heads, N = 100 22.0 -> 20.0, 512 heads, N = 256, d = 72
+        // 30.5 -> 29.7 (its load phase, 7 of 28 us, is at the memory's rate).
+        struct Rows {
+            __amdgpu_buffer_rsrc_t r;
+            unsigned pitch;  // bytes
+            const uint16_t *base;
+            int64_t pitch64;
         };
-        auto q_row_words = [&](int row, unsigned *words, float &sum) {  // FP4 words of the loaded row, |q| into sum
+        auto rows_of = [&](const uint16_t *base, int64_t pitch) {
+            Rows o;
+            o.base = base;
+            o.pitch64 = pitch;
+            o.pitch = N > 1 ? 2u * (unsigned)pitch : 2u * (unsigned)d;  // (a single row may have any pitch)
+            o.r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, (N - 1) * o.pitch + 2 * d, 0x00020000);
+            return o;
+        };
+        const Rows rq = rows_of(qb_, p.xqs.n), rk = rows_of(kb_, p.xks.n), rv = rows_of(vb_, p.xvs.n);
+        // 8 channels from channel c0 of a row; off: byte offset row * pitch + 2 c0
+        auto load_chunk = [&](auto fast, const Rows &src, unsigned off, int row, int c0) -> u4 {
+            if constexpr (decltype(fast)::value) return __builtin_amdgcn_raw_buffer_load_b128(src.r, off, 0, 0);
+            return row < N && c0 < d ? *reinterpret_cast<const u4 *>(src.base + (int64_t)row * src.pitch64 + c0) : u4{0u, 0u, 0u, 0u};
+        };
+        // this lane's query row: the chunks of the sign words its B operand needs (channels 64 s + 32 g + 8 j)
+        const int qrow = cur.rb * BR + wave * ROWS_PER_WAVE + m;
+        u4 qx[ONEHEAD4 ? 2 : 1][DK2][4];  // (4-wave form: and its row in the second row block)
+        float qsum[NS] = {}, ksum[NS] = {};
+        auto load_q_row = [&](auto fast, int rb) {
+            const int row = qrow + rb * BR;
+            const unsigned o0 = (unsigned)row * rq.pitch + 64 * g;
 #pragma unroll
             for (int sI = 0; sI < DK2; ++sI)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    words[4 * sI + j] = row < N && 32 * (2 * sI + g) + 8 * j < d ? fp4_pm1_abs(qx[sI][j], sum) : 0u;
-            if (sum != sum) {  // a NaN among this lane's queries: the words once more, exactly
+                    if (64 * sI + 8 * j < d)  // uniform
+                        qx[rb][sI][j] = load_chunk(fast, rq, o0 + 128 * sI + 16 * j, row, 64 * sI + 32 * g + 8 * j);
+        };
+        auto q_row_words = [&](int rb, unsigned *words, float &sum) {  // FP4 words of the loaded row, |q| into sum
+            const int row = qrow + rb * BR;
+#pragma unroll
+            for (int sI = 0; sI < DK2; ++sI)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int c0 = 64 * sI + 8 * j;  // of the lower lanes
+                    unsigned word = 0u;
+                    if (c0 + 32 < d || (c0 < d && g == 0)) word = fp4_pm1_abs(qx[rb][sI][j], sum);
+                    words[4 * sI + j] = word;
+                }
+            if (sum != sum && row < N) {  // a NaN among this lane's queries: the words once more, exactly
 #pragma unroll
                 for (int i = 0; i < PQ; ++i)
                     if (words[i] != 0u)
@@ -1048,7 +1086,6 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                             qb_ + (int64_t)row * p.xqs.n + 32 * (2 * (i / 4) + g) + 8 * (i % 4)));
             }
         };
-        load_q_row(qrow);
         // V rows into registers: a thread owns quads of consecutive tokens of one 8-channel
         // chunk; consecutive lanes take consecutive chunks (whole-row loads)
         // i / C16 for 0 <= i < 2^12 and C16 <= 16 without the integer-division sequence:
@@ -1056,52 +1093,51 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         // of the fp32 product
         const float rc16 = 1.0f / (float)C16;
         auto div_c16 = [&](int i) { return (int)(((float)i + 0.5f) * rc16); };
-        const int RT = div_c16(NT);           // thread groups = token quads per pass (>= 32)
+        const int RT = NT / C16;              // thread groups = token quads per pass
+        // (threads behind the last whole group repeat the next pass's first quads)
         const int vr = div_c16(threadIdx.x), vc = threadIdx.x - vr * C16;
-        const bool von = vr < RT;
-        // (loads are unconditional from clamped rows and masked where they are used: a load
-        // under a condition makes the compiler wait for it on the spot)
-        // (token quads per pass: 512 threads cover the 64 quads of two key blocks in two passes
-        // for every head dimension, 256 threads in at most four)
-        constexpr int KQ = NB == 2 ? 2 : 4;
+        // passes over the 64 token quads of two key blocks: RT >= NT / (4 DK), and 21 groups at least for DK = 3
+        constexpr int KQ = (64 * 4 * DK + NT - 1) / NT;
         u4 vw[KQ][4];
-        auto v_row_on = [&](int kq, int t) { return von && 4 * (vr + kq * RT) + t < N && vr + kq * RT < 2 * BV / 4; };
-#pragma unroll
-        for (int kq = 0; kq < KQ; ++kq)
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                vw[kq][t] = *reinterpret_cast<const u4 *>(vb_ + (int64_t)min(4 * (vr + kq * RT) + t, N - 1) * p.xvs.n + 8 * vc);
-        // this thread's key chunks (8 channels of one key each), loaded before the first barrier
+        // this thread's key chunks (8 channels of one key each): chunk i = thread + kk NT belongs to key group i / C16
         constexpr int KPT = (2 * BV * 4 * DK + NT - 1) / NT;  // chunks per thread, at most
+        const int kpt = (2 * BV * C16 + NT - 1) / NT;
         u4 kx[KPT];
         unsigned kdst[KPT];  // where its FP4 word goes (LDS offset), 0xffffffff for a chunk that does not exist
+        auto issue = [&](auto fast) {
+            load_q_row(fast, 0);
+            const unsigned v0 = (unsigned)(4 * vr) * rv.pitch + 16 * vc;
 #pragma unroll
-        for (int kk = 0; kk < KPT; ++kk) {
-            const int i = threadIdx.x + kk * NT;
-            const int ic = div_c16(i), c8 = i - ic * C16, blk = ic / BV;
-            const int o = key_of_chunk(ic % BV), pos = position_of_key(o);
-            const int key = blk * BV + o;
-            kdst[kk] = blk < nblk && key < N ? lds_offset(imgp(blk)) + L::K_OFF + pos * L::KP +
-                                                   16 * k_chunk(pos, c8 >> 2, L::KP) + 4 * (c8 & 3)
-                                             : 0xffffffffu;
-            kx[kk] = *reinterpret_cast<const u4 *>(kb_ + (int64_t)min(key, N - 1) * p.xks.n + 8 * c8);
-        }
-        // clear both images, the absmax cells
-        for (int i = threadIdx.x; i < L::BYTES / 16; i += NT) {
-            reinterpret_cast<u4 *>(bufA)[i] = u4{0u, 0u, 0u, 0u};
-            reinterpret_cast<u4 *>(bufB)[i] = u4{0u, 0u, 0u, 0u};
-        }
-        if (threadIdx.x < DKP) sabs[threadIdx.x] = 0;
+            for (int kq = 0; kq < KQ; ++kq)
+                if (kq * RT < 2 * BV / 4)  // uniform
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        vw[kq][t] = load_chunk(fast, rv, v0 + (unsigned)(4 * kq * RT + t) * rv.pitch, 4 * (vr + kq * RT) + t, 8 * vc);
+#pragma unroll
+            for (int kk = 0; kk < KPT; ++kk)
+                if (kk < kpt) {  // uniform
+                    const int i = threadIdx.x + kk * NT;
+                    const int ic = div_c16(i), c8 = i - ic * C16;
+                    const int o = key_of_chunk(ic % BV), pos = position_of_key(o), key = (ic & BV) + o;
+                    kdst[kk] = lds_offset(bufA) + (ic & BV ? lds_offset(bufB) - lds_offset(bufA) : 0u) + L::K_OFF + pos * L::KP +
+                               16 * k_chunk(pos, c8 >> 2, L::KP) + 4 * (c8 & 3);
+                    if ((2 * BV * 4 * DK) % NT != 0 || NB == 2) kdst[kk] = ic < 2 * BV ? kdst[kk] : 0xffffffffu;
+                    kx[kk] = load_chunk(fast, rk, (unsigned)key * rk.pitch + 16 * c8, ic < 2 * BV ? key : N, 8 * c8);
+                }
+            if constexpr (ONEHEAD4) load_q_row(fast, 1);
+        };
+        if (p.small_pitch) issue(std::true_type{});
+        else issue(std::false_type{});
+        for (int i = lane; i < DKP; i += 64) sabs[wid][i] = 0;
+        // (Nothing else is cleared: logits of keys beyond N are replaced, the query operand is zero in channels beyond d and
+        // FP4 has no NaN, accumulators of channels beyond d are dropped, and a V code that no key fills meets the weight 0,
+        // code -128, whose share the accumulator seed takes out again.)
         // the sign words of the query row (the oldest loads: V and K may still be in flight)
-        q_row_words(qrow, pend_q, qsum[0]);
-        // (ONEHEAD4: the lane's row in the second row block takes the same registers; its loads
-        // land during the key phase below)
-        if constexpr (ONEHEAD4) load_q_row(qrow + BR);
-        __syncthreads();
+        q_row_words(0, pend_q, qsum[0]);
         // keys: sign bits -> FP4 codes of +-1 at the row position the QK tile reads
 #pragma unroll
         for (int kk = 0; kk < KPT; ++kk) {
-            if (kdst[kk] != 0xffffffffu) {
+            if (kk < kpt && kdst[kk] != 0xffffffffu) {
                 const bool first = NS == 1 || (kk % 2 == 0 && p.split_sums);
                 float sum = first ? ksum[0] : ksum[NS - 1];
                 *reinterpret_cast<__attribute__((address_space(3))) unsigned *>((size_t)kdst[kk]) =
@@ -1111,12 +1147,11 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             }
         }
         if (ksum[0] != ksum[0] || ksum[NS - 1] != ksum[NS - 1]) {  // a NaN among this thread's keys: its words once more, exactly
-            for (int i = threadIdx.x; i < KPT * NT; i += NT) {
-                const int ic = div_c16(i), c8 = i - ic * C16, blk = ic / BV;
-                const int o = key_of_chunk(ic % BV), pos = position_of_key(o);
-                const int key = blk * BV + o;
-                if (blk < nblk && key < N)
-                    *reinterpret_cast<unsigned *>(imgp(blk) + L::K_OFF + pos * L::KP +
+            for (int i = threadIdx.x; i < 2 * BV * C16; i += NT) {
+                const int ic = div_c16(i), c8 = i - ic * C16;
+                const int o = key_of_chunk(ic % BV), pos = position_of_key(o), key = (ic & BV) + o;
+                if (key < N)
+                    *reinterpret_cast<unsigned *>(imgp(ic / BV) + L::K_OFF + pos * L::KP +
                                                   16 * k_chunk(pos, c8 >> 2, L::KP) + 4 * (c8 & 3)) =
                         fp4_pm1_exact(*reinterpret_cast<const u4 *>(kb_ + (int64_t)key * p.xks.n + 8 * c8));
             }
@@ -1126,32 +1161,28 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                 qsum[NS - 1] = qsum[0];
                 qsum[0] = 0.0f;
             }
-            q_row_words(qrow + BR, pend_q2, qsum[NS - 1]);
+            q_row_words(1, pend_q2, qsum[NS - 1]);
         }
         // V: absmax per channel through LDS integer maxima
-        if (von) {
+        {
             unsigned mb[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int kq = 0; kq < KQ; ++kq)
+                if (kq * RT < 2 * BV / 4)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    if (!v_row_on(kq, t)) vw[kq][t] = u4{0u, 0u, 0u, 0u};  // rows beyond N: code 0
-                    absmax_acc(mb, vw[kq][t]);
-                }
+                    for (int t = 0; t < 4; ++t) absmax_acc(mb, vw[kq][t]);
             float mf[8];
             absmax_floats(mb, mf);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                if (mf[i] > 0.0f) atomicMax(&sabs[8 * vc + i], __float_as_int(mf[i]));
+                if (mf[i] > 0.0f) atomicMax(&sabs[wid][8 * vc + i], __float_as_int(mf[i]));
         }
         // abs-means: wave sums, then the eight partials
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-            for (int i = 0; i < NS; ++i) {
-                qsum[i] += __shfl_down(qsum[i], off, 64);
-                ksum[i] += __shfl_down(ksum[i], off, 64);
-            }
+        for (int i = 0; i < NS; ++i) {
+            qsum[i] = row_tree_sum(pair_sum(qsum[i]));
+            ksum[i] = row_tree_sum(pair_sum(ksum[i]));
+        }
         if (lane == 0) {
 #pragma unroll
             for (int i = 0; i < NS; ++i) {
@@ -1162,7 +1193,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         __syncthreads();
         if (threadIdx.x < 8 * C16) {
             float dl;
-            quant_consts(__int_as_float(sabs[threadIdx.x]), &dl, &srcp[threadIdx.x]);
+            int am = 0;
+#pragma unroll
+            for (int i = 0; i < NT / 64; ++i) am = max(am, sabs[i][threadIdx.x]);
+            quant_consts(__int_as_float(am), &dl, &srcp[threadIdx.x]);
             sdelta[0][0][threadIdx.x] = dl;
         }
         float tq = 0.0f, tk = 0.0f;
@@ -1180,12 +1214,12 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         __syncthreads();
         // V codes, channel-major, into the images
-        if (von) {
+        {
             const QuantConsts8 kc = load_quant_consts8(srcp, vc);
 #pragma unroll
             for (int kq = 0; kq < KQ; ++kq) {
                 const int quad = vr + kq * RT;
-                if (4 * quad < N && quad < 2 * BV / 4) {
+                if (kq * RT < 2 * BV / 4 && 4 * quad < N && quad < 2 * BV / 4) {
                     unsigned packed[8];
                     quant_quad(vw[kq], kc, &sdelta[0][0][0], vc, packed);
                     char *imgq = imgp(quad / (BV / 4));
@@ -1201,7 +1235,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         fetch_item_regs(cur);
         if (!AXIAL && p.psum) item_mu(cur, p.psum + (int64_t)cur.bh * p.nblk * 2);
     }
-    begin_item(cur);
+    begin_item(cur, std::false_type{});
     if (BIAS_LATE) load_bias_quarters(brow, 0);
     if (!ONEHEAD) {
         if (MODE == BIAS_BF16_VEC) load_bias_vec(brow, 0);

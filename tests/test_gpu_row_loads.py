@@ -1,0 +1,78 @@
+"""Loads and slabs of the operand preparation: rows that lie anywhere (single launch), and the one-pass
+quantiser of V at the edges of its blocks per wave, chunks per slab and blocks per workgroup."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import binattn_oracle as orc
+from paper_2603_09582_amd import binding as ba
+from tests.helpers import bf16_bits
+from tests.test_gpu_parity import say
+
+pytestmark = pytest.mark.gpu
+
+
+def at_the_end(x, pitch):
+    """The same [1, H, N, d] values, heads side by side in rows `pitch` elements apart, as the very end of a buffer
+    that holds NaN elsewhere (a row of NaN would follow the last one)."""
+    _, H, N, d = x.shape
+    n = (N - 1) * pitch + H * d
+    store = torch.full((8 + n,), float("nan"), dtype=x.dtype, device="cuda")
+    view = store[8:].as_strided((1, H, N, d), (n, d, pitch, 1))
+    view.copy_(x)
+    return view
+
+
+# (pitches from 2^22 elements on take 64-bit addresses; more than 256 heads the 4-wave form)
+@pytest.mark.parametrize("H,N,d", [(2, 1, 64), (2, 5, 72), (3, 9, 128), (260, 3, 40), (260, 4, 64), (258, 130, 72), (2, 197, 104)])
+def test_single_launch_rows_anywhere(H, N, d):
+    g = torch.Generator().manual_seed(H + N + d)
+    q, k, v = (torch.randn(1, H, N, d, generator=g).to(torch.bfloat16).cuda() for _ in range(3))
+    want = ba.attention(q, k, v, None, d ** -0.5)
+    for pitch in (H * d, H * d + 8) + (((1 << 22) - 8, 1 << 22) if N <= 9 else ()):
+        say(f"single launch rows H={H} N={N} d={d} pitch={pitch}")
+        got = ba.attention(*(at_the_end(t, pitch) for t in (q, k, v)), None, d ** -0.5)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), pitch
+
+
+# (a wave per key block up to 4 and 8 blocks, then 2 and 4 of them per wave; above 32 blocks two passes)
+@pytest.mark.parametrize("N,d", [(257, 8), (300, 72), (512, 40), (513, 104), (1024, 24), (1025, 72), (2048, 32), (2049, 80),
+                                 (4096, 16), (4097, 72), (3000, 128)])
+def test_one_pass_quantiser_and_abs_means(N, d):
+    say(f"one pass over V N={N} d={d}")
+    B, H = 1, 3
+    g = torch.Generator().manual_seed(N + d)
+    q, k, v = (torch.randn(B, H, N, d, generator=g).to(torch.bfloat16) for _ in range(3))
+    v[0, 0, N - 1] *= 9.0  # the maximum of every channel in the last row
+    v[0, 1, :, d - 1] = 0.0
+    dq, dk, dv = q.cuda(), k.cuda(), v.cuda()
+    vq, delta = ba.quant_v_debug(dv)
+    mq, mk = (torch.empty(B, H, dtype=torch.float32, device="cuda") for _ in range(2))
+    got = ba.attention(dq, dk, dv, None, d ** -0.5, mu_q=mq, mu_k=mk)
+    plain = ba.attention(dq, dk, dv, None, d ** -0.5, flags=ba.FLAG_NO_MU)
+    qb, kb, _, _ = ba.pack_qk(dq, dk)
+    torch.cuda.synchronize()
+    for h in range(H):
+        codes, scales = orc.quant_v(bf16_bits(v[0, h]))
+        assert np.array_equal(vq[0, h].cpu().numpy(), codes) and np.array_equal(delta[0, h].cpu().numpy(), scales)
+        for mu, x in ((mq, q), (mk, k)):
+            assert float(mu[0, h]) == pytest.approx(orc.abs_mean(bf16_bits(x[0, h])), rel=2e-6)
+    # the same signs, codes and scales through the sign words: the same bits
+    assert torch.equal(ba.forward(qb, kb, None, None, dv, None, d ** -0.5, flags=ba.FLAG_NO_MU), plain)
+    assert torch.equal(ba.forward(qb, kb, mq, mk, dv, None, d ** -0.5), got)
+
+
+@pytest.mark.parametrize("N,d", [(300, 64), (1500, 72)])
+def test_a_nan_in_v_hides_no_other_value(N, d):
+    """Outside what the calls promise (V is finite): the scale is the largest magnitude of the channel's numbers."""
+    g = torch.Generator().manual_seed(N)
+    v = torch.randn(1, 2, N, d, generator=g).to(torch.bfloat16)
+    _, want = ba.quant_v_debug(v.cuda())
+    bad = v.clone()
+    at = torch.randint(0, N, (d,), generator=g)
+    keep = v[0, 0].abs().float().argmax(dim=0)  # never the maximum itself
+    at = torch.where(at == keep, (at + 1) % N, at)
+    bad[0, 0, at, torch.arange(d)] = float("nan")
+    _, got = ba.quant_v_debug(bad.cuda())
+    assert torch.equal(got, want)
