@@ -383,7 +383,7 @@ __device__ __forceinline__ unsigned max_same_chunk(unsigned x) {
 }
 
 template <int C16, int NT>
-__device__ __forceinline__ void phi_block(const PsiArgs &a, int wg, uint32_t *words, float (*wsum)[NT / 64]) {
+__device__ __forceinline__ void phi_block(const PsiArgs &a, int wg, uint32_t *words, char *krows, float (*wsum)[NT / 64]) {
     constexpr int W = (C16 + 3) / 4;
     constexpr int RT = PREP_THREADS / C16;  // tokens per pass (256 threads take a key block)
     constexpr int NP = (BV + RT - 1) / RT;  // passes
@@ -400,6 +400,7 @@ __device__ __forceinline__ void phi_block(const PsiArgs &a, int wg, uint32_t *wo
     const int c = tid % C16, r0 = tid / C16;
     const bool on = r0 < RT;
     words += half * BV * W;
+    krows += half * BV * 4 * KW;
 
     // (unconditional loads from clamped rows, masked where they are used)
     u4 xq[NP], xk[NP];
@@ -410,7 +411,7 @@ __device__ __forceinline__ void phi_block(const PsiArgs &a, int wg, uint32_t *wo
         xk[p] = *reinterpret_cast<const u4 *>(kb + (int64_t)tok * a.ks.n + 8 * c);
     }
     for (int i = tid; i < BV * W; i += PREP_THREADS) words[i] = 0u;
-    // (Image words no key fills - channels beyond d, positions beyond N - stay as they are: the query
+    // (Image words no key fills - channels beyond d, positions beyond N - may hold anything: the query
     // operand is zero in those channels, FP4 has no NaN, and logits of keys beyond N are replaced.)
     __syncthreads();
 
@@ -422,14 +423,14 @@ __device__ __forceinline__ void phi_block(const PsiArgs &a, int wg, uint32_t *wo
         if (on && r0 + p * RT < BV && tok < n1) {
             bytes[(tok - n0) * (4 * W) + c] = (uint8_t)sign_bits8_abs(xq[p], qsum);
             const int pos = position_of_key(tok - n0);
-            *reinterpret_cast<unsigned *>(image + pos * (4 * KW) + 16 * k_chunk(pos, c >> 2, 4 * KW) + 4 * (c & 3)) =
+            *reinterpret_cast<unsigned *>(krows + pos * (4 * KW) + 16 * k_chunk(pos, c >> 2, 4 * KW) + 4 * (c & 3)) =
                 fp4_pm1_abs(xk[p], ksum);
         }
     }
     if (ksum != ksum) {  // a NaN among this thread's keys: its words once more, exactly
         for (int tok = n0 + r0; on && tok < n1; tok += RT) {
             const int pos = position_of_key(tok - n0);
-            *reinterpret_cast<unsigned *>(image + pos * (4 * KW) + 16 * k_chunk(pos, c >> 2, 4 * KW) + 4 * (c & 3)) =
+            *reinterpret_cast<unsigned *>(krows + pos * (4 * KW) + 16 * k_chunk(pos, c >> 2, 4 * KW) + 4 * (c & 3)) =
                 fp4_pm1_exact(*reinterpret_cast<const u4 *>(kb + (int64_t)tok * a.ks.n + 8 * c));
         }
     }
@@ -451,6 +452,12 @@ __device__ __forceinline__ void phi_block(const PsiArgs &a, int wg, uint32_t *wo
     }
     uint32_t *ob = a.q_bits + ((int64_t)bh * N + n0) * W;
     for (int i = tid; i < (n1 - n0) * W; i += PREP_THREADS) ob[i] = words[i];
+    // (whole rows, with whatever lies beyond d and N: see the channel slabs of psi_kernel)
+    if (chunk < a.nblk)
+#pragma unroll
+        for (int j = 0; j < BV * KW / (4 * PREP_THREADS); ++j)
+            *reinterpret_cast<u4 *>(image + 16 * (tid + j * PREP_THREADS)) =
+                *reinterpret_cast<const u4 *>(krows + 16 * (tid + j * PREP_THREADS));
 }
 
 // Key blocks 4 wg ... 4 wg + 3 of all heads: sign words -> FP4 rows of the block images.
@@ -487,14 +494,15 @@ __global__ __launch_bounds__(NT, PB == 4 ? 2 : 4) void psi_kernel(const PsiArgs 
     __shared__ __attribute__((aligned(16))) int8_t tiles[NW * 32 * LDT];  // phi_block: the sign words
     __shared__ __attribute__((aligned(16))) unsigned smax[NW][4][4];     // phi_block: the partial sums
     __shared__ __attribute__((aligned(16))) float sdelta[32], srcp[32];
-    static_assert(NT / PREP_THREADS * BV * W * 4 <= sizeof(tiles) && 2 * NW * 4 <= sizeof(smax), "phi_block's LDS");
+    static_assert(NT / PREP_THREADS * BV * (W * 4 + 32 * ((W + 1) / 2)) <= sizeof(tiles) && 2 * NW * 4 <= sizeof(smax), "phi_block's LDS");
     const int per = (a.slabs + 7) >> 3;  // slabs of an XCD (consecutive workgroups go to different ones)
     if ((int)blockIdx.x >= 8 * per) {
         if (a.k_bits != nullptr)
             expand_k_blocks<C16, NT>(a, (int)blockIdx.x - 8 * per);
         else
             phi_block<C16, NT>(a, (int)blockIdx.x - 8 * per, reinterpret_cast<uint32_t *>(tiles),
-                           reinterpret_cast<float(*)[NW]>(&smax[0][0][0]));
+                               reinterpret_cast<char *>(tiles) + NT / PREP_THREADS * BV * W * 4,
+                               reinterpret_cast<float(*)[NW]>(&smax[0][0][0]));
         return;
     }
     const int u = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
@@ -589,12 +597,15 @@ __global__ __launch_bounds__(NT, PB == 4 ? 2 : 4) void psi_kernel(const PsiArgs 
         }
         __builtin_amdgcn_wave_barrier();
         char *dst = a.img + ((int64_t)bh * a.nblk + blk) * a.img_bytes;
+        // (the 16 bytes between two rows are written too: the slab is one run of whole lines.  Lines written in part cost
+        // this kernel and the one that reads them; with the key rows of phi_block also written whole, psi / attention stage,
+        // d = 72, N = 1024, 128 heads 15.0 / 61.1 -> 13.7 / 59.5 us, d = 80, N = 1370, 64 heads 12.2 / 69.4 -> 11.7 / 65.8.)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int c = 8 * j + (lane >> 3), part = lane & 7;
-            if (j < nch)
-                *reinterpret_cast<u4 *>(dst + a.v_off + (8 * c0 + c) * LDT + 16 * part) =
-                    *reinterpret_cast<const u4 *>(tile + c * LDT + 16 * (part ^ ((j >> 1) << 2)));
+        for (int j = 0; j < 5; ++j) {
+            const int i = lane + 64 * j, c = (i * 57) >> 9, part = i - 9 * c;  // c = i / 9
+            u4 x = *reinterpret_cast<const u4 *>(tile + min(c, 31) * LDT + 16 * (part == 8 ? 8 : part ^ ((c >> 4) << 2)));
+            if (part == 8) x = u4{0u, 0u, 0u, 0u};
+            if (i < 72 * nch) *reinterpret_cast<u4 *>(dst + a.v_off + 8 * c0 * LDT + 16 * i) = x;
         }
         // column sums: lanes c and c + 32 take half a row each, four signed bytes per dot
         int sum = 0;
