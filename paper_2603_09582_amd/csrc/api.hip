@@ -277,6 +277,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         p.nrb = four ? (N + BR - 1) / BR : 1;
         p.nb = four ? 1 : 2;
         p.total_wg = B * H;
+        p.split_from = onehead4_split_from(B * H, p.nrb);
         switch (s.DK) {
             case 1: return launch_onehead_dk<1>(p, mode, st);
             case 2: return launch_onehead_dk<2>(p, mode, st);
@@ -285,7 +286,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
             default: return BINATTN_ERR_SHAPE;
         }
     }
-    p.split_sums = p.small_pitch = 0;
+    p.split_sums = p.small_pitch = p.split_from = 0;
     p.phase512 = bias_dtype == BINATTN_BIAS_BF16 && chunk_rows ? 0 : 1;
     p.xq = p.xk = p.xv = nullptr;
     p.xqs = p.xks = p.xvs = Strides3{0, 0, 0};

@@ -203,6 +203,7 @@ struct FusedParams {
     int small_pitch;     // rows of xq, xk, xv less than 2^22 elements apart
     int use_mu;
     int phase512;        // 8-wave forms: the accumulator's offset is removed where the 4-wave form on the grid of 512 does
+    int split_from;      // 4-wave single launch: heads from this one on take a workgroup per row block (a multiple of 8, or total_wg)
     int split_sums;      // 4-wave single launch: abs-means in the 8-wave form's order
     float *mu_q_out, *mu_k_out;
     const float *ax_y, *ax_x;  // BIAS_AXIAL: fp32 [H][2 Gy - 1], [H][2 Gx - 1]
@@ -216,6 +217,16 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream);
 // The single-launch form for at most two key blocks (nb must be 2, total_wg = B * H).
 // single-launch form: calls with more heads than this use 4-wave workgroups (two per compute unit)
 constexpr int ONEHEAD4_MIN_HEADS = 256;
+// Heads of such a call that are left for a round of their own (512 workgroups fit the chip at once) and are at most half as
+// many as compute units: one workgroup per row block, each after the whole prologue, so that the last round takes half of its
+// block loops.  us per call, whole heads / split, bf16 bias: N = 197, d = 64 520 heads 36.9 / 32.3, 640 36.3 / 31.9, 1152 54.6 / 51.0;
+// N = 256, d = 72 640 heads 41.5 / 37.7; N = 200, d = 32 640 heads 24.6 / 20.2; fp32 bias, d = 96 640 heads 52.6 / 47.3; no bias, d = 64
+// 640 heads 29.8 / 28.2, 1152 44.6 / 42.8.  Above 128 the halves share compute units: 704 heads 37.1 / 36.3, without a bias
+// 30.5 / 31.7, d = 32 25.0 / 25.9; 1280 heads 55.9 / 57.4.
+constexpr int onehead4_split_from(int heads, int row_blocks) {
+    const int left = heads % 512;
+    return row_blocks == 2 && heads > 512 && left > 0 && left <= 128 ? heads - left : heads;
+}
 // ... in the variants whose 256-thread prologue holds a head's loads in registers without spilling
 constexpr bool onehead4_built(int DK, int mode) {
     return DK <= 2 || (DK == 3 && (mode == BIAS_NONE || mode == BIAS_F32_VEC || mode == BIAS_F32_LDS || mode == BIAS_BF16_LDS ||

@@ -91,6 +91,7 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 // the same prologue with 256 threads, then the head's two 128-row blocks one after the other
 // as two items of the persistent stream (the images stay where they are).  Two such workgroups
 // share a compute unit, so one head's loads and preparation overlap the other's block loop.
+// (Heads left for a last round that fills the chip at most half take a workgroup per row block: onehead4_split_from.)
 //
 // WIDE_PAIR_ONCE is the paired form (NB = 2) with the bias copies marked as not worth keeping in the
 // caches, for biases larger than those.
@@ -232,11 +233,18 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         Item t;
         Args &p = args();
         const int nbp = p.B / NIMG, per_xcd = (p.total_wg + 7) >> 3, vmax = 8 * per_xcd;
-        const int u = (v & 7) * per_xcd + (v >> 3);
+        int u = (v & 7) * per_xcd + (v >> 3), row_block = 0;
         t.valid = v < vmax && u < p.total_wg;
+        if (ONEHEAD4 && p.split_from < p.total_wg) {  // heads from split_from on: a workgroup per row block
+            const int s = (v - p.split_from) >> 3, per_tail = (p.total_wg - p.split_from + 7) >> 3;
+            const bool whole = v < p.split_from;
+            u = whole ? (v & 7) * (p.split_from >> 3) + (v >> 3) : p.split_from + (v & 7) * per_tail + (s >> 1);
+            row_block = whole ? 0 : s & 1;
+            t.valid = u < p.total_wg;
+        }
         const int uu = t.valid ? u : 0;
         t.b = ONEHEAD ? uu / p.H : (uu % nbp) * NIMG + isel;
-        t.rb = ONEHEAD4 ? 0 : ONEHEAD ? bsel : ROWS2 ? 2 * ((uu / nbp) % p.nrb) + bsel : (uu / nbp) % p.nrb;
+        t.rb = ONEHEAD4 ? row_block : ONEHEAD ? bsel : ROWS2 ? 2 * ((uu / nbp) % p.nrb) + bsel : (uu / nbp) % p.nrb;
         t.h = ONEHEAD ? uu % p.H : uu / (nbp * p.nrb);
         t.bh = t.b * p.H + t.h;
         return t;
@@ -652,7 +660,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     if (ONEHEAD4) {  // a head's two row blocks, one workgroup
         nxt = cur;
         nxt.rb = 1;
-        nxt.valid = p.nrb > 1;
+        nxt.valid = p.nrb > 1 && (p.split_from == p.total_wg || v < p.split_from);
     } else if (PERSIST) {
         nxt = decode(v + gridDim.x);
     }
@@ -1054,7 +1062,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             return row < N && c0 < d ? *reinterpret_cast<const u4 *>(src.base + (int64_t)row * src.pitch64 + c0) : u4{0u, 0u, 0u, 0u};
         };
         // this lane's query row: the chunks of the sign words its B operand needs (channels 64 s + 32 g + 8 j)
-        const int qrow = cur.rb * BR + wave * ROWS_PER_WAVE + m;
+        const int qrow = (ONEHEAD4 ? 0 : cur.rb * BR) + wave * ROWS_PER_WAVE + m;
         u4 qx[ONEHEAD4 ? 2 : 1][DK2][4];  // (4-wave form: and its row in the second row block)
         float qsum[NS] = {}, ksum[NS] = {};
         auto load_q_row = [&](auto fast, int rb) {
@@ -1162,6 +1170,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                 qsum[0] = 0.0f;
             }
             q_row_words(1, pend_q2, qsum[NS - 1]);
+            if (cur.rb == 1) {  // (uniform)
+#pragma unroll
+                for (int i = 0; i < PQ; ++i) pend_q[i] = pend_q2[i];
+            }
         }
         // V: absmax per channel through LDS integer maxima
         {
@@ -1208,7 +1220,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         const float inv_cnt = 1.0f / ((float)N * (float)d);
         pend_muq = p.use_mu ? tq * inv_cnt : 1.0f;
         pend_muk = p.use_mu ? tk * inv_cnt : 1.0f;
-        if (threadIdx.x == 0) {
+        if (threadIdx.x == 0 && (!ONEHEAD4 || cur.rb == 0)) {
             if (p.mu_q_out) p.mu_q_out[cur.bh] = tq * inv_cnt;
             if (p.mu_k_out) p.mu_k_out[cur.bh] = tk * inv_cnt;
         }
@@ -1390,7 +1402,8 @@ template <int DK>
 int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
     const int needed = ((p.total_wg + 7) / 8) * 8;
     if (p.nb == 1) {  // 4-wave form: the variants onehead4_built() names
-        const dim3 grid((unsigned)needed), block(FUSED_THREADS);
+        // (eight half heads of a row block each, then those heads' other halves, and so on: both on one XCD)
+        const dim3 grid((unsigned)(p.split_from < p.total_wg ? p.split_from + (p.total_wg - p.split_from + 7) / 8 * 16 : needed)), block(FUSED_THREADS);
 #define CASE(M)                                                                                          \
     case M:                                                                                              \
         if constexpr (onehead4_built(DK, M)) {                                                           \

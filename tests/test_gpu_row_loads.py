@@ -76,3 +76,29 @@ def test_a_nan_in_v_hides_no_other_value(N, d):
     bad[0, 0, at, torch.arange(d)] = float("nan")
     _, got = ba.quant_v_debug(bad.cuda())
     assert torch.equal(got, want)
+
+
+# (heads left for a last round: one, a few that do not fill the eight chiplets, the most that are split, one more)
+@pytest.mark.parametrize("B,H,N,d,kind", [(513, 1, 197, 64, "bf16"), (65, 8, 129, 40, "bf16"), (160, 4, 256, 72, "bf16"), (641, 1, 130, 64, "none"),
+                                          (75, 7, 200, 96, "fp32"), (215, 3, 256, 24, "none"), (130, 4, 256, 72, "table"), (1025, 1, 256, 64, "none")])
+def test_heads_of_the_last_round_by_row_blocks(B, H, N, d, kind):
+    """The single launch's 4-wave form takes those heads with a workgroup per row block: the bits of a call that takes
+    the same heads whole."""
+    say(f"last round by row blocks B={B} H={H} N={N} d={d} {kind}")
+    g = torch.Generator().manual_seed(B + N + d)
+    q, k, v = (torch.randn(B, H, N, d, generator=g).to(torch.bfloat16).cuda() for _ in range(3))
+    table = (torch.randn(H, 31, 31, generator=g) * 0.5).cuda()
+    bias = None if kind == "none" else torch.randn(H, N, N, generator=g).to(torch.float32 if kind == "fp32" else torch.bfloat16).cuda()
+
+    def call(b0):
+        mu = [torch.full((B - b0, H), float("nan"), device="cuda") for _ in range(2)]
+        a = (q[b0:], k[b0:], v[b0:])
+        out = (ba.attention_relpos(*a, table, d ** -0.5, mu_q=mu[0], mu_k=mu[1]) if kind == "table" else
+               ba.attention(*a, bias, d ** -0.5, mu_q=mu[0], mu_k=mu[1]))
+        torch.cuda.synchronize()
+        return out, *mu
+
+    b0 = B - 1 - 300 // H  # 301 heads or more, at most 512: no last round of their own
+    assert 256 < (B - b0) * H <= 512
+    for whole, some in zip(call(0), call(b0)):
+        assert torch.equal(whole[b0:], some)
