@@ -245,11 +245,12 @@ int binattn_forward_fused(const void *q, const void *k, const void *v, const int
 /*
  * The whole of Alg. 1 from the bf16 tensors, for any N: phi (Eq. 5), psi (Eq. 7) and the fused
  * loop behind one call.  N <= 256 is binattn_forward_fused (one launch, workspace unused and
- * may be NULL).  Longer sequences take three launches: one pass over Q, K, V that packs the
+ * may be NULL).  Up to 4096 tokens it takes two launches: one pass over Q, K, V that packs the
  * query signs, writes the keys' +-1 operand rows directly (no key sign words in memory),
- * and reduces the V absmax and the |q|, |k| sums per 128 tokens; the V quantisation, which
- * also adds those partial sums in a fixed order (the abs-means are the same bits on every
- * run, unlike binattn_pack_qk's atomics for N > 2048); and binattn_attend.
+ * quantises V and leaves the |q|, |k| sums per 128 tokens; and binattn_attend, which adds those
+ * in a fixed order (the abs-means are the same bits on every run, unlike binattn_pack_qk's
+ * atomics for N > 2048).  Longer sequences take three: the first pass only reduces the V absmax,
+ * and the quantisation follows in a launch of its own, which also adds the sums.
  *   arguments as binattn_forward_fused, plus the workspace of binattn_workspace_bytes.
  */
 int binattn_attention(const void *q, const void *k, const void *v, const int64_t q_strides[3],
@@ -272,7 +273,7 @@ int binattn_forward_fused_relpos(const void *q, const void *k, const void *v, co
 /*
  * binattn_attention with the relative-position table of binattn_attend_relpos as bias (the
  * bias trained in Sec. 5.6), for any N = Gy * Gx within that call's grid limits: one launch
- * where binattn_forward_fused_relpos applies, else the three launches of binattn_attention.
+ * where binattn_forward_fused_relpos applies, else the launches of binattn_attention.
  * No [N, N] bias exists anywhere.  Arguments as binattn_forward_fused_relpos plus the
  * workspace of binattn_workspace_bytes (unused and may be NULL in the one-launch case).
  */
