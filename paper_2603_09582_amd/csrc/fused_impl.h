@@ -35,6 +35,7 @@
 
 #include "attn_tiles.h"
 #include "bias_rows.h"
+#include "head_rows.h"
 #include "quant_v.h"
 
 namespace binattn {
@@ -1101,11 +1102,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         // of the fp32 product
         const float rc16 = 1.0f / (float)C16;
         auto div_c16 = [&](int i) { return (int)(((float)i + 0.5f) * rc16); };
-        const int RT = NT / C16;              // thread groups = token quads per pass
-        // (threads behind the last whole group repeat the next pass's first quads)
+        const int RT = head_v_groups(NT, C16);  // thread groups = token quads per pass
         const int vr = div_c16(threadIdx.x), vc = threadIdx.x - vr * C16;
-        // passes over the 64 token quads of two key blocks: RT >= NT / (4 DK), and 21 groups at least for DK = 3
-        constexpr int KQ = (64 * 4 * DK + NT - 1) / NT;
+        constexpr int KQ = head_v_passes(NT, DK);
         u4 vw[KQ][4];
         // this thread's key chunks (8 channels of one key each): chunk i = thread + kk NT belongs to key group i / C16
         constexpr int KPT = (2 * BV * 4 * DK + NT - 1) / NT;  // chunks per thread, at most
@@ -1117,10 +1116,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             const unsigned v0 = (unsigned)(4 * vr) * rv.pitch + 16 * vc;
 #pragma unroll
             for (int kq = 0; kq < KQ; ++kq)
-                if (kq * RT < 2 * BV / 4)  // uniform
+                if (head_v_pass(kq, RT))  // uniform
 #pragma unroll
                     for (int t = 0; t < 4; ++t)
-                        vw[kq][t] = load_chunk(fast, rv, v0 + (unsigned)(4 * kq * RT + t) * rv.pitch, 4 * (vr + kq * RT) + t, 8 * vc);
+                        vw[kq][t] = load_chunk(fast, rv, v0 + (unsigned)(4 * kq * RT + t) * rv.pitch, 4 * head_v_quad(vr, kq, RT) + t, 8 * vc);
 #pragma unroll
             for (int kk = 0; kk < KPT; ++kk)
                 if (kk < kpt) {  // uniform
@@ -1180,7 +1179,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             unsigned mb[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int kq = 0; kq < KQ; ++kq)
-                if (kq * RT < 2 * BV / 4)
+                if (head_v_pass(kq, RT))
 #pragma unroll
                     for (int t = 0; t < 4; ++t) absmax_acc(mb, vw[kq][t]);
             float mf[8];
@@ -1230,8 +1229,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             const QuantConsts8 kc = load_quant_consts8(srcp, vc);
 #pragma unroll
             for (int kq = 0; kq < KQ; ++kq) {
-                const int quad = vr + kq * RT;
-                if (kq * RT < 2 * BV / 4 && 4 * quad < N && quad < 2 * BV / 4) {
+                const int quad = head_v_quad(vr, kq, RT);
+                if (head_v_pass(kq, RT) && 4 * quad < N && quad < HEAD_QUADS) {
                     unsigned packed[8];
                     quant_quad(vw[kq], kc, &sdelta[0][0][0], vc, packed);
                     char *imgq = imgp(quad / (BV / 4));

@@ -7,7 +7,7 @@ import torch
 from oracle import binattn_oracle as orc
 from paper_2603_09582_amd import binding as ba
 from tests.helpers import bf16_bits
-from tests.test_gpu_parity import say
+from tests.test_gpu_parity import check_close, gpu_out_f64, relpos_dense, say
 
 pytestmark = pytest.mark.gpu
 
@@ -102,3 +102,42 @@ def test_heads_of_the_last_round_by_row_blocks(B, H, N, d, kind):
     assert 256 < (B - b0) * H <= 512
     for whole, some in zip(call(0), call(b0)):
         assert torch.equal(whole[b0:], some)
+
+
+@pytest.mark.parametrize("kind", ["none", "bf16", "odd", "f32", "table"])
+@pytest.mark.parametrize("N", [252, 253, 256])
+def test_last_token_quad_of_the_widest_rows(N, kind):
+    """d = 96 in the 4-wave form: 21 token quads per pass, so that the 64th is a pass of its own.  The last rows hold every
+    channel's maximum."""
+    if kind == "table" and N % 16:
+        pytest.skip("token grids have rows of 16")
+    say(f"last quad of d = 96, N={N}, {kind}")
+    H, d = 260, 96
+    g = torch.Generator().manual_seed(N)
+    q, k, v = (torch.randn(1, H, N, d, generator=g).to(torch.bfloat16) for _ in range(3))
+    v[:, :, N - 4:] = (torch.where(torch.rand(1, H, 4, d, generator=g) < 0.5, -1.25, 1.25) * v.abs().float().amax(dim=2, keepdim=True)).to(torch.bfloat16)
+    table = (torch.randn(H, 31, 31, generator=g) * 0.3).cuda()
+    bias, dense = None, None
+    if kind == "table":
+        dense = relpos_dense(table.cpu(), 16, 16)
+    elif kind != "none":
+        dense = (torch.randn(H, N, N, generator=g) * 0.3).to(torch.float32 if kind == "f32" else torch.bfloat16)
+        store = torch.zeros(H, N, N + (1 if kind == "odd" else -N % 8), dtype=dense.dtype, device="cuda")
+        bias = store[:, :, :N].copy_(dense)
+    a = (q.cuda(), k.cuda(), v.cuda())
+
+    def call(flags):
+        out = (ba.forward_fused_relpos(*a, table, d ** -0.5, flags=flags) if kind == "table" else
+               ba.forward_fused(*a, bias, d ** -0.5, flags=flags))
+        torch.cuda.synchronize()
+        return gpu_out_f64(out)[0]
+
+    got, wide = call(0), call(ba.FLAG_WIDE8)
+    # (V is at most 1.25 times what the forms' 2e-3 stands for elsewhere)
+    assert np.abs(got - wide).max() <= 2.5e-3
+    for h in range(0, H, 37):
+        qq, kk, vv = (bf16_bits(t[0, h]) for t in (q, k, v))
+        codes, scales = orc.quant_v(vv)
+        b = None if dense is None else dense[h].numpy() if dense.dtype == torch.float32 else bf16_bits(dense[h])
+        want = orc.attention_rows(qq, kk, vv, b, d ** -0.5, orc.abs_mean(qq), orc.abs_mean(kk), codes, scales, want=("O2",))
+        check_close(got[h], want["O2"], f"head {h}")

@@ -1,0 +1,53 @@
+"""The index arithmetic of the single launch's V loads (csrc/head_rows.h), run on the host for every head dimension and
+both workgroup sizes: every chunk of every token quad belongs to some thread."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "head_rows.h"
+using namespace binattn;
+
+int main() {
+    long cells = 0;
+    for (int nt : {256, 512})
+        for (int c16 = 1; c16 <= 16; ++c16) {
+            const int dk = (8 * c16 + 31) / 32, groups = head_v_groups(nt, c16);
+            static int owners[HEAD_QUADS][16];
+            for (auto &r : owners) for (int &x : r) x = 0;
+            for (int pass = 0; pass < head_v_passes(nt, dk); ++pass)
+                for (int thread = 0; thread < nt && head_v_pass(pass, groups); ++thread) {
+                    const int quad = head_v_quad(thread / c16, pass, groups);
+                    if (quad < HEAD_QUADS) ++owners[quad][thread % c16];
+                }
+            for (int quad = 0; quad < HEAD_QUADS; ++quad)
+                for (int c = 0; c < c16; ++c, ++cells)
+                    if (owners[quad][c] == 0) { printf("nobody loads quad %d chunk %d: %d threads, d = %d\n", quad, c, nt, 8 * c16); return 1; }
+        }
+    printf("ok %ld\n", cells);
+}
+"""
+
+
+def run(tmp_path, edit=lambda header: header):
+    header = open(os.path.join(ROOT, "paper_2603_09582_amd", "csrc", "head_rows.h")).read()
+    (tmp_path / "head_rows.h").write_text(edit(header))
+    (tmp_path / "check.cpp").write_text(PROGRAM)
+    exe = str(tmp_path / "check")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I", str(tmp_path), str(tmp_path / "check.cpp"), "-o", exe], check=True)
+    return subprocess.run([exe], capture_output=True, text=True, timeout=120)
+
+
+def test_every_chunk_of_every_quad_is_loaded(tmp_path):
+    r = run(tmp_path)
+    assert r.returncode == 0, r.stdout
+    assert int(r.stdout.split()[1]) == 2 * 64 * 136
+
+
+def test_the_check_sees_a_pass_too_few(tmp_path):
+    """Passes counted from nt / (4 dk) groups as if that division left no remainder."""
+    r = run(tmp_path, lambda s: s.replace("return (HEAD_QUADS + nt / (4 * dk) - 1) / (nt / (4 * dk));", "return (HEAD_QUADS * 4 * dk + nt - 1) / nt;"))
+    assert r.returncode == 1 and "nobody loads quad 63 chunk 4: 256 threads, d = 96" in r.stdout
