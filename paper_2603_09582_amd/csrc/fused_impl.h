@@ -193,9 +193,12 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     __shared__ float lut[LUT ? LUTN : 4];
     // delta_v of the current item (two copies: consecutive items alternate)
     __shared__ __attribute__((aligned(16))) float sdelta[2][NIMG][DKP];
-    // partial sums of the abs-means of the next item's head (the decomposed bias has no entry point that leaves them)
+    // partial sums of the abs-means of the next item's head (the decomposed bias has no entry point that leaves them).
+    // Two copies as well: the waves read one at an item's end, behind its last barrier, and the first wave through starts
+    // the copy for the item after the next at once; the block barriers of an item lie between a copy's uses.
     constexpr bool PSUM = PERSIST && !ONEHEAD && !AXIAL;
-    __shared__ __attribute__((aligned(16))) float spsum[PSUM ? 2 * PSI_MAX_BLOCKS + 4 : 4];
+    static_assert(PSI_MAX_BLOCKS <= 32, "item_mu adds up one pair of sums per lane of half a wave");
+    __shared__ __attribute__((aligned(16))) float spsum[2][PSUM ? 2 * PSI_MAX_BLOCKS + 4 : 4];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);  // 32-row group
@@ -702,7 +705,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             if (lane < DKP / 4)  // delta_v of this item, for its epilogue
                 dma16(p.delta + (int64_t)cur.bh * DKP, 16 * lane, lds_offset(&sdelta[parity][isel][0]));
             if (PSUM && p.psum && nxt.valid && 2 * lane < p.nblk)  // the next item's, for item_mu
-                dma16(p.psum + (int64_t)nxt.bh * p.nblk * 2, 16 * lane, lds_offset(spsum));
+                dma16(p.psum + (int64_t)nxt.bh * p.nblk * 2, 16 * lane, lds_offset(&spsum[parity][0]));
         }
         if (sw && nxt.valid) fetch_item_regs(nxt);
         int nklim = N;  // key limit of the shared bias tile's copies below
@@ -995,7 +998,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         v += gridDim.x;
         if (ONEHEAD4) nxt.valid = false;  // (two row blocks)
         else nxt = decode(v + gridDim.x);
-        if (PSUM && args().psum) item_mu(cur, spsum);
+        if (PSUM && args().psum) item_mu(cur, &spsum[parity][0]);
         begin_item(cur, std::integral_constant<bool, ONEHEAD4>{});
         if (TBLK) {  // (the next item's first rows: divided by ITS alpha)
             table_store(tab + (tpar ^ 1) * 4 * TB_CP, inv_alpha);

@@ -141,3 +141,29 @@ def test_last_token_quad_of_the_widest_rows(N, kind):
         b = None if dense is None else dense[h].numpy() if dense.dtype == torch.float32 else bf16_bits(dense[h])
         want = orc.attention_rows(qq, kk, vv, b, d ** -0.5, orc.abs_mean(qq), orc.abs_mean(kk), codes, scales, want=("O2",))
         check_close(got[h], want["O2"], f"head {h}")
+
+
+# (2400 items of a head and row block: more than three in turn for every workgroup of each grid: 512, 768 and 256 pairs)
+@pytest.mark.parametrize("d,kind", [(64, "none"), (64, "bf16"), (64, "odd"), (72, "bf16"), (72, "f32"), (96, "none"), (128, "none"), (128, "bf16"), (128, "f32")])
+def test_abs_means_of_the_head_after_the_next(d, kind):
+    """Heads whose abs-means differ by powers of two, several of them in turn in a workgroup: each with its own logit multiplier."""
+    B, H, N = 100, 8, 300
+    say(f"abs-means by powers of two d={d} {kind}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    q, k, v = (torch.randn(B, H, N, d, generator=g, device="cuda") for _ in range(3))
+    for t in (q, k):
+        t *= torch.exp2(torch.randint(-3, 4, (B, H, 1, 1), generator=g, device="cuda").float())
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    bias = None
+    if kind != "none":
+        dtype = torch.float32 if kind == "f32" else torch.bfloat16
+        bias = torch.randn(H, N, N + (1 if kind == "odd" else -N % 8), generator=g, device="cuda").to(dtype)[:, :, :N]
+    mq, mk = (torch.full((B, H), float("nan"), device="cuda") for _ in range(2))
+    got = ba.attention(q, k, v, bias, d ** -0.5, mu_q=mq, mu_k=mk)
+    qb, kb, _, _ = ba.pack_qk(q, k)
+    want = ba.forward(qb, kb, mq, mk, v, bias, d ** -0.5)  # the same abs-means, one number per head
+    torch.cuda.synchronize()
+    for mu, x in ((mq, q), (mk, k)):  # fp32 sums of 300 d terms in two orders
+        assert torch.allclose(mu.double(), x.double().abs().mean(dim=(2, 3)), rtol=1e-5, atol=0)
+    assert torch.equal(got, want)
