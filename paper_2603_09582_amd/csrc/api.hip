@@ -2,6 +2,7 @@
 // the launch sequences.  See include/binattn.h for the contract.
 #include "bias_rows.h"
 #include "binattn_internal.h"
+#include "head_rows.h"
 
 #include <mutex>
 
@@ -265,8 +266,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         p.xv = static_cast<const uint16_t *>(raw->v);
         p.xqs = raw->qs; p.xks = raw->ks; p.xvs = raw->vs;
         p.mu_q_out = raw->mu_q_out; p.mu_k_out = raw->mu_k_out;
-        const int64_t far = (int64_t)1 << 22;
-        p.small_pitch = raw->qs.n < far && raw->ks.n < far && raw->vs.n < far;
+        p.small_pitch = raw->qs.n < HEAD_FAR_PITCH && raw->ks.n < HEAD_FAR_PITCH && raw->vs.n < HEAD_FAR_PITCH;
         // More heads than compute units: 4-wave workgroups, two per compute unit, each taking
         // the head's two row blocks in turn; otherwise one 8-wave workgroup per head.
         const bool four = B * H > ONEHEAD4_MIN_HEADS && onehead4_built(s.DK, mode) && !(flags & BINATTN_FLAG_WIDE8);

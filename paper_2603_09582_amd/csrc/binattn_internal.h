@@ -200,7 +200,7 @@ struct FusedParams {
     // single-launch short-sequence kernel: the bf16 inputs, whether mu is applied, optional mu exports
     const uint16_t *xq, *xk, *xv;
     Strides3 xqs, xks, xvs;
-    int small_pitch;     // rows of xq, xk, xv less than 2^22 elements apart
+    int small_pitch;     // rows of xq, xk, xv less than HEAD_FAR_PITCH elements apart
     int use_mu;
     int phase512;        // 8-wave forms: the accumulator's offset is removed where the 4-wave form on the grid of 512 does
     int split_from;      // 4-wave single launch: heads from this one on take a workgroup per row block (a multiple of 8, or total_wg)

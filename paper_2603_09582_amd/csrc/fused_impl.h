@@ -1041,7 +1041,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         if (F32L && !BIAS_LATE) load_bias_quarters(bias_row_ptr(cur), 0);
         // Row loads go through buffer descriptors that end with the tensor's last row: rows beyond N read as zeros (no effect on
         // a sum or a maximum, code 0), an address is one 32-bit offset, and nothing is clamped or masked.  (Pitches from
-        // 2^22 elements on do not fit the offsets and take 64-bit addresses.)  With that, nothing cleared that no result
+        // HEAD_FAR_PITCH elements on do not fit the offsets and take 64-bit addresses.)  With that, nothing cleared that no result
         // depends on, passes without work left out, wave sums by lane swaps and no barrier between the key blocks: 3 heads,
         // N = 197, d = 64 13.3 -> 12.1 us, 768 heads 41.5 -> 37.9, 768 heads, N = 100 22.0 -> 20.0, 512 heads, N = 256, d = 72
         // 30.5 -> 29.7 (its load phase, 7 of 28 us, is at the memory's rate).
@@ -1106,7 +1106,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         const float rc16 = 1.0f / (float)C16;
         auto div_c16 = [&](int i) { return (int)(((float)i + 0.5f) * rc16); };
         const int RT = head_v_groups(NT, C16);  // thread groups = token quads per pass
-        const int vr = div_c16(threadIdx.x), vc = threadIdx.x - vr * C16;
+        const int vn = div_c16(threadIdx.x), vr = head_v_group(vn), vc = threadIdx.x - vn * C16;
         constexpr int KQ = head_v_passes(NT, DK);
         u4 vw[KQ][4];
         // this thread's key chunks (8 channels of one key each): chunk i = thread + kk NT belongs to key group i / C16

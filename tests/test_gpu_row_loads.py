@@ -12,12 +12,12 @@ from tests.test_gpu_parity import check_close, gpu_out_f64, relpos_dense, say
 pytestmark = pytest.mark.gpu
 
 
-def at_the_end(x, pitch):
+def at_the_end(x, pitch, other=float("nan")):
     """The same [1, H, N, d] values, heads side by side in rows `pitch` elements apart, as the very end of a buffer
-    that holds NaN elsewhere (a row of NaN would follow the last one)."""
+    that holds `other` elsewhere (a row of it would follow the last one)."""
     _, H, N, d = x.shape
     n = (N - 1) * pitch + H * d
-    store = torch.full((8 + n,), float("nan"), dtype=x.dtype, device="cuda")
+    store = torch.full((8 + n,), other, dtype=x.dtype, device="cuda")
     view = store[8:].as_strided((1, H, N, d), (n, d, pitch, 1))
     view.copy_(x)
     return view
@@ -32,6 +32,20 @@ def test_single_launch_rows_anywhere(H, N, d):
     for pitch in (H * d, H * d + 8) + (((1 << 22) - 8, 1 << 22) if N <= 9 else ()):
         say(f"single launch rows H={H} N={N} d={d} pitch={pitch}")
         got = ba.attention(*(at_the_end(t, pitch) for t in (q, k, v)), None, d ** -0.5)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), pitch
+
+
+# (up to d = 24 one pass has threads for more than the 64 token quads; 16 and 24 only in the 8-wave form)
+@pytest.mark.parametrize("H,d", [(3, 8), (3, 16), (3, 24), (260, 8), (260, 16), (260, 24)])
+def test_single_launch_far_rows_of_small_heads(H, d):
+    N = 5
+    g = torch.Generator().manual_seed(H + d)
+    q, k, v = (torch.randn(1, H, N, d, generator=g).to(torch.bfloat16).cuda() for _ in range(3))
+    want = ba.attention(q, k, v, None, d ** -0.5)
+    for pitch in (1 << 20, (1 << 20) + (1 << 18), 5 << 19, (3 << 20) + 8, (1 << 22) - 8, 1 << 22):
+        say(f"single launch far rows H={H} d={d} pitch={pitch}")
+        got = ba.attention(at_the_end(q, pitch), at_the_end(k, pitch), at_the_end(v, pitch, 1e30), None, d ** -0.5)
         torch.cuda.synchronize()
         assert torch.equal(got, want), pitch
 
