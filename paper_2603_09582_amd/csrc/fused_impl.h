@@ -1106,7 +1106,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         const float rc16 = 1.0f / (float)C16;
         auto div_c16 = [&](int i) { return (int)(((float)i + 0.5f) * rc16); };
         const int RT = head_v_groups(NT, C16);  // thread groups = token quads per pass
-        const int vn = div_c16(threadIdx.x), vr = head_v_group(vn), vc = threadIdx.x - vn * C16;
+        const int vn = div_c16(threadIdx.x), vr = head_v_group(vn, NT, DK), vc = threadIdx.x - vn * C16;
         constexpr int KQ = head_v_passes(NT, DK);
         u4 vw[KQ][4];
         // this thread's key chunks (8 channels of one key each): chunk i = thread + kk NT belongs to key group i / C16
