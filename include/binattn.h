@@ -26,6 +26,10 @@
  *    least 255), whatever the number of blocks.
  *  - Q, K, V and the output are bf16; their base pointers must be 16-byte
  *    aligned and every stride a multiple of 8 elements.
+ *  - An entry point that takes Q, K or V as bf16 may be given one of them as its output as well: the same
+ *    base pointer and strides, no elements shared between heads.  (Every value of a head is read
+ *    before the head's first output is written.)  Outputs that overlap an input in any other way, a bias or
+ *    the workspace are not supported.
  *  - Calls on one stream are ordered; the entry points keep no global mutable
  *    state, so calls on different streams with disjoint buffers are
  *    independent.
@@ -233,7 +237,8 @@ int binattn_forward_relpos(const uint32_t *q_bits, const uint32_t *k_bits, const
  * Results equal binattn_pack_qk + binattn_forward up to the summation order of the
  * abs-means (fixed: the same bits on every run).  N > 256 returns BINATTN_ERR_SHAPE.  A call with more than 256 (batch, head)
  * pairs runs 4-wave workgroups, two per compute unit, each taking a head's two 128-row
- * blocks in turn (BINATTN_FLAG_WIDE8 keeps one 8-wave workgroup per head; same results up
+ * blocks in turn, or one of them where few heads are left for a last round and the output does not
+ * share memory with Q, K or V (BINATTN_FLAG_WIDE8 keeps one 8-wave workgroup per head; same results up
  * to the summation order of the abs-means).
  */
 int binattn_forward_fused(const void *q, const void *k, const void *v, const int64_t q_strides[3],

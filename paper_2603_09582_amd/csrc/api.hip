@@ -35,6 +35,14 @@ int check_strides_bhnd(const int64_t st[3], const Shape &s, Strides3 *out) {
     return BINATTN_OK;
 }
 
+// Whether the memory from the first to the last element of two bf16 [B,H,N,d] tensors has bytes in common (also where
+// the elements themselves interleave).
+bool spans_meet(const void *a, const Strides3 &as, const void *b, const Strides3 &bs, const Shape &s) {
+    auto bytes = [&](const Strides3 &t) { return 2 * (uintptr_t)((s.B - 1) * t.b + (s.H - 1) * t.h + (s.N - 1) * t.n + s.d); };
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    return a0 < b0 + bytes(bs) && b0 < a0 + bytes(as);
+}
+
 int check_workspace(const void *ws, size_t bytes, const Workspace &w) {
     if (!ws) return BINATTN_ERR_WORKSPACE;
     if (!aligned(ws, 256)) return BINATTN_ERR_WORKSPACE;
@@ -277,7 +285,10 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         p.nrb = four ? (N + BR - 1) / BR : 1;
         p.nb = four ? 1 : 2;
         p.total_wg = B * H;
-        p.split_from = onehead4_split_from(B * H, p.nrb);
+        // (An output on the storage of an input: one workgroup reads all of a head before it writes.  Two could not know.)
+        const bool shared = spans_meet(out, os, raw->q, raw->qs, s) || spans_meet(out, os, raw->k, raw->ks, s) ||
+                            spans_meet(out, os, raw->v, raw->vs, s);
+        p.split_from = shared ? B * H : onehead4_split_from(B * H, p.nrb);
         switch (s.DK) {
             case 1: return launch_onehead_dk<1>(p, mode, st);
             case 2: return launch_onehead_dk<2>(p, mode, st);

@@ -181,3 +181,17 @@ def test_abs_means_of_the_head_after_the_next(d, kind):
     for mu, x in ((mq, q), (mk, k)):  # fp32 sums of 300 d terms in two orders
         assert torch.allclose(mu.double(), x.double().abs().mean(dim=(2, 3)), rtol=1e-5, atol=0)
     assert torch.equal(got, want)
+
+
+# (heads of a last round by row blocks; whole heads in the 4- and the 8-wave form; more than two key blocks)
+@pytest.mark.parametrize("B,H,N,d", [(520, 1, 200, 64), (80, 8, 256, 72), (40, 7, 130, 32), (2, 3, 200, 64), (2, 3, 300, 72), (1, 2, 4200, 64)])
+@pytest.mark.parametrize("which", ["q", "k", "v"])
+def test_output_on_the_storage_of_an_input(B, H, N, d, which):
+    say(f"output on the storage of {which} B={B} H={H} N={N} d={d}")
+    g = torch.Generator().manual_seed(N)
+    x = {n: torch.randn(B, N, H, d, generator=g).to(torch.bfloat16).cuda().transpose(1, 2) for n in "qkv"}
+    bias = torch.randn(H, N, N, generator=g).to(torch.bfloat16).cuda() if N < 1000 else None
+    want = ba.attention(x["q"], x["k"], x["v"], bias, d ** -0.5)
+    got = ba.attention(x["q"], x["k"], x["v"], bias, d ** -0.5, out=x[which])
+    torch.cuda.synchronize()
+    assert got.data_ptr() == x[which].data_ptr() and torch.equal(got, want)
