@@ -160,7 +160,7 @@ struct RawInputs {
     float *mu_q_out, *mu_k_out;
 };
 
-// abs-means that the attention kernel adds up itself (launch_phi_psi up to PSI_MAX_BLOCKS key blocks), and their copies
+// abs-means that the attention kernel adds up itself (launch_phi_psi where psi_one_pass says so), and their copies
 // for the caller
 struct MuSums {
     const float *psum;
@@ -528,7 +528,7 @@ int binattn_attention(const void *q, const void *k, const void *v, const int64_t
     const MuSums ms = {reinterpret_cast<const float *>(ws + w.psum), mu_q_out, mu_k_out};
     return attend_impl(reinterpret_cast<const uint32_t *>(ws + w.qbits), mu, mu + s.BH, bias, bias_dtype, bias_strides,
                        nullptr, nullptr, scale, B, H, N, d, out, out_strides, workspace, workspace_bytes, flags, stream,
-                       s.nblk <= PSI_MAX_BLOCKS ? &ms : nullptr);
+                       psi_one_pass(s.BH, d / 8, s.nblk, true) ? &ms : nullptr);
 }
 
 int binattn_forward_fused_relpos(const void *q, const void *k, const void *v, const int64_t q_strides[3],
@@ -579,7 +579,7 @@ int binattn_attention_relpos(const void *q, const void *k, const void *v, const 
     const MuSums ms = {reinterpret_cast<const float *>(ws + w.psum), mu_q_out, mu_k_out};
     return attend_impl(reinterpret_cast<const uint32_t *>(ws + w.qbits), mu, mu + s.BH, nullptr, 0, nullptr, &ax, nullptr,
                        scale, B, H, N, d, out, out_strides, workspace, workspace_bytes, flags, stream,
-                       s.nblk <= PSI_MAX_BLOCKS ? &ms : nullptr);
+                       psi_one_pass(s.BH, d / 8, s.nblk, true) ? &ms : nullptr);
 }
 
 int binattn_logits_debug(const uint32_t *q_bits, const uint32_t *k_bits, int B, int H, int N, int d,

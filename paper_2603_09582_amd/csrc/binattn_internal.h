@@ -132,9 +132,21 @@ inline Workspace make_workspace(const Shape &s) {
     return w;
 }
 
-// Up to this many key blocks psi is one launch whose workgroups hold whole channel slabs of V, and the abs-means of
+// Up to this many key blocks psi can be one launch whose workgroups hold whole channel slabs of V, and the abs-means of
 // the entry point that takes Q, K, V are added up by the attention kernel from their partial sums.
 constexpr int PSI_MAX_BLOCKS = 32;
+constexpr int psi_slabs(int C16) { return (C16 + 3) / 4; }  // slabs of a head, of 8-channel chunks
+// Above 16 key blocks a wave of that launch takes four in turn, which few slabs do not hide: two passes, with a workgroup
+// per key block, are faster there.  us, two passes / one: preparation, d = 64, N = 4096 1 head 7.2 / 9.2, 16 heads 8.5 / 9.9,
+// 32 heads 13.0 / 10.7; d = 32, N = 2049 8 heads 7.0 / 7.8, 32 heads 8.6 / 8.2; d = 104, N = 4096 4 heads 9.7 / 10.5, 16 heads 12.9 / 11.5;
+// but d = 72, N = 2816 4 heads 9.1 / 8.5.  With phi in the same launch, whole call, N = 4096: d = 32 8 heads 47.0 / 48.1, 24 heads
+// 90.9 / 87.9; d = 72 4 heads 59.6 / 60.9, 12 heads 80.3 / 80.2; d = 128 4 heads 67.4 / 66.5.
+constexpr bool psi_one_pass(int BH, int C16, int nblk, bool with_phi) {
+    if (nblk > PSI_MAX_BLOCKS) return false;
+    if (nblk <= 16) return true;
+    const int slabs = BH * psi_slabs(C16);
+    return with_phi ? C16 > 12 || slabs > 16 : (C16 > 8 && C16 < 12) || slabs > 32;
+}
 
 struct Strides3 {
     int64_t b, h, n;

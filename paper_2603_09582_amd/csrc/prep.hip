@@ -366,7 +366,6 @@ struct PsiArgs {
     float *psum;             // [BH][nblk][2]
 };
 constexpr int PSI_K_BLOCKS = 4;  // key blocks whose sign words one workgroup expands
-constexpr int psi_slabs(int C16) { return (C16 + 3) / 4; }                               // slabs of a head
 constexpr int psi_chunks(int C16) { return (C16 + psi_slabs(C16) - 1) / psi_slabs(C16); }  // 8-channel chunks of a slab, at most 4
 
 // maximum over the lanes that hold the same chunk (lane % 4), two 16-bit patterns per dword
@@ -797,7 +796,7 @@ static void launch_quant_v_t(const void *v, Strides3 vs, const uint32_t *k_bits,
                            v_off, cs_off, ws + w.img);
         return;
     }
-    if (s.nblk <= PSI_MAX_BLOCKS) {
+    if (psi_one_pass(s.BH, C16, s.nblk, false)) {
         PsiArgs a = psi_args(v, vs, s, ws, w);
         a.k_bits = k_bits;
         launch_psi_t<C16>(a, s.BH, stream);
@@ -811,12 +810,12 @@ static void launch_quant_v_t(const void *v, Strides3 vs, const uint32_t *k_bits,
 }
 
 // phi + psi for the entry point that takes Q, K, V: one launch (see psi_kernel), the abs-means' partial sums
-// are left to the attention kernel; for more key blocks two launches (see phi_psi1_kernel).
+// are left to the attention kernel; where psi_one_pass says no, two launches (see phi_psi1_kernel).
 template <int C16>
 static void launch_phi_psi_t(const void *q, Strides3 qs, const void *k, Strides3 ks, const void *v, Strides3 vs,
                              const Shape &s, char *ws, const Workspace &w, float *mu_q_out, float *mu_k_out,
                              hipStream_t stream) {
-    if (s.nblk <= PSI_MAX_BLOCKS) {
+    if (psi_one_pass(s.BH, C16, s.nblk, true)) {
         PsiArgs p = psi_args(v, vs, s, ws, w);
         p.q = static_cast<const uint16_t *>(q); p.k = static_cast<const uint16_t *>(k);
         p.qs = qs; p.ks = ks;

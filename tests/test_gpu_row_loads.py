@@ -195,3 +195,29 @@ def test_output_on_the_storage_of_an_input(B, H, N, d, which):
     got = ba.attention(x["q"], x["k"], x["v"], bias, d ** -0.5, out=x[which])
     torch.cuda.synchronize()
     assert got.data_ptr() == x[which].data_ptr() and torch.equal(got, want)
+
+
+# (more than 16 key blocks: two passes up to 16 slabs of 32 channels in the one call - up to 32 in the preparation for d <= 64 and
+# d >= 96 - and one pass above; one pass with any number of them from d = 104, or from 72 to 88 in the preparation)
+@pytest.mark.parametrize("H,N,d", [(16, 2049, 32), (17, 2049, 32), (33, 2100, 24), (5, 2049, 96), (6, 2500, 72), (16, 2049, 64), (17, 2177, 64), (1, 2049, 104), (11, 2049, 96), (9, 2049, 128)])
+def test_one_or_two_passes_over_long_v(H, N, d):
+    """The same codes, scales and abs-means on either side of the rule (half the heads, all of them, and alone), and the outputs
+    of the one call those of the preparation and the attention stage."""
+    say(f"one or two passes H={H} N={N} d={d}")
+    g = torch.Generator().manual_seed(N + d)
+    q, k, v = (torch.randn(1, H, N, d, generator=g).to(torch.bfloat16).cuda() for _ in range(3))
+    res = {}
+    for n in {H, max(1, H // 2), 1}:
+        mu = [torch.full((1, n), float("nan"), device="cuda") for _ in range(2)]
+        a = [t[:, :n] for t in (q, k, v)]
+        qb, kb, _, _ = ba.pack_qk(a[0], a[1])
+        one = ba.attention(*a, None, d ** -0.5, mu_q=mu[0], mu_k=mu[1])
+        res[n] = (one, *mu, *ba.quant_v_debug(a[2]), ba.forward(qb, kb, *mu, a[2], None, d ** -0.5))
+        torch.cuda.synchronize()
+        assert torch.equal(res[n][0], res[n][5])
+    for n, r in res.items():
+        for x, y in zip(res[H][1:5], r[1:5]):  # (an output's last bits depend on where in the grid its head lies)
+            assert torch.equal(x[:, :n], y)
+    codes, scales = orc.quant_v(bf16_bits(v[0, 0]))
+    assert np.array_equal(res[H][3][0, 0].cpu().numpy(), codes) and np.array_equal(res[H][4][0, 0].cpu().numpy(), scales)
+    assert float(res[H][1][0, 0]) == pytest.approx(orc.abs_mean(bf16_bits(q[0, 0])), rel=2e-6)
