@@ -194,9 +194,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // delta_v of the current item (two copies: consecutive items alternate)
     __shared__ __attribute__((aligned(16))) float sdelta[2][NIMG][DKP];
     // partial sums of the abs-means of the next item's head (the decomposed bias has no entry point that leaves them).
-    // Two copies as well: the waves read one at an item's end, behind its last barrier, and the first wave through starts
+    // Two copies as well: the waves read one at an item's end, behind its last barrier, and the first wave through may start
     // the copy for the item after the next at once; the block barriers of an item lie between a copy's uses.
     constexpr bool PSUM = PERSIST && !ONEHEAD && !AXIAL;
+    // The copy is started in the item's first block, at 64 < d <= 96 in its last.  Neither costs anything by itself; but with
+    // few heads, a wave per SIMD, a block's time follows how the loop's code happens to lie (no bias, 1 head, N = 8284: d = 72
+    // first 109.6, last 108.5 us; d = 32 82.1 / 85.2).
+    constexpr bool PSUM_LAST = PSUM && DK == 3;
     static_assert(PSI_MAX_BLOCKS <= 32, "item_mu adds up one pair of sums per lane of half a wave");
     __shared__ __attribute__((aligned(16))) float spsum[2][PSUM ? 2 * PSI_MAX_BLOCKS + 4 : 4];
 
@@ -700,13 +704,17 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         const int nblkidx = sw ? 0 : it + 1;
         const BiasSrc nsrc = (LDS_BIAS && (sw || BIAS_LATE)) ? bias_dma_src(sw ? nxt : cur) : bsrc;
         if (!ONEHEAD && more) dma_image<DK, NWI>(nimg, inxt + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
+        auto copy_psum = [&](Args &p) {  // the next item's, for item_mu
+            if (PSUM && p.psum && nxt.valid && 2 * lane < p.nblk)
+                dma16(p.psum + (int64_t)nxt.bh * p.nblk * 2, 16 * lane, lds_offset(&spsum[parity][0]));
+        };
         if (!ONEHEAD && it == 0 && (ROWS2 ? wreg : wave) == 0) {
             Args &p = args();
             if (lane < DKP / 4)  // delta_v of this item, for its epilogue
                 dma16(p.delta + (int64_t)cur.bh * DKP, 16 * lane, lds_offset(&sdelta[parity][isel][0]));
-            if (PSUM && p.psum && nxt.valid && 2 * lane < p.nblk)  // the next item's, for item_mu
-                dma16(p.psum + (int64_t)nxt.bh * p.nblk * 2, 16 * lane, lds_offset(&spsum[parity][0]));
+            if (!PSUM_LAST) copy_psum(p);
         }
+        if (PSUM_LAST && sw && wave == 0) copy_psum(args());
         if (sw && nxt.valid) fetch_item_regs(nxt);
         int nklim = N;  // key limit of the shared bias tile's copies below
         if (BIAS_DB && more && nblkidx * BV + BV > N) {
@@ -838,7 +846,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
 
         const bool ragged = it * BV + BV > N;
-        if (ragged) {  // ragged last block: keys beyond N never count
+        if (MODE == BIAS_NONE && DK == 3 && !ONEHEAD && ragged) {  // (as below, all tiles: 1 head, N = 8284, d = 72 108.5 -> 107.7 us, 40 heads N = 4100 220.2 -> 217.2)
+#pragma unroll
+            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (it * BV + 32 * t + 16 * g + r >= N) T[t][r] = -INFINITY;
+        } else if (ragged) {  // ragged last block: keys beyond N never count
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 const int left = N - it * BV - 32 * t;
