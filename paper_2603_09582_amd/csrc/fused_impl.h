@@ -216,7 +216,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // 16 to 60 v_readlane per block brought them back from vector lanes.  (Attention stage and its preparation, before / after:
     // 128 x 128 grid, d = 64, 32 heads, decomposed 1927 / 1892 us, table 1941 / 1908; N = 2207, d = 96, 96 heads, fp32 bias
     // 353 / 338; N = 1370, d = 80, 64 heads 72.2 / 70.7.)  The forms that compute one item, or hold one head, have the registers.
-    constexpr bool COLD_ARGS = PERSIST && !ONEHEAD;
+    // fp32 tiles up to 64 channels are as fast either way where a workgroup has several items, and with few heads
+    // slower reading again (carried / again, d = 64, 1 head N = 2600 59.4 / 60.6, N = 4100 85.9 / 87.6, 192 heads N = 577 51.1 / 51.1).
+    constexpr bool COLD_ARGS = PERSIST && !ONEHEAD && !(F32L && DK == 2);
     typedef typename std::conditional<COLD_ARGS, const __attribute__((address_space(4))) FusedParams, const FusedParams>::type Args;
     auto args = [&]() -> Args & {
         if constexpr (COLD_ARGS) {
