@@ -18,14 +18,15 @@ int main() {
     for (int nt : {256, 512})
         for (int c16 = 1; c16 <= 16; ++c16) {
             const int dk = (8 * c16 + 31) / 32, groups = head_v_groups(nt, c16);
-            static int owners[HEAD_QUADS][16];
-            for (auto &r : owners) for (int &x : r) x = 0;
-            for (int pass = 0; pass < head_v_passes(nt, dk); ++pass)
-                for (int thread = 0; thread < nt && head_v_pass(pass, groups); ++thread) {
-                    const int quad = head_v_quad(head_v_group(thread / c16, nt, dk), pass, groups);
-                    if (quad < HEAD_QUADS) ++owners[quad][thread % c16];
-                    for (int64_t pitch : {8, 1 << 10, 1 << 20, (1 << 20) + (1 << 18), 1 << 21, 5 << 19, (3 << 20) + 8, HEAD_FAR_PITCH - 8})
-                        for (int N : {1, 2, 3, 9, 64, 65, 127, 255, 256})
+            for (int N = 1; N <= 4 * HEAD_QUADS; ++N) {
+                static int owners[HEAD_QUADS][16];
+                for (auto &r : owners) for (int &x : r) x = 0;
+                for (int pass = 0; pass < head_v_passes(nt, dk); ++pass)
+                    for (int thread = 0; thread < nt && head_v_pass(pass, groups, head_rows(N)); ++thread) {
+                        const int quad = head_v_quad(head_v_group(thread / c16, nt, dk), pass, groups);
+                        if (quad < HEAD_QUADS) ++owners[quad][thread % c16];
+                        if (N > 3 && N % 64 != 9 && N % 64 != 0 && N % 128 != 127) continue;
+                        for (int64_t pitch : {8, 1 << 10, 1 << 20, (1 << 20) + (1 << 18), 1 << 21, 5 << 19, (3 << 20) + 8, HEAD_FAR_PITCH - 8})
                             for (int t = 0; t < 4; ++t, ++offsets) {
                                 const uint32_t bytes = N > 1 ? 2 * (uint32_t)(pitch < 8 * c16 ? 8 * c16 : pitch) : 16 * c16;
                                 const uint32_t end = (N - 1) * bytes + 16 * c16, off = (4 * quad + t) * bytes + 16 * (thread % c16);
@@ -35,10 +36,11 @@ int main() {
                                     return 1;
                                 }
                             }
-                }
-            for (int quad = 0; quad < HEAD_QUADS; ++quad)
-                for (int c = 0; c < c16; ++c, ++cells)
-                    if (owners[quad][c] == 0) { printf("nobody loads quad %d chunk %d: %d threads, d = %d\n", quad, c, nt, 8 * c16); return 1; }
+                    }
+                for (int quad = 0; 4 * quad < N; ++quad)
+                    for (int c = 0; c < c16; ++c, ++cells)
+                        if (owners[quad][c] == 0) { printf("nobody loads quad %d chunk %d: %d threads, d = %d\n", quad, c, nt, 8 * c16); return 1; }
+            }
         }
     printf("ok %ld %ld\n", cells, offsets);
 }
@@ -57,7 +59,7 @@ def run(tmp_path, edit=lambda header: header):
 def test_every_chunk_is_loaded_and_no_row_beyond_the_sequence(tmp_path):
     r = run(tmp_path)
     assert r.returncode == 0, r.stdout
-    assert int(r.stdout.split()[1]) == 2 * 64 * 136
+    assert int(r.stdout.split()[1]) == 2 * 136 * 4 * (64 * 65 // 2)
 
 
 def test_the_check_sees_a_pass_too_few(tmp_path):
