@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "binattn.h"
+#include "psi_grid.h"
 
 namespace binattn {
 
@@ -135,7 +136,6 @@ inline Workspace make_workspace(const Shape &s) {
 // Up to this many key blocks psi can be one launch whose workgroups hold whole channel slabs of V, and the abs-means of
 // the entry point that takes Q, K, V are added up by the attention kernel from their partial sums.
 constexpr int PSI_MAX_BLOCKS = 32;
-constexpr int psi_slabs(int C16) { return (C16 + 3) / 4; }  // slabs of a head, of 8-channel chunks
 // Above 16 key blocks a wave of that launch takes four in turn, which few slabs do not hide: two passes, with a workgroup
 // per key block, are faster there.  us, two passes / one: preparation, d = 64, N = 4096 1 head 7.2 / 9.2, 16 heads 8.5 / 9.9,
 // 32 heads 13.0 / 10.7; d = 32, N = 2049 8 heads 7.0 / 7.8, 32 heads 8.6 / 8.2; d = 104, N = 4096 4 heads 9.7 / 10.5, 16 heads 12.9 / 11.5;

@@ -12,6 +12,7 @@
 namespace binattn {
 
 constexpr int PREP_THREADS = 256;
+static_assert(PREP_THREADS == PSI_PHI_THREADS, "phi_block and the grid of psi_kernel");
 
 // Key block `blk` of one head: sign words -> FP4 rows of the block image.
 // One thread per (row position, sign word): 32 channels -> 16 bytes of FP4 codes.
@@ -354,18 +355,17 @@ struct PsiArgs {
     const uint16_t *v;
     Strides3 vs;
     const uint32_t *k_bits;  // the sign words of the keys, or null
-    int kblocks;             // key blocks of all heads (k_bits)
     float *delta;            // [BH][DKP]
     char *img;
     int H, N, d, DKP, nblk, img_bytes, v_off, cs_off;
-    int slabs;               // slabs in all
+    int bh0, heads;          // the heads of this launch
+    int slabs;               // their slabs
     // phi
     const uint16_t *q, *k;
     Strides3 qs, ks;
     uint32_t *q_bits;        // [BH][N][W]
     float *psum;             // [BH][nblk][2]
 };
-constexpr int PSI_K_BLOCKS = 4;  // key blocks whose sign words one workgroup expands
 constexpr int psi_chunks(int C16) { return (C16 + psi_slabs(C16) - 1) / psi_slabs(C16); }  // 8-channel chunks of a slab, at most 4
 
 // maximum over the lanes that hold the same chunk (lane % 4), two 16-bit patterns per dword
@@ -390,7 +390,7 @@ __device__ __forceinline__ void phi_block(const PsiArgs &a, int wg, uint32_t *wo
     constexpr int NB = NT / PREP_THREADS;   // key blocks per workgroup
     const int half = threadIdx.x / PREP_THREADS, tid = threadIdx.x % PREP_THREADS;
     const int ngrp = (a.nblk + NB - 1) / NB;
-    const int chunk = NB * (wg % ngrp) + half, bh = wg / ngrp;  // chunk = key block
+    const int chunk = NB * (wg % ngrp) + half, bh = a.bh0 + wg / ngrp;  // chunk = key block
     const int b = bh / a.H, h = bh % a.H;
     const int N = a.N, n0 = chunk * BV, n1 = min(N, n0 + BV);  // (an odd last pair: n1 <= n0, nothing to do)
     char *image = a.img + ((int64_t)bh * a.nblk + chunk) * a.img_bytes;
@@ -459,24 +459,25 @@ __device__ __forceinline__ void phi_block(const PsiArgs &a, int wg, uint32_t *wo
                 *reinterpret_cast<const u4 *>(krows + 16 * (tid + j * PREP_THREADS));
 }
 
-// Key blocks 4 wg ... 4 wg + 3 of all heads: sign words -> FP4 rows of the block images.
+// Key blocks 4 wg ... 4 wg + 3 of the launch's heads: sign words -> FP4 rows of the block images.
 template <int C16, int NT>
 __device__ __forceinline__ void expand_k_blocks(const PsiArgs &a, int wg) {
     constexpr int W = (C16 + 3) / 4, W2 = 2 * ((W + 1) / 2), KP = 16 * W2;
     constexpr int NI = PSI_K_BLOCKS * BV * W2 / NT;  // words of a thread
+    const int first = a.bh0 * a.nblk + PSI_K_BLOCKS * wg, end = (a.bh0 + a.heads) * a.nblk;
     uint32_t word[NI];
 #pragma unroll
     for (int j = 0; j < NI; ++j) {  // (all loads first; unused words: the row's first one)
         const int i = threadIdx.x + j * NT, pos = i / W2 % BV, w = i % W2;
-        const int kb = min(PSI_K_BLOCKS * wg + i / (W2 * BV), a.kblocks - 1), bh = kb / a.nblk;
+        const int kb = min(first + i / (W2 * BV), end - 1), bh = kb / a.nblk;
         const int key = (kb - bh * a.nblk) * BV + key_of_position(pos);
         word[j] = a.k_bits[((int64_t)bh * a.N + min(key, a.N - 1)) * W + (w < W ? w : 0)];
     }
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
         const int i = threadIdx.x + j * NT, pos = i / W2 % BV, w = i % W2;
-        const int kb = PSI_K_BLOCKS * wg + i / (W2 * BV), bh = kb / a.nblk;
-        if (kb >= a.kblocks) break;
+        const int kb = first + i / (W2 * BV), bh = kb / a.nblk;
+        if (kb >= end) break;
         const bool live = (kb - bh * a.nblk) * BV + key_of_position(pos) < a.N;
         u4 o;
 #pragma unroll
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(NT, PB == 4 ? 2 : 4) void psi_kernel(const PsiArgs 
     }
     const int u = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
     if (u >= a.slabs) return;  // uniform over the workgroup
-    const int bh = u / S, c0 = (u % S) * CH;  // first chunk
+    const int bh = a.bh0 + u / S, c0 = (u % S) * CH;  // first chunk
     const int b = bh / a.H, h = bh % a.H, N = a.N;
     const uint16_t *vb = a.v + (int64_t)b * a.vs.b + (int64_t)h * a.vs.h;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -755,19 +756,22 @@ int launch_expand_k(const uint32_t *k_bits, const Shape &s, char *ws, const Work
 // head); longer ones take absmax partials + one more launch.
 constexpr int PREP_FUSED_MAX_BLOCKS = 2;
 
-// psi (and phi, if a.q is set) in one launch.
+// psi (and phi, if a.q is set) in one launch, or as many as the heads take.
 template <int C16>
 static void launch_psi_t(PsiArgs a, int BH, hipStream_t stream) {
-    a.slabs = BH * psi_slabs(C16);
-    a.kblocks = BH * a.nblk;
     // a wave per key block, up to eight of them, then two or four blocks per wave
-    const int nt = a.nblk <= 4 ? 256 : 512, blocks = nt / PREP_THREADS;
-    const int keys = a.q ? BH * ((a.nblk + blocks - 1) / blocks) : a.k_bits ? (a.kblocks + PSI_K_BLOCKS - 1) / PSI_K_BLOCKS : 0;
-    const dim3 grid((unsigned)((a.slabs + 7) / 8 * 8 + keys)), block(nt);
-    if (a.nblk <= 4) hipLaunchKernelGGL((psi_kernel<C16, 256, 1>), grid, block, 0, stream, a);
-    else if (a.nblk <= 8) hipLaunchKernelGGL((psi_kernel<C16, 512, 1>), grid, block, 0, stream, a);
-    else if (a.nblk <= 16) hipLaunchKernelGGL((psi_kernel<C16, 512, 2>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((psi_kernel<C16, 512, 4>), grid, block, 0, stream, a);
+    const int nt = psi_threads(a.nblk);
+    const PsiKeys keys = a.q ? PSI_PHI : a.k_bits ? PSI_EXPAND : PSI_V_ONLY;
+    const int most = psi_heads(C16, a.nblk, keys);
+    for (a.bh0 = 0; a.bh0 < BH; a.bh0 += most) {
+        a.heads = BH - a.bh0 < most ? BH - a.bh0 : most;
+        a.slabs = a.heads * psi_slabs(C16);
+        const dim3 grid((unsigned)psi_workgroups(a.heads, C16, a.nblk, keys)), block(nt);
+        if (a.nblk <= 4) hipLaunchKernelGGL((psi_kernel<C16, 256, 1>), grid, block, 0, stream, a);
+        else if (a.nblk <= 8) hipLaunchKernelGGL((psi_kernel<C16, 512, 1>), grid, block, 0, stream, a);
+        else if (a.nblk <= 16) hipLaunchKernelGGL((psi_kernel<C16, 512, 2>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((psi_kernel<C16, 512, 4>), grid, block, 0, stream, a);
+    }
 }
 static PsiArgs psi_args(const void *v, Strides3 vs, const Shape &s, char *ws, const Workspace &w) {
     PsiArgs a = {};

@@ -221,3 +221,22 @@ def test_one_or_two_passes_over_long_v(H, N, d):
     codes, scales = orc.quant_v(bf16_bits(v[0, 0]))
     assert np.array_equal(res[H][3][0, 0].cpu().numpy(), codes) and np.array_equal(res[H][4][0, 0].cpu().numpy(), scales)
     assert float(res[H][1][0, 0]) == pytest.approx(orc.abs_mean(bf16_bits(q[0, 0])), rel=2e-6)
+
+
+def test_more_heads_than_one_launch_of_the_preparation_takes():
+    """2.1 million heads of N = 513, d = 8: the runtime refuses 2^32 threads or more in a launch.  All heads on the same Q, K, V."""
+    H, N, d = 2_097_150 + 60, 513, 8
+    say(f"preparation in two launches, {H} heads")
+    if torch.cuda.mem_get_info()[0] < ba.workspace_bytes(1, H, N, d) + 3 * H * N * d * 2:
+        pytest.skip("not enough free memory")
+    g = torch.Generator().manual_seed(2)
+    x = [torch.randn(1, 1, N, d, generator=g).to(torch.bfloat16).cuda() for _ in range(3)]
+    want = ba.attention(*x, None, d ** -0.5)
+    got = ba.attention(*(t.expand(1, H, N, d) for t in x), None, d ** -0.5)
+    torch.cuda.synchronize()
+    # (an output's last bits depend on where in the grid its head lies)
+    assert torch.isfinite(got[0, -100:]).all() and (got[0, -100:].float() - want[0].float()).abs().max() <= 2e-3
+    worst = max((got[0, h:h + 65536].float() - want[0].float()).abs().amax().item() for h in range(0, H, 65536))
+    del got
+    torch.cuda.empty_cache()
+    assert worst <= 2e-3
