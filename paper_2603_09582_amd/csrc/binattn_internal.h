@@ -47,14 +47,15 @@ inline Shape make_shape(int B, int H, int N, int d) {
 // one flat asynchronous copy:
 //   K  [BV positions][KP bytes]  FP4 codes of the +-1 keys, 32 bytes per 64 channels, rows in
 //                                MFMA order; the 16-byte chunks of a row are XOR-swizzled (k_chunk)
-//   VT [DKP channels][VP bytes]  V codes, channel-major, BV key bytes per row + 16 pad; 0 for keys
-//                                beyond N
-//   CS [DKP] int32               PV_MAGIC + 128 * (sum of the block's V codes)
-// What no key or channel fills: expand_k_block (sign words) writes zeros for channels beyond d and keys
-// beyond N, phi_psi1_kernel (one call from Q, K, V) leaves old bytes in both; prep_head_kernel zeroes V rows
-// and seeds beyond d, v_quant_kernel leaves old bytes there; the single-launch forms clear their images.  So a
-// consumer replaces the logits of keys beyond N, keeps its query operand zero beyond d and drops the
-// accumulators beyond d.
+//   VT [DKP channels][VP bytes]  V codes, channel-major, BV key bytes per row + 16 pad
+//   CS [DKP] int32               PV_MAGIC + 128 * (sum of the row's BV codes)
+// What no key or channel fills.  K: expand_k_blocks and expand_k_block (sign words) write zeros for channels beyond d
+// and keys beyond N; phi_block (Q, K, V in one pass) writes whole rows, whatever LDS held there; phi_psi1_kernel leaves the
+// workspace's old bytes.  V: codes of keys beyond N are 0, rows and seeds beyond d are zeros from prep_head_kernel and old
+// bytes from psi_kernel and v_quant_kernel.  The single-launch forms, whose images exist in LDS only, clear nothing: V
+// codes of token quads beyond N are old bytes there too, which the seeds include.  So a consumer replaces the
+// logits of keys beyond N (their weight is 0, code -128, and the seed takes its share out again), keeps its query
+// operand zero beyond d (FP4 has no NaN) and drops the accumulators beyond d.
 // Swizzle and padding make the 16-byte reads of 16 consecutive rows fall into 16
 // different 16-byte bank groups of the 256-byte LDS row.
 template <int DK>
@@ -196,7 +197,7 @@ constexpr int TABLE_MAX_G = 32;
 struct FusedParams {
     const uint32_t *q_bits;
     const float *mu_q, *mu_k;  // may be null (taken as 1)
-    const float *psum;         // partial sums of the abs-means, [BH][nblk][2] (then nblk <= 64 and mu_q, mu_k unused), or null
+    const float *psum;         // partial sums of the abs-means, [BH][nblk][2] (then nblk <= PSI_MAX_BLOCKS and mu_q, mu_k unused), or null
     float inv_count;           // 1 / (N d)
     const void *bias;          // may be null
     Strides3 bs;               // bias element strides (batch, head, row)

@@ -240,3 +240,27 @@ def test_more_heads_than_one_launch_of_the_preparation_takes():
     del got
     torch.cuda.empty_cache()
     assert worst <= 2e-3
+
+
+# (grids of rows of 64 stay off the single launch: items of one or two key blocks, several of them in turn in a workgroup)
+@pytest.mark.parametrize("Gy,d,flags", [(1, 64, 0), (2, 72, 0), (4, 64, 0), (1, 64, ba.FLAG_NO_BIAS), (1, 72, ba.FLAG_NO_BIAS), (3, 72, ba.FLAG_NO_BIAS),
+                                        (1, 128, ba.FLAG_NO_BIAS), (1, 32, ba.FLAG_NO_BIAS | ba.FLAG_LUT)])
+def test_abs_means_of_the_head_after_the_next_with_short_items(Gy, d, flags):
+    B, H, Gx = 350, 8, 64
+    N = Gy * Gx
+    say(f"abs-means by powers of two, {Gy} x {Gx} grid d={d} flags={flags}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + Gy)
+    q, k, v = (torch.randn(B, H, N, d, generator=g, device="cuda") for _ in range(3))
+    for t in (q, k):
+        t *= torch.exp2(torch.randint(-3, 4, (B, H, 1, 1), generator=g, device="cuda").float())
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    table = torch.randn(H, 2 * Gy - 1, 2 * Gx - 1, generator=g, device="cuda") * 0.3
+    mq, mk = (torch.full((B, H), float("nan"), device="cuda") for _ in range(2))
+    got = ba.attention_relpos(q, k, v, table, d ** -0.5, mu_q=mq, mu_k=mk, flags=flags)
+    qb, kb, _, _ = ba.pack_qk(q, k)
+    want = ba.forward_relpos(qb, kb, mq, mk, v, table, d ** -0.5, flags=flags)
+    torch.cuda.synchronize()
+    for mu, x in ((mq, q), (mk, k)):
+        assert torch.allclose(mu.double(), x.double().abs().mean(dim=(2, 3)), rtol=1e-5, atol=0)
+    assert torch.equal(got, want)
