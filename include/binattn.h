@@ -254,8 +254,9 @@ int binattn_forward_fused(const void *q, const void *k, const void *v, const int
  * query signs, writes the keys' +-1 operand rows directly (no key sign words in memory),
  * quantises V and leaves the |q|, |k| sums per 128 tokens; and binattn_attend, which adds those
  * in a fixed order (the abs-means are the same bits on every run, unlike binattn_pack_qk's
- * atomics for N > 2048).  Longer sequences take three: the first pass only reduces the V absmax,
- * and the quantisation follows in a launch of its own, which also adds the sums.
+ * atomics for N > 2048).  Longer sequences, and few heads above 2048 tokens, take three: the first
+ * pass only reduces the V absmax, and the quantisation follows in a launch of its own, which also
+ * adds the sums (the same bits).
  *   arguments as binattn_forward_fused, plus the workspace of binattn_workspace_bytes.
  */
 int binattn_attention(const void *q, const void *k, const void *v, const int64_t q_strides[3],

@@ -233,7 +233,7 @@ constexpr int ONEHEAD4_MIN_HEADS = 256;
 // Heads of such a call that are left for a round of their own (512 workgroups fit the chip at once) and are at most half as
 // many as compute units: one workgroup per row block, each after the whole prologue, so that the last round takes half of its
 // block loops.  us per call, whole heads / split, bf16 bias: N = 197, d = 64 520 heads 36.9 / 32.3, 640 36.3 / 31.9, 1152 54.6 / 51.0;
-// N = 256, d = 72 640 heads 41.5 / 37.7; N = 200, d = 32 640 heads 24.6 / 20.2; fp32 bias, d = 96 640 heads 52.6 / 47.3; no bias, d = 64
+// N = 256, d = 72 640 heads 41.5 / 37.7; N = 200, d = 32 640 heads 24.6 / 20.2; fp32 bias, N = 256, d = 96 640 heads 65.7 / 61.1; no bias, d = 64
 // 640 heads 29.8 / 28.2, 1152 44.6 / 42.8.  Above 128 the halves share compute units: 704 heads 37.1 / 36.3, without a bias
 // 30.5 / 31.7, d = 32 25.0 / 25.9; 1280 heads 55.9 / 57.4.
 constexpr int onehead4_split_from(int heads, int row_blocks) {
