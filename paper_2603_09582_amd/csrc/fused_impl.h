@@ -1128,20 +1128,24 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         const int RT = head_v_groups(NT, C16);  // thread groups = token quads per pass
         const int vn = div_c16(threadIdx.x), vr = head_v_group(vn, NT, DK), vc = threadIdx.x - vn * C16;
         constexpr int KQ = head_v_passes(NT, DK);
-        const int rows = head_rows(N);
         u4 vw[KQ][4];
         // this thread's key chunks (8 channels of one key each): chunk i = thread + kk NT belongs to key group i / C16
         constexpr int KPT = (2 * BV * 4 * DK + NT - 1) / NT;  // chunks per thread, at most
-        const int kpt = (rows * C16 + NT - 1) / NT;
+        const int kpt = (2 * BV * C16 + NT - 1) / NT;
+        // All rows are loaded, those beyond N as zeros.  At 64 < d <= 96 the words of the second key block and of the second query
+        // row are left out where N <= 128, or more than 256 heads are slower than with the clamped rows before the descriptors
+        // (us, clamped / all / half: 1080 heads, N = 128, d = 96 35.6 / 36.8 / 34.3, d = 88 34.5 / 35.4 / 33.0; N = 1, d = 96 28.7 / 30.9 /
+        // 28.5).  Narrower and wider heads are not; leaving out loads as well gives 6 % more there, and costs 1 % above 128 tokens.
+        const int rows = DK == 3 && N <= BV ? BV : 2 * BV;
+        const int kwords = (rows * C16 + NT - 1) / NT;
         u4 kx[KPT];
         unsigned kdst[KPT];  // where its FP4 word goes (LDS offset), 0xffffffff for a chunk that does not exist
-        auto issue = [&](auto fast, int rows) {
-            const int kpt = (rows * C16 + NT - 1) / NT;
+        auto issue = [&](auto fast) {
             load_q_row(fast, 0);
             const unsigned v0 = (unsigned)(4 * vr) * rv.pitch + 16 * vc;
 #pragma unroll
             for (int kq = 0; kq < KQ; ++kq)
-                if (head_v_pass(kq, RT, rows))  // uniform
+                if (head_v_pass(kq, RT))  // uniform
 #pragma unroll
                     for (int t = 0; t < 4; ++t)
                         vw[kq][t] = load_chunk(fast, rv, v0 + (unsigned)(4 * kq * RT + t) * rv.pitch, 4 * head_v_quad(vr, kq, RT) + t, 8 * vc);
@@ -1156,24 +1160,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                     if ((2 * BV * 4 * DK) % NT != 0 || NB == 2) kdst[kk] = ic < 2 * BV ? kdst[kk] : 0xffffffffu;
                     kx[kk] = load_chunk(fast, rk, (unsigned)key * rk.pitch + 16 * c8, ic < 2 * BV ? key : N, 8 * c8);
                 }
-            if (ONEHEAD4 && rows > BR) load_q_row(fast, ONEHEAD4 ? 1 : 0);
+            if constexpr (ONEHEAD4) load_q_row(fast, 1);
         };
-        // One key block: half of the loads (everything out, rows beyond it as zeros: more than 256 heads, N <= 128 was 3-10 % slower
-        // than with clamped rows at d = 88 and 96; now, us, all / half: 1080 heads, N = 128, d = 96 37.5 / 32.4, d = 64 27.0 / 24.7).
-        // They are waited for at once, or every wait below would allow for the few loads of this branch in the other one,
-        // too (768 heads, N = 197, d = 64 37.7 -> 38.2).
-        if (!p.small_pitch) {
-            issue(std::false_type{}, 2 * BV);
-        } else if (rows > BV) {
-            issue(std::true_type{}, 2 * BV);
-        } else {
-#pragma unroll
-            for (int kq = 0; kq < KQ; ++kq)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) vw[kq][t] = u4{0u, 0u, 0u, 0u};
-            issue(std::true_type{}, BV);
-            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-        }
+        if (p.small_pitch) issue(std::true_type{});
+        else issue(std::false_type{});
         for (int i = lane; i < DKP; i += 64) sabs[wid][i] = 0;
         // (Nothing else is cleared: logits of keys beyond N are replaced, the query operand is zero in channels beyond d and
         // FP4 has no NaN, accumulators of channels beyond d are dropped, and a V code that no key fills meets the weight 0,
@@ -1183,7 +1173,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         // keys: sign bits -> FP4 codes of +-1 at the row position the QK tile reads
 #pragma unroll
         for (int kk = 0; kk < KPT; ++kk) {
-            if (kk < kpt && kdst[kk] != 0xffffffffu) {
+            if (kk < kwords && kdst[kk] != 0xffffffffu) {
                 const bool first = NS == 1 || (kk % 2 == 0 && p.split_sums);
                 float sum = first ? ksum[0] : ksum[NS - 1];
                 *reinterpret_cast<__attribute__((address_space(3))) unsigned *>((size_t)kdst[kk]) =
@@ -1218,7 +1208,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             unsigned mb[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int kq = 0; kq < KQ; ++kq)
-                if (head_v_pass(kq, RT, 2 * BV))
+                if (head_v_pass(kq, RT))
 #pragma unroll
                     for (int t = 0; t < 4; ++t) absmax_acc(mb, vw[kq][t]);
             float mf[8];
@@ -1269,7 +1259,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 #pragma unroll
             for (int kq = 0; kq < KQ; ++kq) {
                 const int quad = head_v_quad(vr, kq, RT);
-                if (head_v_pass(kq, RT, 2 * BV) && 4 * quad < N && quad < HEAD_QUADS) {
+                if (head_v_pass(kq, RT) && 4 * quad < N && quad < HEAD_QUADS) {
                     unsigned packed[8];
                     quant_quad(vw[kq], kc, &sdelta[0][0][0], vc, packed);
                     char *imgq = imgp(quad / (BV / 4));

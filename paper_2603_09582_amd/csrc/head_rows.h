@@ -12,12 +12,11 @@ namespace binattn {
 constexpr int HEAD_QUADS = 64;  // token quads of two key blocks
 
 // Passes that cover all quads whatever d in (32 (dk - 1), 32 dk] is: the widest rows leave the fewest groups (nt = 256,
-// dk = 3: 21 groups at d = 96, and three passes over 21 quads stop one short of 64).  Passes that begin beyond `rows`, the
-// one or two key blocks that hold the N tokens, are left out.
+// dk = 3: 21 groups at d = 96, and three passes over 21 quads stop one short of 64).  Narrower rows leave out the
+// passes that head_v_pass calls empty.
 constexpr int head_v_passes(int nt, int dk) { return (HEAD_QUADS + nt / (4 * dk) - 1) / (nt / (4 * dk)); }
 constexpr int head_v_groups(int nt, int c16) { return nt / c16; }
-constexpr bool head_v_pass(int pass, int groups, int rows) { return 4 * pass * groups < rows; }
-constexpr int head_rows(int N) { return N <= 2 * HEAD_QUADS ? 2 * HEAD_QUADS : 4 * HEAD_QUADS; }
+constexpr bool head_v_pass(int pass, int groups) { return pass * groups < HEAD_QUADS; }
 // group of a thread, number = thread / c16.  Up to d = 24 there are more than 64 in the one pass: those all take quad
 // 64, which no call has.  (Counted on, their rows, up to 2047, would wrap at far pitches.)  Forms that have no such groups
 // are built without the minimum (512 heads, N = 256, d = 72 29.74 -> 29.62 us).

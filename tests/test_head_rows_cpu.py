@@ -22,7 +22,7 @@ int main() {
                 static int owners[HEAD_QUADS][16];
                 for (auto &r : owners) for (int &x : r) x = 0;
                 for (int pass = 0; pass < head_v_passes(nt, dk); ++pass)
-                    for (int thread = 0; thread < nt && head_v_pass(pass, groups, head_rows(N)); ++thread) {
+                    for (int thread = 0; thread < nt && head_v_pass(pass, groups); ++thread) {
                         const int quad = head_v_quad(head_v_group(thread / c16, nt, dk), pass, groups);
                         if (quad < HEAD_QUADS) ++owners[quad][thread % c16];
                         if (N > 3 && N % 64 != 9 && N % 64 != 0 && N % 128 != 127) continue;
