@@ -852,7 +852,11 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
 
         const bool ragged = it * BV + BV > N;
-        if (MODE == BIAS_NONE && DK == 3 && !ONEHEAD && ragged) {  // (as below, all tiles: 1 head, N = 8284, d = 72 108.5 -> 107.7 us, 40 heads N = 4100 220.2 -> 217.2)
+        // (Tile by tile costs branches in the 8-wave forms over a workspace, and where DK = 3 has no bias: us, by tile / at once, d = 128,
+        // fp32 bias, 18 heads N = 10122 1288 / 1279, d = 64, bf16, 32 heads N = 8192 709.6 / 706.9; no bias, d = 72, 1 head N = 8284
+        // 108.5 / 107.7, 40 heads N = 4100 220.2 / 217.2.)
+        constexpr bool AT_ONCE = !ONEHEAD && (NB == 2 || (MODE == BIAS_NONE && DK == 3));
+        if (AT_ONCE && ragged) {
 #pragma unroll
             for (int t = 0; t < KT; ++t)
 #pragma unroll
