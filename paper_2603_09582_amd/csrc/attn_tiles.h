@@ -119,18 +119,73 @@ __device__ __forceinline__ void dma16(const void *sbase, unsigned voff, unsigned
                      : "memory", "m0");
 }
 
+// NC consecutive KiB (NC = 1 .. 4) the same way: the instruction's offset moves both addresses, so one base and one
+// setting of m0 serve them all.  (A scalar instruction costs the wave as much time as a vector one where two waves share a
+// SIMD; copy by copy a block's image took 5 per KiB.)
+template <int NC>
+__device__ __forceinline__ void dma_kib(const char *sbase, unsigned voff, unsigned lds_base) {
+    static_assert(NC >= 1 && NC <= 4, "the offset field ends at 4095");
+    const uint64_t u = reinterpret_cast<uint64_t>(uniform_ptr(sbase));
+    const unsigned l = __builtin_amdgcn_readfirstlane(lds_base);
+#define HEAD "s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2"
+#define NEXT(o) "\n\tglobal_load_lds_dwordx4 %1, %2 offset:" #o
+    if constexpr (NC == 1) asm volatile(HEAD : : "s"(l), "v"(voff), "s"(u) : "memory", "m0");
+    if constexpr (NC == 2) asm volatile(HEAD NEXT(1024) : : "s"(l), "v"(voff), "s"(u) : "memory", "m0");
+    if constexpr (NC == 3) asm volatile(HEAD NEXT(1024) NEXT(2048) : : "s"(l), "v"(voff), "s"(u) : "memory", "m0");
+    if constexpr (NC == 4) asm volatile(HEAD NEXT(1024) NEXT(2048) NEXT(3072) : : "s"(l), "v"(voff), "s"(u) : "memory", "m0");
+#undef HEAD
+#undef NEXT
+}
+template <int NC>
+__device__ __forceinline__ void dma_run(const char *sbase, unsigned voff, unsigned lds_base) {
+    if constexpr (NC > 4) {
+        dma_kib<4>(sbase, voff, lds_base);
+        dma_run<NC - 4>(sbase + 4096, voff, lds_base + 4096);
+    } else if constexpr (NC > 0) {
+        dma_kib<NC>(sbase, voff, lds_base);
+    }
+}
+
 // Asynchronous copy of one block image (L::BYTES, a multiple of 1 KiB) from
 // global memory straight into LDS by NW waves (wave = 0 .. NW - 1), each of
-// which moves 1 KiB per instruction.
+// which moves a run of KiB.
 template <int DK, int NW = 4>
 __device__ __forceinline__ void dma_image(const char *__restrict__ gsrc, unsigned ldst, int wave, int lane) {
-    using L = Image<DK>;
-    constexpr int NCH = L::BYTES / 1024;
-#pragma unroll
-    for (int i = 0; i < (NCH + NW - 1) / NW; ++i) {
-        const int c = wave + NW * i;
-        if (c < NCH) dma16(gsrc + c * 1024, lane * 16, ldst + c * 1024);
-    }
+    constexpr int NCH = Image<DK>::BYTES / 1024, PER = (NCH + NW - 1) / NW, REST = NCH % PER;
+    const int c = wave * PER;
+    if (c + PER <= NCH)
+        dma_run<PER>(gsrc + c * 1024, lane * 16, ldst + c * 1024);
+    else if (REST > 0 && c < NCH)
+        dma_run<REST>(gsrc + c * 1024, lane * 16, ldst + c * 1024);
+}
+
+// The bias tile of a wave for one whole key block: row groups j = 0 .. 3, SEGS segments of 128 bytes per row; lane offset
+// voff[j] from base[j], each copy to its own KiB of the region, in the order of the region.  (m0 carries minus the
+// instruction's offset, which moves both addresses.)
+template <int SEGS>
+__device__ __forceinline__ void dma_tile(const char *const (&base)[4], const unsigned (&voff)[4], unsigned lds_base) {
+    static_assert(SEGS == 2 || SEGS == 3, "two or three segments per row");
+    const uint64_t b0 = reinterpret_cast<uint64_t>(base[0]), b1 = reinterpret_cast<uint64_t>(base[1]);
+    const uint64_t b2 = reinterpret_cast<uint64_t>(base[2]), b3 = reinterpret_cast<uint64_t>(base[3]);
+    const unsigned l = __builtin_amdgcn_readfirstlane(lds_base);
+#define COPY(v, s, o) "global_load_lds_dwordx4 " v ", " s " offset:" #o "\n\t"
+#define STEP(n) "s_add_u32 m0, m0, " #n "\n\ts_nop 0\n\t"
+#define ROWS2(v, s) COPY(v, s, 0) STEP(0x380) COPY(v, s, 128)
+#define ROWS3(v, s) COPY(v, s, 0) STEP(0x380) COPY(v, s, 128) STEP(0x380) COPY(v, s, 256)
+    if constexpr (SEGS == 2)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
+                     ROWS2("%1", "%5") STEP(0x480) ROWS2("%2", "%6") STEP(0x480) ROWS2("%3", "%7") STEP(0x480) ROWS2("%4", "%8")
+                     : : "s"(l), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(b0), "s"(b1), "s"(b2), "s"(b3)
+                     : "memory", "m0", "scc");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
+                     ROWS3("%1", "%5") STEP(0x500) ROWS3("%2", "%6") STEP(0x500) ROWS3("%3", "%7") STEP(0x500) ROWS3("%4", "%8")
+                     : : "s"(l), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(b0), "s"(b1), "s"(b2), "s"(b3)
+                     : "memory", "m0", "scc");
+#undef COPY
+#undef STEP
+#undef ROWS2
+#undef ROWS3
 }
 
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }

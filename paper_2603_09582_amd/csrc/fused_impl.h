@@ -147,8 +147,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     __shared__ __attribute__((aligned(1024))) char bufB[NIMG * L::BYTES];
     // Staging of the 32 x 128 bias tiles, REGION bytes per 32-row group.
     // NB = 1: one region per wave, private to it.  NB = 2: two buffers shared by the pair.
-    __shared__ __attribute__((aligned(1024))) char biasA[LDS_BIAS ? (NB == 2 && !PAIR ? 8 : 4) * REGION : 1024];
-    __shared__ __attribute__((aligned(1024))) char biasB[BIAS_DB ? 4 * REGION : 1024];
+    __shared__ __attribute__((aligned(1024))) char biasA[LDS_BIAS ? (NB == 2 ? 8 : 4) * REGION : 1024];
+    constexpr unsigned BIAS_B = BIAS_DB ? 4 * REGION : 0;  // the second buffer
     // BIAS_AXIAL: the head's two relative-position tables, already divided by alpha.
     //   axu: four copies of the REVERSED x table, copy j shifted by j entries, so that every
     //        lane finds its 16-entry window (ascending with the key index) 16-byte aligned.
@@ -197,10 +197,6 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // Two copies as well: the waves read one at an item's end, behind its last barrier, and the first wave through may start
     // the copy for the item after the next at once; the block barriers of an item lie between a copy's uses.
     constexpr bool PSUM = PERSIST && !ONEHEAD && !AXIAL;
-    // The copy is started in the item's first block, at 64 < d <= 96 in its last.  Neither costs anything by itself; but with
-    // few heads, a wave per SIMD, a block's time follows how the loop's code happens to lie (no bias, 1 head, N = 8284: d = 72
-    // first 109.6, last 108.5 us; d = 32 82.1 / 85.2).
-    constexpr bool PSUM_LAST = PSUM && DK == 3;
     static_assert(PSI_MAX_BLOCKS <= 32, "item_mu adds up one pair of sums per lane of half a wave");
     __shared__ __attribute__((aligned(16))) float spsum[2][PSUM ? 2 * PSI_MAX_BLOCKS + 4 : 4];
 
@@ -237,7 +233,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // XCD's L2.  The grid size is a multiple of 8, so a workgroup stays on its XCD.
     struct Item {
         int b, h, rb, bh;
-        bool valid;
+        int valid;
     };
     auto decode = [&](int v) -> Item {
         Item t;
@@ -257,6 +253,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         t.rb = ONEHEAD4 ? row_block : ONEHEAD ? bsel : ROWS2 ? 2 * ((uu / nbp) % p.nrb) + bsel : (uu / nbp) % p.nrb;
         t.h = ONEHEAD ? uu % p.H : uu / (nbp * p.nrb);
         t.bh = t.b * p.H + t.h;
+        t.valid = __builtin_amdgcn_readfirstlane(t.valid);
         return t;
     };
 
@@ -265,7 +262,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     if (!cur.valid) return;  // uniform over the workgroup
 
     // ---- per-item state ---------------------------------------------------------
-    const char *imgs;  // block images of the item's head
+    const char *imgs;  // block image to be copied next
     int q;             // this lane's query row
     float inv_alpha, a2;
     v4i qB[DK2];
@@ -276,8 +273,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // tile is its own (NB = 1), two when the tile is shared with the other batch entry.
     constexpr int RGW = PAIR ? 2 : 4;
     const int rg0 = PAIR ? RGW * bsel : 0;  // first row group of the tile this wave copies
-    // The copy address is a wave-uniform base (first row of the group, scalar registers,
-    // advanced by scalar arithmetic) plus a 32-bit lane offset that is fixed for an item.
+    // The copy address is a wave-uniform base (first row of the group and first key of the block to be copied next,
+    // scalar registers, advanced by scalar arithmetic) plus a 32-bit lane offset that is fixed for an item.
     struct BiasSrc {
         const char *base[RGW];
         unsigned voff[RGW];
@@ -401,7 +398,6 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     auto begin_item = [&](const Item &t, auto same_head) {
         constexpr bool SAME_HEAD = decltype(same_head)::value;
         Args &p = args();
-        imgs = image_ptr(t);
         q = t.rb * BR + wave * ROWS_PER_WAVE + m;
         // Logit multiplier alpha of Eq. 6.  Its sign goes into the Q operand and a vanishing
         // alpha clears the Q operand, so that the loop can assume alpha > 0.
@@ -427,9 +423,6 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         if (LUT) hb_run = 0x7fffffff;
         if (MODE == BIAS_BF16_VEC || MODE == BIAS_F32_VEC || F32L) brow = bias_row_ptr(t);
-        if (LDS_BIAS) {
-            bsrc = bias_dma_src(t);
-        }
         if (AXIAL && !SAME_HEAD) {
             // every wave is past the previous item's last block (begin_item follows its closing
             // barrier), so the tables can be overwritten; a barrier publishes the new ones
@@ -533,14 +526,31 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         const int j = idx / SEGS, seg = idx % SEGS;
         const int key0 = blk * BV + KSEG * seg + EC * dma_c[j];
         if (key0 < klim)
-            dma16<WIDE == WIDE_PAIR_ONCE>(src.base[j] + (blk * BV + KSEG * seg) * ESZ, src.voff[j],
-                                          region + ((rg0 + j) * SEGS + seg) * 1024);
+            dma16<WIDE == WIDE_PAIR_ONCE>(src.base[j] + 128 * seg, src.voff[j], region + ((rg0 + j) * SEGS + seg) * 1024);
     };
-    auto dma_bias = [&](const Item &t, const BiasSrc &src, int blk, unsigned region) {  // region: LDS offset of the tile
-        const int klim = STRADDLE ? bias_klimit(t, blk) : N;
-        if (STRADDLE && klim != N) bias_tail(t, blk, region);
+    // block blk of item t into the LDS offset `region`; src is at that block and moves on to the next.  Blocks that end inside
+    // the row, all but the last, need no look at any lane's keys: eight lane masks, branches and 64-bit addresses per block
+    // held the wave as long as its vector work did (190 scalar instructions per block; with them and those of the switch of items
+    // gone from the ordinary block, attention stage, before / after, us: N = 1024, d = 72, 128 heads 51.9 / 48.5, N = 1370, d = 80, 64
+    // heads 58.4 / 52.6, fp32 bias, N = 577, d = 64, 192 heads 39.9 / 36.1, N = 2048, d = 128, 128 heads 213.5 / 195.6).
+    auto dma_bias = [&](const Item &t, BiasSrc &src, int blk, unsigned region) {
+        if constexpr (!PAIR) {
+            if (blk * BV + BV <= N) {
+                dma_tile<SEGS>(src.base, src.voff, region);
+            } else {
+                const int klim = STRADDLE ? bias_klimit(t, blk) : N;
+                if (STRADDLE && klim != N) bias_tail(t, blk, region);
 #pragma unroll
-        for (int idx = 0; idx < SEGS * RGW; ++idx) dma_bias_one(src, blk, klim, region, idx);
+                for (int idx = 0; idx < SEGS * RGW; ++idx) dma_bias_one(src, blk, klim, region, idx);
+            }
+        } else {
+            const int klim = STRADDLE ? bias_klimit(t, blk) : N;
+            if (STRADDLE && klim != N) bias_tail(t, blk, region);
+#pragma unroll
+            for (int idx = 0; idx < SEGS * RGW; ++idx) dma_bias_one(src, blk, klim, region, idx);
+        }
+#pragma unroll
+        for (int j = 0; j < RGW; ++j) src.base[j] += BV * ESZ;
     };
     f4v fraw[F32L ? SEGS : 1][4];      // F32L: the staged quarters of the current block
     f4v freg[F32L ? 4 - SEGS : 1][4];  // F32L: this lane's values of the quarters that are not staged
@@ -663,12 +673,31 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             }
     };
 
+    // Where this lane reads its tile row: chunk c of the row sits at row + 16 (c ^ (m & 7)) = (row + 16 (m & 7)) ^ 16 c (rows are
+    // 128-byte aligned).  Four addresses, which stay in registers: forming them in every block took 14 instructions.
+    // (fp32 tiles above 64 channels have no registers left for them.)
+    const char *bA = biasA + wreg * REGION;
+    constexpr bool BADDR_LATE = F32L && DK == 3;
+    unsigned baddr[LDS_BIAS ? 4 : 1];
+    auto bias_addresses = [&](int ln) {
+        const int mm = ln & 31, gg = ln >> 5;
+        const unsigned row = lds_offset(bA) + (mm >> 3) * (SEGS * 1024) + 128 * ((mm & 7) ^ ((mm >> 3) & 1));
+#pragma unroll
+        for (int i = 0; i < 4; ++i)  // F32L: chunks 4 g + i of a segment; else chunks 2 g, 2 g + 1 of either 32-key half of it
+            baddr[i] = (row + 16 * ((mm & 7) ^ (F32L ? 4 * gg : 2 * gg))) ^ (F32L ? 16u * i : 16u * (4 * (i >> 1) + (i & 1)));
+    };
+    if (LDS_BIAS && !BADDR_LATE) bias_addresses(lane);
+
     // ---- stream position --------------------------------------------------------
     int it = 0;        // key block inside the current item
     // 8-wave single launch (up to 128 tokens leave half of its waves without rows): a wave whose 32 rows all lie beyond N
     // only copies.  12 heads, N = 125 11.0 -> 10.4 us; the branch around the block costs the other forms 1-3 %.
     const bool live = WIDE != WIDE_ONEHEAD || cur.rb * BR + wave * ROWS_PER_WAVE < N;
-    const bool younger = WAVES3 && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
+    // (Flags of the loop are integers in scalar registers that the compiler cannot look into: it makes lane masks out of them
+    // otherwise, five to ten instructions per block for each.)
+    int younger_flag = WAVES3 && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
+    int younger = __builtin_amdgcn_readfirstlane(younger_flag);
+    if (NB == 1) asm volatile("" : "+s"(younger));
     int parity = 0;    // items alternate between the two delta_v copies
     Item nxt = {0, 0, 0, 0, false};
     if (ONEHEAD4) {  // a head's two row blocks, one workgroup
@@ -698,32 +727,48 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     };
     int next_rebase = PAIR ? 0 : first_rebase();
 
+    // Copies of an item's small data, outside the block loop: delta_v of the item that starts (for its epilogue), and the partial
+    // sums of the abs-means of the item after it (for item_mu).  Its first block's end waits for them.
+    auto copy_item_data = [&]() {
+        if (ONEHEAD || (ROWS2 ? wreg : wave) != 0) return;
+        Args &p = args();
+        if (lane < DKP / 4) dma16(p.delta + (int64_t)cur.bh * DKP, 16 * lane, lds_offset(&sdelta[parity][isel][0]));
+        if (PSUM && p.psum && nxt.valid && 2 * lane < p.nblk)
+            dma16(p.psum + (int64_t)nxt.bh * p.nblk * 2, 16 * lane, lds_offset(&spsum[parity][0]));
+    };
+
     // One key/value block of the stream: compute block `it` of item `cur` from the image at
-    // `ibuf` (and bias tile at `bbuf`), prefetch the next block of the stream into the LDS
+    // `ibuf` (and bias tile `bcur` bytes behind the first), prefetch the next block of the stream into the LDS
     // offsets `inxt` / `bnxt`.  Returns false after the last block of the last item.
-    auto step = [&](const char *ibuf, unsigned inxt, const char *bbuf, unsigned bnxt, int tpar) -> bool {
+    auto step = [&](const char *ibuf, unsigned inxt, unsigned bcur, unsigned bnxt, int tpar) -> bool {
         const bool last = it + 1 == p.nblk;          // last block of this item
-        const bool more = !last || (PERSIST && nxt.valid);  // the stream goes on
+        const bool sw = PERSIST && last;             // the next block of the stream belongs to the next item
+        int more = !PERSIST ? p.nblk - 1 - it : last ? nxt.valid : 1;  // not 0: the stream goes on
+        if (!ONEHEAD) asm volatile("" : "+s"(more));
         // 0. start the copies for the next block of the stream
-        const bool sw = PERSIST && last;  // ... which belongs to the next item
-        const char *nimg = sw ? image_ptr(nxt) : imgs + (int64_t)(it + 1) * L::BYTES;
-        const int nblkidx = sw ? 0 : it + 1;
-        const BiasSrc nsrc = (LDS_BIAS && (sw || BIAS_LATE)) ? bias_dma_src(sw ? nxt : cur) : bsrc;
-        if (!ONEHEAD && more) dma_image<DK, NWI>(nimg, inxt + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
-        auto copy_psum = [&](Args &p) {  // the next item's, for item_mu
-            if (PSUM && p.psum && nxt.valid && 2 * lane < p.nblk)
-                dma16(p.psum + (int64_t)nxt.bh * p.nblk * 2, 16 * lane, lds_offset(&spsum[parity][0]));
-        };
-        if (!ONEHEAD && it == 0 && (ROWS2 ? wreg : wave) == 0) {
-            Args &p = args();
-            if (lane < DKP / 4)  // delta_v of this item, for its epilogue
-                dma16(p.delta + (int64_t)cur.bh * DKP, 16 * lane, lds_offset(&sdelta[parity][isel][0]));
-            if (!PSUM_LAST) copy_psum(p);
+        const int nblkidx = last ? 0 : it + 1;
+        if (!ONEHEAD) {
+            if (sw && nxt.valid) {
+                imgs = image_ptr(nxt);
+                fetch_item_regs(nxt);
+                if (LDS_BIAS && !BIAS_DB) bsrc = bias_dma_src(nxt);
+            }
+            if (more) {
+                dma_image<DK, NWI>(imgs, inxt + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
+                imgs += L::BYTES;
+            }
+        } else if (sw && nxt.valid) {
+            fetch_item_regs(nxt);
+            if (LDS_BIAS && !BIAS_LATE) bsrc = bias_dma_src(nxt);
         }
-        if (PSUM_LAST && sw && wave == 0) copy_psum(args());
-        if (sw && nxt.valid) fetch_item_regs(nxt);
+        if (BIAS_LATE && more) {
+            bsrc = bias_dma_src(sw ? nxt : cur);
+#pragma unroll
+            for (int j = 0; j < RGW; ++j) bsrc.base[j] += nblkidx * (BV * ESZ);
+        }
         int nklim = N;  // key limit of the shared bias tile's copies below
-        if (BIAS_DB && more && nblkidx * BV + BV > N) {
+        const bool whole = nblkidx * BV + BV <= N;
+        if (BIAS_DB && more && !whole) {
             nklim = bias_klimit(cur, nblkidx);
             if (nklim != N) bias_tail(cur, nblkidx, bnxt);
         }
@@ -736,33 +781,27 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         // scheduling hint: results do not depend on it.  With three workgroups per CU the last third does
         // (128 x 128 grid, d = 64: table 1968 us with the second half, 1912 with the last third, 2143 without).
         if (NB == 1) {
-            if (younger && (it & 1)) __builtin_amdgcn_s_setprio(1);
-            else __builtin_amdgcn_s_setprio(0);
+            if (!tpar) __builtin_amdgcn_s_setprio(0);
+            else if (younger) __builtin_amdgcn_s_setprio(1);
         }
         if (live) {
         // 1. all LDS reads of the logit phase go out together: bias tile, key rows
         if (LDS_BIAS) {
-            // chunk c of this lane's row sits at row + 16 (c ^ (m & 7)) = (row + 16 (m & 7)) ^ 16 c (rows are
-            // 128-byte aligned); the lane number is made opaque so that the addresses are formed here
-            // instead of being carried through the block loop in eight registers per buffer
-            int ln = lane;
-            asm volatile("" : "+v"(ln));
-            const int mm = ln & 31, gg = ln >> 5;
-            const unsigned row = lds_offset(bbuf) + (mm >> 3) * (SEGS * 1024) + 128 * ((mm & 7) ^ ((mm >> 3) & 1));
+            if (BADDR_LATE) {
+                int ln = lane;  // (opaque: the addresses are formed here)
+                asm volatile("" : "+v"(ln));
+                bias_addresses(ln);
+            }
             if (F32L) {
-                const unsigned a0 = row + 16 * ((mm & 7) ^ (4 * gg));  // chunk 4 gg + i of segment t
 #pragma unroll
                 for (int t = 0; t < SEGS; ++t)
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        fraw[t][i] = *reinterpret_cast<const __attribute__((address_space(3))) f4v *>((size_t)((a0 ^ (16u * i)) + 1024u * t));
+                        fraw[t][i] = *reinterpret_cast<const __attribute__((address_space(3))) f4v *>((size_t)(baddr[i] + 1024u * t));
             } else {
-                const unsigned a0 = row + 16 * ((mm & 7) ^ (2 * gg));
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {  // chunk 2 gg + 4 (t & 1) + i % 2 of the 64-key half t / 2, t = i / 2
-                    const unsigned c = 16u * (4 * ((i >> 1) & 1) + (i & 1));
-                    braw[i] = *reinterpret_cast<const __attribute__((address_space(3))) u4v *>((size_t)((a0 ^ c) + 1024u * (i >> 2)));
-                }
+                for (int i = 0; i < 8; ++i)  // chunk 2 gg + 4 (t & 1) + i % 2 of the 64-key half t / 2, t = i / 2
+                    braw[i] = *reinterpret_cast<const __attribute__((address_space(3))) u4v *>((size_t)(baddr[2 * ((i >> 1) & 1) + (i & 1)] + bcur + 1024u * (i >> 2)));
             }
         }
         v4i ka[KT][DK2];
@@ -833,7 +872,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             load_bias_vec(sw ? bias_row_ptr(nxt) : brow, nblkidx);
         if (LDS_BIAS && !BIAS_DB && more) {
             wait_lds();                       // this block's tile has been read into registers
-            dma_bias(sw ? nxt : cur, nsrc, nblkidx, bnxt);    // refill the wave's own region
+            dma_bias(sw ? nxt : cur, bsrc, nblkidx, bnxt);    // refill the wave's own region
         }
         //    the LDS reads of the P.V phase go out now and land during the exponentials
         v16i acc[DK];
@@ -911,10 +950,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                 }
             }
         } else {
-        // 2. running maximum (Alg. 1: m_ij = max(m_i,j-1, rowmax S_ij))
-        float mx;
+        // 2. running maximum (Alg. 1: m_ij = max(m_i,j-1, rowmax S_ij); both lanes of a row hold the same m_run)
+        float mx = m_run;
         if (AXIAL) {  // per-tile maxima, each shifted by the tile's y term
-            mx = -INFINITY;
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 float mt = T[t][0];
@@ -923,14 +961,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                 mx = fmaxf(mx, mt + wt[t]);
             }
         } else {
-            mx = T[0][0];
 #pragma unroll
             for (int t = 0; t < KT; ++t)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, T[t][r]);
         }
-        const float m_new = fmaxf(m_run, pair_max(mx));
-        const float m_use = (m_new == -INFINITY) ? 0.0f : m_new;  // whole row masked so far
+        const float m_new = pair_max(mx);
+        const float m_use = (MODE != BIAS_NONE && m_new == -INFINITY) ? 0.0f : m_new;  // whole row masked so far
         resc = __builtin_amdgcn_exp2f((m_run - m_use) * a2);  // e^{m_old - m_new}
         const float cexp = LOG2_255_F - m_use * a2;
         m_run = m_new;
@@ -951,7 +988,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const float pe = __builtin_amdgcn_exp2f(fmaf(T[t][4 * i + j], a2, ce));
-                    if (j & 1) ls1 += pe; else ls0 += pe;
+                    if (!(ONEHEAD && DK == 4) && t == 0 && i == 0 && j < 2) (j ? ls1 : ls0) = pe;  // (there one register too many)
+                    else if (j & 1) ls1 += pe; else ls0 += pe;
                     w = __builtin_amdgcn_cvt_pk_u8_f32(pe, j, w);
                 }
                 pk[t][i] = (int)(w ^ 0x80808080u);  // code - 128 as signed bytes
@@ -967,7 +1005,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             // The shared bias tile of the next block (BIAS_DB), one copy per tile of exponentials:
             // issued in one burst at the start of the block, beside the image copies, they fill
             // the memory pipeline's queue and hold the wave there (1.5 % of the block time).
-            if (BIAS_DB && more && t < 2 * RGW) dma_bias_one(nsrc, nblkidx, nklim, bnxt, t);
+            if (BIAS_DB && more && t < 2 * RGW) {
+                if (whole)
+                    dma16<WIDE == WIDE_PAIR_ONCE>(bsrc.base[t / 2] + 128 * (t & 1), bsrc.voff[t / 2], bnxt + ((rg0 + t / 2) * 2 + (t & 1)) * 1024);
+                else
+                    dma_bias_one(bsrc, nblkidx, nklim, bnxt, t);
+                if (t & 1) bsrc.base[t / 2] += BV * ESZ;
+            }
         }
         }
         if (BIAS_LATE) {
@@ -1023,6 +1067,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         if (ONEHEAD4) nxt.valid = false;  // (two row blocks)
         else nxt = decode(v + gridDim.x);
         if (PSUM && args().psum) item_mu(cur, &spsum[parity][0]);
+        if (!ONEHEAD4) parity ^= 1;  // (the single-launch forms keep one copy of delta_v)
+        copy_item_data();
         begin_item(cur, std::integral_constant<bool, ONEHEAD4>{});
         if (TBLK) {  // (the next item's first rows: divided by ITS alpha)
             table_store(tab + (tpar ^ 1) * 4 * TB_CP, inv_alpha);
@@ -1030,12 +1076,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         it = 0;
         if (!PAIR) next_rebase = first_rebase();
-        if (!ONEHEAD4) parity ^= 1;  // (the single-launch forms keep one copy of delta_v)
         return true;
     };
 
     // ---- prologue: first block of the first item --------------------------------
-    const char *bA = biasA + wreg * REGION, *bB = BIAS_DB ? biasB + wave * REGION : bA;
     if constexpr (ONEHEAD) {
         // phi and psi of Alg. 1 for this head, straight into the two LDS images.
         constexpr int NT = FUSED_THREADS * NB;
@@ -1275,7 +1319,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             }
         }
     } else {
-        dma_image<DK, NWI>(image_ptr(cur), lds_offset(bufA) + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
+        imgs = image_ptr(cur);
+        dma_image<DK, NWI>(imgs, lds_offset(bufA) + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
+        imgs += L::BYTES;
+        if (LDS_BIAS) {
+            bsrc = bias_dma_src(cur);
+            dma_bias(cur, bsrc, 0, lds_offset(bA));
+        }
         fetch_item_regs(cur);
         if (!AXIAL && p.psum) item_mu(cur, p.psum + (int64_t)cur.bh * p.nblk * 2);
     }
@@ -1284,7 +1334,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     if (!ONEHEAD) {
         if (MODE == BIAS_BF16_VEC) load_bias_vec(brow, 0);
         if (F32L) load_bias_quarters(brow, 0);
-        if (LDS_BIAS) dma_bias(cur, bsrc, 0, lds_offset(bA));
+        copy_item_data();
     }
     if (TBLK) {
         tblk_load(cur, 0);
@@ -1331,9 +1381,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         return PHASE ? it == next_rebase : it >= REBASE && (it & (REBASE - 2)) == 0;
     };
     for (;;) {
-        if (!step(imgA, lds_offset(bufB), bA, lds_offset(bB), 0)) break;
+        if (!step(imgA, lds_offset(bufB), 0, lds_offset(bA) + BIAS_B, 0)) break;
         if (PHASE && rebase_now()) rebase();
-        if (!step(imgB, lds_offset(bufA), bB, lds_offset(bA), 1)) break;
+        if (!step(imgB, lds_offset(bufA), BIAS_B, lds_offset(bA), 1)) break;
         if (rebase_now()) rebase();
     }
 }
