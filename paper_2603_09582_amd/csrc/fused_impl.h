@@ -266,7 +266,11 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     int q;             // this lane's query row
     float inv_alpha, a2;
     v4i qB[DK2];
+    // fp32 tiles' register quarters are loaded before the exponentials of the block before; where the registers do not hold them then
+    // (24 bytes per lane were spilled), behind them, and the bias addresses are formed in every block
+    constexpr bool BIAS_LATE = F32L && ONEHEAD4 && DK == 3;
     const char *brow = nullptr;  // this lane's bias row (register modes)
+    constexpr bool BROW_AHEAD = MODE == BIAS_BF16_VEC || (F32L && !BIAS_LATE);  // ... that of the block loaded next
     // Dense tiles are fetched with full-cache-line requests (8 lanes cover the 128 bytes of one row
     // segment) straight into LDS; which lane fetches what and where it lands: bias_rows.h.
     // A wave copies RGW of the four 8-row groups of its 32-row tile: all four when the
@@ -422,7 +426,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             __syncthreads();
         }
         if (LUT) hb_run = 0x7fffffff;
-        if (MODE == BIAS_BF16_VEC || MODE == BIAS_F32_VEC || F32L) brow = bias_row_ptr(t);
+        if (MODE == BIAS_F32_VEC || BIAS_LATE) brow = bias_row_ptr(t);
         if (AXIAL && !SAME_HEAD) {
             // every wave is past the previous item's last block (begin_item follows its closing
             // barrier), so the tables can be overwritten; a barrier publishes the new ones
@@ -554,9 +558,6 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     };
     f4v fraw[F32L ? SEGS : 1][4];      // F32L: the staged quarters of the current block
     f4v freg[F32L ? 4 - SEGS : 1][4];  // F32L: this lane's values of the quarters that are not staged
-    // ... loaded before the exponentials of the block before; where the registers do not hold them then
-    // (24 bytes per lane were spilled), behind them, and the bias addresses are formed in every block
-    constexpr bool BIAS_LATE = F32L && ONEHEAD4 && DK == 3;
     auto load_bias_quarters = [&](const char *row, int blk) {
         const float *src = reinterpret_cast<const float *>(row) + blk * BV + 16 * g;
 #pragma unroll
@@ -688,6 +689,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     };
     if (LDS_BIAS && !BADDR_LATE) bias_addresses(lane);
 
+    // The persistent forms end inside the loop: a way out of it to the function's end leaves ten moves between scalar registers (and
+    // as many through vector registers) in every block.  (Attention stage, us: N = 1024, d = 72, 128 heads 48.4 / 47.2, N = 1370, d = 80, 64
+    // heads 52.4 / 51.4, fp32 bias, N = 577, d = 64, 192 heads 36.1 / 35.7.  Where registers are at their limit it spills one.)
+    constexpr bool ENDS = PERSIST && !WAVES3 && DK < 4;
     // ---- stream position --------------------------------------------------------
     int it = 0;        // key block inside the current item
     // 8-wave single launch (up to 128 tokens leave half of its waves without rows): a wave whose 32 rows all lie beyond N
@@ -737,35 +742,37 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             dma16(p.psum + (int64_t)nxt.bh * p.nblk * 2, 16 * lane, lds_offset(&spsum[parity][0]));
     };
 
+    constexpr bool FETCH_AFTER = MODE == BIAS_BF16_VEC && DK == 4;  // (spills 84 bytes otherwise)
     // One key/value block of the stream: compute block `it` of item `cur` from the image at
     // `ibuf` (and bias tile `bcur` bytes behind the first), prefetch the next block of the stream into the LDS
     // offsets `inxt` / `bnxt`.  Returns false after the last block of the last item.
     auto step = [&](const char *ibuf, unsigned inxt, unsigned bcur, unsigned bnxt, int tpar) -> bool {
-        const bool last = it + 1 == p.nblk;          // last block of this item
-        const bool sw = PERSIST && last;             // the next block of the stream belongs to the next item
-        int more = !PERSIST ? p.nblk - 1 - it : last ? nxt.valid : 1;  // not 0: the stream goes on
-        if (!ONEHEAD) asm volatile("" : "+s"(more));
         // 0. start the copies for the next block of the stream
-        const int nblkidx = last ? 0 : it + 1;
-        if (!ONEHEAD) {
-            if (sw && nxt.valid) {
-                imgs = image_ptr(nxt);
-                fetch_item_regs(nxt);
-                if (LDS_BIAS && !BIAS_DB) bsrc = bias_dma_src(nxt);
+        int nblkidx = it + 1;  // its number in its item
+        int more = PERSIST ? 1 : p.nblk - nblkidx;  // not 0: the stream goes on
+        if (__builtin_expect(nblkidx == p.nblk, 0)) {  // the last block of this item: the next one belongs to the next item
+            if (PERSIST) more = nxt.valid;
+            nblkidx = 0;
+            if (PERSIST && more) {
+                if (!ONEHEAD) imgs = image_ptr(nxt);
+                if (!FETCH_AFTER) fetch_item_regs(nxt);
+                if (LDS_BIAS && !BIAS_DB && !BIAS_LATE) bsrc = bias_dma_src(nxt);
+                if (BROW_AHEAD) brow = bias_row_ptr(nxt);
             }
-            if (more) {
-                dma_image<DK, NWI>(imgs, inxt + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
-                imgs += L::BYTES;
-            }
-        } else if (sw && nxt.valid) {
-            fetch_item_regs(nxt);
-            if (LDS_BIAS && !BIAS_LATE) bsrc = bias_dma_src(nxt);
+        }
+        if (!ONEHEAD && !ROWS2) asm volatile("" : "+s"(more));
+        if (!ONEHEAD && PERSIST && !ROWS2) asm volatile("" : "+s"(nblkidx));
+        const bool sw = PERSIST && nblkidx == 0;
+        if (!ONEHEAD && more) {
+            dma_image<DK, NWI>(imgs, inxt + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
+            imgs += L::BYTES;
         }
         if (BIAS_LATE && more) {
             bsrc = bias_dma_src(sw ? nxt : cur);
 #pragma unroll
             for (int j = 0; j < RGW; ++j) bsrc.base[j] += nblkidx * (BV * ESZ);
         }
+        if (FETCH_AFTER && sw && more) fetch_item_regs(nxt);
         int nklim = N;  // key limit of the shared bias tile's copies below
         const bool whole = nblkidx * BV + BV <= N;
         if (BIAS_DB && more && !whole) {
@@ -867,9 +874,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (F32L && !BIAS_LATE && more) load_bias_quarters(sw ? bias_row_ptr(nxt) : brow, nblkidx);
+        if (F32L && !BIAS_LATE && more) load_bias_quarters(brow, nblkidx);
         if (MODE == BIAS_BF16_VEC && more)  // braw is free again
-            load_bias_vec(sw ? bias_row_ptr(nxt) : brow, nblkidx);
+            load_bias_vec(brow, nblkidx);
         if (LDS_BIAS && !BIAS_DB && more) {
             wait_lds();                       // this block's tile has been read into registers
             dma_bias(sw ? nxt : cur, bsrc, nblkidx, bnxt);    // refill the wave's own region
@@ -1056,12 +1063,15 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         // but tiles of a wave's own to fill again)
         if (!ONEHEAD) __syncthreads();
 
-        if (!last) {
+        if (nblkidx != 0) {
             ++it;
             return true;
         }
         finish_item(cur, &sdelta[parity][isel][0]);
-        if (!PERSIST || !nxt.valid) return false;
+        if (!PERSIST || !nxt.valid) {
+            if (ENDS) __builtin_amdgcn_endpgm();
+            return false;
+        }
         cur = nxt;
         v += gridDim.x;
         if (ONEHEAD4) nxt.valid = false;  // (two row blocks)
@@ -1105,8 +1115,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             bsrc = bias_dma_src(cur);
             dma_bias(cur, bsrc, 0, lds_offset(bA));
         }
-        if (MODE == BIAS_BF16_VEC) load_bias_vec(bias_row_ptr(cur), 0);
-        if (F32L && !BIAS_LATE) load_bias_quarters(bias_row_ptr(cur), 0);
+        if (BROW_AHEAD) brow = bias_row_ptr(cur);
+        if (MODE == BIAS_BF16_VEC) load_bias_vec(brow, 0);
+        if (F32L && !BIAS_LATE) load_bias_quarters(brow, 0);
         // Row loads go through buffer descriptors that end with the tensor's last row: rows beyond N read as zeros (no effect on
         // a sum or a maximum, code 0), an address is one 32-bit offset, and nothing is clamped or masked.  (Pitches from
         // HEAD_FAR_PITCH elements on do not fit the offsets and take 64-bit addresses.)  With that, nothing cleared that no result
@@ -1332,6 +1343,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     begin_item(cur, std::false_type{});
     if (BIAS_LATE) load_bias_quarters(brow, 0);
     if (!ONEHEAD) {
+        if (BROW_AHEAD) brow = bias_row_ptr(cur);
         if (MODE == BIAS_BF16_VEC) load_bias_vec(brow, 0);
         if (F32L) load_bias_quarters(brow, 0);
         copy_item_data();
