@@ -155,9 +155,11 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     //        Neighbouring queries use copies 3, 2, 1, 0 at one offset, then the next lower
     //        offset: a copy pitch of 16 entries beyond a multiple of 64 puts the 16-byte reads
     //        of 16 consecutive lanes on 16 different bank groups.
-    //   axw: the y table (one entry per lane and 16-key tile)
+    //   axw: the y table (one entry per lane and 16-key tile), behind zeros for the grid rows past the last one that the last
+    //        block's keys beyond N would lie in
     constexpr bool AXIAL = MODE == BIAS_AXIAL;
     constexpr int AXL = 2 * AXIAL_MAX_G + 16;  // pitch of a copy, in entries
+    constexpr int AXW0 = 8;
     __shared__ __attribute__((aligned(16))) float axu[AXIAL ? 4 * AXL : 4];
     __shared__ float axw[AXIAL ? AXL : 4];
     // BIAS_TABLE / BIAS_TABLE_BLK: rows of the head's (2 Gy - 1) x (2 Gx - 1) table divided by alpha,
@@ -362,22 +364,38 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         Args &p = args();
         return uniform_ptr(p.img + (int64_t)t.bh * p.nblk * L::BYTES);
     };
-    // ---- BIAS_TABLE / BIAS_TABLE_BLK: staging of table rows [row0, row0 + nrows) -------------
+    // ---- BIAS_TABLE / BIAS_TABLE_BLK: staging of table rows from row0 on -------------
+    // (Clipping the rows of every block against the grid, and a tile's window against its rows, took 105 scalar and 29 vector
+    // instructions per block, now 25 and 17.  Attention stage, us: table, 128 x 128, d = 64, 32 heads 1840 / 1774, 32 x 32, d = 72, 128 heads
+    // 45.6 / 43.5; decomposed, where the same holds of the tables' windows, 1820 / 1782.)
+    // Entry kk of reversed row r is a lane's i = r (2 Gx) + kk.  The loads go through a buffer descriptor that ends with the head's
+    // table: places that hold no entry (rows outside the table, the place behind a row) read as zero or as a neighbour, and only
+    // keys past the end of the sequence, whose logits are replaced, see them.  So a block takes one number, row0 LX.
     float tstage[TABLE || TBLK ? TB_PER : 1];
-    auto table_load = [&](const Item &t, int row0, int nrows) {  // global loads only
-        const int LX = 2 * p.Gx - 1, LY = 2 * p.Gy - 1, sh = p.gx_shift + 1;
-        const char *tb = uniform_ptr(reinterpret_cast<const char *>(p.table + (int64_t)t.h * LY * LX + row0 * LX));
-        int tid = 64 * (4 * bsel + wave) + lane;  // (opaque: the 32-bit offsets are formed here, not carried through the block loop)
-        asm volatile("" : "+v"(tid));
+    __amdgpu_buffer_rsrc_t trsrc;
+    unsigned tvoff[TABLE || TBLK ? TB_PER : 1];
+    auto table_place = [&](int i) -> int {  // table entry of stage entry i, from the first row's first on
+        const int LX = 2 * p.Gx - 1, sh = p.gx_shift + 1;
+        return (i >> sh) * LX + LX - 1 - (i & ((1 << sh) - 1));
+    };
+    auto table_begin = [&](const Item &t) {
+        Args &p = args();
+        const int LX = 2 * p.Gx - 1, LY = 2 * p.Gy - 1;
+        trsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(uniform_ptr(p.table + (int64_t)t.h * LY * LX)), 0, 4 * LY * LX, 0x00020000);
 #pragma unroll
-        for (int j = 0; j < TB_PER; ++j) {
-            const int i = tid + j * FUSED_THREADS * NB;
-            const int row = i >> sh, kk = i & ((1 << sh) - 1);
-            const bool on = row < nrows && kk < LX;
-            // (places that hold no entry get the first one: only keys past the end of the sequence,
-            // whose logits are replaced, read them.  A select on the loaded value would wait for it here.)
-            tstage[j] = *reinterpret_cast<const float *>(tb + (on ? 4u * (unsigned)(row * LX + (LX - 1 - kk)) : 0u));
+        for (int j = 0; j < TB_PER; ++j) tvoff[j] = 4u * (unsigned)table_place(64 * (4 * bsel + wave) + lane + j * FUSED_THREADS * NB);
+    };
+    auto table_load = [&](int row0) {  // global loads only
+        if (DK == 4) {  // (formed here: no registers to carry them)
+            int tid = 64 * (4 * bsel + wave) + lane;
+            asm volatile("" : "+v"(tid));
+#pragma unroll
+            for (int j = 0; j < TB_PER; ++j) tvoff[j] = 4u * (unsigned)table_place(tid + j * FUSED_THREADS * NB);
         }
+        const unsigned o = 4u * (unsigned)(row0 * (2 * p.Gx - 1));
+#pragma unroll
+        for (int j = 0; j < TB_PER; ++j)
+            tstage[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(trsrc, tvoff[j] + o, 0, 0));
     };
     auto table_store = [&](float *dst, float ia) {
 #pragma unroll
@@ -390,12 +408,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                 dst[c * TB_CP + i - c] = x;
         }
     };
-    // BIAS_TABLE_BLK: the rows of one (item, key block)
-    auto tblk_load = [&](const Item &t, int blk) {
-        const int iy_lo = (t.rb * BR) >> p.gx_shift, iy_hi = min((t.rb * BR + BR - 1) >> p.gx_shift, p.Gy - 1);
-        const int jy_lo = (blk * BV) >> p.gx_shift, jy_hi = min((blk * BV + BV - 1) >> p.gx_shift, p.Gy - 1);
-        const int dy_min = iy_lo - jy_hi;
-        table_load(t, dy_min + p.Gy - 1, iy_hi - jy_lo - dy_min + 1);
+    // BIAS_TABLE_BLK: the rows of one (row block, key block): row 0 is that of the first query row and the last key row
+    auto tblk_load = [&](int rb, int blk) {
+        table_load(((rb * BR) >> p.gx_shift) + p.Gy - 1 - ((blk * BV + BV - 1) >> p.gx_shift));
     };
     // turn the fetched registers into the item's state
     // (same_head: the head's tables are in LDS already)
@@ -449,8 +464,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 #pragma unroll
             for (int j = 0; j < NW; ++j) {
                 const int i = tid + j * NTA;
-                tw[j] = wy[i < LY ? i : 0];
-                if (i >= LY) tw[j] = 0.0f;
+                const bool on = i >= AXW0 && i < LY + AXW0;
+                tw[j] = wy[on ? i - AXW0 : 0];
+                if (!on) tw[j] = 0.0f;
             }
 #pragma unroll
             for (int j = 0; j < NU; ++j) {
@@ -472,12 +488,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             const int qc = min(q, N - 1);
             const int ix = qc & (p.Gx - 1), iy = qc >> p.gx_shift;
             const int s0 = p.Gx - 1 - ix;  // reversed-table index of key column 0
-            ax_ub = (s0 & 3) * AXL + (s0 & ~3);
-            ax_wb = iy + p.Gy - 1;
+            ax_ub = (s0 & 3) * AXL + (s0 & ~3) + ((16 * g) & (p.Gx - 1));
+            ax_wb = iy + p.Gy - 1 + AXW0 - (p.Gx == 16 ? g : 0);
         }
         if (TABLE && !SAME_HEAD) {
             // (as above: the previous item's last block is behind every wave)
-            table_load(t, 0, 2 * p.Gy - 1);
+            table_begin(t);
+            table_load(0);
             table_store(tab, inv_alpha);
             __syncthreads();
         }
@@ -489,8 +506,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         if (TBLK) {
             const int qc = min(q, N - 1);
             const int s0 = p.Gx - 1 - (qc & (p.Gx - 1));  // reversed-row index of key column 0
-            // ... of the row with jy = jy_hi of a block (row 0 of the staged rows: iy = iy_lo, jy = jy_hi)
-            ax_ub = (s0 & 3) * TB_CP + (s0 & ~3) + (((qc >> p.gx_shift) - ((t.rb * BR) >> p.gx_shift)) << (p.gx_shift + 1));
+            // ... of the row of a block's last keys (row 0 of the staged rows: iy = iy_lo, jy = jy_hi), plus the step from a 32-key
+            // tile's first 16 keys to its last, which is the same in all tiles
+            ax_ub = (s0 & 3) * TB_CP + (s0 & ~3) + (((qc >> p.gx_shift) - ((t.rb * BR) >> p.gx_shift)) << (p.gx_shift + 1)) +
+                    g * (p.Gx == 16 ? -2 * 16 : 16);
         }
         m_run = -INFINITY;
         l_run = 0.0f;
@@ -779,7 +798,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             nklim = bias_klimit(cur, nblkidx);
             if (nklim != N) bias_tail(cur, nblkidx, bnxt);
         }
-        if (TBLK && more) tblk_load(sw ? nxt : cur, nblkidx);  // lands during this block, stored at its end
+        if (TBLK && more) {  // land during this block, stored at its end
+            if (sw) table_begin(nxt);
+            tblk_load(sw ? nxt.rb : cur.rb, nblkidx);
+        }
 
         // Two 4-wave workgroups share a CU, and the SIMDs issue the older wave first: the
         // workgroup dispatched first then runs ~25 % faster than the other and leaves the CU
@@ -821,38 +843,44 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         v16f T[KT];
         float wt[KT];  // BIAS_AXIAL: the y term of tile t (constant over its 16 keys), else 0
         if (AXIAL) {
+            // A block starts on a grid row up to Gx = 128, so a tile's place in it does not depend on the block (Gx = 256: two blocks
+            // to a row); the first keys' places are in the lane's bases.
+            const int xb = (it * BV) & (p.Gx - 1), yb = (it * BV) >> p.gx_shift;
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
-                const int key0 = it * BV + 32 * t + 16 * g;
-                const int jx0 = key0 & (p.Gx - 1), jy = min(key0 >> p.gx_shift, p.Gy - 1);
-                const float *win = axu + ax_ub + jx0;
-                v16f cin;
+                const float *win = axu + ax_ub + xb + ((32 * t) & (p.Gx - 1));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const f4v x = *reinterpret_cast<const f4v *>(win + 4 * i);
-                    cin[4 * i] = x[0]; cin[4 * i + 1] = x[1]; cin[4 * i + 2] = x[2]; cin[4 * i + 3] = x[3];
+                    T[t][4 * i] = x[0]; T[t][4 * i + 1] = x[1]; T[t][4 * i + 2] = x[2]; T[t][4 * i + 3] = x[3];
                 }
-                wt[t] = axw[ax_wb - jy];
-                T[t] = qk_mfma<DK2>(ka[t], qB, cin);
+                wt[t] = axw[ax_wb - yb - ((32 * t) >> p.gx_shift)];
             }
+#pragma unroll
+            for (int t = 0; t < KT; ++t) T[t] = qk_mfma<DK2>(ka[t], qB, T[t]);
         } else if (TABLE || TBLK) {
-            const float *tcur = tab + (TBLK ? tpar * 4 * TB_CP : 0) + ax_ub;
-            const int jy0 = TBLK ? min((it * BV + BV - 1) >> p.gx_shift, p.Gy - 1) : 0;
-            // offset of the window of 16 keys of one grid row (Gx >= 16), scalar arithmetic
-            auto window = [&](int key0) { return (key0 & (p.Gx - 1)) + (jy0 - min(key0 >> p.gx_shift, p.Gy - 1)) * (2 * p.Gx); };
+            // Windows of 16 keys of one grid row (16 <= Gx).  A block starts on a grid row up to Gx = 128, so a tile's place in the
+            // staged rows does not depend on the block (Gx = 256: two blocks to a row).
+            const float *tcur = tab + (TBLK ? tpar * 4 * TB_CP : 0) + ax_ub + (TBLK ? (it * BV) & (p.Gx - 1) : 0);
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
-                const int o0 = window(it * BV + 32 * t), o1 = window(it * BV + 32 * t + 16);
-                const float *win = tcur + (g ? o1 : o0);
-                v16f cin;
+                int o0, o1;
+                if (TBLK) {
+                    o0 = o1 = ((32 * t) & (p.Gx - 1)) + (((BV - 1) >> p.gx_shift) - ((32 * t) >> p.gx_shift)) * (2 * p.Gx);
+                } else {
+                    auto window = [&](int key0) { return (key0 & (p.Gx - 1)) - min(key0 >> p.gx_shift, p.Gy - 1) * (2 * p.Gx); };
+                    o0 = window(it * BV + 32 * t), o1 = window(it * BV + 32 * t + 16);
+                }
+                const float *win = tcur + (TBLK ? o0 : g ? o1 : o0);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const f4v x = *reinterpret_cast<const f4v *>(win + 4 * i);
-                    cin[4 * i] = x[0]; cin[4 * i + 1] = x[1]; cin[4 * i + 2] = x[2]; cin[4 * i + 3] = x[3];
+                    T[t][4 * i] = x[0]; T[t][4 * i + 1] = x[1]; T[t][4 * i + 2] = x[2]; T[t][4 * i + 3] = x[3];
                 }
                 wt[t] = 0.0f;
-                T[t] = qk_mfma<DK2>(ka[t], qB, cin);
             }
+#pragma unroll
+            for (int t = 0; t < KT; ++t) T[t] = qk_mfma<DK2>(ka[t], qB, T[t]);
         } else if (LUT) {
             // 1.5 * 2^23 + d - I: an integer in [0, 2 d] on top of the float-bit offset, so the bit
             // pattern read as an integer is PV_MAGIC_BITS + (d - I) and all further logit
@@ -1058,7 +1086,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         if (TBLK && more && !sw) table_store(tab + (tpar ^ 1) * 4 * TB_CP, inv_alpha);
         __builtin_amdgcn_sched_barrier(0);  // keep the wait at the very end of the block
-        wait_vmem();      // this wave's copies for the next block have landed
+        if (TBLK) __builtin_amdgcn_s_waitcnt(0x0F70);  // (vmcnt(0) in the form the compiler counts: see the decomposed bias's tables)
+        else wait_vmem();  // this wave's copies for the next block have landed
         // everyone is done with this block's buffers, the next ones are complete (the single-launch forms have nothing
         // but tiles of a wave's own to fill again)
         if (!ONEHEAD) __syncthreads();
@@ -1349,7 +1378,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         copy_item_data();
     }
     if (TBLK) {
-        tblk_load(cur, 0);
+        table_begin(cur);
+        tblk_load(cur.rb, 0);
         table_store(tab, inv_alpha);
     }
     wait_vmem();
