@@ -285,6 +285,8 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         p.nrb = four ? (N + BR - 1) / BR : 1;
         p.nb = four ? 1 : 2;
         p.total_wg = B * H;
+        p.div_inner = make_fast_div(H);
+        p.div_rows = make_fast_div(1);
         // (An output on the storage of an input: one workgroup reads all of a head before it writes.  Two could not know.)
         const bool shared = spans_meet(out, os, raw->q, raw->qs, s) || spans_meet(out, os, raw->k, raw->ks, s) ||
                             spans_meet(out, os, raw->v, raw->vs, s);
@@ -310,6 +312,8 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         p.nb = 2;
         p.nrb = (p.nrb + 1) / 2;
         p.total_wg = p.nrb * H * B;
+        p.div_inner = make_fast_div(B);
+        p.div_rows = make_fast_div(p.nrb);
         return launch_fused_dk<4>(p, mode, st);
     }
     // Long sequences with a batch-shared, LDS-staged bias: pair batch entries in one
@@ -327,6 +331,8 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     // 8 x 12 heads 464 / 467; but N = 2048, 8 heads (67 MB) 180.0 / 178.6 and N = 3137 (odd rows) 156 / 148.
     if (p.nb == 2 && aligned(bias, 128) && bs.h % 64 == 0 && bs.n % 64 == 0 && streamed) p.wide = 4;
     p.total_wg = p.nrb * H * (B / p.nb);
+    p.div_inner = make_fast_div(B / p.nb);
+    p.div_rows = make_fast_div(p.nrb);
     if (mode == BIAS_BF16_LDS && p.nb == 1 && N % 8 == 0) mode = BIAS_BF16_LDS8;
     switch (s.DK) {
         case 1: return launch_fused_dk<1>(p, mode, st);

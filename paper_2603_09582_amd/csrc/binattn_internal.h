@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "binattn.h"
+#include "fast_div.h"
 #include "psi_grid.h"
 
 namespace binattn {
@@ -208,6 +209,7 @@ struct FusedParams {
     const char *img;     // block images
     const float *delta;
     int B, H, N, d, nblk, nrb, total_wg;
+    FastDiv div_inner, div_rows;  // work item number -> (batch, row block, head): by B / nb and nrb; single-launch forms: by H
     int nb;              // batch entries per workgroup (1 or 2)
     int wide;            // 0; 1 / 3: single-launch forms (8 / 4 waves); 2: 8-wave workgroups over row-block pairs (nrb counts pairs); 4: paired form, bias copied past the caches
     // single-launch short-sequence kernel: the bf16 inputs, whether mu is applied, optional mu exports

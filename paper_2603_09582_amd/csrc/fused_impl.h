@@ -35,6 +35,7 @@
 
 #include "attn_tiles.h"
 #include "bias_rows.h"
+#include "fast_div.h"
 #include "head_rows.h"
 #include "quant_v.h"
 
@@ -237,9 +238,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         int b, h, rb, bh;
         int valid;
     };
-    auto decode = [&](int v) -> Item {
+    // (What takes the arguments as `p`: the loop passes args(), the start of the kernel the arguments themselves, which are all
+    // fetched at once then.)
+    auto decode = [&](int v, auto &p) -> Item {
         Item t;
-        Args &p = args();
         const int nbp = p.B / NIMG, per_xcd = (p.total_wg + 7) >> 3, vmax = 8 * per_xcd;
         int u = (v & 7) * per_xcd + (v >> 3), row_block = 0;
         t.valid = v < vmax && u < p.total_wg;
@@ -251,16 +253,22 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             t.valid = u < p.total_wg;
         }
         const int uu = t.valid ? u : 0;
-        t.b = ONEHEAD ? uu / p.H : (uu % nbp) * NIMG + isel;
-        t.rb = ONEHEAD4 ? row_block : ONEHEAD ? bsel : ROWS2 ? 2 * ((uu / nbp) % p.nrb) + bsel : (uu / nbp) % p.nrb;
-        t.h = ONEHEAD ? uu % p.H : uu / (nbp * p.nrb);
+        const int q1 = fast_div(uu, p.div_inner.m, p.div_inner.s), q2 = ONEHEAD ? 0 : fast_div(q1, p.div_rows.m, p.div_rows.s);  // by H; by nbp, then by nrb
+        t.b = ONEHEAD ? q1 : (uu - q1 * nbp) * NIMG + isel;
+        t.rb = ONEHEAD4 ? row_block : ONEHEAD ? bsel : ROWS2 ? 2 * (q1 - q2 * p.nrb) + bsel : q1 - q2 * p.nrb;
+        t.h = ONEHEAD ? uu - q1 * p.H : q2;
         t.bh = t.b * p.H + t.h;
         t.valid = __builtin_amdgcn_readfirstlane(t.valid);
         return t;
     };
 
+    // (row-block pairs have no register left for more of them at once)
+    auto first_args = [&]() -> typename std::conditional<ROWS2, Args, const FusedParams>::type & {
+        if constexpr (ROWS2) return args();
+        else return p;
+    };
     int v = blockIdx.x;
-    Item cur = decode(v);
+    Item cur = decode(v, first_args());
     if (!cur.valid) return;  // uniform over the workgroup
 
     // ---- per-item state ---------------------------------------------------------
@@ -304,13 +312,12 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     unsigned pend_q[PQ];
     unsigned pend_q2[ONEHEAD4 ? PQ : 1];  // ONEHEAD4: this lane's row in the second row block
     float pend_muq = 1.0f, pend_muk = 1.0f;
-    auto fetch_item_regs = [&](const Item &t) {
+    auto fetch_item_regs = [&](const Item &t, auto &p) {
         if constexpr (ONEHEAD4) {  // made by the prologue
 #pragma unroll
             for (int w = 0; w < PQ; ++w) pend_q[w] = pend_q2[w];
             return;
         }
-        Args &p = args();
         const int qc = min(t.rb * BR + wave * ROWS_PER_WAVE + m, N - 1), W = (d + 31) / 32;
         const uint32_t *qw = p.q_bits + ((int64_t)t.bh * N + qc) * W;
 #pragma unroll
@@ -321,15 +328,22 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // The abs-means of an item from the partial sums of its key blocks: one pair per lane, at most PSI_MAX_BLOCKS, in
     // the tree over lanes i, i + 16, i + 8, i + 4, i + 2, i + 1 (the same bits on every run, and those of the tree in
     // v_quant_kernel); exported with the head's first row block.
-    auto item_mu = [&](const Item &t, const float *ps) {
-        Args &p = args();
+    struct MuParts {
         float s[2];
+    };
+    auto mu_parts = [&](const float *ps, auto &p) -> MuParts {
+        MuParts o;
         int ln = lane;  // (opaque: no address is kept for this in the block loop)
         asm volatile("" : "+v"(ln));
 #pragma unroll
+        for (int i = 0; i < 2; ++i) o.s[i] = ln < p.nblk ? ps[2 * ln + i] : 0.0f;
+        return o;
+    };
+    auto item_mu = [&](const Item &t, const MuParts &parts, auto &p) {
+        float s[2];
+#pragma unroll
         for (int i = 0; i < 2; ++i) {
-            s[i] = ln < p.nblk ? ps[2 * ln + i] : 0.0f;
-            s[i] = row_tree_sum(s[i]);
+            s[i] = row_tree_sum(parts.s[i]);
             s[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s[i]))) * p.inv_count;
         }
         if (t.rb == 0 && wave == 0 && lane == 0) {
@@ -340,15 +354,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         pend_muk = p.use_mu ? s[1] : 1.0f;
     };
     // bias pointers of an item (no memory access)
-    auto bias_row_ptr = [&](const Item &t) -> const char * {
-        Args &p = args();
+    auto bias_row_ptr = [&](const Item &t, auto &p) -> const char * {
         const int qc = min(t.rb * BR + wave * ROWS_PER_WAVE + m, N - 1);
         return static_cast<const char *>(p.bias) +
                ((int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)qc * p.bs.n) * bsb;
     };
-    auto bias_dma_src = [&](const Item &t) -> BiasSrc {
+    auto bias_dma_src = [&](const Item &t, auto &p) -> BiasSrc {
         BiasSrc o;
-        Args &p = args();
 #pragma unroll
         for (int j = 0; j < RGW; ++j) {
             const int rg = rg0 + j;
@@ -360,8 +372,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         return o;
     };
-    auto image_ptr = [&](const Item &t) -> const char * {
-        Args &p = args();
+    auto image_ptr = [&](const Item &t, auto &p) -> const char * {
         return uniform_ptr(p.img + (int64_t)t.bh * p.nblk * L::BYTES);
     };
     // ---- BIAS_TABLE / BIAS_TABLE_BLK: staging of table rows from row0 on -------------
@@ -378,8 +389,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         const int LX = 2 * p.Gx - 1, sh = p.gx_shift + 1;
         return (i >> sh) * LX + LX - 1 - (i & ((1 << sh) - 1));
     };
-    auto table_begin = [&](const Item &t) {
-        Args &p = args();
+    auto table_begin = [&](const Item &t, auto &p) {
         const int LX = 2 * p.Gx - 1, LY = 2 * p.Gy - 1;
         trsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(uniform_ptr(p.table + (int64_t)t.h * LY * LX)), 0, 4 * LY * LX, 0x00020000);
 #pragma unroll
@@ -414,9 +424,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     };
     // turn the fetched registers into the item's state
     // (same_head: the head's tables are in LDS already)
-    auto begin_item = [&](const Item &t, auto same_head) {
+    auto begin_item = [&](const Item &t, auto same_head, auto &p) {
         constexpr bool SAME_HEAD = decltype(same_head)::value;
-        Args &p = args();
         q = t.rb * BR + wave * ROWS_PER_WAVE + m;
         // Logit multiplier alpha of Eq. 6.  Its sign goes into the Q operand and a vanishing
         // alpha clears the Q operand, so that the loop can assume alpha > 0.
@@ -441,7 +450,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             __syncthreads();
         }
         if (LUT) hb_run = 0x7fffffff;
-        if (MODE == BIAS_F32_VEC || BIAS_LATE) brow = bias_row_ptr(t);
+        if (MODE == BIAS_F32_VEC || BIAS_LATE) brow = bias_row_ptr(t, p);
         if (AXIAL && !SAME_HEAD) {
             // every wave is past the previous item's last block (begin_item follows its closing
             // barrier), so the tables can be overwritten; a barrier publishes the new ones
@@ -493,7 +502,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         if (TABLE && !SAME_HEAD) {
             // (as above: the previous item's last block is behind every wave)
-            table_begin(t);
+            table_begin(t, p);
             table_load(0);
             table_store(tab, inv_alpha);
             __syncthreads();
@@ -729,7 +738,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         nxt.rb = 1;
         nxt.valid = p.nrb > 1 && (p.split_from == p.total_wg || v < p.split_from);
     } else if (PERSIST) {
-        nxt = decode(v + gridDim.x);
+        nxt = decode(v + gridDim.x, first_args());
     }
 
     // The block before which the accumulator's offset is next removed (see the loop).  A 4-wave item that
@@ -753,9 +762,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 
     // Copies of an item's small data, outside the block loop: delta_v of the item that starts (for its epilogue), and the partial
     // sums of the abs-means of the item after it (for item_mu).  Its first block's end waits for them.
-    auto copy_item_data = [&]() {
+    auto copy_item_data = [&](auto &p) {
         if (ONEHEAD || (ROWS2 ? wreg : wave) != 0) return;
-        Args &p = args();
         if (lane < DKP / 4) dma16(p.delta + (int64_t)cur.bh * DKP, 16 * lane, lds_offset(&sdelta[parity][isel][0]));
         if (PSUM && p.psum && nxt.valid && 2 * lane < p.nblk)
             dma16(p.psum + (int64_t)nxt.bh * p.nblk * 2, 16 * lane, lds_offset(&spsum[parity][0]));
@@ -773,10 +781,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             if (PERSIST) more = nxt.valid;
             nblkidx = 0;
             if (PERSIST && more) {
-                if (!ONEHEAD) imgs = image_ptr(nxt);
-                if (!FETCH_AFTER) fetch_item_regs(nxt);
-                if (LDS_BIAS && !BIAS_DB && !BIAS_LATE) bsrc = bias_dma_src(nxt);
-                if (BROW_AHEAD) brow = bias_row_ptr(nxt);
+                if (!ONEHEAD) imgs = image_ptr(nxt, args());
+                if (!FETCH_AFTER) fetch_item_regs(nxt, args());
+                if (LDS_BIAS && !BIAS_DB && !BIAS_LATE) bsrc = bias_dma_src(nxt, args());
+                if (BROW_AHEAD) brow = bias_row_ptr(nxt, args());
             }
         }
         if (!ONEHEAD && !ROWS2) asm volatile("" : "+s"(more));
@@ -787,11 +795,11 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             imgs += L::BYTES;
         }
         if (BIAS_LATE && more) {
-            bsrc = bias_dma_src(sw ? nxt : cur);
+            bsrc = bias_dma_src(sw ? nxt : cur, args());
 #pragma unroll
             for (int j = 0; j < RGW; ++j) bsrc.base[j] += nblkidx * (BV * ESZ);
         }
-        if (FETCH_AFTER && sw && more) fetch_item_regs(nxt);
+        if (FETCH_AFTER && sw && more) fetch_item_regs(nxt, args());
         int nklim = N;  // key limit of the shared bias tile's copies below
         const bool whole = nblkidx * BV + BV <= N;
         if (BIAS_DB && more && !whole) {
@@ -799,7 +807,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             if (nklim != N) bias_tail(cur, nblkidx, bnxt);
         }
         if (TBLK && more) {  // land during this block, stored at its end
-            if (sw) table_begin(nxt);
+            if (sw) table_begin(nxt, args());
             tblk_load(sw ? nxt.rb : cur.rb, nblkidx);
         }
 
@@ -1051,7 +1059,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         if (BIAS_LATE) {
             __builtin_amdgcn_sched_barrier(0);
-            if (more) load_bias_quarters(bias_row_ptr(sw ? nxt : cur), nblkidx);
+            if (more) load_bias_quarters(bias_row_ptr(sw ? nxt : cur, args()), nblkidx);
         }
         l_run = fmaf(l_run, resc, ls0 + ls1);
         rho = fmaf(rho, resc, 1.0f);
@@ -1104,11 +1112,11 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         cur = nxt;
         v += gridDim.x;
         if (ONEHEAD4) nxt.valid = false;  // (two row blocks)
-        else nxt = decode(v + gridDim.x);
-        if (PSUM && args().psum) item_mu(cur, &spsum[parity][0]);
+        else nxt = decode(v + gridDim.x, args());
+        if (PSUM && args().psum) item_mu(cur, mu_parts(&spsum[parity][0], args()), args());
         if (!ONEHEAD4) parity ^= 1;  // (the single-launch forms keep one copy of delta_v)
-        copy_item_data();
-        begin_item(cur, std::integral_constant<bool, ONEHEAD4>{});
+        copy_item_data(args());
+        begin_item(cur, std::integral_constant<bool, ONEHEAD4>{}, args());
         if (TBLK) {  // (the next item's first rows: divided by ITS alpha)
             table_store(tab + (tpar ^ 1) * 4 * TB_CP, inv_alpha);
             __syncthreads();
@@ -1141,10 +1149,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         // Every global load of the head goes out before the first one is used, oldest first in
         // the order of use: the bias tile, this lane's query chunks, the V rows, the key chunks.
         if (LDS_BIAS) {
-            bsrc = bias_dma_src(cur);
+            bsrc = bias_dma_src(cur, first_args());
             dma_bias(cur, bsrc, 0, lds_offset(bA));
         }
-        if (BROW_AHEAD) brow = bias_row_ptr(cur);
+        if (BROW_AHEAD) brow = bias_row_ptr(cur, first_args());
         if (MODE == BIAS_BF16_VEC) load_bias_vec(brow, 0);
         if (F32L && !BIAS_LATE) load_bias_quarters(brow, 0);
         // Row loads go through buffer descriptors that end with the tensor's last row: rows beyond N read as zeros (no effect on
@@ -1359,26 +1367,31 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             }
         }
     } else {
-        imgs = image_ptr(cur);
+        // Everything the first block needs is under way before the first of it is waited for: the kernel's arguments fetched at once, the
+        // item's number divided by products, the tiles not behind the abs-means (4.6 us from the start to the first block before,
+        // N = 1024, d = 72, 128 heads; attention stage, us, before / after: 64 heads, N = 128, d = 72 9.1 / 8.6, 512 heads 16.0 / 15.3, N = 1024, 128 heads 53.1 / 52.0).
+        MuParts parts = {};
+        if (!AXIAL && p.psum) parts = mu_parts(p.psum + (int64_t)cur.bh * p.nblk * 2, first_args());
+        fetch_item_regs(cur, first_args());
+        imgs = image_ptr(cur, first_args());
         dma_image<DK, NWI>(imgs, lds_offset(bufA) + isel * L::BYTES, ROWS2 ? wreg : wave, lane);
         imgs += L::BYTES;
         if (LDS_BIAS) {
-            bsrc = bias_dma_src(cur);
+            bsrc = bias_dma_src(cur, first_args());
             dma_bias(cur, bsrc, 0, lds_offset(bA));
         }
-        fetch_item_regs(cur);
-        if (!AXIAL && p.psum) item_mu(cur, p.psum + (int64_t)cur.bh * p.nblk * 2);
+        if (!AXIAL && p.psum) item_mu(cur, parts, first_args());
     }
-    begin_item(cur, std::false_type{});
+    begin_item(cur, std::false_type{}, first_args());
     if (BIAS_LATE) load_bias_quarters(brow, 0);
     if (!ONEHEAD) {
-        if (BROW_AHEAD) brow = bias_row_ptr(cur);
+        if (BROW_AHEAD) brow = bias_row_ptr(cur, first_args());
         if (MODE == BIAS_BF16_VEC) load_bias_vec(brow, 0);
         if (F32L) load_bias_quarters(brow, 0);
-        copy_item_data();
+        copy_item_data(first_args());
     }
     if (TBLK) {
-        table_begin(cur);
+        table_begin(cur, p);
         tblk_load(cur.rb, 0);
         table_store(tab, inv_alpha);
     }
