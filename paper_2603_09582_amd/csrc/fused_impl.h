@@ -100,12 +100,17 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 //
 // WIDE_WAVES3 is the ordinary 4-wave form compiled for three waves per SIMD (168 registers), three
 // workgroups per compute unit, in the variants of use_waves3.
-enum { WIDE_NONE = 0, WIDE_ONEHEAD = 1, WIDE_ROWS2 = 2, WIDE_ONEHEAD4 = 3, WIDE_PAIR_ONCE = 4, WIDE_WAVES3 = 5 };
+//
+// WIDE_SHORT and WIDE_SHORT4 are the single-launch forms for 128 < N <= 224, whose second key block ends at least 32 keys early:
+// the 32-key tiles behind N are left out of it, and waves whose rows all lie there out of the second row block.  (us, without / with: N = 197, d = 64 3 heads 12.14 / 11.70, 512 heads 25.2 / 24.2, 768 heads
+// 38.1 / 36.3, N = 129 35.4 / 30.5; the branches cost calls whose last tile holds a key 1.2-1.5 %, so those keep the forms without.)
+enum { WIDE_NONE = 0, WIDE_ONEHEAD = 1, WIDE_ROWS2 = 2, WIDE_ONEHEAD4 = 3, WIDE_PAIR_ONCE = 4, WIDE_WAVES3 = 5, WIDE_SHORT = 6, WIDE_SHORT4 = 7 };
 template <int DK, int MODE, int NB, int WIDE = WIDE_NONE>
 __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) void fused_kernel(const FusedParams p) {
     using L = Image<DK>;
-    constexpr bool ONEHEAD4 = WIDE == WIDE_ONEHEAD4;
-    constexpr bool ONEHEAD = WIDE == WIDE_ONEHEAD || ONEHEAD4, ROWS2 = WIDE == WIDE_ROWS2;
+    constexpr bool SHORT = WIDE == WIDE_SHORT || WIDE == WIDE_SHORT4;
+    constexpr bool ONEHEAD4 = WIDE == WIDE_ONEHEAD4 || WIDE == WIDE_SHORT4;
+    constexpr bool ONEHEAD = WIDE == WIDE_ONEHEAD || SHORT || ONEHEAD4, ROWS2 = WIDE == WIDE_ROWS2;
     constexpr bool WAVES3 = WIDE == WIDE_WAVES3;
     static_assert(WIDE == WIDE_NONE || ONEHEAD4 || WAVES3 || NB == 2, "the wide forms use 8 waves");
     static_assert(!ONEHEAD4 || NB == 1, "the 4-wave single-launch form");
@@ -725,7 +730,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     int it = 0;        // key block inside the current item
     // 8-wave single launch (up to 128 tokens leave half of its waves without rows): a wave whose 32 rows all lie beyond N
     // only copies.  12 heads, N = 125 11.0 -> 10.4 us; the branch around the block costs the other forms 1-3 %.
-    const bool live = WIDE != WIDE_ONEHEAD || cur.rb * BR + wave * ROWS_PER_WAVE < N;
+    const bool live = !(ONEHEAD && NB == 2) || cur.rb * BR + wave * ROWS_PER_WAVE < N;
     // (Flags of the loop are integers in scalar registers that the compiler cannot look into: it makes lane masks out of them
     // otherwise, five to ten instructions per block for each.)
     int younger_flag = WAVES3 && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
@@ -821,7 +826,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             if (!tpar) __builtin_amdgcn_s_setprio(0);
             else if (younger) __builtin_amdgcn_s_setprio(1);
         }
-        if (live) {
+        // WIDE_SHORT: tile t of the second block holds no key (its weights are 0, code -128)
+        auto dead_tile = [&](int t) -> bool { return SHORT && tpar == 1 && t > 0 && BV + 32 * t >= N; };
+        if ((live && (WIDE != WIDE_SHORT4 || cur.rb * BR + wave * ROWS_PER_WAVE < N))) {
         // 1. all LDS reads of the logit phase go out together: bias tile, key rows
         if (LDS_BIAS) {
             if (BADDR_LATE) {
@@ -906,7 +913,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 wt[t] = 0.0f;
-                T[t] = qk_mfma<DK2>(ka[t], qB, bias_tile(it, t));
+                if (!dead_tile(t)) T[t] = qk_mfma<DK2>(ka[t], qB, bias_tile(it, t));
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -948,7 +955,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 const int left = N - it * BV - 32 * t;
-                if (left >= 32) continue;  // uniform
+                if (left >= 32 || dead_tile(t)) continue;  // uniform
                 const int lim = left - 16 * g;
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
@@ -1006,8 +1013,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         } else {
 #pragma unroll
             for (int t = 0; t < KT; ++t)
+                if (!dead_tile(t))
 #pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, T[t][r]);
+                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, T[t][r]);
         }
         const float m_new = pair_max(mx);
         const float m_use = (MODE != BIAS_NONE && m_new == -INFINITY) ? 0.0f : m_new;  // whole row masked so far
@@ -1019,6 +1027,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
             if (t == 0) __builtin_amdgcn_sched_barrier(0);
+            if (dead_tile(t)) {
+                pk[t] = v4i{(int)0x80808080u, (int)0x80808080u, (int)0x80808080u, (int)0x80808080u};
+                continue;
+            }
             if constexpr (VDEMAND) {
 #pragma unroll
                 for (int cb = 0; cb < PRE; ++cb)
@@ -1535,15 +1547,25 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
     return check_launch();
 }
 
+// WIDE_SHORT and WIDE_SHORT4: the biases that come with token counts like 197
+constexpr bool short_built(int mode) { return mode == BIAS_NONE || mode == BIAS_BF16_LDS || mode == BIAS_F32_LDS; }
+
 template <int DK>
 int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
     const int needed = ((p.total_wg + 7) / 8) * 8;
+    const bool ends_early = p.N > BV && p.N <= 2 * BV - 32;
     if (p.nb == 1) {  // 4-wave form: the variants onehead4_built() names
         // (eight half heads of a row block each, then those heads' other halves, and so on: both on one XCD)
         const dim3 grid((unsigned)(p.split_from < p.total_wg ? p.split_from + (p.total_wg - p.split_from + 7) / 8 * 16 : needed)), block(FUSED_THREADS);
 #define CASE(M)                                                                                          \
     case M:                                                                                              \
         if constexpr (onehead4_built(DK, M)) {                                                           \
+            if constexpr (short_built(M)) {                                                              \
+                if (ends_early) {                                                                        \
+                    hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_SHORT4>), grid, block, 0, stream, p); \
+                    return check_launch();                                                               \
+                }                                                                                        \
+            }                                                                                            \
             hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_ONEHEAD4>), grid, block, 0, stream, p);     \
             return check_launch();                                                                       \
         }                                                                                                \
@@ -1557,7 +1579,16 @@ int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
     }
     const dim3 grid((unsigned)needed), block(FUSED_THREADS * 2);
     switch (mode) {
-#define CASE(M) case M: hipLaunchKernelGGL((fused_kernel<DK, M, 2, WIDE_ONEHEAD>), grid, block, 0, stream, p); break;
+#define CASE(M)                                                                                          \
+    case M:                                                                                              \
+        if constexpr (short_built(M)) {                                                                  \
+            if (ends_early) {                                                                            \
+                hipLaunchKernelGGL((fused_kernel<DK, M, 2, WIDE_SHORT>), grid, block, 0, stream, p);     \
+                break;                                                                                   \
+            }                                                                                            \
+        }                                                                                                \
+        hipLaunchKernelGGL((fused_kernel<DK, M, 2, WIDE_ONEHEAD>), grid, block, 0, stream, p);           \
+        break;
         CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE)
         CASE(BIAS_BF16_LDS) CASE(BIAS_F32_LDS)
 #undef CASE

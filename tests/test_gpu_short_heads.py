@@ -1,0 +1,31 @@
+"""The single launch where the second key block ends early (128 < N <= 224): 32-key tiles and waves without keys and rows are left
+out there.  Against the launches over a workspace, which leave nothing out."""
+import pytest
+import torch
+
+from paper_2603_09582_amd import binding as ba
+
+pytestmark = pytest.mark.gpu
+
+
+# both sides of every tile's edge; two heads take 8 waves each, 260 four (d <= 96)
+@pytest.mark.parametrize("N", [129, 160, 161, 192, 193, 224, 225])
+@pytest.mark.parametrize("heads,d", [(2, 32), (2, 64), (2, 72), (2, 128), (260, 32), (260, 64), (260, 96)])
+@pytest.mark.parametrize("bias", ["none", "bf16", "fp32", "masked"])
+def test_single_launch_with_an_early_end(N, heads, d, bias):
+    g = torch.Generator(device="cuda").manual_seed(N * 7 + heads + d)
+    q, k, v = (torch.randn(heads // 2, 2, N, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    b = None
+    if bias != "none":
+        b = torch.randn(2, N, N, generator=g, device="cuda").to(torch.float32 if bias == "fp32" else torch.bfloat16)
+    if bias == "masked":  # rows that see the second block alone, and rows that do not see it
+        b[:, : N // 2, :128] = float("-inf")
+        b[:, N // 2:, 128:] = float("-inf")
+    scale = d ** -0.5
+    got = ba.forward_fused(q, k, v, b, scale).float()
+    qb, kb, mq, mk = ba.pack_qk(q, k)
+    ref = ba.forward(qb, kb, mq, mk, v, b, scale).float()
+    # the abs-means differ in their last bits, so codes of P fall to the other side of a half-integer: an output moves by up to max |v| / 255
+    # per code (under 6 / 255, and where one key carries a row there is one such code), plus 2^-8 of bf16 on either side
+    assert torch.isfinite(got).all()
+    assert ((got - ref).abs() <= 2.4e-2 + 2e-2 * ref.abs()).all()
