@@ -278,7 +278,8 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         // More heads than compute units: 4-wave workgroups, two per compute unit, each taking
         // the head's two row blocks in turn; otherwise one 8-wave workgroup per head.
         const bool four = B * H > ONEHEAD4_MIN_HEADS && onehead4_built(s.DK, mode) && !(flags & BINATTN_FLAG_WIDE8);
-        p.wide = four ? 3 : 1;
+        const bool three = four && onehead_three(s.DK, mode, N, B * H);
+        p.wide = three ? 8 : four ? 3 : 1;
         // (which order the 4-wave form adds the abs-means in: the relative-position table and bf16 rows that
         // are not whole 16-byte chunks take the 8-wave form's at 64 < d <= 96)
         p.split_sums = s.DK == 3 && (mode == BIAS_TABLE || (mode == BIAS_BF16_LDS && !chunk_rows)) ? 1 : 0;
@@ -290,7 +291,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         // (An output on the storage of an input: one workgroup reads all of a head before it writes.  Two could not know.)
         const bool shared = spans_meet(out, os, raw->q, raw->qs, s) || spans_meet(out, os, raw->k, raw->ks, s) ||
                             spans_meet(out, os, raw->v, raw->vs, s);
-        p.split_from = shared ? B * H : onehead4_split_from(B * H, p.nrb);
+        p.split_from = shared ? B * H : three ? onehead_three_split_from(B * H, p.nrb) : onehead4_split_from(B * H, p.nrb);
         switch (s.DK) {
             case 1: return launch_onehead_dk<1>(p, mode, st);
             case 2: return launch_onehead_dk<2>(p, mode, st);

@@ -159,12 +159,12 @@ __device__ __forceinline__ void dma_image(const char *__restrict__ gsrc, unsigne
         dma_run<REST>(gsrc + c * 1024, lane * 16, ldst + c * 1024);
 }
 
-// The bias tile of a wave for one whole key block: row groups j = 0 .. 3, SEGS segments of 128 bytes per row; lane offset
+// The staged part of a wave's bias tile for one whole key block: row groups j = 0 .. 3, SEGS segments of 128 bytes per row; lane offset
 // voff[j] from base[j], each copy to its own KiB of the region, in the order of the region.  (m0 carries minus the
 // instruction's offset, which moves both addresses.)
 template <int SEGS>
 __device__ __forceinline__ void dma_tile(const char *const (&base)[4], const unsigned (&voff)[4], unsigned lds_base) {
-    static_assert(SEGS == 2 || SEGS == 3, "two or three segments per row");
+    static_assert(SEGS >= 1 && SEGS <= 3, "one to three segments per row");
     const uint64_t b0 = reinterpret_cast<uint64_t>(base[0]), b1 = reinterpret_cast<uint64_t>(base[1]);
     const uint64_t b2 = reinterpret_cast<uint64_t>(base[2]), b3 = reinterpret_cast<uint64_t>(base[3]);
     const unsigned l = __builtin_amdgcn_readfirstlane(lds_base);
@@ -172,7 +172,12 @@ __device__ __forceinline__ void dma_tile(const char *const (&base)[4], const uns
 #define STEP(n) "s_add_u32 m0, m0, " #n "\n\ts_nop 0\n\t"
 #define ROWS2(v, s) COPY(v, s, 0) STEP(0x380) COPY(v, s, 128)
 #define ROWS3(v, s) COPY(v, s, 0) STEP(0x380) COPY(v, s, 128) STEP(0x380) COPY(v, s, 256)
-    if constexpr (SEGS == 2)
+    if constexpr (SEGS == 1)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
+                     COPY("%1", "%5", 0) STEP(0x400) COPY("%2", "%6", 0) STEP(0x400) COPY("%3", "%7", 0) STEP(0x400) COPY("%4", "%8", 0)
+                     : : "s"(l), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(b0), "s"(b1), "s"(b2), "s"(b3)
+                     : "memory", "m0", "scc");
+    else if constexpr (SEGS == 2)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\t"
                      ROWS2("%1", "%5") STEP(0x480) ROWS2("%2", "%6") STEP(0x480) ROWS2("%3", "%7") STEP(0x480) ROWS2("%4", "%8")
                      : : "s"(l), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(b0), "s"(b1), "s"(b2), "s"(b3)

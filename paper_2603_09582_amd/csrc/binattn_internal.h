@@ -211,7 +211,7 @@ struct FusedParams {
     int B, H, N, d, nblk, nrb, total_wg;
     FastDiv div_inner, div_rows;  // work item number -> (batch, row block, head): by B / nb and nrb; single-launch forms: by H
     int nb;              // batch entries per workgroup (1 or 2)
-    int wide;            // 0; 1 / 3: single-launch forms (8 / 4 waves); 2: 8-wave workgroups over row-block pairs (nrb counts pairs); 4: paired form, bias copied past the caches
+    int wide;            // 0; 1 / 3 / 8: single-launch forms (8 waves / 4 / 4, three per compute unit); 2: 8-wave workgroups over row-block pairs (nrb counts pairs); 4: paired form, bias copied past the caches
     // single-launch short-sequence kernel: the bf16 inputs, whether mu is applied, optional mu exports
     const uint16_t *xq, *xk, *xv;
     Strides3 xqs, xks, xvs;
@@ -241,6 +241,27 @@ constexpr int ONEHEAD4_MIN_HEADS = 256;
 constexpr int onehead4_split_from(int heads, int row_blocks) {
     const int left = heads % 512;
     return row_blocks == 2 && heads > 512 && left > 0 && left <= 128 ? heads - left : heads;
+}
+// Three 4-wave workgroups per compute unit instead of two (32 < d <= 64).  Without a bias they are at least as fast everywhere (us,
+// two / three: N = 197 400 heads 19.8 / 19.7, 768 31.6 / 28.1, 1536 54.5 / 48.4, N = 256 1024 42.5 / 38.3, N = 100 768 18.6 / 15.8) and the only form.  With bf16
+// tiles a head takes longer and what counts is how full the last round of 768 is (N = 197 512 heads 24.5 / 26.4, 768 36.6 / 33.3, 896
+// 42.5 / 40.4, 960 43.8 / 46.0, 1152 52.2 / 54.3, 1280 56.6 / 55.2, 1536 67.1 / 64.8, 1664 72.5 / 67.8); N <= 128 and N > 224 spill there, and fp32 tiles do
+// not fit.
+constexpr bool onehead_three_only(int DK, int mode) { return DK == 2 && mode == BIAS_NONE; }
+constexpr bool onehead_three(int DK, int mode, int N, int heads) {
+    if (onehead_three_only(DK, mode)) return true;
+    const int left = heads % 768;
+    return DK == 2 && mode == BIAS_BF16_LDS && N > BV && N <= 2 * BV - 32 && heads > 512 && (left <= 128 || left >= 512);
+}
+// Heads from which on they take a workgroup per row block: as many as fill a first round of 768, a last round of at most 128 heads,
+// and as many as fill a last one that is three quarters full.  (us, whole heads / split, bf16, N = 197: 520 heads 31.8 / 27.2, 640 32.2 / 28.1, 704 32.5 / 32.4,
+// 832 43.6 / 38.2, 1400 62.7 / 58.0, but 1280 55.2 / 55.8, 2048 81.6 / 83.2, without a bias 1024 35.4 / 35.4.)  A multiple of 8.
+constexpr int onehead_three_split_from(int heads, int row_blocks) {
+    const int left = heads % 768;
+    int halves = 0;
+    if (heads > 512 && heads < 768) halves = 768 - heads;
+    if (heads > 768) halves = left <= 128 ? left : left >= 576 ? 768 - left : 0;
+    return row_blocks == 2 && halves > 0 ? (heads - halves) / 8 * 8 : heads;
 }
 // ... in the variants whose 256-thread prologue holds a head's loads in registers without spilling
 constexpr bool onehead4_built(int DK, int mode) {

@@ -101,15 +101,20 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 // WIDE_WAVES3 is the ordinary 4-wave form compiled for three waves per SIMD (168 registers), three
 // workgroups per compute unit, in the variants of use_waves3.
 //
+// WIDE_TRI4 and WIDE_TRISHORT4 are ONEHEAD4 (the latter with what WIDE_SHORT4 leaves out) for three workgroups per compute unit:
+// 168 registers, 53 KB of LDS.  Of a bf16 tile half the keys are staged, the others loaded into registers a block ahead; V rows are
+// read behind the exponentials, the second row's words kept in LDS.  Chosen by onehead_three.
+//
 // WIDE_SHORT and WIDE_SHORT4 are the single-launch forms for 128 < N <= 224, whose second key block ends at least 32 keys early:
 // the 32-key tiles behind N are left out of it, and waves whose rows all lie there out of the second row block.  (us, without / with: N = 197, d = 64 3 heads 12.14 / 11.70, 512 heads 25.2 / 24.2, 768 heads
 // 38.1 / 36.3, N = 129 35.4 / 30.5; the branches cost calls whose last tile holds a key 1.2-1.5 %, so those keep the forms without.)
-enum { WIDE_NONE = 0, WIDE_ONEHEAD = 1, WIDE_ROWS2 = 2, WIDE_ONEHEAD4 = 3, WIDE_PAIR_ONCE = 4, WIDE_WAVES3 = 5, WIDE_SHORT = 6, WIDE_SHORT4 = 7 };
+enum { WIDE_NONE = 0, WIDE_ONEHEAD = 1, WIDE_ROWS2 = 2, WIDE_ONEHEAD4 = 3, WIDE_PAIR_ONCE = 4, WIDE_WAVES3 = 5, WIDE_SHORT = 6, WIDE_SHORT4 = 7, WIDE_TRI4 = 8, WIDE_TRISHORT4 = 9 };
 template <int DK, int MODE, int NB, int WIDE = WIDE_NONE>
-__global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) void fused_kernel(const FusedParams p) {
+__global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 || WIDE >= WIDE_TRI4 ? 3 : 2)) void fused_kernel(const FusedParams p) {
     using L = Image<DK>;
-    constexpr bool SHORT = WIDE == WIDE_SHORT || WIDE == WIDE_SHORT4;
-    constexpr bool ONEHEAD4 = WIDE == WIDE_ONEHEAD4 || WIDE == WIDE_SHORT4;
+    constexpr bool TRI = WIDE == WIDE_TRI4 || WIDE == WIDE_TRISHORT4;
+    constexpr bool SHORT = WIDE == WIDE_SHORT || WIDE == WIDE_SHORT4 || WIDE == WIDE_TRISHORT4;
+    constexpr bool ONEHEAD4 = WIDE == WIDE_ONEHEAD4 || WIDE == WIDE_SHORT4 || TRI;
     constexpr bool ONEHEAD = WIDE == WIDE_ONEHEAD || SHORT || ONEHEAD4, ROWS2 = WIDE == WIDE_ROWS2;
     constexpr bool WAVES3 = WIDE == WIDE_WAVES3;
     static_assert(WIDE == WIDE_NONE || ONEHEAD4 || WAVES3 || NB == 2, "the wide forms use 8 waves");
@@ -131,7 +136,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // (two segments); an fp32 tile would be 16 KiB per wave, so its first SEGS 32-key quarters (one per
     // QK tile) are staged and the others go straight into registers, one block ahead: three
     // quarters where two 4-wave workgroups (or one of 8 waves) fit a compute unit's LDS that way.
-    constexpr int SEGS = !F32L ? 2 : (NB == 1 && DK == 3) ? 2 : 3;
+    constexpr int SEGS = TRI ? 1 : !F32L ? 2 : (NB == 1 && DK == 3) ? 2 : 3;
     constexpr int ESZ = F32L ? 4 : 2, KSEG = 128 / ESZ, EC = 16 / ESZ;  // element size, keys per segment / 16-byte chunk
     constexpr int REGION = SEGS * 4096;  // bytes of a wave's 32-row tile
     static_assert(!F32L || !PAIR, "fp32 tiles are private");
@@ -143,7 +148,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // V operand rows of this many channel blocks are fetched from LDS before the
     // exponential phase (the rest just before their MFMAs): hides the LDS latency
     // where the register budget allows it.
-    constexpr int PRE = (DK == 2 && WAVES3) ? (PV_EARLY ? 1 : 0) : DK <= 2 ? DK : ((DK == 4 && MODE == BIAS_TABLE_BLK) || MODE == BIAS_F32_LDS) ? 0 : 1;
+    constexpr int PRE = TRI ? 0 : (DK == 2 && WAVES3) ? (PV_EARLY ? 1 : 0) : DK <= 2 ? DK : ((DK == 4 && MODE == BIAS_TABLE_BLK) || MODE == BIAS_F32_LDS) ? 0 : 1;
     // ... and at three waves per SIMD each tile's V rows are read under its own exponentials (the
     // registers do not hold them all).
     constexpr bool VDEMAND = PV_EARLY && WAVES3;
@@ -285,7 +290,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // (24 bytes per lane were spilled), behind them, and the bias addresses are formed in every block
     constexpr bool BIAS_LATE = F32L && ONEHEAD4 && DK == 3;
     const char *brow = nullptr;  // this lane's bias row (register modes)
-    constexpr bool BROW_AHEAD = MODE == BIAS_BF16_VEC || (F32L && !BIAS_LATE);  // ... that of the block loaded next
+    constexpr bool HI_REGS = TRI && BF16L;  // the second half of a bf16 tile goes straight into registers
+    constexpr bool BROW_AHEAD = MODE == BIAS_BF16_VEC || HI_REGS || (F32L && !BIAS_LATE);  // ... that of the block loaded next
     // Dense tiles are fetched with full-cache-line requests (8 lanes cover the 128 bytes of one row
     // segment) straight into LDS; which lane fetches what and where it lands: bias_rows.h.
     // A wave copies RGW of the four 8-row groups of its 32-row tile: all four when the
@@ -315,12 +321,13 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     // (sign words; in the single-launch forms the FP4 operand words themselves)
     constexpr int PQ = ONEHEAD ? 4 * DK2 : 2 * DK2;
     unsigned pend_q[PQ];
+    __shared__ __attribute__((aligned(16))) unsigned row2_words[TRI ? FUSED_THREADS : 1][TRI ? PQ : 1];  // (three waves per SIMD keep them in LDS)
     unsigned pend_q2[ONEHEAD4 ? PQ : 1];  // ONEHEAD4: this lane's row in the second row block
     float pend_muq = 1.0f, pend_muk = 1.0f;
     auto fetch_item_regs = [&](const Item &t, auto &p) {
         if constexpr (ONEHEAD4) {  // made by the prologue
 #pragma unroll
-            for (int w = 0; w < PQ; ++w) pend_q[w] = pend_q2[w];
+            for (int w = 0; w < PQ; ++w) pend_q[w] = TRI ? row2_words[TRI ? threadIdx.x : 0][w] : pend_q2[w];
             return;
         }
         const int qc = min(t.rb * BR + wave * ROWS_PER_WAVE + m, N - 1), W = (d + 31) / 32;
@@ -360,20 +367,24 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     };
     // bias pointers of an item (no memory access)
     auto bias_row_ptr = [&](const Item &t, auto &p) -> const char * {
-        const int qc = min(t.rb * BR + wave * ROWS_PER_WAVE + m, N - 1);
+        int ln = lane;
+        if (TRI) asm volatile("" : "+v"(ln));  // (opaque: the second row block's addresses are formed where it starts)
+        const int qc = min(t.rb * BR + wave * ROWS_PER_WAVE + (ln & 31), N - 1);
         return static_cast<const char *>(p.bias) +
                ((int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)qc * p.bs.n) * bsb;
     };
     auto bias_dma_src = [&](const Item &t, auto &p) -> BiasSrc {
         BiasSrc o;
+        int ln = lane;
+        if (TRI) asm volatile("" : "+v"(ln));
 #pragma unroll
         for (int j = 0; j < RGW; ++j) {
             const int rg = rg0 + j;
             const int row0 = bias_group_row(t.rb * BR + wave * ROWS_PER_WAVE, rg, N);  // uniform
-            const int row = bias_copy_row(row0, rg, lane, N);
+            const int row = bias_copy_row(row0, rg, ln, N);
             o.base[j] = uniform_ptr(static_cast<const char *>(p.bias) +
                                     ((int64_t)t.b * p.bs.b + (int64_t)t.h * p.bs.h + (int64_t)row0 * p.bs.n) * ESZ);
-            o.voff[j] = (unsigned)(row - row0) * (unsigned)p.bs.n * (unsigned)ESZ + 16u * dma_c[j];
+            o.voff[j] = (unsigned)(row - row0) * (unsigned)p.bs.n * (unsigned)ESZ + 16u * (TRI ? bias_copy_chunk(rg, ln) : dma_c[j]);
         }
         return o;
     };
@@ -561,7 +572,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     };
     auto dma_bias_one = [&](const BiasSrc &src, int blk, int klim, unsigned region, int idx) {  // copy idx = SEGS j + segment
         const int j = idx / SEGS, seg = idx % SEGS;
-        const int key0 = blk * BV + KSEG * seg + EC * dma_c[j];
+        int ln = lane;
+        if (TRI) asm volatile("" : "+v"(ln));
+        const int key0 = blk * BV + KSEG * seg + EC * (TRI ? bias_copy_chunk(rg0 + j, ln) : dma_c[j]);
         if (key0 < klim)
             dma16<WIDE == WIDE_PAIR_ONCE>(src.base[j] + 128 * seg, src.voff[j], region + ((rg0 + j) * SEGS + seg) * 1024);
     };
@@ -629,6 +642,26 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                     braw[i] = u4v{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16),
                                   e[6] | (e[7] << 16)};
                 }
+            }
+        }
+    };
+    // HI_REGS: this lane's values of keys 64 .. 127 of a block.  Chunks may read on behind a row's end, but not behind the tensor's.
+    auto load_bias_hi = [&](const char *row, int blk) {
+        const uint16_t *src = reinterpret_cast<const uint16_t *>(row) + blk * BV + 16 * g;
+        const uint16_t *end = static_cast<const uint16_t *>(p.bias) + p.bias_end;
+#pragma unroll
+        for (int i = 4; i < 8; ++i) {
+            if (blk * BV + 32 * (i >> 1) >= N) continue;  // (uniform)
+            const int o = 32 * (i >> 1) + 8 * (i & 1);
+            if (src + o + 8 <= end) {
+                braw[i] = *reinterpret_cast<const u4v_a2 *>(src + o);
+            } else {
+                const uint16_t *s2 = src + o;
+                asm volatile("" : "+v"(s2));  // (opaque: nothing of this rare way is kept in registers)
+                unsigned e[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) e[j] = s2 + j < end ? s2[j] : 0u;
+                braw[i] = u4v{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
             }
         }
     };
@@ -733,7 +766,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
     const bool live = !(ONEHEAD && NB == 2) || cur.rb * BR + wave * ROWS_PER_WAVE < N;
     // (Flags of the loop are integers in scalar registers that the compiler cannot look into: it makes lane masks out of them
     // otherwise, five to ten instructions per block for each.)
-    int younger_flag = WAVES3 && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
+    int younger_flag = (WAVES3 || TRI) && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
     int younger = __builtin_amdgcn_readfirstlane(younger_flag);
     if (NB == 1) asm volatile("" : "+s"(younger));
     int parity = 0;    // items alternate between the two delta_v copies
@@ -828,7 +861,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         // WIDE_SHORT: tile t of the second block holds no key (its weights are 0, code -128)
         auto dead_tile = [&](int t) -> bool { return SHORT && tpar == 1 && t > 0 && BV + 32 * t >= N; };
-        if ((live && (WIDE != WIDE_SHORT4 || cur.rb * BR + wave * ROWS_PER_WAVE < N))) {
+        if ((live && (!(SHORT && ONEHEAD4) || cur.rb * BR + wave * ROWS_PER_WAVE < N))) {
         // 1. all LDS reads of the logit phase go out together: bias tile, key rows
         if (LDS_BIAS) {
             if (BADDR_LATE) {
@@ -844,7 +877,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
                         fraw[t][i] = *reinterpret_cast<const __attribute__((address_space(3))) f4v *>((size_t)(baddr[i] + 1024u * t));
             } else {
 #pragma unroll
-                for (int i = 0; i < 8; ++i)  // chunk 2 gg + 4 (t & 1) + i % 2 of the 64-key half t / 2, t = i / 2
+                for (int i = 0; i < (HI_REGS ? 4 : 8); ++i)  // chunk 2 gg + 4 (t & 1) + i % 2 of the 64-key half t / 2, t = i / 2
                     braw[i] = *reinterpret_cast<const __attribute__((address_space(3))) u4v *>((size_t)(baddr[2 * ((i >> 1) & 1) + (i & 1)] + bcur + 1024u * (i >> 2)));
             }
         }
@@ -918,6 +951,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
         }
         __builtin_amdgcn_sched_barrier(0);
         if (F32L && !BIAS_LATE && more) load_bias_quarters(brow, nblkidx);
+        if (HI_REGS && more) load_bias_hi(brow, nblkidx);  // (braw is free again)
         if (MODE == BIAS_BF16_VEC && more)  // braw is free again
             load_bias_vec(brow, nblkidx);
         if (LDS_BIAS && !BIAS_DB && more) {
@@ -1165,6 +1199,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             dma_bias(cur, bsrc, 0, lds_offset(bA));
         }
         if (BROW_AHEAD) brow = bias_row_ptr(cur, first_args());
+        if (HI_REGS) load_bias_hi(brow, 0);
         if (MODE == BIAS_BF16_VEC) load_bias_vec(brow, 0);
         if (F32L && !BIAS_LATE) load_bias_quarters(brow, 0);
         // Row loads go through buffer descriptors that end with the tensor's last row: rows beyond N read as zeros (no effect on
@@ -1309,6 +1344,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 ? 3 : 2)) 
             if (cur.rb == 1) {  // (uniform)
 #pragma unroll
                 for (int i = 0; i < PQ; ++i) pend_q[i] = pend_q2[i];
+            }
+            if (TRI) {
+#pragma unroll
+                for (int i = 0; i < PQ; ++i) row2_words[threadIdx.x][i] = pend_q2[i];
             }
         }
         // V: absmax per channel through LDS integer maxima
@@ -1559,7 +1598,17 @@ int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
         const dim3 grid((unsigned)(p.split_from < p.total_wg ? p.split_from + (p.total_wg - p.split_from + 7) / 8 * 16 : needed)), block(FUSED_THREADS);
 #define CASE(M)                                                                                          \
     case M:                                                                                              \
-        if constexpr (onehead4_built(DK, M)) {                                                           \
+        if constexpr (onehead_three_only(DK, M)) {                                                       \
+            if (ends_early) hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_TRISHORT4>), grid, block, 0, stream, p); \
+            else hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_TRI4>), grid, block, 0, stream, p);     \
+            return check_launch();                                                                       \
+        } else if constexpr (onehead4_built(DK, M)) {                                                    \
+            if constexpr (DK == 2 && M == BIAS_BF16_LDS) {                                               \
+                if (p.wide == WIDE_TRI4) {                                                               \
+                    hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_TRISHORT4>), grid, block, 0, stream, p); \
+                    return check_launch();                                                               \
+                }                                                                                        \
+            }                                                                                            \
             if constexpr (short_built(M)) {                                                              \
                 if (ends_early) {                                                                        \
                     hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_SHORT4>), grid, block, 0, stream, p); \

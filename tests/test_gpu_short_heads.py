@@ -8,9 +8,10 @@ from paper_2603_09582_amd import binding as ba
 pytestmark = pytest.mark.gpu
 
 
-# both sides of every tile's edge; two heads take 8 waves each, 260 four (d <= 96)
-@pytest.mark.parametrize("N", [129, 160, 161, 192, 193, 224, 225])
-@pytest.mark.parametrize("heads,d", [(2, 32), (2, 64), (2, 72), (2, 128), (260, 32), (260, 64), (260, 96)])
+# both sides of every tile's edge; two heads take 8 waves each, 260 four (d <= 96); 520 heads, d = 64, three workgroups per compute unit with
+# the last heads split by row blocks, 768 whole ones
+@pytest.mark.parametrize("N", [100, 129, 160, 161, 192, 193, 224, 225, 256])
+@pytest.mark.parametrize("heads,d", [(2, 32), (2, 64), (2, 72), (2, 128), (260, 32), (260, 64), (260, 96), (520, 64), (768, 64)])
 @pytest.mark.parametrize("bias", ["none", "bf16", "fp32", "masked"])
 def test_single_launch_with_an_early_end(N, heads, d, bias):
     g = torch.Generator(device="cuda").manual_seed(N * 7 + heads + d)
@@ -19,8 +20,9 @@ def test_single_launch_with_an_early_end(N, heads, d, bias):
     if bias != "none":
         b = torch.randn(2, N, N, generator=g, device="cuda").to(torch.float32 if bias == "fp32" else torch.bfloat16)
     if bias == "masked":  # rows that see the second block alone, and rows that do not see it
-        b[:, : N // 2, :128] = float("-inf")
-        b[:, N // 2:, 128:] = float("-inf")
+        edge = 128 if N > 128 else 64
+        b[:, : N // 2, :edge] = float("-inf")
+        b[:, N // 2:, edge:] = float("-inf")
     scale = d ** -0.5
     got = ba.forward_fused(q, k, v, b, scale).float()
     qb, kb, mq, mk = ba.pack_qk(q, k)
