@@ -291,7 +291,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         // (An output on the storage of an input: one workgroup reads all of a head before it writes.  Two could not know.)
         const bool shared = spans_meet(out, os, raw->q, raw->qs, s) || spans_meet(out, os, raw->k, raw->ks, s) ||
                             spans_meet(out, os, raw->v, raw->vs, s);
-        p.split_from = shared ? B * H : three ? onehead_three_split_from(B * H, p.nrb) : onehead4_split_from(B * H, p.nrb);
+        p.split_from = shared ? B * H : onehead_split_from(s.DK, mode, three, B * H, p.nrb);
         switch (s.DK) {
             case 1: return launch_onehead_dk<1>(p, mode, st);
             case 2: return launch_onehead_dk<2>(p, mode, st);

@@ -263,6 +263,14 @@ constexpr int onehead_three_split_from(int heads, int row_blocks) {
     if (heads > 768) halves = left <= 128 ? left : left >= 576 ? 768 - left : 0;
     return row_blocks == 2 && halves > 0 ? (heads - halves) / 8 * 8 : heads;
 }
+// Up to 32 channels three fit as well, without a bias and with bf16 tiles.  Where the rule above splits none, the one for rounds of 512
+// may: it leaves the last round shorter by 128 heads (d = 32, N = 200, bf16, rounds of 512 only / both: 576 heads 20.1 / 19.7, 832 29.9 / 26.7,
+// 1152 31.6 / 31.6; d = 64 without a bias 1152 40.2 / 37.4).
+constexpr int onehead_split_from(int DK, int mode, bool three, int heads, int row_blocks) {
+    const bool slots768 = three || (DK == 1 && (mode == BIAS_NONE || mode == BIAS_BF16_LDS));
+    const int from = slots768 ? onehead_three_split_from(heads, row_blocks) : heads;
+    return from < heads ? from : onehead4_split_from(heads, row_blocks);
+}
 // ... in the variants whose 256-thread prologue holds a head's loads in registers without spilling
 constexpr bool onehead4_built(int DK, int mode) {
     return DK <= 2 || (DK == 3 && (mode == BIAS_NONE || mode == BIAS_F32_VEC || mode == BIAS_F32_LDS || mode == BIAS_BF16_LDS ||
