@@ -247,6 +247,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     FusedParams p;
     p.q_bits = q_bits;
     const bool use_mu = !(flags & BINATTN_FLAG_NO_MU);
+    const bool half = half_form(s.DK, d);
     p.mu_q = use_mu ? mu_q : nullptr;
     p.mu_k = use_mu ? mu_k : nullptr;
     p.psum = ms ? ms->psum : nullptr;
@@ -293,10 +294,10 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
                             spans_meet(out, os, raw->v, raw->vs, s);
         p.split_from = shared ? B * H : onehead_split_from(s.DK, mode, three, B * H, p.nrb);
         switch (s.DK) {
-            case 1: return launch_onehead_dk<1>(p, mode, st);
-            case 2: return launch_onehead_dk<2>(p, mode, st);
-            case 3: return launch_onehead_dk<3>(p, mode, st);
-            case 4: return launch_onehead_dk<4>(p, mode, st);
+            case 1: return launch_onehead_dk<1, 0>(p, mode, st);
+            case 2: return half ? launch_onehead_dk<2, FORM_HALF>(p, mode, st) : launch_onehead_dk<2, 0>(p, mode, st);
+            case 3: return half ? launch_onehead_dk<3, FORM_HALF>(p, mode, st) : launch_onehead_dk<3, 0>(p, mode, st);
+            case 4: return launch_onehead_dk<4, 0>(p, mode, st);
             default: return BINATTN_ERR_SHAPE;
         }
     }
@@ -315,7 +316,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         p.total_wg = p.nrb * H * B;
         p.div_inner = make_fast_div(B);
         p.div_rows = make_fast_div(p.nrb);
-        return launch_fused_dk<4>(p, mode, st);
+        return launch_fused_dk<4, 0>(p, mode, st);
     }
     // Long sequences with a batch-shared, LDS-staged bias: pair batch entries in one
     // workgroup so that the bias stream is fetched once per pair.  Rows that start on 4-byte words only: where the
@@ -336,10 +337,10 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
     p.div_rows = make_fast_div(p.nrb);
     if (mode == BIAS_BF16_LDS && p.nb == 1 && N % 8 == 0) mode = BIAS_BF16_LDS8;
     switch (s.DK) {
-        case 1: return launch_fused_dk<1>(p, mode, st);
-        case 2: return launch_fused_dk<2>(p, mode, st);
-        case 3: return launch_fused_dk<3>(p, mode, st);
-        case 4: return launch_fused_dk<4>(p, mode, st);
+        case 1: return launch_fused_dk<1, 0>(p, mode, st);
+        case 2: return half ? launch_fused_dk<2, FORM_HALF>(p, mode, st) : launch_fused_dk<2, 0>(p, mode, st);
+        case 3: return half ? launch_fused_dk<3, FORM_HALF>(p, mode, st) : launch_fused_dk<3, 0>(p, mode, st);
+        case 4: return launch_fused_dk<4, 0>(p, mode, st);
         default: return BINATTN_ERR_SHAPE;
     }
 }

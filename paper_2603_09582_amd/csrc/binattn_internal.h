@@ -226,8 +226,11 @@ struct FusedParams {
     int Gy, Gx, gx_shift;      // BIAS_AXIAL / BIAS_TABLE: token grid, Gx = 1 << gx_shift
 };
 
-// Defined (and explicitly instantiated) in fused_dk<DK>.hip, DK = ceil(d / 32).
-template <int DK>
+// The kernels of a head dimension, DK = ceil(d / 32), defined (and explicitly instantiated) in fused_dk<DK>.hip; FORMS = FORM_HALF, in
+// fused_dk<DK>_half.hip, where d ends in the first half of the last 32 channels.
+constexpr int FORM_HALF = 16;
+constexpr bool half_form(int DK, int d) { return (DK == 2 || DK == 3) && d <= 32 * DK - 16; }
+template <int DK, int FORMS>
 int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream);
 // The single-launch form for at most two key blocks (nb must be 2, total_wg = B * H).
 // single-launch form: calls with more heads than this use 4-wave workgroups (two per compute unit)
@@ -277,7 +280,7 @@ constexpr bool onehead4_built(int DK, int mode) {
                        mode == BIAS_AXIAL || mode == BIAS_TABLE));
 }
 
-template <int DK>
+template <int DK, int FORMS>
 int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream);
 
 inline int check_launch() {

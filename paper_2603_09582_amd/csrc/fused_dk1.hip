@@ -3,6 +3,6 @@
 #include "fused_impl.h"
 
 namespace binattn {
-template int launch_fused_dk<1>(const FusedParams &, int, hipStream_t);
-template int launch_onehead_dk<1>(const FusedParams &, int, hipStream_t);
+template int launch_fused_dk<1, 0>(const FusedParams &, int, hipStream_t);
+template int launch_onehead_dk<1, 0>(const FusedParams &, int, hipStream_t);
 }

@@ -109,8 +109,13 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 // the 32-key tiles behind N are left out of it, and waves whose rows all lie there out of the second row block.  (us, without / with: N = 197, d = 64 3 heads 12.14 / 11.70, 512 heads 25.2 / 24.2, 768 heads
 // 38.1 / 36.3, N = 129 35.4 / 30.5; the branches cost calls whose last tile holds a key 1.2-1.5 %, so those keep the forms without.)
 enum { WIDE_NONE = 0, WIDE_ONEHEAD = 1, WIDE_ROWS2 = 2, WIDE_ONEHEAD4 = 3, WIDE_PAIR_ONCE = 4, WIDE_WAVES3 = 5, WIDE_SHORT = 6, WIDE_SHORT4 = 7, WIDE_TRI4 = 8, WIDE_TRISHORT4 = 9 };
-template <int DK, int MODE, int NB, int WIDE = WIDE_NONE>
-__global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 || WIDE >= WIDE_TRI4 ? 3 : 2)) void fused_kernel(const FusedParams p) {
+//
+// FORM is one of these, plus FORM_HALF where at least half of the last 32-channel block lies beyond d (d = 40, 48, 72, 80): its upper two quads
+// of channels per lane have no carry, no seeds and no output.  (Attention stage, us, without / with: N = 1024, d = 72, 128 heads, bf16 46.1 / 45.6, table
+// 42.1 / 40.7, N = 1370, d = 80, 64 heads 53.2 / 52.0; one launch, N = 256, d = 72, 512 heads 29.8 / 29.2.)
+template <int DK, int MODE, int NB, int FORM = WIDE_NONE>
+__global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || (FORM & 15) >= WIDE_TRI4 ? 3 : 2)) void fused_kernel(const FusedParams p) {
+    constexpr int WIDE = FORM & 15;
     using L = Image<DK>;
     constexpr bool TRI = WIDE == WIDE_TRI4 || WIDE == WIDE_TRISHORT4;
     constexpr bool SHORT = WIDE == WIDE_SHORT || WIDE == WIDE_SHORT4 || WIDE == WIDE_TRISHORT4;
@@ -124,6 +129,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 || WIDE >=
     constexpr int NIMG = PAIR ? 2 : 1;          // operand images per buffer
     constexpr bool PERSIST = NB == 1 || ROWS2;
     constexpr int DKP = 32 * DK;
+    constexpr bool HALF = (FORM & FORM_HALF) != 0;
+    auto live_quads = [](int cb) constexpr -> int { return HALF && cb == DK - 1 ? 2 : 4; };  // of a lane, 4 channels each
     constexpr int DK2 = L::DK2;
     constexpr bool F32L = MODE == BIAS_F32_LDS;
     constexpr bool BF16L = MODE == BIAS_BF16_LDS || MODE == BIAS_BF16_LDS8, LDS_BIAS = BF16L || F32L;
@@ -720,7 +727,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 || WIDE >=
 #pragma unroll
         for (int cb = 0; cb < DK; ++cb)
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
+            for (int k = 0; k < live_quads(cb) / 2; ++k) {
                 unsigned w[2][2];  // [quad 2k / 2k+1][dword]
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
@@ -964,7 +971,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 || WIDE >=
 #pragma unroll
         for (int cb = 0; cb < PRE; ++cb) {
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
+            for (int q4 = 0; q4 < live_quads(cb); ++q4) {
                 const v4i c4 = *reinterpret_cast<const v4i *>(ibuf + L::CS_OFF + 4 * (32 * cb + 8 * q4 + 4 * g));
                 acc[cb][4 * q4] = c4[0]; acc[cb][4 * q4 + 1] = c4[1];
                 acc[cb][4 * q4 + 2] = c4[2]; acc[cb][4 * q4 + 3] = c4[3];
@@ -1121,7 +1128,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 || WIDE >=
 #pragma unroll
         for (int cb = PRE; cb < DK; ++cb) {
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
+            for (int q4 = 0; q4 < live_quads(cb); ++q4) {
                 const v4i c4 = *reinterpret_cast<const v4i *>(ibuf + L::CS_OFF + 4 * (32 * cb + 8 * q4 + 4 * g));
                 acc[cb][4 * q4] = c4[0]; acc[cb][4 * q4 + 1] = c4[1];
                 acc[cb][4 * q4 + 2] = c4[2]; acc[cb][4 * q4 + 3] = c4[3];
@@ -1136,7 +1143,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 || WIDE >=
 #pragma unroll
         for (int cb = 0; cb < DK; ++cb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) Of[cb][r] = fmaf(Of[cb][r], resc, __int_as_float(acc[cb][r]));
+            for (int r = 0; r < 4 * live_quads(cb); ++r) Of[cb][r] = fmaf(Of[cb][r], resc, __int_as_float(acc[cb][r]));
         }
         if (TBLK && more && !sw) table_store(tab + (tpar ^ 1) * 4 * TB_CP, inv_alpha);
         __builtin_amdgcn_sched_barrier(0);  // keep the wait at the very end of the block
@@ -1476,7 +1483,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, (WIDE == WIDE_WAVES3 || WIDE >=
 #pragma unroll
         for (int cb = 0; cb < DK; ++cb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) Of[cb][r] = fmaf(-PV_MAGIC_F, rho, Of[cb][r]);
+            for (int r = 0; r < 4 * live_quads(cb); ++r) Of[cb][r] = fmaf(-PV_MAGIC_F, rho, Of[cb][r]);
         rho = 0.0f;
         if (!PAIR) next_rebase += REBASE;
     };
@@ -1520,7 +1527,7 @@ constexpr bool waves2_built(int DK, int mode) {
     return !use_waves3(DK, mode, 1) && !(DK == 1 && (mode == BIAS_BF16_LDS || mode == BIAS_BF16_LDS8));
 }
 
-template <int DK>
+template <int DK, int FORMS>
 int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
     // NB = 1, persistent grid: as many workgroups as fit on the chip at once (two 4-wave
     // workgroups per CU, 256 CUs), a multiple of 8 so that a workgroup's items stay on one
@@ -1530,9 +1537,9 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
         if constexpr (DK == 4) {
             const dim3 grid((unsigned)(needed < 256 ? needed : 256)), block(FUSED_THREADS * 2);
             if (mode == BIAS_BF16_LDS)
-                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2, WIDE_ROWS2>), grid, block, 0, stream, p);
+                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2, WIDE_ROWS2 | FORMS>), grid, block, 0, stream, p);
             else if (mode == BIAS_F32_LDS)
-                hipLaunchKernelGGL((fused_kernel<DK, BIAS_F32_LDS, 2, WIDE_ROWS2>), grid, block, 0, stream, p);
+                hipLaunchKernelGGL((fused_kernel<DK, BIAS_F32_LDS, 2, WIDE_ROWS2 | FORMS>), grid, block, 0, stream, p);
             else
                 return BINATTN_ERR_DTYPE;
             return check_launch();
@@ -1547,9 +1554,9 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
         if constexpr (DK <= 2) {
             if (mode != BIAS_BF16_LDS) return BINATTN_ERR_DTYPE;
             if (p.wide == WIDE_PAIR_ONCE)
-                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2, WIDE_PAIR_ONCE>), grid, block, 0, stream, p);
+                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2, WIDE_PAIR_ONCE | FORMS>), grid, block, 0, stream, p);
             else
-                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2>), grid, block, 0, stream, p);
+                hipLaunchKernelGGL((fused_kernel<DK, BIAS_BF16_LDS, 2, FORMS>), grid, block, 0, stream, p);
             return check_launch();
         }
         return BINATTN_ERR_SHAPE;
@@ -1560,11 +1567,11 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
     case M:                                                                                           \
         if constexpr (use_waves3(DK, M, 513)) {                                                       \
             if (waves3 || !waves2_built(DK, M)) {                                                     \
-                hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_WAVES3>), grid, block, 0, stream, p); \
+                hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_WAVES3 | FORMS>), grid, block, 0, stream, p); \
                 break;                                                                                \
             }                                                                                         \
         }                                                                                             \
-        if constexpr (waves2_built(DK, M)) hipLaunchKernelGGL((fused_kernel<DK, M, 1>), grid, block, 0, stream, p); \
+        if constexpr (waves2_built(DK, M)) hipLaunchKernelGGL((fused_kernel<DK, M, 1, FORMS>), grid, block, 0, stream, p); \
         break;
         CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE_BLK)
         case BIAS_BF16_LDS:
@@ -1577,7 +1584,7 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
 #undef CASE
         case BIAS_F32_LDS:
             if constexpr (DK <= 3) {
-                hipLaunchKernelGGL((fused_kernel<DK, BIAS_F32_LDS, 1>), grid, block, 0, stream, p);
+                hipLaunchKernelGGL((fused_kernel<DK, BIAS_F32_LDS, 1, FORMS>), grid, block, 0, stream, p);
                 break;
             }
             return BINATTN_ERR_SHAPE;
@@ -1589,7 +1596,7 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream) {
 // WIDE_SHORT and WIDE_SHORT4: the biases that come with token counts like 197
 constexpr bool short_built(int mode) { return mode == BIAS_NONE || mode == BIAS_BF16_LDS || mode == BIAS_F32_LDS; }
 
-template <int DK>
+template <int DK, int FORMS>
 int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
     const int needed = ((p.total_wg + 7) / 8) * 8;
     const bool ends_early = p.N > BV && p.N <= 2 * BV - 32;
@@ -1599,23 +1606,23 @@ int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
 #define CASE(M)                                                                                          \
     case M:                                                                                              \
         if constexpr (onehead_three_only(DK, M)) {                                                       \
-            if (ends_early) hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_TRISHORT4>), grid, block, 0, stream, p); \
-            else hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_TRI4>), grid, block, 0, stream, p);     \
+            if (ends_early) hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_TRISHORT4 | FORMS>), grid, block, 0, stream, p); \
+            else hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_TRI4 | FORMS>), grid, block, 0, stream, p);     \
             return check_launch();                                                                       \
         } else if constexpr (onehead4_built(DK, M)) {                                                    \
             if constexpr (DK == 2 && M == BIAS_BF16_LDS) {                                               \
                 if (p.wide == WIDE_TRI4) {                                                               \
-                    hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_TRISHORT4>), grid, block, 0, stream, p); \
+                    hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_TRISHORT4 | FORMS>), grid, block, 0, stream, p); \
                     return check_launch();                                                               \
                 }                                                                                        \
             }                                                                                            \
             if constexpr (short_built(M)) {                                                              \
                 if (ends_early) {                                                                        \
-                    hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_SHORT4>), grid, block, 0, stream, p); \
+                    hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_SHORT4 | FORMS>), grid, block, 0, stream, p); \
                     return check_launch();                                                               \
                 }                                                                                        \
             }                                                                                            \
-            hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_ONEHEAD4>), grid, block, 0, stream, p);     \
+            hipLaunchKernelGGL((fused_kernel<DK, M, 1, WIDE_ONEHEAD4 | FORMS>), grid, block, 0, stream, p);     \
             return check_launch();                                                                       \
         }                                                                                                \
         return BINATTN_ERR_SHAPE;
@@ -1632,11 +1639,11 @@ int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
     case M:                                                                                              \
         if constexpr (short_built(M)) {                                                                  \
             if (ends_early) {                                                                            \
-                hipLaunchKernelGGL((fused_kernel<DK, M, 2, WIDE_SHORT>), grid, block, 0, stream, p);     \
+                hipLaunchKernelGGL((fused_kernel<DK, M, 2, WIDE_SHORT | FORMS>), grid, block, 0, stream, p);     \
                 break;                                                                                   \
             }                                                                                            \
         }                                                                                                \
-        hipLaunchKernelGGL((fused_kernel<DK, M, 2, WIDE_ONEHEAD>), grid, block, 0, stream, p);           \
+        hipLaunchKernelGGL((fused_kernel<DK, M, 2, WIDE_ONEHEAD | FORMS>), grid, block, 0, stream, p);           \
         break;
         CASE(BIAS_NONE) CASE(BIAS_LUT) CASE(BIAS_BF16_VEC) CASE(BIAS_F32_VEC) CASE(BIAS_AXIAL) CASE(BIAS_TABLE)
         CASE(BIAS_BF16_LDS) CASE(BIAS_F32_LDS)
