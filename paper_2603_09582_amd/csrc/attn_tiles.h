@@ -199,7 +199,9 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 // max / sum over the two lanes L and L ^ 32 (they share a query row), on the vector ALU.
 __device__ __forceinline__ float pair_max(float x) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    float o;  // (fmaxf would quiet both operands first, two instructions more; they are results of maxima)
+    asm("v_max_f32 %0, %1, %2" : "=v"(o) : "v"(r[0]), "v"(r[1]));
+    return o;
 }
 __device__ __forceinline__ float pair_sum(float x) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);

@@ -786,6 +786,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
         nxt = decode(v + gridDim.x, first_args());
     }
 
+    // (-infinity that the compiler cannot see: a maximum of two matrix results alone first quiets both, two instructions more)
+    float ninf = -INFINITY;
+    if (AXIAL) asm volatile("" : "+s"(ninf));
     // The block before which the accumulator's offset is next removed (see the loop).  A 4-wave item that
     // starts on buffer B (an odd number of blocks per item, after an odd number of items) is rebased before
     // blocks 9, 17, ... instead of 8, 16, ...: which it is shows in the last bits of the carry.  The grid of
@@ -1046,9 +1049,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
         if (AXIAL) {  // per-tile maxima, each shifted by the tile's y term
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
-                float mt = T[t][0];
+                float mt = ninf;
 #pragma unroll
-                for (int r = 1; r < 16; ++r) mt = fmaxf(mt, T[t][r]);
+                for (int r = 0; r < 16; ++r) mt = fmaxf(mt, T[t][r]);
                 mx = fmaxf(mx, mt + wt[t]);
             }
         } else {
