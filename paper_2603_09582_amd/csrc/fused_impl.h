@@ -151,14 +151,18 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
     // The generated biases leave the memory pipeline idle: there the prefetched channel blocks'
     // matrix instructions of a tile are issued right behind its codes and run under the next
     // tile's exponentials (128 x 128 grid, d = 64: 2155 -> 2083 us; nothing or a loss above d = 64).
-    constexpr bool PV_EARLY = (MODE == BIAS_AXIAL || MODE == BIAS_TABLE_BLK) && DK <= 2;
+    // So are those of all channel blocks, whose V rows are read under the tile's own exponentials, in the 4-wave workgroups with bf16
+    // tiles at 64 < d <= 96 and fp32 tiles at 32 < d <= 64 (attention stage, us: N = 1024, d = 72, 128 heads 46.1 / 45.8, N = 1370, 64 heads, d = 80
+    // 51.3 / 50.8, d = 88 52.4 / 51.1, fp32, N = 577, 192 heads 35.9 / 35.5; bf16 at d = 64 nothing, d = 128 191 / 200, the paired form 2616 / 2838).
+    constexpr bool ALL_EARLY = !ONEHEAD && NB == 1 && ((DK == 3 && BF16L) || (DK == 2 && F32L));
+    constexpr bool PV_EARLY = ((MODE == BIAS_AXIAL || MODE == BIAS_TABLE_BLK) && DK <= 2) || ALL_EARLY;
     // V operand rows of this many channel blocks are fetched from LDS before the
     // exponential phase (the rest just before their MFMAs): hides the LDS latency
     // where the register budget allows it.
-    constexpr int PRE = TRI ? 0 : (DK == 2 && WAVES3) ? (PV_EARLY ? 1 : 0) : DK <= 2 ? DK : ((DK == 4 && MODE == BIAS_TABLE_BLK) || MODE == BIAS_F32_LDS) ? 0 : 1;
+    constexpr int PRE = ALL_EARLY ? DK : TRI ? 0 : (DK == 2 && WAVES3) ? (PV_EARLY ? 1 : 0) : DK <= 2 ? DK : ((DK == 4 && MODE == BIAS_TABLE_BLK) || MODE == BIAS_F32_LDS) ? 0 : 1;
     // ... and at three waves per SIMD each tile's V rows are read under its own exponentials (the
     // registers do not hold them all).
-    constexpr bool VDEMAND = PV_EARLY && WAVES3;
+    constexpr bool VDEMAND = (PV_EARLY && WAVES3) || ALL_EARLY;
     // key blocks between two removals of the accumulator's float-bit offset (a power of two)
     constexpr int REBASE = 8;
     __shared__ __attribute__((aligned(1024))) char bufA[NIMG * L::BYTES];
@@ -1099,7 +1103,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
 #pragma unroll
                 for (int cb = 0; cb < PRE; ++cb)
                     acc[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(va[cb][t], pk[t], acc[cb], 0, 0, 0);
-                if (AXIAL || WAVES3) __builtin_amdgcn_sched_barrier(0);
+                if (AXIAL || WAVES3 || ALL_EARLY) __builtin_amdgcn_sched_barrier(0);
             }
             // The shared bias tile of the next block (BIAS_DB), one copy per tile of exponentials:
             // issued in one burst at the start of the block, beside the image copies, they fill
