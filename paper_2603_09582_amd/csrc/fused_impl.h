@@ -594,9 +594,14 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
     // held the wave as long as its vector work did (190 scalar instructions per block; with them and those of the switch of items
     // gone from the ordinary block, attention stage, before / after, us: N = 1024, d = 72, 128 heads 51.9 / 48.5, N = 1370, d = 80, 64
     // heads 58.4 / 52.6, fp32 bias, N = 577, d = 64, 192 heads 39.9 / 36.1, N = 2048, d = 128, 128 heads 213.5 / 195.6).
-    auto dma_bias = [&](const Item &t, BiasSrc &src, int blk, unsigned region) {
+    // `ends`: where the caller's code knows it, and the other copy routine is left out of it.  The single launch runs through its
+    // code once, cold, and pays for its length: its first tile and second block are mostly ragged, the first block of its second row
+    // block, where it has two key blocks, never is.  N <= 128, d = 64, 4-wave form (whole call, both routines everywhere / so, us):
+    // 768 heads, N = 100 21.0 / 20.5, 512 heads, N = 64 12.9 / 12.6, 1024 heads, N = 120 25.5 / 25.2; N = 128 itself 14.4 / 14.6.
+    constexpr int ENDS_INSIDE = 1, ENDS_RAGGED = 2;
+    auto dma_bias = [&](const Item &t, BiasSrc &src, int blk, unsigned region, int ends) {
         if constexpr (!PAIR) {
-            if (blk * BV + BV <= N) {
+            if (ends ? ends == ENDS_INSIDE : blk * BV + BV <= N) {
                 dma_tile<SEGS>(src.base, src.voff, region);
             } else {
                 const int klim = STRADDLE ? bias_klimit(t, blk) : N;
@@ -869,9 +874,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
         // its first workgroup) therefore raises its priority on every other block.  Only a
         // scheduling hint: results do not depend on it.  With three workgroups per CU the last third does
         // (128 x 128 grid, d = 64: table 1968 us with the second half, 1912 with the last third, 2143 without).
+        // The single launch, two blocks an item at most, gains nothing by it (1024 heads, N = 120, d = 64 25.5 / 25.4).
         if (NB == 1) {
             if (!tpar) __builtin_amdgcn_s_setprio(0);
-            else if (younger) __builtin_amdgcn_s_setprio(1);
+            else if (younger && !ONEHEAD) __builtin_amdgcn_s_setprio(1);
         }
         // WIDE_SHORT: tile t of the second block holds no key (its weights are 0, code -128)
         auto dead_tile = [&](int t) -> bool { return SHORT && tpar == 1 && t > 0 && BV + 32 * t >= N; };
@@ -970,7 +976,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
             load_bias_vec(brow, nblkidx);
         if (LDS_BIAS && !BIAS_DB && more) {
             wait_lds();                       // this block's tile has been read into registers
-            dma_bias(sw ? nxt : cur, bsrc, nblkidx, bnxt);    // refill the wave's own region
+            dma_bias(sw ? nxt : cur, bsrc, nblkidx, bnxt, !ONEHEAD ? 0 : tpar ? ENDS_INSIDE : ENDS_RAGGED);    // refill the wave's own region
         }
         //    the LDS reads of the P.V phase go out now and land during the exponentials
         v16i acc[DK];
@@ -1210,7 +1216,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
         // the order of use: the bias tile, this lane's query chunks, the V rows, the key chunks.
         if (LDS_BIAS) {
             bsrc = bias_dma_src(cur, first_args());
-            dma_bias(cur, bsrc, 0, lds_offset(bA));
+            dma_bias(cur, bsrc, 0, lds_offset(bA), ENDS_RAGGED);
         }
         if (BROW_AHEAD) brow = bias_row_ptr(cur, first_args());
         if (HI_REGS) load_bias_hi(brow, 0);
@@ -1443,7 +1449,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
         imgs += L::BYTES;
         if (LDS_BIAS) {
             bsrc = bias_dma_src(cur, first_args());
-            dma_bias(cur, bsrc, 0, lds_offset(bA));
+            dma_bias(cur, bsrc, 0, lds_offset(bA), 0);
         }
         if (!AXIAL && p.psum) item_mu(cur, parts, first_args());
     }
