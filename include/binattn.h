@@ -73,8 +73,8 @@ enum {
                                  replaces), so it is opt-in and kept for comparison         */
     BINATTN_FLAG_WIDE8 = 8,   /* single-launch forms only: one 8-wave workgroup per head even
                                  when the call has more heads than the chip has compute units
-                                 (by default such calls use 4-wave workgroups, two per compute
-                                 unit).  Same results; kept for comparison                    */
+                                 (by default such calls use 4-wave workgroups, two or three per
+                                 compute unit).  Same results; kept for comparison            */
 };
 
 /* variants of binattn_logits_debug */
