@@ -135,9 +135,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
     constexpr bool F32L = MODE == BIAS_F32_LDS;
     constexpr bool BF16L = MODE == BIAS_BF16_LDS || MODE == BIAS_BF16_LDS8, LDS_BIAS = BF16L || F32L;
     // A chunk can straddle the end of a row.  Where none can, the block loop is built without the code for it:
-    // its branches sit between the logits and the exponentials and cost 2-3 % even where they are never taken
-    // (attention stage, with / without: N = 520, d = 64, 192 heads 34.0 / 33.0 us, N = 1024, d = 72, 128 heads 52.0 / 51.5, N = 1376, d = 96,
-    // 192 heads 152.3 / 149.4; nothing in the 8-wave forms).
+    // its branches sat between the logits and the exponentials and cost 2-3 % even where they were never taken.  Since blocks inside
+    // the rows take a path of their own it makes no difference any more (attention stage, with / without: N = 520, d = 64, 192 heads
+    // 30.7 / 30.6 us, N = 1024, d = 72, 128 heads 51.1 / 51.7, N = 1376, d = 96, 192 heads 132.6 / 133.8).
     constexpr bool STRADDLE = MODE != BIAS_BF16_LDS8;
     // Staged bias rows: SEGS segments of 128 bytes per row and block.  A bf16 tile is staged whole
     // (two segments); an fp32 tile would be 16 KiB per wave, so its first SEGS 32-key quarters (one per
