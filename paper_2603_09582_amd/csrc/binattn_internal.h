@@ -7,6 +7,7 @@
 
 #include "binattn.h"
 #include "fast_div.h"
+#include "head_split.h"
 #include "psi_grid.h"
 
 namespace binattn {
@@ -235,16 +236,6 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream);
 // The single-launch form for at most two key blocks (nb must be 2, total_wg = B * H).
 // single-launch form: calls with more heads than this use 4-wave workgroups (two per compute unit)
 constexpr int ONEHEAD4_MIN_HEADS = 256;
-// Heads of such a call that are left for a round of their own (512 workgroups fit the chip at once) and are at most half as
-// many as compute units: one workgroup per row block, each after the whole prologue, so that the last round takes half of its
-// block loops.  us per call, whole heads / split, bf16 bias: N = 197, d = 64 520 heads 36.9 / 32.3, 640 36.3 / 31.9, 1152 54.6 / 51.0;
-// N = 256, d = 72 640 heads 41.5 / 37.7; N = 200, d = 32 640 heads 24.6 / 20.2; fp32 bias, N = 256, d = 96 640 heads 65.7 / 61.1; no bias, d = 64
-// 640 heads 29.8 / 28.2, 1152 44.6 / 42.8.  Above 128 the halves share compute units: 704 heads 37.1 / 36.3, without a bias
-// 30.5 / 31.7, d = 32 25.0 / 25.9; 1280 heads 55.9 / 57.4.
-constexpr int onehead4_split_from(int heads, int row_blocks) {
-    const int left = heads % 512;
-    return row_blocks == 2 && heads > 512 && left > 0 && left <= 128 ? heads - left : heads;
-}
 // Three 4-wave workgroups per compute unit instead of two (32 < d <= 64).  Without a bias they are at least as fast everywhere (us,
 // two / three: N = 197 400 heads 19.8 / 19.7, 768 31.6 / 28.1, 1536 54.5 / 48.4, N = 256 1024 42.5 / 38.3, N = 100 768 18.6 / 15.8) and the only form.  With bf16
 // tiles a head takes longer and what counts is how full the last round of 768 is (N = 197 512 heads 24.5 / 26.4, 768 36.6 / 33.3, 896
@@ -256,25 +247,13 @@ constexpr bool onehead_three(int DK, int mode, int N, int heads) {
     const int left = heads % 768;
     return DK == 2 && mode == BIAS_BF16_LDS && N > BV && N <= 2 * BV - 32 && heads > 512 && (left <= 128 || left >= 512);
 }
-// Heads from which on they take a workgroup per row block: as many as fill a first round of 768, a last round of at most 128 heads,
-// and as many as fill a last one that is three quarters full.  (us, whole heads / split, bf16, N = 197: 520 heads 31.8 / 27.2, 640 32.2 / 28.1, 704 32.5 / 32.4,
-// 832 43.6 / 38.2, 1400 62.7 / 58.0, but 1280 55.2 / 55.8, 2048 81.6 / 83.2, without a bias 1024 35.4 / 35.4.)  A multiple of 8.
-constexpr int onehead_three_split_from(int heads, int row_blocks) {
-    const int left = heads % 768;
-    int halves = 0;
-    if (heads > 512 && heads < 768) halves = 768 - heads;
-    if (heads > 768) halves = left <= 128 ? left : left >= 576 ? 768 - left : 0;
-    return row_blocks == 2 && halves > 0 ? (heads - halves) / 8 * 8 : heads;
-}
-// Up to 32 channels three fit as well, without a bias and with bf16 tiles.  Where the rule above splits none, the one for rounds of 512
-// may: it leaves the last round shorter by 128 heads (d = 32, N = 200, bf16, rounds of 512 only / both: 576 heads 20.1 / 19.7, 832 29.9 / 26.7,
-// 1152 31.6 / 31.6; d = 64 without a bias 1152 40.2 / 37.4).
+// The first head that is split by row blocks (head_split.h): for rounds of 768 where three workgroups share a compute unit, which
+// they do up to 32 channels as well, without a bias and with bf16 tiles.
 constexpr int onehead_split_from(int DK, int mode, bool three, int heads, int row_blocks) {
-    const bool slots768 = three || (DK == 1 && (mode == BIAS_NONE || mode == BIAS_BF16_LDS));
-    const int from = slots768 ? onehead_three_split_from(heads, row_blocks) : heads;
-    return from < heads ? from : onehead4_split_from(heads, row_blocks);
+    if (row_blocks != 2) return heads;
+    return three || (DK == 1 && (mode == BIAS_NONE || mode == BIAS_BF16_LDS)) ? split_of_768(heads) : split_last(heads, 512);
 }
-// ... in the variants whose 256-thread prologue holds a head's loads in registers without spilling
+// The 4-wave form is built in the variants whose 256-thread prologue holds a head's loads in registers without spilling
 constexpr bool onehead4_built(int DK, int mode) {
     return DK <= 2 || (DK == 3 && (mode == BIAS_NONE || mode == BIAS_F32_VEC || mode == BIAS_F32_LDS || mode == BIAS_BF16_LDS ||
                        mode == BIAS_AXIAL || mode == BIAS_TABLE));

@@ -93,7 +93,7 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 // the same prologue with 256 threads, then the head's two 128-row blocks one after the other
 // as two items of the persistent stream (the images stay where they are).  Two such workgroups
 // share a compute unit, so one head's loads and preparation overlap the other's block loop.
-// (Heads left for a last round that fills the chip at most half take a workgroup per row block: onehead4_split_from.)
+// (Heads left for a last round that fills the chip at most half take a workgroup per row block: head_split.h.)
 //
 // WIDE_PAIR_ONCE is the paired form (NB = 2) with the bias copies marked as not worth keeping in the
 // caches, for biases larger than those.
@@ -267,10 +267,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
         int u = (v & 7) * per_xcd + (v >> 3), row_block = 0;
         t.valid = v < vmax && u < p.total_wg;
         if (ONEHEAD4 && p.split_from < p.total_wg) {  // heads from split_from on: a workgroup per row block
-            const int s = (v - p.split_from) >> 3, per_tail = (p.total_wg - p.split_from + 7) >> 3;
-            const bool whole = v < p.split_from;
-            u = whole ? (v & 7) * (p.split_from >> 3) + (v >> 3) : p.split_from + (v & 7) * per_tail + (s >> 1);
-            row_block = whole ? 0 : s & 1;
+            u = split_head(v, p.split_from, p.total_wg);
+            row_block = split_row_block(v, p.split_from);
             t.valid = u < p.total_wg;
         }
         const int uu = t.valid ? u : 0;
@@ -1614,8 +1612,7 @@ int launch_onehead_dk(const FusedParams &p, int mode, hipStream_t stream) {
     const int needed = ((p.total_wg + 7) / 8) * 8;
     const bool ends_early = p.N > BV && p.N <= 2 * BV - 32;
     if (p.nb == 1) {  // 4-wave form: the variants onehead4_built() names
-        // (eight half heads of a row block each, then those heads' other halves, and so on: both on one XCD)
-        const dim3 grid((unsigned)(p.split_from < p.total_wg ? p.split_from + (p.total_wg - p.split_from + 7) / 8 * 16 : needed)), block(FUSED_THREADS);
+        const dim3 grid((unsigned)(p.split_from < p.total_wg ? split_grid(p.split_from, p.total_wg) : needed)), block(FUSED_THREADS);
 #define CASE(M)                                                                                          \
     case M:                                                                                              \
         if constexpr (onehead_three_only(DK, M)) {                                                       \
