@@ -780,9 +780,12 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
     const bool live = !(ONEHEAD && NB == 2) || cur.rb * BR + wave * ROWS_PER_WAVE < N;
     // (Flags of the loop are integers in scalar registers that the compiler cannot look into: it makes lane masks out of them
     // otherwise, five to ten instructions per block for each.)
-    int younger_flag = (WAVES3 || TRI) && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
-    int younger = __builtin_amdgcn_readfirstlane(younger_flag);
-    if (NB == 1) asm volatile("" : "+s"(younger));
+    int younger = 0;
+    if constexpr (NB == 1 && !ONEHEAD) {
+        const int flag = WAVES3 && gridDim.x > 512 ? 3 * blockIdx.x >= 2 * gridDim.x : 2 * blockIdx.x >= gridDim.x;
+        younger = __builtin_amdgcn_readfirstlane(flag);
+        asm volatile("" : "+s"(younger));
+    }
     int parity = 0;    // items alternate between the two delta_v copies
     Item nxt = {0, 0, 0, 0, false};
     if (ONEHEAD4) {  // a head's two row blocks, one workgroup
@@ -872,10 +875,17 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
         // its first workgroup) therefore raises its priority on every other block.  Only a
         // scheduling hint: results do not depend on it.  With three workgroups per CU the last third does
         // (128 x 128 grid, d = 64: table 1968 us with the second half, 1912 with the last third, 2143 without).
-        // The single launch, two blocks an item at most, gains nothing by it (1024 heads, N = 120, d = 64 25.5 / 25.4).
-        if (NB == 1) {
+        // The single launch has at most two blocks an item: one of at most 128 keys has nothing to raise, and the flag formed for it cost
+        // 0.1 .. 0.6 us (us, with / without: d = 64, bf16, N = 128 896 heads 24.4 / 23.9, N = 100 768 heads 20.0 / 19.5).  The second block is raised where
+        // all of it counts (N > 224; us, never raised / so: d = 32, fp32 N = 240 260 heads 20.4 / 19.2, d = 64 24.2 / 22.9, d = 96, N = 256 384 heads
+        // 34.4 / 33.8); where it ends early, and with three workgroups per unit, it goes either way (N = 197, no bias, d = 32 500 heads 13.9 / 13.6,
+        // 768 18.6 / 18.9, fp32, d = 64 768 heads 37.7 / 38.1).
+        if constexpr (NB == 1 && !ONEHEAD) {
             if (!tpar) __builtin_amdgcn_s_setprio(0);
-            else if (younger && !ONEHEAD) __builtin_amdgcn_s_setprio(1);
+            else if (younger) __builtin_amdgcn_s_setprio(1);
+        } else if constexpr (ONEHEAD4 && !SHORT && !TRI) {
+            if (!tpar) __builtin_amdgcn_s_setprio(0);
+            else if (2 * blockIdx.x >= gridDim.x) __builtin_amdgcn_s_setprio(1);
         }
         // WIDE_SHORT: tile t of the second block holds no key (its weights are 0, code -128)
         auto dead_tile = [&](int t) -> bool { return SHORT && tpar == 1 && t > 0 && BV + 32 * t >= N; };
