@@ -593,9 +593,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
     // gone from the ordinary block, attention stage, before / after, us: N = 1024, d = 72, 128 heads 51.9 / 48.5, N = 1370, d = 80, 64
     // heads 58.4 / 52.6, fp32 bias, N = 577, d = 64, 192 heads 39.9 / 36.1, N = 2048, d = 128, 128 heads 213.5 / 195.6).
     // `ends`: where the caller's code knows it, and the other copy routine is left out of it.  The single launch runs through its
-    // code once, cold, and pays for its length: its first tile and second block are mostly ragged, the first block of its second row
-    // block, where it has two key blocks, never is.  N <= 128, d = 64, 4-wave form (whole call, both routines everywhere / so, us):
-    // 768 heads, N = 100 21.0 / 20.5, 512 heads, N = 64 12.9 / 12.6, 1024 heads, N = 120 25.5 / 25.2; N = 128 itself 14.4 / 14.6.
+    // code once, cold, and pays for its length.  Its first tile takes the ragged routine whatever its length (us, both / so: bf16, 300 heads
+    // d = 32, N = 50 9.62 / 9.37, d = 64, N = 50 11.85 / 11.43, d = 96, N = 100 15.9 / 15.7, 360 heads d = 96, N = 128 16.1 / 16.3).  The second block of
+    // the short forms is ragged, the first block of a second row block whole.  N > 224 has both (N = 256, 384 heads, one / both: fp32, d = 32
+    // 18.4 / 17.7, d = 64 25.2 / 24.2, bf16, d = 64 23.5 / 23.1).
     constexpr int ENDS_INSIDE = 1, ENDS_RAGGED = 2;
     auto dma_bias = [&](const Item &t, BiasSrc &src, int blk, unsigned region, int ends) {
         if constexpr (!PAIR) {
@@ -984,7 +985,7 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
             load_bias_vec(brow, nblkidx);
         if (LDS_BIAS && !BIAS_DB && more) {
             wait_lds();                       // this block's tile has been read into registers
-            dma_bias(sw ? nxt : cur, bsrc, nblkidx, bnxt, !ONEHEAD ? 0 : tpar ? ENDS_INSIDE : ENDS_RAGGED);    // refill the wave's own region
+            dma_bias(sw ? nxt : cur, bsrc, nblkidx, bnxt, !(SHORT || (ONEHEAD && NB == 2)) ? 0 : tpar ? ENDS_INSIDE : ENDS_RAGGED);    // refill the wave's own region
         }
         //    the LDS reads of the P.V phase go out now and land during the exponentials
         v16i acc[DK];
