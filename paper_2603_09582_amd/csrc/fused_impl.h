@@ -772,8 +772,10 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
 
     // The persistent forms end inside the loop: a way out of it to the function's end leaves ten moves between scalar registers (and
     // as many through vector registers) in every block.  (Attention stage, us: N = 1024, d = 72, 128 heads 48.4 / 47.2, N = 1370, d = 80, 64
-    // heads 52.4 / 51.4, fp32 bias, N = 577, d = 64, 192 heads 36.1 / 35.7.  Where registers are at their limit it spills one.)
-    constexpr bool ENDS = PERSIST && !WAVES3 && DK < 4;
+    // heads 52.4 / 51.4, fp32 bias, N = 577, d = 64, 192 heads 36.1 / 35.7.  Where registers are at their limit it spills one.  Above 64
+    // channels fp32 tiles lose by it, whole calls, us, way out / so: d = 96 N = 10000 4 heads 444 / 455, N = 2207 32 heads 169.8 / 172.9, N = 6000 1 head
+    // 131.7 / 135.7, d = 80 N = 1370 64 heads 80.9 / 81.9.)
+    constexpr bool ENDS = PERSIST && !WAVES3 && DK < 4 && !(F32L && DK == 3);
     // ---- stream position --------------------------------------------------------
     int it = 0;        // key block inside the current item
     // 8-wave single launch (up to 128 tokens leave half of its waves without rows): a wave whose 32 rows all lie beyond N
