@@ -238,14 +238,15 @@ int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream);
 constexpr int ONEHEAD4_MIN_HEADS = 256;
 // Three 4-wave workgroups per compute unit instead of two (32 < d <= 64).  Without a bias they are at least as fast everywhere (us,
 // two / three: N = 197 400 heads 19.8 / 19.7, 768 31.6 / 28.1, 1536 54.5 / 48.4, N = 256 1024 42.5 / 38.3, N = 100 768 18.6 / 15.8) and the only form.  With bf16
-// tiles a head takes longer and what counts is how full the last round of 768 is (N = 197 512 heads 24.5 / 26.4, 768 36.6 / 33.3, 896
-// 42.5 / 40.4, 960 43.8 / 46.0, 1152 52.2 / 54.3, 1280 56.6 / 55.2, 1536 67.1 / 64.8, 1664 72.5 / 67.8); N <= 128 and N > 224 spill there, and fp32 tiles do
-// not fit.
+// tiles a head takes longer: up to 512 heads, one round of either, two are faster (N = 197 24.5 / 26.4).  Above, three / two, each with its best split,
+// over N = 129, 160, 180, 197, 224 and d = 40, 48, 64 (mean, least .. most): 513 heads 0.87, 0.81 .. 0.92, 700 0.91, 0.84 .. 0.95, 870 0.97, 0.92 .. 1.03, 960 0.98, 0.94 .. 1.05,
+// 1200 0.91, 0.86 .. 0.94, 1480 0.92, 0.88 .. 0.97, 1800 0.90, 0.87 .. 0.94, 2304 0.88, 0.84 .. 0.93, 3500 0.88, 0.82 .. 0.96; between 897 and 1024, where
+// 768 leave a last round that is less than a third full and 512 fill theirs, it goes either way with N (d = 40, 960 heads N = 129 30.8 / 32.4, d = 64 N = 224
+// 41.9 / 39.4), and two stay.  N <= 128 and N > 224 spill there, and fp32 tiles do not fit.
 constexpr bool onehead_three_only(int DK, int mode) { return DK == 2 && mode == BIAS_NONE; }
 constexpr bool onehead_three(int DK, int mode, int N, int heads) {
     if (onehead_three_only(DK, mode)) return true;
-    const int left = heads % 768;
-    return DK == 2 && mode == BIAS_BF16_LDS && N > BV && N <= 2 * BV - 32 && heads > 512 && (left <= 128 || left >= 512);
+    return DK == 2 && mode == BIAS_BF16_LDS && N > BV && N <= 2 * BV - 32 && heads > 512 && !(heads > 896 && heads <= 1024);
 }
 // The first head that is split by row blocks (head_split.h): for rounds of 768 where three workgroups share a compute unit, which
 // they do up to 32 channels as well, without a bias and with bf16 tiles.

@@ -97,7 +97,8 @@ def test_a_nan_in_v_hides_no_other_value(N, d):
 @pytest.mark.parametrize("B,H,N,d,kind", [(513, 1, 197, 64, "bf16"), (65, 8, 129, 40, "bf16"), (160, 4, 256, 72, "bf16"), (641, 1, 130, 64, "none"),
                                           (75, 7, 200, 96, "fp32"), (215, 3, 256, 24, "none"), (130, 4, 256, 72, "table"), (1025, 1, 256, 64, "none"),
                                           (769, 1, 197, 64, "bf16"), (835, 1, 197, 64, "bf16"), (833, 1, 200, 32, "bf16"), (700, 1, 225, 32, "none"),
-                                          (1401, 1, 197, 64, "none"), (1401, 1, 197, 64, "bf16"), (173, 8, 224, 48, "bf16")])
+                                          (1401, 1, 197, 64, "none"), (1401, 1, 197, 64, "bf16"), (173, 8, 224, 48, "bf16"),
+                                          (896, 1, 160, 40, "bf16"), (897, 1, 160, 40, "bf16"), (1024, 1, 224, 64, "bf16"), (150, 8, 160, 56, "bf16")])
 def test_heads_of_the_last_round_by_row_blocks(B, H, N, d, kind):
     """The single launch's 4-wave form takes those heads with a workgroup per row block: the bits of a call that takes
     the same heads whole."""
