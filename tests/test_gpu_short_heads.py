@@ -1,5 +1,5 @@
 """The single launch where the second key block ends early (128 < N <= 224): 32-key tiles and waves without keys and rows are left
-out there.  Against the launches over a workspace, which leave nothing out."""
+out there.  Against the launches over a workspace and the 8-wave form, bit for bit."""
 import pytest
 import torch
 
@@ -24,10 +24,15 @@ def test_single_launch_with_an_early_end(N, heads, d, bias):
         b[:, : N // 2, :edge] = float("-inf")
         b[:, N // 2:, edge:] = float("-inf")
     scale = d ** -0.5
-    got = ba.forward_fused(q, k, v, b, scale).float()
+    mu = [torch.empty(heads // 2, 2, device="cuda") for _ in range(2)]
+    got = ba.forward_fused(q, k, v, b, scale, mu_q=mu[0], mu_k=mu[1])
+    wide = ba.forward_fused(q, k, v, b, scale, flags=ba.FLAG_WIDE8 | ba.FLAG_NO_MU)
+    some = ba.forward_fused(q, k, v, b, scale, flags=ba.FLAG_NO_MU)
     qb, kb, mq, mk = ba.pack_qk(q, k)
-    ref = ba.forward(qb, kb, mq, mk, v, b, scale).float()
-    # the abs-means differ in their last bits, so codes of P fall to the other side of a half-integer: an output moves by up to max |v| / 255
-    # per code (under 6 / 255, and where one key carries a row there is one such code), plus 2^-8 of bf16 on either side
-    assert torch.isfinite(got).all()
-    assert ((got - ref).abs() <= 2.4e-2 + 2e-2 * ref.abs()).all()
+    ref = ba.forward(qb, kb, mu[0], mu[1], v, b, scale)  # the same abs-means
+    assert torch.isfinite(got.float()).all()
+    # a tile that is left out would have had weights of 0 and codes of -128: the same bits
+    assert torch.equal(got, ref)
+    assert torch.equal(some, wide)
+    for m, n in ((mu[0], mq), (mu[1], mk)):  # fp32 sums of N d terms in two orders
+        assert torch.allclose(m, n, rtol=1e-5, atol=0)
