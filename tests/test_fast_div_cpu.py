@@ -28,7 +28,9 @@ static bool divisor(int d) {
     return check(top, d, f) && check(top - 1, d, f) && check(0, d, f);
 }
 int main() {
-    for (int d = 1; d <= 70000; ++d)
+    for (int d = 1; d <= 1 << 17; ++d)  // row blocks of up to 2^24 tokens
+        if (!divisor(d)) return 1;
+    for (int i = 0, d = 1 << 17; d < 1 << 24; d += 1 + (++i * 2654435761u >> 22))  // batch and heads up to 2^24
         if (!divisor(d)) return 1;
     for (int s = 17; s < 31; ++s)
         for (int o = -3; o <= 3; ++o)
@@ -51,7 +53,7 @@ def run(tmp_path, edit=lambda header: header):
 def test_quotients(tmp_path):
     r = run(tmp_path)
     assert r.returncode == 0, r.stdout
-    assert int(r.stdout.split()[1]) > 50_000_000
+    assert int(r.stdout.split()[1]) > 150_000_000
 
 
 def test_the_check_sees_a_multiplier_that_is_one_too_small(tmp_path):
