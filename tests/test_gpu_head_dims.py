@@ -51,3 +51,20 @@ def test_head_dimensions(d, B, H, N, bias):
     ref = algorithm1(q, k, v, b, scale)
     # rows of 50 and more keys: the stated tolerance of the outputs
     assert ((got.double() - ref).abs() <= 1e-2 + 2e-2 * ref.abs()).all()
+
+
+# (a bias of more than 256 MB is copied past the caches where its rows start on 128-byte lines: here by its pitch)
+@pytest.mark.parametrize("d", [24, 40, 48, 64])
+def test_two_batch_entries_share_a_streamed_bias(d):
+    B, H, N, pitch = 2, 1, 1000, 134_272
+    g = torch.Generator(device="cuda").manual_seed(d)
+    q, k, v = (torch.randn(B, H, N, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    b = (torch.randn(H, N, N, generator=g, device="cuda") * 0.3).to(torch.bfloat16)
+    store = torch.full((N * pitch,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    far = store.as_strided((H, N, N), (N * pitch, pitch, 1)).copy_(b)
+    scale = d ** -0.5
+    got, near, alone = ba.attention(q, k, v, far, scale), ba.attention(q, k, v, b, scale), ba.attention(q[:1], k[:1], v[:1], b, scale)
+    # (an even number of key blocks: the accumulator's offset is removed before the same ones in every form)
+    assert torch.equal(got, near) and torch.equal(got[:1], alone)
+    ref = algorithm1(q, k, v, b, scale)
+    assert ((got.double() - ref).abs() <= 1e-2 + 2e-2 * ref.abs()).all()
