@@ -236,9 +236,9 @@ int binattn_forward_relpos(const uint32_t *q_bits, const uint32_t *k_bits, const
  *   mu_k_out   : optional (may be NULL) float32 [B, H]: the abs-means that were used.
  * Results equal binattn_pack_qk + binattn_forward up to the summation order of the
  * abs-means (fixed: the same bits on every run).  N > 256 returns BINATTN_ERR_SHAPE.  A call with more than 256 (batch, head)
- * pairs runs 4-wave workgroups, two per compute unit, each taking a head's two 128-row
- * blocks in turn, or one of them where few heads are left for a last round and the output does not
- * share memory with Q, K or V (BINATTN_FLAG_WIDE8 keeps one 8-wave workgroup per head; same results up
+ * pairs runs 4-wave workgroups, two or three per compute unit, each taking a head's two 128-row
+ * blocks in turn, or one of them: for the last heads, where that fills a round better, and where the output
+ * does not share memory with Q, K or V (BINATTN_FLAG_WIDE8 keeps one 8-wave workgroup per head; same results up
  * to the summation order of the abs-means).
  */
 int binattn_forward_fused(const void *q, const void *k, const void *v, const int64_t q_strides[3],

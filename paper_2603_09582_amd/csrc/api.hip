@@ -276,7 +276,7 @@ int attend_impl(const uint32_t *q_bits, const float *mu_q, const float *mu_k, co
         p.xqs = raw->qs; p.xks = raw->ks; p.xvs = raw->vs;
         p.mu_q_out = raw->mu_q_out; p.mu_k_out = raw->mu_k_out;
         p.small_pitch = raw->qs.n < HEAD_FAR_PITCH && raw->ks.n < HEAD_FAR_PITCH && raw->vs.n < HEAD_FAR_PITCH;
-        // More heads than compute units: 4-wave workgroups, two per compute unit, each taking
+        // More heads than compute units: 4-wave workgroups, two or three per compute unit, each taking
         // the head's two row blocks in turn; otherwise one 8-wave workgroup per head.
         const bool four = B * H > ONEHEAD4_MIN_HEADS && onehead4_built(s.DK, mode) && !(flags & BINATTN_FLAG_WIDE8);
         const bool three = four && onehead_three(s.DK, mode, N, B * H);

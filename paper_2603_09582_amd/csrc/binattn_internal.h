@@ -233,8 +233,8 @@ constexpr int FORM_HALF = 16;
 constexpr bool half_form(int DK, int d) { return (DK == 2 || DK == 3) && d <= 32 * DK - 16; }
 template <int DK, int FORMS>
 int launch_fused_dk(const FusedParams &p, int mode, hipStream_t stream);
-// The single-launch form for at most two key blocks (nb must be 2, total_wg = B * H).
-// single-launch form: calls with more heads than this use 4-wave workgroups (two per compute unit)
+// The single-launch forms, for at most two key blocks (total_wg = B * H): nb = 2 for one 8-wave workgroup per head, 1 for 4-wave
+// workgroups, which calls with more heads than this take (two or three per compute unit).
 constexpr int ONEHEAD4_MIN_HEADS = 256;
 // Three 4-wave workgroups per compute unit instead of two (32 < d <= 64).  Without a bias they are at least as fast everywhere (us,
 // two / three: N = 197 400 heads 19.8 / 19.7, 768 31.6 / 28.1, 1536 54.5 / 48.4, N = 256 1024 42.5 / 38.3, N = 100 768 18.6 / 15.8) and the only form.  With bf16

@@ -93,7 +93,7 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 // the same prologue with 256 threads, then the head's two 128-row blocks one after the other
 // as two items of the persistent stream (the images stay where they are).  Two such workgroups
 // share a compute unit, so one head's loads and preparation overlap the other's block loop.
-// (Heads left for a last round that fills the chip at most half take a workgroup per row block: head_split.h.)
+// (The last heads take a workgroup per row block where that fills a round better: head_split.h.)
 //
 // WIDE_PAIR_ONCE is the paired form (NB = 2) with the bias copies marked as not worth keeping in the
 // caches, for biases larger than those.
@@ -134,10 +134,9 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
     constexpr int DK2 = L::DK2;
     constexpr bool F32L = MODE == BIAS_F32_LDS;
     constexpr bool BF16L = MODE == BIAS_BF16_LDS || MODE == BIAS_BF16_LDS8, LDS_BIAS = BF16L || F32L;
-    // A chunk can straddle the end of a row.  Where none can, the block loop is built without the code for it:
-    // its branches sat between the logits and the exponentials and cost 2-3 % even where they were never taken.  Since blocks inside
-    // the rows take a path of their own it makes no difference any more (attention stage, with / without: N = 520, d = 64, 192 heads
-    // 30.7 / 30.6 us, N = 1024, d = 72, 128 heads 51.1 / 51.7, N = 1376, d = 96, 192 heads 132.6 / 133.8).
+    // A chunk can straddle the end of a row.  Where none can, the block loop is built without the code for it (whole calls, us, with /
+    // without: N = 392, 640 heads d = 16 63.8 / 62.2, d = 32 68.1 / 66.6, d = 80 95.3 / 94.1, N = 520, 48 heads d = 72 21.4 / 21.2, N = 1376, 96 heads d = 96
+    // 100.1 / 98.4).  It is the ragged last block that gains: over long rows either may be ahead by 1 % (N = 4096, 8 heads d = 96 86.2 / 85.3, d = 72 82.1 / 83.1).
     constexpr bool STRADDLE = MODE != BIAS_BF16_LDS8;
     // Staged bias rows: SEGS segments of 128 bytes per row and block.  A bf16 tile is staged whole
     // (two segments); an fp32 tile would be 16 KiB per wave, so its first SEGS 32-key quarters (one per
@@ -154,6 +153,8 @@ __global__ __launch_bounds__(FUSED_THREADS * NB, ((FORM & 15) == WIDE_WAVES3 || 
     // So are those of all channel blocks, whose V rows are read under the tile's own exponentials, in the 4-wave workgroups with bf16
     // tiles at 64 < d <= 96 and fp32 tiles at 32 < d <= 64 (attention stage, us: N = 1024, d = 72, 128 heads 46.1 / 45.8, N = 1370, 64 heads, d = 80
     // 51.3 / 50.8, d = 88 52.4 / 51.1, fp32, N = 577, 192 heads 35.9 / 35.5; bf16 at d = 64 nothing, d = 128 191 / 200, the paired form 2616 / 2838).
+    // The single launch is built without (whole calls, without / with: d = 72, N = 256 512 heads 29.2 / 29.0, 768 43.4 / 43.0, N = 128 600 heads 21.9 / 22.1, d = 96,
+    // N = 256 768 heads 49.6 / 50.3, fp32, d = 64, N = 256 768 heads 38.0 / 37.5, N = 128 600 heads 20.0 / 20.1): ahead by 1 % with two blocks, behind with one.
     constexpr bool ALL_EARLY = !ONEHEAD && NB == 1 && ((DK == 3 && BF16L) || (DK == 2 && F32L));
     constexpr bool PV_EARLY = ((MODE == BIAS_AXIAL || MODE == BIAS_TABLE_BLK) && DK <= 2) || ALL_EARLY;
     // V operand rows of this many channel blocks are fetched from LDS before the
